@@ -11,22 +11,28 @@
 //   or (3,3) (Eqs. pade11, pade22, pade33; A and B are matrix polynomials in
 //   C, the leading factor folded into A), L = L_0 + sum eta_k dL_k.
 //
-// Derivatives are closed-form:
-//  * in C-space along the symmetric basis E_v (xx,yy,zz,yz,xz,xy; the shear
-//    ones are e_a e_b^T + e_b e_a^T); A, B commute with C, so with
-//    dX_v = dX/dC[E_v] and d2X_uv its second derivative (X = A, B):
-//    dH = (dA - H dB) B^-1,
-//    d2H = (d2A - dH_u dB_v - dH_v dB_u - H d2B) B^-1, where
-//    d(C^2)[E] = CE + EC, d(C^3)[E] = EC^2 + CEC + C^2E,
-//    d2(C^2)[E_u, E_v] = E_u E_v + E_v E_u,
-//    d2(C^3)[E_u, E_v] = (E_u E_v + E_v E_u) C + C (E_u E_v + E_v E_u) + E_u C E_v + E_v C E_u;
-//  * chain rule through C(F, G(eta)), J_t(eta), L(eta):
-//    dC/dF_ij = a_i (x) G_j + G_j (x) a_i  (a_i = row i of F G),
-//    dC/deta_k = -(Q_k C + C Q_k^T), Q_k = G dU_k,  dJ_t/deta_k = J_t tr Q_k,
-//    d2C/dF_ij dF_kl = delta_ik (G_j (x) G_l + G_l (x) G_j),
-//    d2C/dF deta_k = -(Q_k dC_F + dC_F Q_k^T),
-//    d2C/deta_k deta_l = sym2(Q_k Q_l C + Q_l Q_k C + Q_k C Q_l^T),
-//    d2J_t/deta_k deta_l = J_t (tr Q_k tr Q_l - tr(Q_k Q_l)).
+// Derivatives are closed-form, in three spaces:
+//  * C-space, along the symmetric basis E_v (xx,yy,zz,yz,xz,xy; the shear ones
+//    are e_a e_b^T + e_b e_a^T).  A and B are polynomials in C, so dH along E
+//    is a sum of products of functions of C around E,
+//      dH[E] = sum_p A_p E C^p B^-1,  A_p = sum_{q > p} (a_q - H b_q) C^(q-1-p),
+//    and every term of the second derivative w_CC besides dH : L dH is a form
+//    tr(M E_u N E_v) of 3x3 matrices: with T = L H, Y = T B^-1,
+//      T : d2H_uv = Y : (d2A - H d2B) - Y : (dH_u dB_v + dH_v dB_u),
+//      d2(C^2) = E_u E_v + E_v E_u,
+//      d2(C^3) = (E_u E_v + E_v E_u) C + C (E_u E_v + E_v E_u) + E_u C E_v + E_v C E_u.
+//    A basis pair costs 1, 2 or 4 products per form instead of 3x3 products
+//    with the basis matrices' zeros.
+//  * F^t-space (6 components, G = (F^t)^-1): dC/dF^t[E] = -(G E C + C E G),
+//    d J_t[E] = J_t tr(G E), and their second derivatives; the order parameters
+//    enter through dF^t/deta_k (the constants U_k - I under Eq. LinMix) and
+//    through L(eta), which is linear.
+//  * Green-strain space: with eps = sym(F^T dF) in engineering components,
+//    dC = 2 G eps G, so the density's dependence on F is through eps alone:
+//    second derivatives D_ee (6x6), D_ek (6xN), the stress S (dpsi = S : eps)
+//    and F itself give the derivatives with respect to F,
+//      d2psi/dF_ij dF_kl = sum_ab F_ia D_(aj)(bl) F_kb + delta_ik S_jl,
+//      d2psi/dF_ij deta_k = sum_a F_ia D_(aj)k,  dpsi/dF = F S.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -61,6 +67,38 @@ struct DevCard {
   double logU[NV][6];  // log U_k (logarithmic mixing rule, Sec. 2.1)
 };
 
+// Boundary of a computation phase: the values given are computed before it
+// and their uses come after it, so that the unrolled phases' temporaries are
+// not all live at once.
+__device__ __forceinline__ void phase(double& x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+v"(x));
+#endif
+}
+// The card as one phase reads it: its constants are loaded no earlier (all of
+// them at once would not fit the scalar registers), by scalar loads.
+#if defined(__HIP_DEVICE_COMPILE__)
+typedef const DevCard __attribute__((address_space(4))) PhaseCard;
+__device__ __forceinline__ PhaseCard& phase(const DevCard& cd) {
+  PhaseCard* p = (PhaseCard*)&cd;
+  asm volatile("" : "+s"(p));
+  return *p;
+}
+#else
+typedef const DevCard PhaseCard;
+__host__ __device__ inline PhaseCard& phase(const DevCard& cd) { return cd; }
+#endif
+template <int N>
+__device__ __forceinline__ void phase(double (&x)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) phase(x[i]);
+}
+template <int N, int M>
+__device__ __forceinline__ void phase(double (&x)[N][M]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) phase(x[i]);
+}
+
 // symmetric index map (xx,yy,zz,yz,xz,xy)
 __host__ __device__ constexpr int SI(int a, int b) {
   return a == b ? a : (a + b == 3 ? 3 : (a + b == 2 ? 4 : 5));
@@ -91,35 +129,6 @@ __device__ __forceinline__ void mm(const double a[9], const double b[9], double 
       c[3 * i + j] = a[3 * i] * b[j] + a[3 * i + 1] * b[3 + j] + a[3 * i + 2] * b[6 + j];
 }
 
-__device__ __forceinline__ double ddot9(const double a[9], const double b[9]) {
-  double s = 0.0;
-#pragma unroll
-  for (int i = 0; i < 9; ++i) s += a[i] * b[i];
-  return s;
-}
-
-// sum_ab a_ab b_ba
-__device__ __forceinline__ double trprod(const double a[9], const double b[9]) {
-  double s = 0.0;
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) s += a[3 * i + j] * b[3 * j + i];
-  return s;
-}
-
-// Contraction X : E_v of a full matrix with the symmetric basis element E_v.
-__device__ __forceinline__ double contract_basis(const double x[9], int v) {
-  switch (v) {
-    case 0: return x[0];
-    case 1: return x[4];
-    case 2: return x[8];
-    case 3: return x[5] + x[7];
-    case 4: return x[2] + x[6];
-    default: return x[1] + x[3];
-  }
-}
-
 // engineering (Voigt strain) form of symmetric components
 __device__ __forceinline__ void eng(const double s[6], double e[6]) {
   e[0] = s[0]; e[1] = s[1]; e[2] = s[2];
@@ -141,20 +150,6 @@ __device__ __forceinline__ double sym_inv(const double s[6], double r[6]) {
   r[3] = (xy * xz - xx * yz) * id;
   r[2] = (xx * yy - xy * xy) * id;
   return det;
-}
-
-// Symmetric basis element E_v as a full matrix.
-__device__ __forceinline__ void basis(int v, double e[9]) {
-#pragma unroll
-  for (int i = 0; i < 9; ++i) e[i] = 0.0;
-  switch (v) {
-    case 0: e[0] = 1.0; break;
-    case 1: e[4] = 1.0; break;
-    case 2: e[8] = 1.0; break;
-    case 3: e[5] = e[7] = 1.0; break;
-    case 4: e[2] = e[6] = 1.0; break;
-    default: e[1] = e[3] = 1.0; break;
-  }
 }
 
 __host__ __device__ constexpr int hidx(int p, int q) {  // packed upper triangle, p <= q < NQ
@@ -190,32 +185,20 @@ __device__ __forceinline__ void axpy_c(double c, const double m[N], double x[N])
 }
 
 // Quantities shared by the gradient and the Hessian.
+template <int PD>
 struct LocalBase {
   double Jt;
-  double G[9];    // (F^t)^-1, full
-  double Fe[9];   // F G
-  double C[9];    // full symmetric
-  double w;       // 1/2 H : L H
-  double wC[6];   // dw/dC along E_v
-  double wEta[NV]; // partial dw/deta_k at fixed C
-  double dh[6][6];  // engineering components of dH_v
-  double h[6];      // engineering H
-  double T[6];      // L H (tensor components)
-  double Binv[9];
-  double H[9];
+  double G[9];     // (F^t)^-1, full symmetric
+  double C[9];     // C^e, full symmetric
+  double H[9];     // Hencky strain, full symmetric
+  double Binv[9];  // B^-1, full symmetric
+  double h[6];     // engineering H
+  double T[9];     // L H, full symmetric
+  double w;        // 1/2 H : L H
+  double wEta[NV]; // dw/deta_k at fixed C: 1/2 h : dL_k h
+  double Sf[9];    // dw/dC: dw = Sf : dC, full symmetric
+  double B1[9];    // C Sf G
 };
-
-// With the logarithmic mixing rule F^t depends nonlinearly on eta: its
-// first derivatives dF^t/deta_k are kept per Gauss point.
-struct LocalBaseLog : LocalBase {
-  double dFt[NV][6];  // dF^t / deta_k (symmetric components)
-};
-template <int MIX> struct BaseOf { using type = LocalBase; };
-template <> struct BaseOf<1> { using type = LocalBaseLog; };
-
-// dF^t / deta_k: the constant U_k - I (Eq. LinMix) or the stored derivative
-__device__ __forceinline__ const double* dFt_of(const LocalBase& b, const DevCard& cd, int k) { return cd.dU[k]; }
-__device__ __forceinline__ const double* dFt_of(const LocalBaseLog& b, const DevCard& cd, int k) { return b.dFt[k]; }
 
 // Terms of the power series of exp: exact to rounding for ||M||_F <= 1
 // (the omitted tail is below 1/19! ~ 8e-18 there; the order parameters of
@@ -315,15 +298,93 @@ __device__ __forceinline__ void log_mixing_second(const double eh[NV], const Dev
   }
 }
 
-// Hencky energy (Pade order PD) and its first C-derivatives; MIX: the
-// mixing rule of F^t (0: Eq. LinMix, 1: logarithmic).
-template <int PD, int MIX = 0>
+// d/deta_k of F^t: the constants U_k - I (Eq. LinMix), or per point with
+// logarithmic mixing, where F^t depends nonlinearly on eta.
+template <int MIX>
+struct MixDerivative {
+  template <class Card>
+  __device__ __forceinline__ double operator()(Card& cd, int k, int v) const { return cd.dU[k][v]; }
+};
+template <>
+struct MixDerivative<1> {
+  double dFt[NV][6];
+  template <class Card>
+  __device__ __forceinline__ double operator()(Card&, int k, int v) const { return dFt[k][v]; }
+};
+
+// corners a <= b of basis element E_v (xx,yy,zz,yz,xz,xy)
+__host__ __device__ constexpr int BA(int v) { return v < 3 ? v : (v == 3 ? 1 : 0); }
+__host__ __device__ constexpr int BB(int v) { return v < 3 ? v : (v == 5 ? 1 : 2); }
+
+// (M E_v N)_ij
+__device__ __forceinline__ double sandwich(const double M[9], const double N[9], int v, int i, int j) {
+  const int a = BA(v), b = BB(v);
+  double r = M[3 * i + a] * N[3 * b + j];
+  if (v >= 3) r += M[3 * i + b] * N[3 * a + j];
+  return r;
+}
+// tr(M E_u N E_v)
+__device__ __forceinline__ double bilinear(const double M[9], const double N[9], int u, int v) {
+  const int a = BA(u), b = BB(u), c = BA(v), d = BB(v);
+  double r = M[3 * d + a] * N[3 * b + c];
+  if (u >= 3) r += M[3 * d + b] * N[3 * a + c];
+  if (v >= 3) r += M[3 * c + a] * N[3 * b + d];
+  if (u >= 3 && v >= 3) r += M[3 * c + b] * N[3 * a + d];
+  return r;
+}
+// product of two symmetric matrices that commute (functions of C): symmetric
+__device__ __forceinline__ void mm_sym(const double a[9], const double b[9], double c[9]) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int j = i; j < 3; ++j)
+      c[3 * i + j] = c[3 * j + i] = a[3 * i] * b[j] + a[3 * i + 1] * b[3 + j] + a[3 * i + 2] * b[6 + j];
+}
+__device__ __forceinline__ double ident(int i) { return i % 4 == 0 ? 1.0 : 0.0; }
+
+// A_p of dH[E] = sum_p A_p E C^p B^-1 (p = 0 .. deg - 1): symmetric functions
+// of C; Cp holds C and C^2
+template <int PD>
+__device__ __forceinline__ void hencky_factor(int p, const double C[9], const double C2[9], const double H[9],
+                                              double A[9]) {
+  using P = Pade<PD>;
+  double b[9];
+#pragma unroll
+  for (int i = 0; i < 9; ++i) A[i] = P::a(p + 1) * ident(i), b[i] = P::b(p + 1) * ident(i);
+  if (p + 2 <= P::deg) axpy_c<9>(P::a(p + 2), C, A), axpy_c<9>(P::b(p + 2), C, b);
+  if (p + 3 <= P::deg) axpy_c<9>(P::a(p + 3), C2, A), axpy_c<9>(P::b(p + 3), C2, b);
+  if (p + 1 == P::deg) {  // b is a multiple of the identity
+#pragma unroll
+    for (int i = 0; i < 9; ++i) A[i] -= P::b(P::deg) * H[i];
+  } else {
+    double Hb[9];
+    mm_sym(H, b, Hb);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) A[i] -= Hb[i];
+  }
+}
+
+// y = L x of a Voigt stiffness (symmetric: its upper triangle is read)
+template <class M>
+__device__ __forceinline__ void voigt_product(M& L, const double x[6], double y[6]) {
+#pragma unroll
+  for (int i = 0; i < 6; ++i) {
+    double s = 0.0;
+#pragma unroll
+    for (int j = 0; j < 6; ++j) s += (i <= j ? L[i][j] : L[j][i]) * x[j];
+    y[i] = s;
+  }
+}
+
+// Hencky energy (Pade order PD) and its first C-derivative; MIX: the mixing
+// rule of F^t (0: Eq. LinMix, 1: logarithmic).
+template <int PD, int MIX>
 __device__ __forceinline__ void local_base(const double F[9], const double eh[NV], const DevCard& cd,
-                                           typename BaseOf<MIX>::type& b) {
+                                           LocalBase<PD>& b, MixDerivative<MIX>& dm) {
   using P = Pade<PD>;
   double Ft[6];
   if constexpr (MIX == 1) {
-    log_mixing(eh, cd, Ft, b.dFt);
+    log_mixing(eh, cd, Ft, dm.dFt);
   } else {
 #pragma unroll
     for (int v = 0; v < 6; ++v) {
@@ -333,250 +394,102 @@ __device__ __forceinline__ void local_base(const double F[9], const double eh[NV
       Ft[v] = s;
     }
   }
-  double Gs[6];
+  double Gs[6], Fe[9], C2[9], C3[9];
   b.Jt = sym_inv(Ft, Gs);
   full_from_sym(Gs, b.G);
-  mm(F, b.G, b.Fe);
-  // C = Fe^T Fe
+  mm(F, b.G, Fe);
 #pragma unroll
   for (int a = 0; a < 3; ++a)
 #pragma unroll
-    for (int c = 0; c < 3; ++c)
-      b.C[3 * a + c] = b.Fe[a] * b.Fe[c] + b.Fe[3 + a] * b.Fe[3 + c] + b.Fe[6 + a] * b.Fe[6 + c];
-  double C2[9], C3[9];
-  if constexpr (P::deg >= 2) mm(b.C, b.C, C2);
-  if constexpr (P::deg >= 3) mm(C2, b.C, C3);
+    for (int c = a; c < 3; ++c)
+      b.C[3 * a + c] = b.C[3 * c + a] = Fe[a] * Fe[c] + Fe[3 + a] * Fe[3 + c] + Fe[6 + a] * Fe[6 + c];
+  if constexpr (P::deg >= 2) mm_sym(b.C, b.C, C2);
+  if constexpr (P::deg >= 3) mm_sym(C2, b.C, C3);
   double Am[9], Bf[9];
 #pragma unroll
   for (int i = 0; i < 9; ++i) {
-    const double id = (i % 4 == 0) ? 1.0 : 0.0;
-    Am[i] = P::a(0) * id + P::a(1) * b.C[i];
-    Bf[i] = P::b(0) * id + P::b(1) * b.C[i];
+    Am[i] = P::a(0) * ident(i) + P::a(1) * b.C[i];
+    Bf[i] = P::b(0) * ident(i) + P::b(1) * b.C[i];
   }
-  if constexpr (P::deg >= 2) {
-    axpy_c<9>(P::a(2), C2, Am);
-    axpy_c<9>(P::b(2), C2, Bf);
-  }
-  if constexpr (P::deg >= 3) {
-    axpy_c<9>(P::a(3), C3, Am);
-    axpy_c<9>(P::b(3), C3, Bf);
-  }
-  double Bs[6], Bi[6];
+  if constexpr (P::deg >= 2) axpy_c<9>(P::a(2), C2, Am), axpy_c<9>(P::b(2), C2, Bf);
+  if constexpr (P::deg >= 3) axpy_c<9>(P::a(3), C3, Am), axpy_c<9>(P::b(3), C3, Bf);
+  double Bs[6], Bi[6], Hs[6], Ts[6];
   sym_of(Bf, Bs);
   sym_inv(Bs, Bi);
   full_from_sym(Bi, b.Binv);
-  double Hf[9];
-  mm(Am, b.Binv, Hf);
-  double Hs[6];
-  sym_of(Hf, Hs);
-  full_from_sym(Hs, b.H);
+  mm_sym(Am, b.Binv, b.H);
+  sym_of(b.H, Hs);
   eng(Hs, b.h);
-  // mixed stiffness and Hencky stress
-  double Lm[6][6];
-#pragma unroll
-  for (int i = 0; i < 6; ++i)
-#pragma unroll
-    for (int j = 0; j < 6; ++j) {
-      double s = cd.L0[i][j];
-#pragma unroll
-      for (int k = 0; k < NV; ++k) s += eh[k] * cd.dL[k][i][j];
-      Lm[i][j] = s;
-    }
-  double w = 0.0;
-#pragma unroll
-  for (int i = 0; i < 6; ++i) {
-    double s = 0.0;
-#pragma unroll
-    for (int j = 0; j < 6; ++j) s += Lm[i][j] * b.h[j];
-    b.T[i] = s;
-    w += b.h[i] * s;
-  }
-  b.w = 0.5 * w;
-  // partial derivative w.r.t. eta at fixed C: 1/2 h^T dL_k h
+  // Hencky stress T = L h of the mixed stiffness, dw/deta_k at fixed C
+  voigt_product(cd.L0, b.h, Ts);
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
-    double s = 0.0;
+    double d[6], e = 0.0;
+    voigt_product(phase(cd).dL[k], b.h, d);
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
-      double t = 0.0;
-#pragma unroll
-      for (int j = 0; j < 6; ++j) t += cd.dL[k][i][j] * b.h[j];
-      s += b.h[i] * t;
+      Ts[i] += eh[k] * d[i];
+      e += b.h[i] * d[i];
     }
-    b.wEta[k] = 0.5 * s;
+    b.wEta[k] = 0.5 * e;
+    phase(Ts);
+    phase(b.wEta[k]);
   }
-  // dH along the C basis and dw/dC
+  double w = 0.0;
 #pragma unroll
-  for (int v = 0; v < 6; ++v) {
-    double E[9], dA[9], dB[9], HdB[9], X[9], dHf[9], dHs[6];
-    basis(v, E);
+  for (int i = 0; i < 6; ++i) w += b.h[i] * Ts[i];
+  b.w = 0.5 * w;
+  full_from_sym(Ts, b.T);
+  // dw/dC = sym sum_p C^p B^-1 T A_p
+  double S[9], N[9];
 #pragma unroll
-    for (int i = 0; i < 9; ++i) {
-      dA[i] = P::a(1) * E[i];
-      dB[i] = P::b(1) * E[i];
+  for (int i = 0; i < 9; ++i) S[i] = 0.0, N[i] = b.Binv[i];
+#pragma unroll
+  for (int p = 0; p < P::deg; ++p) {
+    double A[9], TA[9], X[9];
+    hencky_factor<PD>(p, b.C, C2, b.H, A);
+    mm(b.T, A, TA);
+    mm(N, TA, X);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) S[i] += X[i];
+    if (p + 1 < P::deg) {
+      double Nn[9];
+      mm_sym(b.C, N, Nn);
+#pragma unroll
+      for (int i = 0; i < 9; ++i) N[i] = Nn[i];
     }
-    if constexpr (P::deg >= 2) {
-      double CE[9], d2[9];
-      mm(b.C, E, CE);
-#pragma unroll
-      for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) d2[3 * a + c] = CE[3 * a + c] + CE[3 * c + a];
-      axpy_c<9>(P::a(2), d2, dA);
-      axpy_c<9>(P::b(2), d2, dB);
-      if constexpr (P::deg >= 3) {
-        double C2E[9], CEC[9], d3[9];
-        mm(C2, E, C2E);
-        mm(CE, b.C, CEC);
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-#pragma unroll
-          for (int c = 0; c < 3; ++c) d3[3 * a + c] = C2E[3 * a + c] + C2E[3 * c + a] + CEC[3 * a + c];
-        axpy_c<9>(P::a(3), d3, dA);
-        axpy_c<9>(P::b(3), d3, dB);
-      }
-    }
-    mm(b.H, dB, HdB);
-#pragma unroll
-    for (int i = 0; i < 9; ++i) X[i] = dA[i] - HdB[i];
-    mm(X, b.Binv, dHf);
-    sym_of(dHf, dHs);
-    eng(dHs, b.dh[v]);
-    double s = 0.0;
-#pragma unroll
-    for (int i = 0; i < 6; ++i) s += b.T[i] * b.dh[v][i];
-    b.wC[v] = s;
   }
-}
-
-// Symmetric components of dC along variable q (0..8: F_ij row-major; 9..: eta).
-template <class B>
-__device__ __forceinline__ void dC_of(const B& b, const DevCard& cd, int q, double dc[6], double dcf[9]) {
-  if (q < 9) {
-    const int i = q / 3, j = q % 3;
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-      for (int c = 0; c < 3; ++c)
-        dcf[3 * a + c] = b.Fe[3 * i + a] * b.G[3 * c + j] + b.G[3 * a + j] * b.Fe[3 * i + c];
-  } else {
-    const int k = q - 9;
-    double dU[9], Q[9], X[9];
-    full_from_sym(dFt_of(b, cd, k), dU);
-    mm(b.G, dU, Q);
-    mm(Q, b.C, X);
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) dcf[3 * a + c] = -(X[3 * a + c] + X[3 * c + a]);
-  }
-  dc[0] = dcf[0]; dc[1] = dcf[4]; dc[2] = dcf[8];
-  dc[3] = dcf[5]; dc[4] = dcf[2]; dc[5] = dcf[1];
-}
-
-// a[i] for a runtime i in 0..N-1 (selection, no indexing: the array stays
-// in registers)
-__device__ __forceinline__ double pick6(int i, double a0, double a1, double a2, double a3, double a4, double a5) {
-  double r = a0;
-  r = (i == 1) ? a1 : r;
-  r = (i == 2) ? a2 : r;
-  r = (i == 3) ? a3 : r;
-  r = (i == 4) ? a4 : r;
-  r = (i == 5) ? a5 : r;
-  return r;
-}
-// a[i] of the N values at a (same selection chain)
-template <int N>
-__device__ __forceinline__ double pick_n(int i, const double* a) {
-  if constexpr (N == 6) {
-    return pick6(i, a[0], a[1], a[2], a[3], a[4], a[5]);
-  } else {
-    double r = a[0];
-#pragma unroll
-    for (int j = 1; j < N; ++j) r = (i == j) ? a[j] : r;
-    return r;
-  }
-}
-template <int N>
-__device__ __forceinline__ double pick(int i, const double (&a)[N]) {
-  if constexpr (N == 6) {
-    return pick6(i, a[0], a[1], a[2], a[3], a[4], a[5]);
-  } else {
-    double r = a[0];
-#pragma unroll
-    for (int j = 1; j < N; ++j) r = (i == j) ? a[j] : r;
-    return r;
-  }
-}
-// a[i][v] for a runtime i (selection, as pick)
-template <int N, int M>
-__device__ __forceinline__ double pick_row(int i, const double (&a)[N][M], int v) {
-  if constexpr (N == 6) {
-    return pick6(i, a[0][v], a[1][v], a[2][v], a[3][v], a[4][v], a[5][v]);
-  } else {
-    double r = a[0][v];
-#pragma unroll
-    for (int j = 1; j < N; ++j) r = (i == j) ? a[j][v] : r;
-    return r;
-  }
-}
-
-// Q_k = G dF^t/deta_k (full)
-template <class B>
-__device__ __forceinline__ void Q_of(const B& b, const DevCard& cd, int k, double Q[9]) {
-  double dU[9];
-  full_from_sym(dFt_of(b, cd, k), dU);
-  mm(b.G, dU, Q);
-}
-
-// dC/deta_k = -(Q_k C + C Q_k^T) as symmetric components (and full)
-__device__ __forceinline__ void dC_eta(const LocalBase& b, const double Q[9], double dc[6], double dcf[9]) {
-  double X[9];
-  mm(Q, b.C, X);
-#pragma unroll
-  for (int a = 0; a < 3; ++a)
-#pragma unroll
-    for (int c = 0; c < 3; ++c) dcf[3 * a + c] = -(X[3 * a + c] + X[3 * c + a]);
-  dc[0] = dcf[0]; dc[1] = dcf[4]; dc[2] = dcf[8];
-  dc[3] = dcf[5]; dc[4] = dcf[2]; dc[5] = dcf[1];
-}
-
-// dC/dF_ij (q = 3 i + j) as symmetric components
-__device__ __forceinline__ void dC_F(const LocalBase& b, int q, double dc[6]) {
-  const int i = q / 3, j = q % 3;
-  // dcf[a][c] = Fe[i][a] G[c][j] + G[a][j] Fe[i][c]
-  auto f = [&](int a, int c) { return b.Fe[3 * i + a] * b.G[3 * c + j] + b.G[3 * a + j] * b.Fe[3 * i + c]; };
-  dc[0] = f(0, 0); dc[1] = f(1, 1); dc[2] = f(2, 2);
-  dc[3] = f(1, 2); dc[4] = f(0, 2); dc[5] = f(0, 1);
+  double Ss[6], SG[9];
+  sym_of(S, Ss);
+  full_from_sym(Ss, b.Sf);
+  mm(b.Sf, b.G, SG);
+  mm(b.C, SG, b.B1);
 }
 
 __device__ __forceinline__ double neg_part(double x) { return x < 0.0 ? x : 0.0; }
 
-// Gradient of the local density: g[NQ].
-template <int PD, int MIX = 0>
-__device__ __forceinline__ void local_gradient(const double F[9], const double eh[NV], const double ehn[NV],
-                                               const DevCard& cd, double g[NQ]) {
-  typename BaseOf<MIX>::type b;
-  local_base<PD, MIX>(F, eh, cd, b);
+// stress S (dpsi = S : sym(F^T dF), 6 components) and the derivative phi of
+// the elastic energy along F^t (dpsi = sum_v phi_v dF^t_v at fixed L)
+template <int PD>
+__device__ __forceinline__ void local_first(const LocalBase<PD>& b, double S[6], double phi[6]) {
+  double SG[9];
+  mm(b.Sf, b.G, SG);
 #pragma unroll
-  for (int q = 0; q < NQ; ++q) {
-    double dc[6], dcf[9];
-    dC_of(b, cd, q, dc, dcf);
-    double wq = 0.0;
-#pragma unroll
-    for (int v = 0; v < 6; ++v) wq += b.wC[v] * dc[v];
-    if (q < 9) {
-      g[q] = b.Jt * wq;
-    } else {
-      const int k = q - 9;
-      double dU[9], Q[9];
-      full_from_sym(dFt_of(b, cd, k), dU);
-      mm(b.G, dU, Q);
-      const double trQ = Q[0] + Q[4] + Q[8];
-      g[q] = b.Jt * (wq + b.wEta[k]) + b.Jt * trQ * b.w;
-    }
+  for (int v = 0; v < 6; ++v) {
+    const int i = BA(v), j = BB(v);
+    S[v] = 2.0 * b.Jt * (b.G[3 * i] * SG[j] + b.G[3 * i + 1] * SG[3 + j] + b.G[3 * i + 2] * SG[6 + j]);
+    // tr(G E_v) = G_ii or 2 G_ij; dC = -(G E C + C E G) gives -(B1 + B1^T) : E
+    phi[v] = b.Jt * (v < 3 ? b.G[3 * i + j] * b.w - 2.0 * b.B1[3 * i + j]
+                           : 2.0 * (b.G[3 * i + j] * b.w - b.B1[3 * i + j] - b.B1[3 * j + i]));
   }
-  // order-parameter terms: chemical, double obstacle, viscous, penalty
+}
+
+// eta part of the gradient: elastic through F^t and L, chemical, double
+// obstacle, viscous and penalty terms
+template <int MIX>
+__device__ __forceinline__ void eta_gradient(const double eh[NV], const double ehn[NV], const DevCard& cd, double Jt,
+                                             const double wEta[NV], const MixDerivative<MIX>& dm, const double phi[6],
+                                             double g[NV]) {
   double eta[NV + 1], etan[NV + 1];
   double s = 0.0, sn = 0.0;
 #pragma unroll
@@ -595,87 +508,151 @@ __device__ __forceinline__ void local_gradient(const double F[9], const double e
   const double n0 = neg_part(eta[0]);
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
-    g[9 + k] += cd.dF0[k] + (We[k + 1] - We[0]) + cd.rho * ((eta[k + 1] - etan[k + 1]) - d0)
-                + cd.eps * (neg_part(eta[k + 1]) - n0);
+    double t = Jt * wEta[k];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) t += phi[i] * dm(cd, k, i);
+    g[k] = t;
+    g[k] += cd.dF0[k] + (We[k + 1] - We[0]) + cd.rho * ((eta[k + 1] - etan[k + 1]) - d0)
+            + cd.eps * (neg_part(eta[k + 1]) - n0);
   }
 }
 
-// Gradient and packed upper-triangular Hessian of the local density; entry
-// hidx(p, q) of the Hessian is stored to D[hidx(p, q) * ds] as soon as it is
-// known (nothing of it is kept in registers).
+// dpsi/dF = F S
+__device__ __forceinline__ void first_piola(const double F[9], const double S[6], double g[9]) {
+  double Sm[9];
+  full_from_sym(S, Sm);
+  mm(F, Sm, g);
+}
+
+// Gradient of the local density: g[NQ].
 template <int PD, int MIX = 0>
+__device__ __forceinline__ void local_gradient(const double F[9], const double eh[NV], const double ehn[NV],
+                                               const DevCard& cd, double g[NQ]) {
+  LocalBase<PD> b;
+  MixDerivative<MIX> dm;
+  double S[6], phi[6];
+  local_base<PD, MIX>(F, eh, cd, b, dm);
+  local_first<PD>(b, S, phi);
+  first_piola(F, S, g);
+  eta_gradient<MIX>(eh, ehn, cd, b.Jt, b.wEta, dm, phi, g + 9);
+}
+
+// index of D_ee entry (u, v) among its 21 upper entries
+__host__ __device__ constexpr int eidx(int u, int v) {
+  return u <= v ? u * 6 - u * (u - 1) / 2 + (v - u) : v * 6 - v * (v - 1) / 2 + (u - v);
+}
+
+// 2 G q G for the symmetric tensor whose contraction components are q
+// (tensor components q_aa and q_ab / 2): sum_i (dC along eps_w)_i q_i
+__device__ __forceinline__ void to_strain(const double G[9], const double q[6], double r[6]) {
+  const double Q[9] = {q[0], 0.5 * q[5], 0.5 * q[4], 0.5 * q[5], q[1], 0.5 * q[3], 0.5 * q[4], 0.5 * q[3], q[2]};
+  double GQ[9];
+  mm(G, Q, GQ);
+#pragma unroll
+  for (int w = 0; w < 6; ++w) {
+    const int i = BA(w), j = BB(w);
+    r[w] = 2.0 * (GQ[3 * i] * G[j] + GQ[3 * i + 1] * G[3 + j] + GQ[3 * i + 2] * G[6 + j]);
+  }
+}
+
+// Gradient and second derivatives of the local density in (eps, eta), handed
+// to out as soon as they are known (so that few stay live): out.strain(g, S,
+// D_ee) with the gradient, the stress and the upper triangle, out.eps_eta(k, d)
+// with the six entries D_(.)k, out.eta_eta(k, l, val) for l <= k.
+template <int PD, int MIX, class Out>
 __device__ __forceinline__ void local_hessian(const double F[9], const double eh[NV], const double ehn[NV],
-                                              const DevCard& cd, double g[NQ], double* __restrict__ D,
-                                              int64_t ds) {
+                                              const DevCard& cd, Out&& out) {
   using P = Pade<PD>;
-  typename BaseOf<MIX>::type b;
-  local_base<PD, MIX>(F, eh, cd, b);
+  LocalBase<PD> b;
+  MixDerivative<MIX> dm;
+  double S[6], phi[6], g[NQ];
+  local_base<PD, MIX>(F, eh, cd, b, dm);
+  local_first<PD>(b, S, phi);
+  first_piola(F, S, g);
+  eta_gradient<MIX>(eh, ehn, cd, b.Jt, b.wEta, dm, phi, g + 9);
+  out.gradient(g, S);
+  
   // ---- second derivatives in C-space -------------------------------------
-  double wCC[6][6];
-  double wCeta[6][NV];  // [v][k]
+  double dh[6][6];  // engineering components of dH along E_v
+  double wCC[21];   // upper triangle
   {
-    double Lm[6][6];
+    constexpr int NF = 2 * P::deg - 1;  // forms tr(M_q E_u C^q B^-1 E_v), q < NF
+    double C2[9], N[NF][9], M[NF][9], Y[9], Yt[9];
+    if constexpr (P::deg >= 2) mm_sym(b.C, b.C, C2);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) N[0][i] = b.Binv[i];
+#pragma unroll
+    for (int q = 1; q < NF; ++q) mm_sym(b.C, N[q - 1], N[q]);
+    mm(b.T, b.Binv, Y);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) Yt[i] = Y[3 * (i % 3) + i / 3];
+#pragma unroll
+    for (int q = 0; q < NF; ++q)
+#pragma unroll
+      for (int i = 0; i < 9; ++i) M[q][i] = 0.0;
+#pragma unroll
+    for (int v = 0; v < 6; ++v)
+#pragma unroll
+      for (int i = 0; i < 6; ++i) dh[v][i] = 0.0;
+#pragma unroll
+    for (int p = 0; p < P::deg; ++p) {
+      double A[9], YA[9];
+      hencky_factor<PD>(p, b.C, C2, b.H, A);
+#pragma unroll
+      for (int v = 0; v < 6; ++v)
+#pragma unroll
+        for (int i = 0; i < 6; ++i) dh[v][i] += sandwich(A, N[p], v, BA(i), BB(i));
+      // Y : (dH_u dB_v), dB_v = sum_r Bc_r E_v C^r: M_(p+r) += Bc_r Y^T A_p
+      mm(Yt, A, YA);
+#pragma unroll
+      for (int r = 0; r < P::deg; ++r) {
+        axpy_c<9>(P::b(r + 1), YA, M[p + r]);
+        if (r + 2 <= P::deg) {
+          double X[9];
+          mm(b.C, YA, X);
+          axpy_c<9>(P::b(r + 2), X, M[p + r]);
+        }
+        if (r + 3 <= P::deg) {
+          double X[9];
+          mm(C2, YA, X);
+          axpy_c<9>(P::b(r + 3), X, M[p + r]);
+        }
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < 6; ++v)
+#pragma unroll
+      for (int i = 3; i < 6; ++i) dh[v][i] *= 2.0;
+    // Y : (d2A - H d2B) = Zt : (E_u E_v + E_v E_u) + Z3 : (E_u C E_v + E_v C E_u), Z_p = a_p Y - b_p H Y
+    double Zt[9], Z3[9];  // transposed
+    if constexpr (P::deg >= 2) {
+      double YtH[9];
+      mm(Yt, b.H, YtH);
+#pragma unroll
+      for (int i = 0; i < 9; ++i) Zt[i] = P::a(2) * Yt[i] - P::b(2) * YtH[i];
+      if constexpr (P::deg >= 3) {
+        double ZC[9], CZ[9];
+#pragma unroll
+        for (int i = 0; i < 9; ++i) Z3[i] = P::a(3) * Yt[i] - P::b(3) * YtH[i];
+        mm(Z3, b.C, ZC);
+        mm(b.C, Z3, CZ);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) Zt[i] += ZC[i] + CZ[i];
+      }
+    }
+    phase(dh);
+    phase(M);
+    double Lm[21];  // mixed stiffness
+    PhaseCard& cl = phase(cd);
 #pragma unroll
     for (int i = 0; i < 6; ++i)
 #pragma unroll
-      for (int j = 0; j < 6; ++j) {
-        double s = cd.L0[i][j];
+      for (int j = i; j < 6; ++j) {
+        double s = cl.L0[i][j];
 #pragma unroll
-        for (int k = 0; k < NV; ++k) s += eh[k] * cd.dL[k][i][j];
-        Lm[i][j] = s;
+        for (int k = 0; k < NV; ++k) s += eh[k] * cl.dL[k][i][j];
+        Lm[eidx(i, j)] = s;
       }
-    // T : d2H_uv = Y : (d2A - H d2B) - V_u : dB_v - V_v : dB_u with Y = T B^-1,
-    // V_u = dH_u Y.  Y : (d2A - H d2B) = Zt : (E_u E_v + E_v E_u)
-    // + Z_3 : (E_u C E_v + E_v C E_u) with Z_p = a_p Y - b_p H Y and
-    // Zt = Z_2 + Z_3 C + C Z_3;  V : dB_v = Vt : E_v with
-    // Vt = b_1 V + b_2 (CV + VC) + b_3 (V C^2 + C V C + C^2 V).
-    double Tf[9], Ts[6] = {b.T[0], b.T[1], b.T[2], b.T[3], b.T[4], b.T[5]};
-    full_from_sym(Ts, Tf);
-    double Y[9], HY[9], Zt[9], Z3[9], C2[9];
-    mm(Tf, b.Binv, Y);
-    mm(b.H, Y, HY);
-    if constexpr (P::deg >= 2) {
-#pragma unroll
-      for (int i = 0; i < 9; ++i) Zt[i] = P::a(2) * Y[i] - P::b(2) * HY[i];
-    }
-    if constexpr (P::deg >= 3) {
-      double ZC[9], CZ[9];
-#pragma unroll
-      for (int i = 0; i < 9; ++i) Z3[i] = P::a(3) * Y[i] - P::b(3) * HY[i];
-      mm(Z3, b.C, ZC);
-      mm(b.C, Z3, CZ);
-#pragma unroll
-      for (int i = 0; i < 9; ++i) Zt[i] += ZC[i] + CZ[i];
-      mm(b.C, b.C, C2);
-    }
-    double vt[6][6];
-#pragma unroll
-    for (int u = 0; u < 6; ++u) {
-      double dHs[6] = {b.dh[u][0], b.dh[u][1], b.dh[u][2],
-                       0.5 * b.dh[u][3], 0.5 * b.dh[u][4], 0.5 * b.dh[u][5]};
-      double dHf[9], V[9], Vt[9];
-      full_from_sym(dHs, dHf);
-      mm(dHf, Y, V);
-#pragma unroll
-      for (int i = 0; i < 9; ++i) Vt[i] = P::b(1) * V[i];
-      if constexpr (P::deg >= 2) {
-        double CV[9], VC[9];
-        mm(b.C, V, CV);
-        mm(V, b.C, VC);
-#pragma unroll
-        for (int i = 0; i < 9; ++i) Vt[i] += P::b(2) * (CV[i] + VC[i]);
-        if constexpr (P::deg >= 3) {
-          double VC2[9], CVC[9], C2V[9];
-          mm(V, C2, VC2);
-          mm(CV, b.C, CVC);
-          mm(C2, V, C2V);
-#pragma unroll
-          for (int i = 0; i < 9; ++i) Vt[i] += P::b(3) * (VC2[i] + CVC[i] + C2V[i]);
-        }
-      }
-#pragma unroll
-      for (int v = 0; v < 6; ++v) vt[u][v] = contract_basis(Vt, v);
-    }
 #pragma unroll
     for (int u = 0; u < 6; ++u) {
       double LdH[6];
@@ -683,240 +660,252 @@ __device__ __forceinline__ void local_hessian(const double F[9], const double eh
       for (int i = 0; i < 6; ++i) {
         double s = 0.0;
 #pragma unroll
-        for (int j = 0; j < 6; ++j) s += Lm[i][j] * b.dh[u][j];
+        for (int j = 0; j < 6; ++j) s += Lm[eidx(i, j)] * dh[u][j];
         LdH[i] = s;
       }
+      phase(LdH);
 #pragma unroll
       for (int v = 0; v <= u; ++v) {
         double s = 0.0;
 #pragma unroll
-        for (int i = 0; i < 6; ++i) s += b.dh[v][i] * LdH[i];
-        double zd = 0.0;
-        if constexpr (P::deg >= 2) {
-          double Eu[9], Ev[9], P1[9], P2[9];
-          basis(u, Eu);
-          basis(v, Ev);
-          mm(Eu, Ev, P1);
-          mm(Ev, Eu, P2);
+        for (int i = 0; i < 6; ++i) s += dh[v][i] * LdH[i];
 #pragma unroll
-          for (int i = 0; i < 9; ++i) zd += Zt[i] * (P1[i] + P2[i]);
-          if constexpr (P::deg >= 3) {
-            double EC[9], ECE1[9], ECE2[9];
-            mm(Eu, b.C, EC);
-            mm(EC, Ev, ECE1);
-            mm(Ev, b.C, EC);
-            mm(EC, Eu, ECE2);
-#pragma unroll
-            for (int i = 0; i < 9; ++i) zd += Z3[i] * (ECE1[i] + ECE2[i]);
-          }
+        for (int q = 0; q < NF; ++q) s -= bilinear(M[q], N[q], u, v) + bilinear(M[q], N[q], v, u);
+        if constexpr (P::deg >= 2) {  // tr(Z^T (E_u E_v + E_v E_u)): one factor the identity
+          const int a = BA(u), bb = BB(u), c = BA(v), d = BB(v);
+          auto one = [&](int i, int j, int k2, int l) {  // tr(Zt e_i e_j^T e_k e_l^T)
+            if (j == k2) s += Zt[3 * l + i];
+          };
+          auto prod = [&](int i, int j, int k2, int l, bool ss, bool tt) {
+            one(i, j, k2, l);
+            if (ss) one(j, i, k2, l);
+            if (tt) one(i, j, l, k2);
+            if (ss && tt) one(j, i, l, k2);
+          };
+          prod(a, bb, c, d, u >= 3, v >= 3);
+          prod(c, d, a, bb, v >= 3, u >= 3);
         }
-        const double val = s + zd - vt[u][v] - vt[v][u];
-        wCC[u][v] = val;
-        wCC[v][u] = val;
+        if constexpr (P::deg >= 3) s += bilinear(Z3, b.C, u, v) + bilinear(Z3, b.C, v, u);
+        wCC[eidx(v, u)] = s;
       }
     }
+  }
+  phase(wCC);
+  // ---- Green-strain space: D_ee = J_t dC_u : w_CC : dC_v along eps --------------
+  {
+    double Me[6][6], Dee[21];  // Me[w]: dC along eps_w (2 G E_w G, shear G E_w G)
 #pragma unroll
-    for (int k = 0; k < NV; ++k) {
-      double dLh[6];
+    for (int w = 0; w < 6; ++w)
 #pragma unroll
       for (int i = 0; i < 6; ++i) {
-        double s = 0.0;
-#pragma unroll
-        for (int j = 0; j < 6; ++j) s += cd.dL[k][i][j] * b.h[j];
-        dLh[i] = s;
+        const double m = sandwich(b.G, b.G, w, BA(i), BB(i));
+        Me[w][i] = w < 3 ? 2.0 * m : m;
       }
 #pragma unroll
-      for (int v = 0; v < 6; ++v) {
+    for (int w = 0; w < 6; ++w) {
+      double col[6];
+#pragma unroll
+      for (int u = 0; u < 6; ++u) {
         double s = 0.0;
 #pragma unroll
-        for (int i = 0; i < 6; ++i) s += dLh[i] * b.dh[v][i];
-        wCeta[v][k] = s;
+        for (int i = 0; i < 6; ++i) s += wCC[eidx(u, i)] * Me[w][i];
+        col[u] = b.Jt * s;
       }
+#pragma unroll
+      for (int u = 0; u <= w; ++u) {
+        double s = 0.0;
+#pragma unroll
+        for (int i = 0; i < 6; ++i) s += Me[u][i] * col[i];
+        Dee[eidx(u, w)] = s;
+      }
+#pragma unroll
+      for (int u = 0; u <= w; ++u) phase(Dee[eidx(u, w)]);
     }
+    out.strain(S, Dee);
   }
-  // ---- chain rule ---------------------------------------------------------
-  // Few arrays stay live: dC along F is rebuilt from F G and G when needed,
-  // Q_k = G dU_k from the card, and the eta-eta products pair by pair.
-  // S: symmetric tensor with S : dC = sum_v wC_v dc_v
-  double Sf[9];
+  
+  // ---- F^t space ---------------------------------------------------------------
+  double X[21];     // second derivative along F^t at fixed L, / J_t
+  double Te[6][6];  // [v][w]: mixed (F^t_v, eps_w), / J_t
+  double gam[6];    // tr(G E_v)
   {
-    double Ss[6] = {b.wC[0], b.wC[1], b.wC[2], 0.5 * b.wC[3], 0.5 * b.wC[4], 0.5 * b.wC[5]};
-    full_from_sym(Ss, Sf);
-  }
-  double GSG[9];
-  {
-    double GS[9];
-    mm(b.G, Sf, GS);
-    mm(GS, b.G, GSG);
-  }
-  // per eta_k: dC (dce), dw/deta_k (wqe), dJ_t (Jq)
-  double dce[NV][6], wqe[NV], Jq[NV];
-#pragma unroll
-  for (int k = 0; k < NV; ++k) {
-    double Q[9], dcf[9];
-    Q_of(b, cd, k, Q);
-    Jq[k] = b.Jt * (Q[0] + Q[4] + Q[8]);
-    dC_eta(b, Q, dce[k], dcf);
-    double s = b.wEta[k];
-#pragma unroll
-    for (int v = 0; v < 6; ++v) s += b.wC[v] * dce[k][v];
-    wqe[k] = s;
-    g[9 + k] = b.Jt * wqe[k] + Jq[k] * b.w;
-  }
-  // eta-eta block
-  double eta[NV + 1], etan[NV + 1];
-  {
-    double s = 0.0, sn = 0.0;
-#pragma unroll
-    for (int k = 0; k < NV; ++k) { eta[k + 1] = eh[k]; etan[k + 1] = ehn[k]; s += eh[k]; sn += ehn[k]; }
-    eta[0] = 1.0 - s;
-    etan[0] = 1.0 - sn;
-  }
-  const double pen0 = (eta[0] < 0.0) ? cd.eps : 0.0;
-  // Runtime (not unrolled) loops over the pairs k <= l: unrolled, the
-  // compiler keeps every Q_l product of all pairs live at once.  Values of
-  // the per-eta register arrays are picked by static-index selection.
-#pragma unroll 1
-  for (int k = 0; k < NV; ++k) {
-    double Qk[9], SQ[9], Rk[9], Uk[9], WCk[6], dk[6], wek[6];
-    Q_of(b, cd, k, Qk);
-    mm(Sf, Qk, SQ);
-    mm(b.C, SQ, Rk);  // C S Q_k
-    mm(SQ, b.C, Uk);  // S Q_k C
+    double Nv[6][6];  // [v]: dC along F^t_v, -(G E_v C + C E_v G)
+    double A1[9], P2[9], wC[6], wq[6];
+    mm(b.Sf, b.G, A1);
+    mm_sym(b.G, A1, P2);
 #pragma unroll
     for (int v = 0; v < 6; ++v) {
-      dk[v] = pick_row(k, dce, v);
-      wek[v] = pick(k, wCeta[v]);
-    }
+      const int a = BA(v), c = BB(v);
+      gam[v] = v < 3 ? b.G[3 * a + c] : 2.0 * b.G[3 * a + c];
+      wC[v] = v < 3 ? b.Sf[3 * a + c] : 2.0 * b.Sf[3 * a + c];
+      wq[v] = v < 3 ? -2.0 * b.B1[3 * a + c] : -2.0 * (b.B1[3 * a + c] + b.B1[3 * c + a]);
 #pragma unroll
-    for (int u = 0; u < 6; ++u) {
-      double s = 0.0;
-#pragma unroll
-      for (int v = 0; v < 6; ++v) s += wCC[u][v] * dk[v];
-      WCk[u] = s;
+      for (int i = 0; i < 6; ++i)
+        Nv[v][i] = -(sandwich(b.G, b.C, v, BA(i), BB(i)) + sandwich(b.C, b.G, v, BA(i), BB(i)));
     }
-    const double trk = Qk[0] + Qk[4] + Qk[8];
-    const double Jqk = pick(k, Jq);
-    const double wqk = pick(k, wqe);
-    const double etak = pick_n<NV>(k, eta + 1);
-#pragma unroll 1
-    for (int l = k; l < NV; ++l) {
-      double Ql[9], SQl[9], Rl[9], dl[6], wel[6];
-      Q_of(b, cd, l, Ql);
-      mm(Sf, Ql, SQl);
-      mm(b.C, SQl, Rl);  // C S Q_l
+    phase(Nv);
+#pragma unroll
+    for (int v = 0; v < 6; ++v) {
+      double wN[6];
+#pragma unroll
+      for (int u = 0; u < 6; ++u) {
+        double s = 0.0;
+#pragma unroll
+        for (int i = 0; i < 6; ++i) s += wCC[eidx(u, i)] * Nv[v][i];
+        wN[u] = s;
+      }
+#pragma unroll
+      for (int u = 0; u <= v; ++u) {
+        double s = 0.0;
+#pragma unroll
+        for (int i = 0; i < 6; ++i) s += Nv[u][i] * wN[i];
+        s += 2.0 * (bilinear(b.B1, b.G, u, v) + bilinear(b.B1, b.G, v, u) + bilinear(P2, b.C, u, v));
+        s += gam[u] * wq[v] + gam[v] * wq[u] + (gam[u] * gam[v] - bilinear(b.G, b.G, u, v)) * b.w;
+        X[eidx(u, v)] = s;
+      }
+      // w_CC dC_v - 2 (Sf G E_v) : E_u + tr(G E_v) w_C
+#pragma unroll
+      for (int u = 0; u < 6; ++u) {
+        const int a = BA(u), c = BB(u), p = BA(v), q = BB(v);
+        double t = 0.0;  // (A1 E_v)_ij = A1_ip [j == q] (+ A1_iq [j == p])
+        if (c == q) t += A1[3 * a + p];
+        if (v >= 3 && c == p) t += A1[3 * a + q];
+        if (u >= 3) {
+          if (a == q) t += A1[3 * c + p];
+          if (v >= 3 && a == p) t += A1[3 * c + q];
+        }
+        wN[u] += gam[v] * wC[u] - 2.0 * t;
+      }
+      to_strain(b.G, wN, Te[v]);
+      phase(Te[v]);
+#pragma unroll
+      for (int u = 0; u <= v; ++u) phase(X[eidx(u, v)]);
+    }
+  }
+  // ---- order parameters ----------------------------------------------------
+  const double eta0 = [&] {
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) s += eh[k];
+    return 1.0 - s;
+  }();
+  const double pen0 = (eta0 < 0.0) ? cd.eps : 0.0;
+  double Y[NV][6];  // mixed (F^t_v, L through eta_k), / J_t
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    double wCe[6], d[6], z[6];  // wCe: mixed (C along E_v, L through eta_k)
+    PhaseCard& ck = phase(cd);
+    {
+      double dLh[6];
+      voigt_product(ck.dL[k], b.h, dLh);
 #pragma unroll
       for (int v = 0; v < 6; ++v) {
-        dl[v] = pick_row(l, dce, v);
-        wel[v] = pick(l, wCeta[v]);
+        double s = 0.0;
+#pragma unroll
+        for (int i = 0; i < 6; ++i) s += dLh[i] * dh[v][i];
+        wCe[v] = s;
       }
+    }
+    to_strain(b.G, wCe, d);
+#pragma unroll
+    for (int w = 0; w < 6; ++w) {
+      double s = d[w];
+#pragma unroll
+      for (int v = 0; v < 6; ++v) s += Te[v][w] * dm(ck, k, v);
+      d[w] = b.Jt * s;
+    }
+    out.eps_eta(k, d);
+    {  // sum_i (dC along F^t_v)_i wCe_i = -2 sym(G q C) : E_v
+      const double Q[9] = {wCe[0], 0.5 * wCe[5], 0.5 * wCe[4], 0.5 * wCe[5], wCe[1],
+                           0.5 * wCe[3], 0.5 * wCe[4], 0.5 * wCe[3], wCe[2]};
+      double GQ[9], R[9];
+      mm(b.G, Q, GQ);
+      mm(GQ, b.C, R);
+#pragma unroll
+      for (int v = 0; v < 6; ++v) {
+        const int i = BA(v), j = BB(v);
+        Y[k][v] = b.wEta[k] * gam[v] - 2.0 * (v < 3 ? R[3 * i + j] : R[3 * i + j] + R[3 * j + i]);
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < 6; ++v) {
+      double s = Y[k][v];
+#pragma unroll
+      for (int i = 0; i < 6; ++i) s += X[eidx(v, i)] * dm(ck, k, i);
+      z[v] = s;
+    }
+#pragma unroll
+    for (int l = 0; l <= k; ++l) {
       double s = 0.0;
 #pragma unroll
-      for (int u = 0; u < 6; ++u) s += WCk[u] * dl[u];
-      s += 2.0 * (trprod(Rk, Ql) + trprod(Rl, Qk) + ddot9(Uk, Ql));
-#pragma unroll
-      for (int v = 0; v < 6; ++v) s += wel[v] * dk[v] + wek[v] * dl[v];
-      const double trl = Ql[0] + Ql[4] + Ql[8];
-      const double Jkl = b.Jt * (trk * trl - trprod(Qk, Ql));
-      const double Jql = pick(l, Jq);
-      const double wql = pick(l, wqe);
-      double val = b.Jt * s + Jqk * wql + Jql * wqk + Jkl * b.w;
-      if constexpr (MIX == 1) {
-        // second derivative of F^t (nonzero under logarithmic mixing):
-        // d2C gains -(Q_kl C + C Q_kl^T) and d2J_t gains J_t tr Q_kl, with
-        // Q_kl = G d2F^t/deta_k deta_l
-        double S2[9], Qkl[9], dckl[6], dcfkl[9];
+      for (int v = 0; v < 6; ++v) s += dm(ck, l, v) * z[v] + dm(ck, k, v) * Y[l][v];
+      double val = b.Jt * s;
+      if constexpr (MIX == 1) {  // second derivative of F^t
+        double S2[9], S2s[6];
         log_mixing_second(eh, cd, k, l, S2);
-        mm(b.G, S2, Qkl);
-        dC_eta(b, Qkl, dckl, dcfkl);
-        double wkl = 0.0;
+        sym_of(S2, S2s);
 #pragma unroll
-        for (int v = 0; v < 6; ++v) wkl += b.wC[v] * dckl[v];
-        val += b.Jt * (wkl + (Qkl[0] + Qkl[4] + Qkl[8]) * b.w);
+        for (int v = 0; v < 6; ++v) val += phi[v] * S2s[v];
       }
-      // order-parameter terms
-      val += cd.Sw[k][l] + cd.rho * ((k == l ? 1.0 : 0.0) + 1.0) + pen0;
-      if (k == l && etak < 0.0) val += cd.eps;
-      D[hidx(9 + k, 9 + l) * ds] = val;
+      val += ck.Sw[k][l] + ck.rho * ((k == l ? 1.0 : 0.0) + 1.0) + pen0;
+      if (k == l && eh[k] < 0.0) val += ck.eps;
+      out.eta_eta(k, l, val);
     }
+    phase(Y[k]);
   }
-  // F-eta block, runtime loop over k: with ak = wCeta[., k] - 2 (S Q_k) : E_.
-  // and wdk = wCC dC_k (wCC symmetric), entry (F_q, eta_k) is
-  // J_t (wdk + ak) . dC_q + dJ_t/deta_k  dw/dF_q
-#pragma unroll 1
-  for (int k = 0; k < NV; ++k) {
-    double Q[9], P[9], t[6];
-    Q_of(b, cd, k, Q);
-    mm(Sf, Q, P);  // S G dU_k
+}
+
+// Packed upper triangle of the Hessian in (F, eta), entry hidx(p, q) stored to
+// D[hidx(p, q) * ds + off]: D and ds uniform over the wavefront and a 32-bit
+// lane offset, so that the 120 addresses are scalar.
+struct PackedOut {
+  const double* F;
+  double* D;
+  int64_t ds;
+  uint32_t off;
+  double* g;
+  __device__ __forceinline__ void gradient(const double gr[NQ], const double*) const {
 #pragma unroll
-    for (int u = 0; u < 6; ++u) {
-      double wdk = 0.0;
+    for (int i = 0; i < NQ; ++i) g[i] = gr[i];
+  }
+  __device__ __forceinline__ void eps_eta(int k, const double d[6]) const {
 #pragma unroll
-      for (int v = 0; v < 6; ++v)
-        wdk += wCC[u][v] * pick_row(k, dce, v);
-      t[u] = wdk + pick(k, wCeta[u]) -
-             2.0 * contract_basis(P, u);
-    }
-    const double Jqk = pick(k, Jq);
+    for (int i = 0; i < 3; ++i)
 #pragma unroll
-    for (int q = 0; q < 9; ++q) {
-      double dcq[6];
-      dC_F(b, q, dcq);
-      double wq = 0.0, s = 0.0;
+      for (int j = 0; j < 3; ++j)
+        (D + hidx(3 * i + j, 9 + k) * ds)[off] =
+            F[3 * i] * d[SI(0, j)] + F[3 * i + 1] * d[SI(1, j)] + F[3 * i + 2] * d[SI(2, j)];
+  }
+  __device__ __forceinline__ void eta_eta(int k, int l, double v) const { (D + hidx(9 + l, 9 + k) * ds)[off] = v; }
+  // F-F block from D_ee and the stress
+  __device__ __forceinline__ void strain(const double S[6], const double Dee[21]) const {
 #pragma unroll
-      for (int v = 0; v < 6; ++v) {
-        wq += b.wC[v] * dcq[v];
-        s += t[v] * dcq[v];
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+      for (int l = 0; l < 3; ++l) {
+        double t[6];
+#pragma unroll
+        for (int u = 0; u < 6; ++u)
+          t[u] = Dee[eidx(u, SI(0, l))] * F[3 * k] + Dee[eidx(u, SI(1, l))] * F[3 * k + 1] +
+                 Dee[eidx(u, SI(2, l))] * F[3 * k + 2];
+#pragma unroll
+        for (int i = 0; i <= k; ++i)
+#pragma unroll
+          for (int j = 0; j < 3; ++j) {
+            if (3 * i + j > 3 * k + l) continue;
+            double s = F[3 * i] * t[SI(0, j)] + F[3 * i + 1] * t[SI(1, j)] + F[3 * i + 2] * t[SI(2, j)];
+            if (i == k) s += S[SI(j, l)];
+            (D + hidx(3 * i + j, 3 * k + l) * ds)[off] = s;
+          }
       }
-      D[hidx(q, 9 + k) * ds] = b.Jt * s + Jqk * wq;
-    }
   }
-  // F-F block and the F part of the gradient
-#pragma unroll
-  for (int q = 0; q < 9; ++q) {
-    double dcq[6];
-    dC_F(b, q, dcq);
-    double wq = 0.0;
-#pragma unroll
-    for (int v = 0; v < 6; ++v) wq += b.wC[v] * dcq[v];
-    g[q] = b.Jt * wq;
-    double WCq[6];
-#pragma unroll
-    for (int u = 0; u < 6; ++u) {
-      double s = 0.0;
-#pragma unroll
-      for (int v = 0; v < 6; ++v) s += wCC[u][v] * dcq[v];
-      WCq[u] = s;
-    }
-    const int i = q / 3, j = q % 3;
-#pragma unroll
-    for (int r = q; r < 9; ++r) {
-      double dcr[6];
-      dC_F(b, r, dcr);
-      double s = 0.0;
-#pragma unroll
-      for (int u = 0; u < 6; ++u) s += WCq[u] * dcr[u];
-      const int k = r / 3, l = r % 3;
-      if (i == k) s += 2.0 * GSG[3 * j + l];
-      D[hidx(q, r) * ds] = b.Jt * s;
-    }
-  }
-  // order-parameter gradient terms
-  double We[NV + 1];
-#pragma unroll
-  for (int i = 0; i < NV + 1; ++i) {
-    double t = 0.0;
-#pragma unroll
-    for (int j = 0; j < NV + 1; ++j) t += cd.W[i][j] * eta[j];
-    We[i] = t;
-  }
-  const double d0 = eta[0] - etan[0];
-  const double n0 = neg_part(eta[0]);
-#pragma unroll
-  for (int k = 0; k < NV; ++k) {
-    g[9 + k] += cd.dF0[k] + (We[k + 1] - We[0]) + cd.rho * ((eta[k + 1] - etan[k + 1]) - d0)
-                + cd.eps * (neg_part(eta[k + 1]) - n0);
-  }
+};
+
+template <int PD, int MIX = 0>
+__device__ __forceinline__ void local_hessian_packed(const double F[9], const double eh[NV], const double ehn[NV],
+                                                     const DevCard& cd, double g[NQ], double* __restrict__ D,
+                                                     int64_t ds, uint32_t off) {
+  local_hessian<PD, MIX>(F, eh, ehn, cd, PackedOut{F, D, ds, off, g});
 }
 
 }  // namespace mvpf

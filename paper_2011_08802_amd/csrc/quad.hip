@@ -82,15 +82,15 @@ __device__ __forceinline__ void qp_body(const Grid& g, const Chunk& ck, const do
     }
   }
   const int64_t stride = (int64_t)8 * ck.NEcpad;
-  double* out = qp + (int64_t)gp * ck.NEcpad + el;
+  const uint32_t off = (uint32_t)gp * (uint32_t)ck.NEcpad + (uint32_t)el;  // < 8 NEcpad
   double gr[NQ];
   if (HESS) {
-    local_hessian<PD, MIX>(F, eh, ehn, *cd, gr, out + (int64_t)NQ * stride, stride);
+    local_hessian_packed<PD, MIX>(F, eh, ehn, *cd, gr, qp + (int64_t)NQ * stride, stride, off);
   } else {
     local_gradient<PD, MIX>(F, eh, ehn, *cd, gr);
   }
 #pragma unroll
-  for (int c = 0; c < NQ; ++c) out[(int64_t)c * stride] = gr[c];
+  for (int c = 0; c < NQ; ++c) (qp + (int64_t)c * stride)[off] = gr[c];
 }
 template <bool HESS, int PD, int MIX>
 __global__ void __launch_bounds__(128) qp_kernel(Grid g, Chunk ck, const double* __restrict__ state,
