@@ -1207,6 +1207,21 @@ int setup_enqueue(mvpf_problem* p) {
 
 // after the problem's stream has been synchronised
 int setup_finish(mvpf_problem* p) {
+  if (*host_status(p) == GJ_REJECTED) {
+    // the coarsest operator's block elimination failed its check: invert it
+    // with pivoting over all rows (its dense copy is untouched)
+    hipStream_t s = p->stream;
+    Level& C = p->lev[p->L - 1];
+    const int nd = C.ndense;
+    double* work = coarse_dense(p);
+    HIPCHK(hipMemsetAsync(setup_status(p), 0, sizeof(int), s));
+    if (dense_invert_pivoted(nd, work, C.Ainv, work + (int64_t)nd * nd, setup_status(p), s) != 0) {
+      p->err = "coarse inversion launch failed";
+      return MVPF_EDEVICE;
+    }
+    HIPCHK(hipMemcpyAsync(host_status(p), setup_status(p), sizeof(int), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+  }
   if (*host_status(p)) {
     p->err = "singular 9x9 diagonal block or coarse operator";
     return MVPF_ESINGULAR;
@@ -1424,7 +1439,6 @@ struct mvpf_batch {
   hipEvent_t enter = nullptr, leave = nullptr;
   // the coarsest-level inversions of all problems as one batched inversion
   mvpf::GJJob* gj_tab = nullptr;
-  int* gj_sel = nullptr;
   std::vector<int> gj_n;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -2209,7 +2223,7 @@ int batch_assemble(mvpf_batch* b, const double* depths, hipStream_t s) {
     // after the assembly so that the host feeds the assembly stream first
     host([b]() -> int {
       BCHK(hipStreamWaitEvent(b->work, b->fork, 0));
-      if (dense_invert_batch(b->gj_tab, b->gj_sel, b->gj_n, b->work) != 0) {
+      if (dense_invert_batch(b->gj_tab, b->gj_n, b->work) != 0) {
         b->err = "batched coarse inversion launch failed";
         return MVPF_EDEVICE;
       }
@@ -2268,7 +2282,6 @@ void batch_free(mvpf_batch* b) {
   if (b->enter) (void)hipEventDestroy(b->enter);
   if (b->leave) (void)hipEventDestroy(b->leave);
   if (b->gj_tab) (void)hipFree(b->gj_tab);
-  if (b->gj_sel) (void)hipFree(b->gj_sel);
   if (b->jobs_dev) (void)hipFree(b->jobs_dev);
   b->jobs_dev = nullptr;
   b->jobs_cap = 0;
@@ -2286,7 +2299,6 @@ void batch_free(mvpf_batch* b) {
   b->gjobs_host = nullptr;
   b->bcol_host = nullptr;
   b->gj_tab = nullptr;
-  b->gj_sel = nullptr;
   if (b->work) {
     (void)hipStreamSynchronize(b->work);
     (void)hipStreamDestroy(b->work);
@@ -3055,11 +3067,8 @@ int mvpf_create_batch(int n, const mvpf_mesh* meshes, const mvpf_material* mats,
       tab[i] = gj_make_job(nd, work, C.Ainv, work + (int64_t)nd * nd, setup_status(p));
       b->gj_n[i] = nd;
     }
-    const std::vector<int> sel = dense_invert_batch_selection(b->gj_n);
     if (hipMalloc((void**)&b->gj_tab, sizeof(GJJob) * n) != hipSuccess ||
-        hipMalloc((void**)&b->gj_sel, sizeof(int) * n) != hipSuccess ||
-        hipMemcpy(b->gj_tab, tab.data(), sizeof(GJJob) * n, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(b->gj_sel, sel.data(), sizeof(int) * n, hipMemcpyHostToDevice) != hipSuccess) {
+        hipMemcpy(b->gj_tab, tab.data(), sizeof(GJJob) * n, hipMemcpyHostToDevice) != hipSuccess) {
       g_create_err = "batch job tables failed";
       rc = MVPF_ENOMEM;
     }
@@ -3137,7 +3146,7 @@ int mvpf_batch_newton_system(mvpf_batch* b, const double* depths) {
     // every problem's dense coarse matrix is ready; each problem's setup waits
     if (rc == 0) {
       for (int i = 0; i < b->n; ++i) BCHK(hipStreamWaitEvent(b->work, b->probs[i]->ev_fork, 0));
-      if (dense_invert_batch(b->gj_tab, b->gj_sel, b->gj_n, b->work) != 0) {
+      if (dense_invert_batch(b->gj_tab, b->gj_n, b->work) != 0) {
         b->err = "batched coarse inversion launch failed";
         rc = MVPF_EDEVICE;
       }

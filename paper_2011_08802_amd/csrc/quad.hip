@@ -514,7 +514,7 @@ __device__ __forceinline__ void block_inverse_regs(const Grid& g, const double* 
 #pragma unroll
     for (int m = 0; m < NDOF; ++m) dst[m] = dst[m] == k ? p : (dst[m] == p ? k : dst[m]);
   }
-  if (n < g.N && !ok) atomicOr(status, 1);
+  if (n < g.N && !ok) atomicOr(status, SETUP_SINGULAR);
 #pragma unroll
   for (int r = 0; r < NDOF; ++r)
 #pragma unroll
@@ -564,7 +564,7 @@ __device__ __forceinline__ void block_inverse_lds(const Grid& g, const double* _
           for (int cc = 0; cc < 2 * NDOF; ++cc) MM(r, cc) -= f * MM(c, cc);
       }
     }
-    if (!ok) atomicOr(status, 1);
+    if (!ok) atomicOr(status, SETUP_SINGULAR);
   }
   for (int e = 0; e < NBLK; ++e) {
     const double v = ok ? MM(e / NDOF, NDOF + e % NDOF) : 0.0;

@@ -1,0 +1,45 @@
+"""Kernels and dispatch branches at the sizes where they can go wrong, against
+the oracle (same tolerances as test_gpu_parity.py)."""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+
+import synth
+from gpu_util import OracleCase, gpu_problem, rel, seeded_state
+from test_gpu_parity import _coarse_case, _dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("nx,ny,nz,coarse_dof", [(2, 2, 2, 72), (6, 6, 6, 576), (4, 4, 36, 1539)])
+def test_coarse_block_elimination_sizes(nx, ny, nz, coarse_dof):
+    """The blocked inversion at a size of one full and one partial 64-unknown
+    block, of whole blocks only, and just above the 24 blocks up to which a
+    step is one launch: coarse operator, V-cycle and FGMRES solve vs the
+    oracle."""
+    h = 1.0 / max(nx, ny, nz)
+    p = synth.Problem(nx, ny, nz, lx=nx * h, ly=ny * h, lz=nz * h, n_levels=2, patch=2, depth_increment=0.01)
+    _coarse_case(p, 2, coarse_dof, f"{nx}x{ny}x{nz} L2")
+
+
+def test_coarse_inverse_of_an_indefinite_operator():
+    """An austenite with c11 < c12 (negative tetragonal shear modulus) makes
+    the operators indefinite (about a quarter of the coarsest level's
+    eigenvalues are negative), and the elimination with pivoting inside 64 x 64
+    blocks loses digits: its check sends the matrix to the elimination with
+    pivoting over all rows.  The V-cycle, which contains that inverse, agrees
+    with the oracle's LU; condition 1.4e6."""
+    nx, ny, nz = 6, 8, 10
+    h = 1.0 / nz
+    p = synth.Problem(nx, ny, nz, lx=nx * h, ly=ny * h, lz=nz * h, n_levels=2, patch=4, depth_increment=0.01)
+    p = replace(p, material=replace(p.material, cubic=(60.0, 126.0, 96.0)))
+    U, En = seeded_state(p, 5e-4)
+    oc = OracleCase(p, U, En, p.depth_increment, direct=False)
+    v = np.random.default_rng(7).standard_normal(oc.sys.b.shape[0])
+    gp = gpu_problem(p, U, En, "fp64")
+    gp.newton_system(p.depth_increment)
+    z = gp.precondition(_dev(v)).cpu().numpy()
+    zo = oc.mg.precondition(v)
+    assert rel(z, zo) < 1e-10, rel(z, zo)
+    gp.close()
