@@ -460,11 +460,12 @@ double stored_blocks(const Grid& g) { return 0.5 * (stencil_blocks(g) + g.N); }
 
 // Algorithmic bytes of one damped point-block Jacobi sweep on level g:
 // the operator (stored half-stencil blocks, or on a matrix-free level the
-// 8 x 120 Gauss-point Hessian values per element), the block inverses, x, b
+// 8 x 93 Gauss-point tangent values per element), the block inverses, x, b
 // and the new x.
+constexpr double MF_VALUES = 8.0 * 93;
 template <typename T>
 double sweep_bytes(const Grid& g, bool mf) {
-  const double op = mf ? 960.0 * g.NE : stored_blocks(g) * NBLK;
+  const double op = mf ? MF_VALUES * g.NE : stored_blocks(g) * NBLK;
   const double dinv = (mf && sizeof(T) == 4) ? NSYM : NBLK;  // packed symmetric FP32 inverses
   return sizeof(T) * (op + (double)g.N * (dinv + 3 * NDOF));
 }
@@ -532,7 +533,7 @@ void vcycle(mvpf_problem* p, int l) {
     launch_defect<T>(L.g, opA<T>(L), (const T*)L.x, (const T*)L.b, (T*)L.r, p->Cbuf, s, p->row_G[l]);
   if (l == 0 && p->timing)
     timer_end(p, p->t_resid,
-              sizeof(T) * ((use_mf(p) ? 960.0 * L.g.NE : stored_blocks(L.g) * NBLK) + (double)L.g.N * 3 * NDOF));
+              sizeof(T) * ((use_mf(p) ? MF_VALUES * L.g.NE : stored_blocks(L.g) * NBLK) + (double)L.g.N * 3 * NDOF));
   Level& C = p->lev[l + 1];
   launch_restrict<T>(L.g, C.g, (const T*)L.r, C.mask, (T*)C.b, s);
   vcycle<T>(p, l + 1);
@@ -667,7 +668,7 @@ struct Krylov {
       launch_spmv<double, TZ, double>(g, p->lev[0].A64, zj(), w, p->Cbuf, s, p->outer_G);
     }
     if (p->timing)
-      timer_end(p, p->t_outer, 8.0 * (use_mf(p) ? 960.0 * g.NE : stored_blocks(g) * NBLK) +
+      timer_end(p, p->t_outer, 8.0 * (use_mf(p) ? MF_VALUES * g.NE : stored_blocks(g) * NBLK) +
                                    (double)g.N * NDOF * (sizeof(TZ) + sizeof(double)));
     launch_multidot(n, p->V, n, j + 1, w, p->red, s);
     launch_reduce(j + 1, nb, p->red, h1(), 0, s);
@@ -1095,6 +1096,20 @@ int finish_system(mvpf_problem* p, bool coarse_inline) {
   return 0;
 }
 
+// diagonal blocks of the matrix-free finest level from its Gauss-point
+// tangents, slab by slab where the element buffer does not hold the whole level
+int mf_diagonal(mvpf_problem* p, double depth) {
+  Level& L0 = p->lev[0];
+  const int64_t have = (int64_t)NPAIR * NBLK * p->ne_cap;
+  int64_t cap = L0.g.NEpad;
+  while (mf_diag_values(cap, L0.g.nx) > have) cap = cap / 2 / TILE * TILE;
+  cap = std::max<int64_t>(cap, std::min<int64_t>(p->ne_cap, L0.g.NEpad));
+  for (const Chunk& ck : make_chunks(L0.g, cap))
+    launch_mf_diag(L0.g, ck, p->Dmf64, p->card, p->elem, L0.diag64, p->stream);
+  if (contact(p)) launch_contact_diag(L0.g, make_sphere(L0.g, p->load, depth), L0.state, L0.diag64, p->stream);
+  return 0;
+}
+
 // Galerkin hierarchy (opts.coarse = MVPF_COARSE_GALERKIN, galerkin.hip): the
 // finest tangent's element matrices (all 36 node pairs, contact included)
 // are coarsened slab by slab into level 1's, each level's into the next's;
@@ -1116,11 +1131,11 @@ int build_system_galerkin(mvpf_problem* p, double depth, bool coarse_inline) {
     timer_begin(p, p->t_qp);
     launch_qp(L0.g, ck, L0.state, p->card, p->pade, p->mixing, p->qp, true, s);
     timer_end(p, p->t_qp, 8.0 * 8 * QP_HESS * (double)ck.NEc);
-    if (mf) launch_mf_pack(L0.g, ck, p->qp, p->Dmf64, p->Dmf32, s);
+    if (mf) launch_qp_mf(L0.g, ck, L0.state, p->card, p->pade, p->mixing, p->qp, p->Dmf64, p->Dmf32, s);
     launch_residual_gather(L0.g, ck, L0.state, p->qp, p->card, p->R, s);
-    launch_element_matrices(L0.g, ck, p->qp, p->card, p->elem, s, false);
-    if (contact(p)) launch_contact_element(L0.g, ck, make_sphere(L0.g, p->load, depth), L0.state, p->elem, s, false);
-    launch_jacobian_gather(L0.g, ck, p->elem, L0.A64, L0.A32, L0.diag64, s, mf);
+    launch_element_matrices(L0.g, ck, p->qp, p->card, p->elem, s);
+    if (contact(p)) launch_contact_element(L0.g, ck, make_sphere(L0.g, p->load, depth), L0.state, p->elem, s);
+    if (!mf) launch_jacobian_gather(L0.g, ck, p->elem, L0.A64, L0.A32, L0.diag64, s);
     // level-1 layers Z whose child layers 2Z and 2Z + 1 this slab holds (slabs
     // overlap by one element layer, so each layer is met in one of them)
     const int ez0 = (int)(ck.e0 / nxy), ez1 = (int)((ck.e0 + ck.NEc) / nxy);
@@ -1138,8 +1153,9 @@ int build_system_galerkin(mvpf_problem* p, double depth, bool coarse_inline) {
     p->err = "internal: coarse layers left out of the Galerkin product";
     return MVPF_EDEVICE;
   }
+  if (mf) TRY(mf_diagonal(p, depth));
   TRY(system_rhs(p, depth));
-  launch_apply_dirichlet(L0.g, L0.mask, L0.A64, L0.A32, L0.diag64, s);
+  launch_apply_dirichlet(L0.g, L0.mask, mf ? nullptr : L0.A64, mf ? nullptr : L0.A32, L0.diag64, s);
   auto whole = [](const Grid& g) { return Chunk{0, g.NE, g.NEpad, 0, g.Npad}; };
   for (int l = 1; l < Lc; ++l) {
     const Grid& g = p->lev[l].g;
@@ -1169,22 +1185,28 @@ int build_system(mvpf_problem* p, double depth, bool coarse_inline = true) {
   TRY(launch_check(p, "coarse assembly"));
   TRY(coarse_fork(p, coarse_inline));
   for (int l = Lc - 1; l >= 1; --l) assemble_coarse_level(p, l, depth);
-  // finest: residual and unconstrained tangent
+  // finest: residual and unconstrained tangent (on a matrix-free level the
+  // Gauss-point tangents and the diagonal blocks)
+  const bool mf = use_mf(p);
   for (const Chunk& ck : make_chunks(L0.g, p->ne_use)) {
     timer_begin(p, p->t_qp);
-    launch_qp(L0.g, ck, L0.state, p->card, p->pade, p->mixing, p->qp, true, s);
-    // written: gradient (15) and packed Hessian (120) per Gauss point
-    timer_end(p, p->t_qp, 8.0 * 8 * QP_HESS * (double)ck.NEc);
-    const bool mf = use_mf(p);  // only the diagonal blocks are assembled
-    if (mf) launch_mf_pack(L0.g, ck, p->qp, p->Dmf64, p->Dmf32, s);
+    if (mf)
+      launch_qp_mf(L0.g, ck, L0.state, p->card, p->pade, p->mixing, p->qp, p->Dmf64, p->Dmf32, s);
+    else
+      launch_qp(L0.g, ck, L0.state, p->card, p->pade, p->mixing, p->qp, true, s);
+    // written per Gauss point: gradient, and the packed Hessian or its Green-strain form
+    timer_end(p, p->t_qp, 8.0 * (double)ck.NEc *
+                              (mf ? 8 * NQ + MF_VALUES * (p->Dmf32 ? 1.5 : 1.0) : 8.0 * QP_HESS));
     launch_residual_gather(L0.g, ck, L0.state, p->qp, p->card, p->R, s);
-    launch_element_matrices(L0.g, ck, p->qp, p->card, p->elem, s, mf);
-    if (contact(p)) launch_contact_element(L0.g, ck, make_sphere(L0.g, p->load, depth), L0.state, p->elem, s, mf);
-    launch_jacobian_gather(L0.g, ck, p->elem, L0.A64, L0.A32, L0.diag64, s, mf);
+    if (mf) continue;
+    launch_element_matrices(L0.g, ck, p->qp, p->card, p->elem, s);
+    if (contact(p)) launch_contact_element(L0.g, ck, make_sphere(L0.g, p->load, depth), L0.state, p->elem, s);
+    launch_jacobian_gather(L0.g, ck, p->elem, L0.A64, L0.A32, L0.diag64, s);
   }
+  if (mf) TRY(mf_diagonal(p, depth));
   // lifting of the prescribed increment, then symmetric elimination
   TRY(system_rhs(p, depth));
-  launch_apply_dirichlet(L0.g, L0.mask, L0.A64, L0.A32, L0.diag64, s);
+  launch_apply_dirichlet(L0.g, L0.mask, mf ? nullptr : L0.A64, mf ? nullptr : L0.A32, L0.diag64, s);
   return finish_system(p, coarse_inline);
 }
 
@@ -2066,7 +2088,7 @@ struct AsmStep {
 int batch_assemble(mvpf_batch* b, const double* depths, hipStream_t s) {
   std::vector<AsmStep> steps;
   std::vector<AJob> all;
-  auto add = [&](int op, int pade, const std::vector<AJob>& jobs, const std::vector<char>& diag) {
+  auto add = [&](int op, int pade, const std::vector<AJob>& jobs) {
     if (jobs.empty()) return;
     AsmStep st;
     st.op = op;
@@ -2075,7 +2097,7 @@ int batch_assemble(mvpf_batch* b, const double* depths, hipStream_t s) {
     st.count = (int)jobs.size();
     for (size_t k = 0; k < jobs.size(); ++k) {
       AJob j = jobs[k];
-      j.nblk = assembly_job_blocks(op, j, !diag.empty() && diag[k]);
+      j.nblk = assembly_job_blocks(op, j);
       j.block0 = st.blocks;
       st.blocks += j.nblk;
       all.push_back(j);
@@ -2102,14 +2124,14 @@ int batch_assemble(mvpf_batch* b, const double* depths, hipStream_t s) {
     j.mask = L.mask;
     return j;
   };
-  auto qp_steps = [&](const std::vector<mvpf_problem*>& ps, const std::vector<AJob>& js) {
+  auto qp_steps = [&](int op, const std::vector<mvpf_problem*>& ps, const std::vector<AJob>& js) {
     for (int mix : {0, 1})
       for (int pd : {11, 22, 33}) {
         std::vector<AJob> sel;
         for (size_t k = 0; k < ps.size(); ++k)
           if ((ps[k]->pade == pd || (pd == 22 && ps[k]->pade != 11 && ps[k]->pade != 33)) && ps[k]->mixing == mix)
             sel.push_back(js[k]);
-        add(AOP_QP_HESS, pd + mix * QP_LOG_MIX, sel, {});
+        add(op, pd + mix * QP_LOG_MIX, sel);
       }
   };
   const int n = b->n;
@@ -2132,8 +2154,8 @@ int batch_assemble(mvpf_batch* b, const double* depths, hipStream_t s) {
       js.push_back(job(p, l));
       lv.push_back(l);
     }
-    qp_steps(ps, js);
-    add(AOP_ELEMENT, 0, js, {});
+    qp_steps(AOP_QP_HESS, ps, js);
+    add(AOP_ELEMENT, 0, js);
     for (size_t q = 0; q < ps.size(); ++q)
       if (contact(ps[q])) {
         mvpf_problem* p = ps[q];
@@ -2146,8 +2168,8 @@ int batch_assemble(mvpf_batch* b, const double* depths, hipStream_t s) {
           return 0;
         });
       }
-    add(AOP_GATHER, 0, js, {});
-    add(AOP_DIRICHLET, 0, js, {});
+    add(AOP_GATHER, 0, js);
+    add(AOP_DIRICHLET, 0, js);
     if (k == 0) {
       // every coarsest operator into its dense matrix (inverted below)
       host([b, s]() -> int {
@@ -2161,47 +2183,54 @@ int batch_assemble(mvpf_batch* b, const double* depths, hipStream_t s) {
       });
     }
   }
-  // finest level: only the diagonal blocks on matrix-free levels
+  // finest level: Gauss-point tangents and diagonal blocks on matrix-free
+  // levels, every stored block on the others
   {
-    std::vector<AJob> js, pk;
-    std::vector<char> diag;
+    std::vector<AJob> js, mj, aj;
+    std::vector<mvpf_problem*> mp, ap;
     for (mvpf_problem* p : b->probs) {
       AJob j = job(p, 0);
       j.R = p->R;
-      js.push_back(j);
-      diag.push_back(use_mf(p) ? 1 : 0);
       if (use_mf(p)) {
-        AJob q = j;
-        q.D64 = p->Dmf64;
-        q.D32 = p->Dmf32;
-        pk.push_back(q);
+        j.D64 = p->Dmf64;
+        j.D32 = p->Dmf32;
+        j.A64 = nullptr;
+        j.A32 = nullptr;
+        mj.push_back(j);
+        mp.push_back(p);
+      } else {
+        aj.push_back(j);
+        ap.push_back(p);
       }
+      js.push_back(j);
     }
-    qp_steps(b->probs, js);
-    add(AOP_MF_PACK, 0, pk, {});
-    add(AOP_RESIDUAL, 0, js, {});
-    add(AOP_ELEMENT, 0, js, diag);
+    qp_steps(AOP_QP_MF, mp, mj);
+    qp_steps(AOP_QP_HESS, ap, aj);
+    add(AOP_RESIDUAL, 0, js);
+    add(AOP_MF_DIAG, 0, mj);
+    add(AOP_ELEMENT, 0, aj);
+    add(AOP_MF_DIAG_GATHER, 0, mj);
     for (int i = 0; i < n; ++i)
       if (contact(b->probs[i])) {
         mvpf_problem* p = b->probs[i];
         const double d = depths[i];
         host([p, d] {
           Level& L0 = p->lev[0];
-          launch_contact_element(L0.g, make_chunks(L0.g, p->ne_use)[0], make_sphere(L0.g, p->load, d), L0.state,
-                                 p->elem, p->stream, use_mf(p));
+          const Sphere sp = make_sphere(L0.g, p->load, d);
+          if (use_mf(p))
+            launch_contact_diag(L0.g, sp, L0.state, L0.diag64, p->stream);
+          else
+            launch_contact_element(L0.g, make_chunks(L0.g, p->ne_use)[0], sp, L0.state, p->elem, p->stream);
           return 0;
         });
       }
-    std::vector<AJob> ga = js;
-    for (size_t q = 0; q < ga.size(); ++q)
-      if (diag[q]) ga[q].A64 = nullptr, ga[q].A32 = nullptr;  // diagonal blocks only
-    add(AOP_GATHER, 0, ga, diag);
+    add(AOP_GATHER, 0, aj);
     for (int i = 0; i < n; ++i) {
       mvpf_problem* p = b->probs[i];
       const double d = depths[i];
       host([p, d] { return system_rhs(p, d); });
     }
-    add(AOP_DIRICHLET, 0, js, {});
+    add(AOP_DIRICHLET, 0, js);
   }
   // smoother setup on every level but the coarsest, the inversions, the join
   {
@@ -2218,7 +2247,7 @@ int batch_assemble(mvpf_batch* b, const double* depths, hipStream_t s) {
         j.status = setup_status(p);
         bi.push_back(j);
       }
-    add(AOP_BLOCK_INVERSE, 0, bi, {});
+    add(AOP_BLOCK_INVERSE, 0, bi);
     // all coarsest-level inversions at once on the work stream, enqueued
     // after the assembly so that the host feeds the assembly stream first
     host([b]() -> int {

@@ -119,17 +119,17 @@ __host__ __device__ constexpr int pair_index(int a, int b) { return a * 8 - (a *
 __host__ __device__ constexpr int pair_a(int p) { return p < 8 ? 0 : p < 15 ? 1 : p < 21 ? 2 : p < 26 ? 3 : p < 30 ? 4 : p < 33 ? 5 : p < 35 ? 6 : 7; }
 __host__ __device__ constexpr int pair_b(int p) { return pair_a(p) + p - pair_index(pair_a(p), pair_a(p)); }
 
-// Matrix-free finest level: Gauss-point Hessian entry k (packed upper
-// triangle, 0..119) of point g of element e in storage type T.  Hessian
-// entries come in groups of V = 16 / sizeof(T) per lane (one 16-byte load)
-// and 64 lanes (8 elements x 8 points) per group, so a wavefront reads 1 KB
-// contiguous (and, wave-contiguous, the 8 elements' 120 x 64 entries in one
-// span).
-template <typename T>
-__host__ __device__ inline int64_t mf_index(int64_t NEpad, int k, int g, int64_t e) {
-  constexpr int V = 16 / (int)sizeof(T);
-  return ((((e >> 3) * (NHP / V) + k / V) * 64) + g * 8 + (e & 7)) * V + k % V;
-}
+// Matrix-free finest level: the tangent of a Gauss point in Green-strain form.
+// The density depends on F through C = F^T F, so its 15 x 15 Hessian in (F, eta)
+// follows from 93 values instead of 120 (local.h): G = F - I, the stress S, the
+// second derivatives D_ee (upper triangle, row-major), D_ek (six per order
+// parameter) and D_kk (row k, columns l <= k), padded to 96.
+constexpr int MF_G = 0, MF_S = 9, MF_EE = 15, MF_EK = 36, MF_KK = 72, MF_NK = 96;
+// Entry k of point g of element e in storage type T: entries come in groups of
+// V = 16 / sizeof(T) per lane (one 16-byte load) and 64 lanes (8 elements x 8
+// points) per group, so a wavefront reads 1 KB contiguous (and, wave-contiguous,
+// the 8 elements' 96 x 64 entries in one span): vector k / V of the point is
+//   ((e / 8) (MF_NK / V) + k / V) 64 + 8 g + e % 8.
 
 // Element outputs of the matrix-free product, merged along x.  A node with
 // offset (by, bz) in the element row r = ey + ny ez (node row j = ey + by,
@@ -311,12 +311,11 @@ void launch_qp(const Grid& g, const Chunk& ck, const double* state, const DevCar
                double* qp, bool hess, hipStream_t s);
 void launch_residual_gather(const Grid& g, const Chunk& ck, const double* state, const double* qp, const DevCard* cd,
                             double* R, hipStream_t s);
-// diag_only: only the 8 diagonal node pairs / the diagonal blocks (the
-// matrix-free finest level needs nothing else)
 void launch_element_matrices(const Grid& g, const Chunk& ck, const double* qp, const DevCard* cd, double* elem,
-                             hipStream_t s, bool diag_only = false);
+                             hipStream_t s);
 void launch_jacobian_gather(const Grid& g, const Chunk& ck, const double* elem, double* A64, float* A32, double* diag64,
-                            hipStream_t s, bool diag_only = false);
+                            hipStream_t s);
+// A64 = A32 = null: the diagonal blocks only
 void launch_apply_dirichlet(const Grid& g, const uint16_t* mask, double* A64, float* A32, double* diag64,
                             hipStream_t s);
 // Galerkin coarsening (galerkin.hip): element matrices of the parent layers
@@ -333,9 +332,11 @@ void launch_block_inverse(const Grid& g, const double* diag64, double* Dinv64, f
 Sphere make_sphere(const Grid& g, const mvpf_loading& ld, double depth);
 void launch_contact_residual(const Grid& g, const Sphere& sp, const double* state, double* R, hipStream_t s);
 // adds the face stiffness to the element matrices if the chunk holds the top
-// element layer (diagonal node pairs only when diag_only)
+// element layer
 void launch_contact_element(const Grid& g, const Chunk& ck, const Sphere& sp, const double* state, double* elem,
-                            hipStream_t s, bool diag_only = false);
+                            hipStream_t s);
+// adds it to the diagonal blocks
+void launch_contact_diag(const Grid& g, const Sphere& sp, const double* state, double* diag64, hipStream_t s);
 void launch_contact_load(const Grid& g, const Sphere& sp, const double* state, double* out, hipStream_t s);
 // matrix-free contact stiffness: the face outputs K_c x of every top face
 // (zero without contact) into the contact part of the element-output buffer
@@ -346,7 +347,15 @@ void launch_contact_apply(const Grid& g, const Sphere* sp, const double* state, 
 // matrix-free finest level (mf.hip): laid out for the six-variant card
 constexpr bool MF_AVAILABLE = NV == 6;
 size_t mf_hessian_values(const Grid& g);
-void launch_mf_pack(const Grid& g, const Chunk& ck, const double* qp, double* D64, float* D32, hipStream_t s);
+// Gauss-point tangents of a slab in Green-strain form, FP64 and (unless null)
+// FP32, and the gradients into qp (as launch_qp)
+void launch_qp_mf(const Grid& g, const Chunk& ck, const double* state, const DevCard* cd, int pade, int mixing,
+                  double* qp, double* D64, float* D32, hipStream_t s);
+// diagonal blocks of a slab's node rows from the tangents; elem: scratch of
+// mf_diag_values(NEcpad, nx) values
+void launch_mf_diag(const Grid& g, const Chunk& ck, const double* D64, const DevCard* cd, double* elem, double* diag64,
+                    hipStream_t s);
+int64_t mf_diag_values(int64_t ne, int nx);
 template <typename TD, typename TX, typename T>
 // elems_per_wg: elements per workgroup (8, 16 or 32 = 64, 128 or 256 threads)
 void launch_mf_element(const Grid& g, const TD* D, const TX* x, const uint16_t* mask, const DevCard* cd, T* E,
@@ -539,25 +548,27 @@ struct AJob {
   float *A32, *Dinv32, *D32, *DinvS32;
   const uint16_t* mask;
   int* status;
-  int64_t eb0, neb;          // element groups of the Hessian pack
-  int npair, nblocks, nup;   // pairs of the element matrices; gather blocks
+  int nblocks, nup;          // gather blocks, stored blocks per tile
   int block0, nblk;
 };
 constexpr int QP_LOG_MIX = 1000;  // added to the Pade order of a batched Hessian launch: logarithmic mixing
 enum AssemblyOp {
   AOP_QP_HESS,        // Gauss-point gradients and Hessians (Pade order, + QP_LOG_MIX for log mixing)
-  AOP_ELEMENT,        // element matrices (npair pairs)
-  AOP_GATHER,         // stored blocks (nup per tile; A64 / A32 null: diagonal only)
-  AOP_DIRICHLET,      // symmetric elimination on the stored blocks
+  AOP_QP_MF,          // the same into the matrix-free layout
+  AOP_ELEMENT,        // element matrices
+  AOP_GATHER,         // stored blocks
+  AOP_MF_DIAG,        // element parts of the diagonal blocks (matrix-free levels)
+  AOP_MF_DIAG_GATHER, // diagonal blocks from them
+  AOP_DIRICHLET,      // symmetric elimination on the stored blocks (A64 / A32 null: diagonal only)
   AOP_BLOCK_INVERSE,  // 9x9 diagonal-block inverses
   AOP_RESIDUAL,       // residual rows from the Gauss-point gradients
-  AOP_MF_PACK,        // Gauss-point Hessians into the matrix-free layout
 };
-// fills the job's derived fields (npair, nblocks, nup, eb0, neb) and returns its workgroups
-int assembly_job_blocks(int op, AJob& j, bool diag_only);
+// fills the job's derived fields (nblocks, nup) and returns its workgroups
+int assembly_job_blocks(int op, AJob& j);
 void launch_assembly_batch(int op, int pade, const AJob* jobs, int njobs, int blocks, hipStream_t s);
-void launch_mf_pack_batch(const AJob* jobs, int njobs, int blocks, hipStream_t s);
-int mf_pack_job_blocks(AJob& j);
+void launch_mf_diag_batch(int op, const AJob* jobs, int njobs, int blocks, hipStream_t s);
+int mf_diag_blocks(const Chunk& ck);
+int mf_diag_gather_blocks(const Chunk& ck);
 void launch_krylov_batch(int op, const KJob* jobs, int njobs, int blocks, hipStream_t s);
 template <typename TZ>
 void launch_mf_outer_batch(int op, const BJob* jobs, int njobs, int blocks, hipStream_t s, int threads = 256);

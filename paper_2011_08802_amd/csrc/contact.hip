@@ -82,7 +82,7 @@ __global__ void __launch_bounds__(256) contact_residual_kernel(Grid g, Sphere s,
 // top element; element-local nodes 4..7 are the face's nodes 0..3).
 __global__ void __launch_bounds__(256) contact_element_kernel(Grid g, Chunk ck, Sphere s,
                                                               const double* __restrict__ state,
-                                                              double* __restrict__ E, bool diag_only) {
+                                                              double* __restrict__ E) {
   const int t = blockIdx.x * 256 + threadIdx.x;
   if (t >= g.nx * g.ny) return;
   const int fi = t % g.nx, fj = t / g.nx;
@@ -112,7 +112,7 @@ __global__ void __launch_bounds__(256) contact_element_kernel(Grid g, Chunk ck, 
   }
   if (!any) return;
   for (int a = 0; a < 4; ++a)
-    for (int b = a; b < (diag_only ? a + 1 : 4); ++b) {
+    for (int b = a; b < 4; ++b) {
       double K[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -127,6 +127,38 @@ __global__ void __launch_bounds__(256) contact_element_kernel(Grid g, Chunk ck, 
 #pragma unroll
         for (int k3 = 0; k3 < 3; ++k3) Ep[(int64_t)(NDOF * i3 + k3) * ck.NEcpad] += K[SI(i3, k3)];
     }
+}
+
+// Diagonal blocks of the top nodes += face stiffness, u-u entries (one thread
+// per top node).
+__global__ void __launch_bounds__(256) contact_diag_kernel(Grid g, Sphere s, const double* __restrict__ state,
+                                                           double* __restrict__ diag64) {
+  const int t = blockIdx.x * 256 + threadIdx.x;
+  if (t >= g.nnx * g.nny) return;
+  const int i = t % g.nnx, j = t / g.nnx;
+  const double w = 0.25 * g.h * g.h * s.eps;
+  double K[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  for (int fj = j - 1; fj <= j; ++fj)
+    for (int fi = i - 1; fi <= i; ++fi) {
+      if (fi < 0 || fi >= g.nx || fj < 0 || fj >= g.ny) continue;
+      const int a = (i - fi) + 2 * (j - fj);
+      for (int q = 0; q < 4; ++q) {
+        FacePoint fp;
+        face_point(g, s, state, fi, fj, q, fp);
+        if (!(fp.gap < 0.0)) continue;
+        const double ir = 1.0 / fp.r, gr = fp.gap * ir;
+        const double nn = fp.N[a] * fp.N[a];
+        const double cn = nn * w * (1.0 - gr) * ir * ir, ci = nn * w * gr;
+#pragma unroll
+        for (int v = 0; v < 6; ++v) K[v] += cn * fp.d[BA(v)] * fp.d[BB(v)] + (v < 3 ? ci : 0.0);
+      }
+    }
+  const int n = t + g.nnx * g.nny * g.nz;
+  double* db = diag64 + (int64_t)(n >> 6) * Lay<double>::SLICE;
+#pragma unroll
+  for (int r = 0; r < 3; ++r)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) db[Lay<double>::off(NDOF * r + c, n & 63)] += K[SI(r, c)];
 }
 
 // Face stiffness times x for the top faces (matrix-free finest level), into
@@ -227,10 +259,14 @@ bool chunk_has_top_layer(const Grid& g, const Chunk& ck) {
 }
 
 void launch_contact_element(const Grid& g, const Chunk& ck, const Sphere& s, const double* state, double* elem,
-                            hipStream_t st, bool diag_only) {
+                            hipStream_t st) {
   if (!chunk_has_top_layer(g, ck)) return;
   const int n = g.nx * g.ny;
-  contact_element_kernel<<<(n + 255) / 256, 256, 0, st>>>(g, ck, s, state, elem, diag_only);
+  contact_element_kernel<<<(n + 255) / 256, 256, 0, st>>>(g, ck, s, state, elem);
+}
+
+void launch_contact_diag(const Grid& g, const Sphere& s, const double* state, double* diag64, hipStream_t st) {
+  contact_diag_kernel<<<(g.nnx * g.nny + 255) / 256, 256, 0, st>>>(g, s, state, diag64);
 }
 
 void launch_contact_load(const Grid& g, const Sphere& s, const double* state, double* out, hipStream_t st) {

@@ -1,16 +1,22 @@
 // Matrix-free application of the finest-level tangent from its Gauss-point
 // Hessians (Sec. 3.4: K = d^2 Pi / dU^2, here never assembled on the finest
 // level).  With v_g = B_g x_e the 15 local variables of Gauss point g
-// (reference-cube gradients of u, h * eta) and D_g the packed 15 x 15 Hessian
-// of the density,
+// (reference-cube gradients of u, h * eta) and D_g the 15 x 15 Hessian of the
+// density,
 //   (K x)_a = h/8 sum_g B_{g,a}^T D_g v_g  +  the gradient-energy term
 //             h/8 sum_g dN_a . (Mg (x) I) grad_ref eta,
 // which is the element matrix of the assembled path applied to x_e (same
 // 2x2x2 rule; the Laplacian term is exact under it).
 //
-// Stored per element: 8 x 120 Hessian values (3.8 KB in FP32) instead of the
-// half-stencil blocks of its node (4.7 KB) plus the assembled path's
-// transposed contributions (0.9 KB written and read per sweep).
+// D_g is stored in Green-strain form, 93 values padded to 96 (the density
+// depends on F through F^T F only): D v costs the same number of operations as
+// with the 120 packed entries of D_g, and the product is bound by streaming
+// them.  64^3, FP32: 188 -> 156 us per product (0.81 GB, 5.2 TB/s); 128x128x64:
+// FP32 750 -> 611 us, FP64 1513 -> 1212 us (5.3 TB/s).  Error of the FP32
+// product against 64 bits 6.1e-8 -> 6.4e-8.
+// Stored per element: 3 KB in FP32 instead of the half-stencil blocks of its
+// node (4.7 KB) plus the assembled path's transposed contributions (0.9 KB
+// written and read per sweep).
 //
 // Kernel layout: a wavefront covers 8 elements x 8 Gauss points (lane =
 // 8 * element + j).  Lane j loads the 9 unknowns of corner j of its element
@@ -26,65 +32,14 @@
 // defect or damped point-block Jacobi update), so results are reproducible
 // bit for bit.
 //
-// The lane layout (9 unknowns per corner, 15 local variables, 120 Hessian
-// entries streamed as 30 16-byte vectors) is that of the six-variant card:
+// The lane layout (9 unknowns per corner, 15 local variables, 96 tangent
+// values streamed as 24 16-byte vectors) is that of the six-variant card:
 // a library built for another number of variants never enables the
 // matrix-free level (its finest level is assembled like the others) and
 // launches none of these kernels.
-#include "common.h"
+#include "pair.h"
 
 namespace mvpf {
-
-constexpr double MGQ0 = 0.21132486540518711775;  // (1 - 1/sqrt 3) / 2
-constexpr double MGQ1 = 0.78867513459481288225;
-
-// Lane exchanges inside groups of 8 lanes by DPP (no LDS traffic): xor 1 and
-// xor 2 are quad permutations; xor 4 is the half-row mirror (lane i <- 7 - i)
-// followed by the quad reversal (i <- i ^ 3), since (7 - i) ^ 3 = i ^ 4.
-template <int X, typename T>
-__device__ __forceinline__ T lane_xor(T v) {
-  if constexpr (X == 1) return dpp_t<0xB1>(v);       // quad_perm [1,0,3,2]
-  else if constexpr (X == 2) return dpp_t<0x4E>(v);  // quad_perm [2,3,0,1]
-  else return dpp_t<0x1B>(dpp_t<0x141>(v));          // row_half_mirror, then quad_perm [3,2,1,0]
-}
-
-// One direction of the trilinear interpolation at the Gauss points, by lane
-// pairs (sum factorisation).  Each lane holds n values belonging to its node
-// index bit b along this direction; with t = (partner's value) - (own value)
-// it gets, at its Gauss coordinate q (the same bit selects q), the
-// interpolated value s = own + qq t (qq = q for b = 0, 1 - q for b = 1) and,
-// for the first nd values, the difference across the pair, d = sg t (sg = +1
-// for b = 0, -1 for b = 1): the derivative along this direction on the unit
-// reference cube.  The partner's value enters only through the subtraction,
-// so the lane exchange folds into it (a DPP operand), and no lane selects
-// are needed.
-template <int X, typename T, int n, int nd>
-__device__ __forceinline__ void interp_pair(const T (&in)[n], T qq, T sg, T (&s)[n], T (&d)[nd]) {
-#pragma unroll
-  for (int k = 0; k < n; ++k) {
-    const T t = lane_xor<X>(in[k]) - in[k];
-    s[k] = in[k] + qq * t;
-    if (k < nd) d[k] = sg * t;
-  }
-}
-
-// Transpose of interp_pair: a lane at Gauss coordinate q along this
-// direction holds coefficients a (of the values) and bs = sb * b (of the
-// derivatives, sb = -1 for node bit 0, +1 for bit 1: the sign is applied by
-// the caller where b is formed); afterwards it holds, for its node bit, the
-// sum over both Gauss points of a * phi(q) + b * phi', phi = 1 - q or q,
-// phi' = -1 or +1.  Own part a mq + bs, partner's part a tq - bs (mq = 1 - q,
-// tq = q for bit 0; mq = q, tq = 1 - q for bit 1); the exchange folds into the
-// final addition.
-template <int X, typename T, int n>
-__device__ __forceinline__ void interp_pair_t(const T (&a)[n], const T (&bs)[n], T mq, T tq, T (&out)[n]) {
-#pragma unroll
-  for (int k = 0; k < n; ++k) {
-    const T mine = a[k] * mq + bs[k];
-    const T theirs = a[k] * tq - bs[k];
-    out[k] = mine + lane_xor<X>(theirs);
-  }
-}
 
 // elements per workgroup of the element kernels: 8, 16 or 32
 constexpr int MF_MAX_EPW = 32;
@@ -123,14 +78,11 @@ __device__ __forceinline__ void mf_element_body(const Grid& g, const TD* __restr
   const int64_t e = (t >> 6) * 8 + (lane >> 3);
   const bool active = e < g.NE;  // inactive lanes hold zeros and still take part in the exchanges
   const bool b0 = gp & 1, b1 = (gp >> 1) & 1, b2 = (gp >> 2) & 1;
-  // per direction: qq (interpolation weight of the partner's difference) and
-  // sg (sign of the derivative) of the forward stages; mq / tq (own and
-  // partner's weight) and sb (derivative sign) of the transposed stages
+  // weight of the partner in the interpolation, of the own and the partner's
+  // part in the transposed stages (the points sit symmetrically: the same for
+  // both sides), and the sign of the derivative per direction
   const T one = (T)1, lo = (T)MGQ0, hi = (T)MGQ1;
-  const T qq0 = b0 ? one - hi : lo, qq1 = b1 ? one - hi : lo, qq2 = b2 ? one - hi : lo;
   const T sg0 = b0 ? -one : one, sg1 = b1 ? -one : one, sg2 = b2 ? -one : one;
-  const T mq0 = b0 ? hi : one - lo, mq1 = b1 ? hi : one - lo, mq2 = b2 ? hi : one - lo;
-  const T tq0 = b0 ? one - hi : lo, tq1 = b1 ? one - hi : lo, tq2 = b2 ? one - hi : lo;
   const T h = (T)g.h, c1 = (T)(0.125 * g.h);
   // the unknowns of corner gp
   T xa[9];
@@ -147,11 +99,11 @@ __device__ __forceinline__ void mf_element_body(const Grid& g, const TD* __restr
 #pragma unroll
     for (int c = 0; c < 9; ++c) xa[c] = ((mb >> c) & 1) ? (T)0 : (T)xl[c];
   }
-  // Hessians of Gauss point gp (packed upper triangle, row-major p <= q),
-  // 16-byte non-temporal loads (streamed once per product: x and the
-  // element outputs stay in the caches)
+  // tangent of Gauss point gp in Green-strain form (MF_G ... of common.h),
+  // 16-byte non-temporal loads (streamed once per product: x and the element
+  // outputs stay in the caches)
   constexpr int V = 16 / (int)sizeof(TD);
-  constexpr int NV = 120 / V;
+  constexpr int NV = MF_NK / V;
   typedef TD VT __attribute__((ext_vector_type(V)));
   const VT* Dp = reinterpret_cast<const VT*>(D) + ((e >> 3) * NV * 64 + gp * 8 + (e & 7));
   constexpr int64_t ks = 64;
@@ -162,17 +114,17 @@ __device__ __forceinline__ void mf_element_body(const Grid& g, const TD* __restr
   }
   // interpolation to Gauss point gp: x, then y, then z
   T s1[9], d1[9];
-  interp_pair<1>(xa, qq0, sg0, s1, d1);
+  interp_pair<1>(xa, lo, sg0, s1, d1);
   T sd1[18], s2[18], d2[9];
 #pragma unroll
   for (int c = 0; c < 9; ++c) sd1[c] = s1[c], sd1[9 + c] = d1[c];
-  interp_pair<2>(sd1, qq1, sg1, s2, d2);  // s2 = (value, d/dx) at (q0, q1); d2 = d/dy
+  interp_pair<2>(sd1, lo, sg1, s2, d2);  // s2 = (value, d/dx) at (q0, q1); d2 = d/dy
   T sd2[27], s3[27], d3[9];
 #pragma unroll
   for (int c = 0; c < 18; ++c) sd2[c] = s2[c];
 #pragma unroll
   for (int c = 0; c < 9; ++c) sd2[18 + c] = d2[c];
-  interp_pair<4>(sd2, qq2, sg2, s3, d3);  // s3 = (value, d/dx, d/dy); d3 = d/dz
+  interp_pair<4>(sd2, lo, sg2, s3, d3);  // s3 = (value, d/dx, d/dy); d3 = d/dz
   // v: reference gradients of u (3 x 3), h * eta (6); ge: reference gradients of eta
   T v[15], ge[18];
 #pragma unroll
@@ -182,7 +134,9 @@ __device__ __forceinline__ void mf_element_body(const Grid& g, const TD* __restr
     v[9 + m] = h * s3[3 + m];
     ge[3 * m] = s3[12 + m], ge[3 * m + 1] = s3[21 + m], ge[3 * m + 2] = d3[3 + m];
   }
-  // w = D v
+  // w = D v: with F = I + G, eps = sym(F^T dF) (engineering shears),
+  // sigma = D_ee eps + D_ek eta, t = D_ek^T eps + D_kk eta, and back through
+  // dF: F sigma + dF S
   T w[15];
 #pragma unroll
   for (int k = 0; k < 15; ++k) w[k] = 0;
@@ -199,14 +153,69 @@ __device__ __forceinline__ void mf_element_body(const Grid& g, const TD* __restr
     }
   }
   if (load) {
+    // entry k of the stream (each taken once, in order): its vector's first
+    // entry issues the load PF vectors ahead
+    auto entry = [&](int k) -> T {
+      if (!SPARSE && k % V == 0 && k / V + PF < NV) dq[k / V + PF] = __builtin_nontemporal_load(Dp + (k / V + PF) * ks);
+      return (T)dq[k / V][k % V];
+    };
+    T G[9], eps[6], sig[6];
 #pragma unroll
-    for (int p = 0, k = 0; p < 15; ++p)
+    for (int k = 0; k < 9; ++k) G[k] = entry(MF_G + k);
 #pragma unroll
-      for (int qq = p; qq < 15; ++qq, ++k) {
-        if (!SPARSE && k % V == 0 && k / V + PF < NV) dq[k / V + PF] = __builtin_nontemporal_load(Dp + (k / V + PF) * ks);
-        const T d = (T)dq[k / V][k % V];
-        w[p] += d * v[qq];
-        if (qq != p) w[qq] += d * v[p];
+    for (int u = 0; u < 6; ++u) {
+      const int j = BA(u), l = BB(u);
+      T s = j == l ? v[4 * j] : v[3 * j + l] + v[3 * l + j];
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        s += G[3 * i + j] * v[3 * i + l];
+        if (j != l) s += G[3 * i + l] * v[3 * i + j];
+      }
+      eps[u] = s;
+      sig[u] = 0;
+    }
+#pragma unroll
+    for (int u = 0; u < 6; ++u) {
+      const T d = entry(MF_S + u);
+      const int j = BA(u), l = BB(u);
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        w[3 * i + j] += d * v[3 * i + l];
+        if (j != l) w[3 * i + l] += d * v[3 * i + j];
+      }
+    }
+#pragma unroll
+    for (int p = 0, k = MF_EE; p < 6; ++p)
+#pragma unroll
+      for (int q = p; q < 6; ++q, ++k) {
+        const T d = entry(k);
+        sig[p] += d * eps[q];
+        if (q != p) sig[q] += d * eps[p];
+      }
+#pragma unroll
+    for (int m = 0; m < 6; ++m)
+#pragma unroll
+      for (int u = 0; u < 6; ++u) {
+        const T d = entry(MF_EK + 6 * m + u);
+        sig[u] += d * v[9 + m];
+        w[9 + m] += d * eps[u];
+      }
+#pragma unroll
+    for (int m = 0, k = MF_KK; m < 6; ++m)
+#pragma unroll
+      for (int l = 0; l <= m; ++l, ++k) {
+        const T d = entry(k);
+        w[9 + m] += d * v[9 + l];
+        if (l != m) w[9 + l] += d * v[9 + m];
+      }
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        T s = sig[SI(i, j)];
+#pragma unroll
+        for (int l = 0; l < 3; ++l) s += G[3 * i + l] * sig[SI(l, j)];
+        w[3 * i + j] += s;
       }
   }
   // gradient energy: z = (Mg (x) I) grad_ref eta
@@ -241,17 +250,17 @@ __device__ __forceinline__ void mf_element_body(const Grid& g, const TD* __restr
   for (int c = 0; c < 9; ++c) bz[9 + c] = 0, bz[18 + c] = 0;
   // back to the corners: z (27 sums: value, x, y coefficients), then y, then x
   T r3[27];
-  interp_pair_t<4>(a3, bz, mq2, tq2, r3);
+  interp_pair_t<4>(a3, bz, hi, lo, r3);
   T a2[18], by[18], r2[18];
 #pragma unroll
   for (int c = 0; c < 18; ++c) a2[c] = r3[c], by[c] = 0;
 #pragma unroll
   for (int c = 0; c < 9; ++c) by[c] = r3[18 + c];
-  interp_pair_t<2>(a2, by, mq1, tq1, r2);
+  interp_pair_t<2>(a2, by, hi, lo, r2);
   T a1[9], bx[9], out[9];
 #pragma unroll
   for (int c = 0; c < 9; ++c) a1[c] = r2[c], bx[c] = r2[9 + c];
-  interp_pair_t<1>(a1, bx, mq0, tq0, out);
+  interp_pair_t<1>(a1, bx, hi, lo, out);
   // Element outputs through LDS: a lane holds corner gp's 9 values; staged
   // per stream (gp, c), the workgroup merges each element's left corners
   // with the right corners of its predecessor in the same row and stores
@@ -390,67 +399,241 @@ __global__ void __launch_bounds__(256) mf_gather_kernel(Grid g, const T* __restr
   mf_gather_body<MODE, T, TX, TY>(g, E, Cf, epw, mask, x, b, Dinv, omega, y, blockIdx.x);
 }
 
-// Gauss-point Hessians of a slab (standard Gauss-point layout, entries
-// 15.. of qp) -> matrix-free layout, FP64 and (optionally) FP32.  One thread
-// per group of 4 consecutive entries of one (point, element), in the order of
-// the matrix-free layout, so that every wavefront writes whole 1 KB spans.
-__device__ __forceinline__ void mf_pack_body(const Grid& g, const Chunk& ck, const double* __restrict__ qp,
-                                             double* __restrict__ D64, float* __restrict__ D32, int64_t eb0,
-                                             int64_t neb, int bid) {
-  const int64_t t = (int64_t)bid * 256 + threadIdx.x;
-  const int64_t per = neb * 64;  // threads per entry group
-  const int k4 = (int)(t / per);
-  if (k4 >= 30) return;
-  const int64_t r = t - (int64_t)k4 * per;
-  const int lane = (int)(r & 63);
-  const int gp = lane >> 3;
-  const int64_t e = (eb0 + (r >> 6)) * 8 + (lane & 7);
-  const int64_t el = e - ck.e0;
-  if (el < 0 || el >= ck.NEc) return;
-  const int64_t stride = (int64_t)8 * ck.NEcpad;
-  const double* src = qp + (int64_t)(15 + 4 * k4) * stride + (int64_t)gp * ck.NEcpad + el;
-  double d[4];
-#pragma unroll
-  for (int u = 0; u < 4; ++u) d[u] = src[(int64_t)u * stride];
-  if (D64) {
-    *reinterpret_cast<double2*>(D64 + mf_index<double>(g.NEpad, 4 * k4, gp, e)) = make_double2(d[0], d[1]);
-    *reinterpret_cast<double2*>(D64 + mf_index<double>(g.NEpad, 4 * k4 + 2, gp, e)) = make_double2(d[2], d[3]);
-  }
-  if (D32)
-    *reinterpret_cast<float4*>(D32 + mf_index<float>(g.NEpad, 4 * k4, gp, e)) =
-        make_float4((float)d[0], (float)d[1], (float)d[2], (float)d[3]);
+size_t mf_hessian_values(const Grid& g) { return MF_AVAILABLE ? (size_t)MF_NK * 8 * g.NEpad : 0; }
+
+// ---- diagonal blocks from the Gauss-point tangents ----------------------------
+// One direction of a diagonal block's quadrature by lane pairs: a lane holds a
+// coefficient at its Gauss point and ends with both points' sum for its own
+// corner, weighted by phi^2 (VV), phi phi' (VD) or phi'^2 = 1 (DD).
+enum PairType { PAIR_VV, PAIR_VD, PAIR_DD };
+struct PairWeights {
+  double mv, tv, md, td;  // own and partner's weight of VV, of VD
+};
+__device__ __forceinline__ PairWeights pair_weights(bool b) {
+  const double mq = MGQ1, tq = MGQ0;  // a corner's shape value at the nearer and the farther point
+  const double sg = b ? 1.0 : -1.0;
+  return PairWeights{mq * mq, tq * tq, mq * sg, -tq * sg};
+}
+template <int X, int TYPE>
+__device__ __forceinline__ double pair_sum(double a, const PairWeights& w) {
+  if constexpr (TYPE == PAIR_VV) return a * w.mv + lane_xor<X>(a * w.tv);
+  else if constexpr (TYPE == PAIR_VD) return a * w.md + lane_xor<X>(a * w.td);
+  else return a + lane_xor<X>(a);
 }
 
-__global__ void __launch_bounds__(256) mf_pack_kernel(Grid g, Chunk ck, const double* __restrict__ qp,
-                                                      double* __restrict__ D64, float* __restrict__ D32,
-                                                      int64_t eb0, int64_t neb) {
-  mf_pack_body(g, ck, qp, D64, D32, eb0, neb, blockIdx.x);
+// Merged element parts of the 9x9 diagonal blocks (45 symmetric entries per
+// corner), straight from the FP64 Gauss-point tangents: lane = 8 * element +
+// Gauss point as in the element product.  Every coefficient of B^T D B on the
+// diagonal is a product of one-dimensional weights, so the eight points are
+// summed by three pair exchanges per coefficient (297 in all) instead of one
+// 9x9 product per corner and point.  Elements of one slab (whole layers),
+// chunk-local index el; streams as for the element outputs, 45 values instead
+// of 9.  Bound: FP64 issue (~2000 instructions per point) and the tangents'
+// 0.77 KB per point, read once; 64^3: 0.58 ms, and 0.18
+// ms for the node sums.
+constexpr int DG_EPW = 32;
+__host__ __device__ inline int64_t dg_nw(const Chunk& ck) { return ck.NEcpad / DG_EPW; }
+__host__ __device__ inline int64_t dg_w_offset(const Chunk& ck) { return (int64_t)4 * NSYM * ck.NEcpad; }
+__host__ __device__ inline int64_t dg_r_offset(const Chunk& ck) { return dg_w_offset(ck) + 4 * NSYM * dg_nw(ck); }
+
+__device__ __forceinline__ void mf_diag_body(const Grid& g, const Chunk& ck, const double* __restrict__ D,
+                                             const DevCard* __restrict__ cd, double* __restrict__ E, int wg, int nb) {
+  __shared__ double eo[72 * (DG_EPW + 1)];
+  const int xcd = wg & 7;
+  const int bid = xcd * (nb >> 3) + min(xcd, nb & 7) + (wg >> 3);
+  const int lane = threadIdx.x & 63, gp = lane & 7, jw = threadIdx.x >> 3;
+  const int el = bid * DG_EPW + jw;
+  const bool active = el < ck.NEc;
+  const int64_t e = ck.e0 + (active ? el : 0);
+  const double2* Dp = reinterpret_cast<const double2*>(D) + ((e >> 3) * (MF_NK / 2) * 64 + gp * 8 + (e & 7));
+  const PairWeights wx = pair_weights(gp & 1), wy = pair_weights((gp >> 1) & 1), wz = pair_weights((gp >> 2) & 1);
+  const double h = g.h, cuu = 0.125 * h, cue = 0.125 * h * h, cee = 0.125 * h * h * h;
+  double out[NSYM];
+  double F[9];
+  {
+    double2 v[(MF_EK) / 2];
+#pragma unroll
+    for (int k = 0; k < MF_EK / 2; ++k) v[k] = Dp[k * 64];
+    auto at = [&](int k) { return (k & 1) ? v[k >> 1].y : v[k >> 1].x; };
+#pragma unroll
+    for (int i = 0; i < 9; ++i) F[i] = at(MF_G + i) + (i % 4 == 0 ? 1.0 : 0.0);
+    // u-u: D(ij, kl) = sum_ab F_ia F_kb D_(aj)(bl) + delta_ik S_jl, weights dN_j dN_l
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      double t[6][3];  // [aj][l]: sum_b D_(aj)(bl) F_kb
+#pragma unroll
+      for (int u = 0; u < 6; ++u)
+#pragma unroll
+        for (int l = 0; l < 3; ++l)
+          t[u][l] = at(MF_EE + eidx(u, SI(0, l))) * F[3 * k] + at(MF_EE + eidx(u, SI(1, l))) * F[3 * k + 1] +
+                    at(MF_EE + eidx(u, SI(2, l))) * F[3 * k + 2];
+#pragma unroll
+      for (int i = 0; i <= k; ++i) {
+        double d[6];  // coefficients of dN_j dN_l, j <= l (xx, yy, zz, yz, xz, xy)
+#pragma unroll
+        for (int u = 0; u < 6; ++u) {
+          const int j = BA(u), l = BB(u);
+          double s = F[3 * i] * t[SI(0, j)][l] + F[3 * i + 1] * t[SI(1, j)][l] + F[3 * i + 2] * t[SI(2, j)][l];
+          if (j != l)
+            s += F[3 * i] * t[SI(0, l)][j] + F[3 * i + 1] * t[SI(1, l)][j] + F[3 * i + 2] * t[SI(2, l)][j];
+          if (i == k) s += (j != l ? 2.0 : 1.0) * at(MF_S + u);
+          d[u] = cuu * s;
+        }
+        // z, y, x
+        const double xx = pair_sum<2, PAIR_VV>(pair_sum<4, PAIR_VV>(d[0], wz), wy);
+        const double yy = pair_sum<2, PAIR_DD>(pair_sum<4, PAIR_VV>(d[1], wz), wy);
+        const double zz = pair_sum<2, PAIR_VV>(pair_sum<4, PAIR_DD>(d[2], wz), wy);
+        const double yz = pair_sum<2, PAIR_VD>(pair_sum<4, PAIR_VD>(d[3], wz), wy);
+        const double xz = pair_sum<2, PAIR_VV>(pair_sum<4, PAIR_VD>(d[4], wz), wy);
+        const double xy = pair_sum<2, PAIR_VD>(pair_sum<4, PAIR_VV>(d[5], wz), wy);
+        out[sym_index(i, k)] = pair_sum<1, PAIR_DD>(xx, wx) + pair_sum<1, PAIR_VV>(yy + zz + yz, wx) +
+                               pair_sum<1, PAIR_VD>(xz + xy, wx);
+      }
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < 6; ++m) {  // u-eta, weights dN_j N
+    double d[6];
+#pragma unroll
+    for (int u = 0; u < 3; ++u) {
+      const double2 v = Dp[(MF_EK / 2 + 3 * m + u) * 64];
+      d[2 * u] = v.x, d[2 * u + 1] = v.y;
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      double c[3];
+#pragma unroll
+      for (int j = 0; j < 3; ++j)
+        c[j] = cue * (F[3 * i] * d[SI(0, j)] + F[3 * i + 1] * d[SI(1, j)] + F[3 * i + 2] * d[SI(2, j)]);
+      const double x = pair_sum<2, PAIR_VV>(pair_sum<4, PAIR_VV>(c[0], wz), wy);
+      const double y = pair_sum<2, PAIR_VD>(pair_sum<4, PAIR_VV>(c[1], wz), wy);
+      const double z = pair_sum<2, PAIR_VV>(pair_sum<4, PAIR_VD>(c[2], wz), wy);
+      out[sym_index(i, 3 + m)] = pair_sum<1, PAIR_VD>(x, wx) + pair_sum<1, PAIR_VV>(y + z, wx);
+    }
+  }
+  {
+    double2 v[(MF_NK - MF_KK) / 2];
+#pragma unroll
+    for (int k = 0; k < (MF_NK - MF_KK) / 2; ++k) v[k] = Dp[(MF_KK / 2 + k) * 64];
+    // eta-eta, weight N^2, and the gradient energy h Lap_aa Mg with Lap_aa = 1/3
+#pragma unroll
+    for (int m = 0, k = 0; m < 6; ++m)
+#pragma unroll
+      for (int l = 0; l <= m; ++l, ++k) {
+        const double d = cee * ((k & 1) ? v[k >> 1].y : v[k >> 1].x);
+        out[sym_index(3 + l, 3 + m)] =
+            pair_sum<1, PAIR_VV>(pair_sum<2, PAIR_VV>(pair_sum<4, PAIR_VV>(d, wz), wy), wx) + h / 3.0 * cd->Mg[l][m];
+      }
+  }
+  // merge along x and store, nine entries at a time through LDS
+  double* __restrict__ W = E + dg_w_offset(ck);
+  double* __restrict__ Rr = E + dg_r_offset(ck);
+  const int nr = ck.NEc / g.nx;
+  const int ex0 = (bid * DG_EPW) % g.nx;
+#pragma unroll
+  for (int r = 0; r < 5; ++r) {
+    if (r > 0) __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 9; ++c) eo[(gp * 9 + c) * (DG_EPW + 1) + jw] = out[9 * r + c];
+    __syncthreads();
+    for (int idx = threadIdx.x; idx < 36 * DG_EPW; idx += 256) {
+      const int s = idx / DG_EPW, jj = idx & (DG_EPW - 1);
+      const int q = s / 9, c = s - 9 * q;
+      const int ell = bid * DG_EPW + jj;
+      if (ell >= ck.NEc) continue;
+      int ex = ex0 + jj;
+      while (ex >= g.nx) ex -= g.nx;
+      const double* left = eo + (18 * q + c) * (DG_EPW + 1);
+      const double* right = eo + (18 * q + 9 + c) * (DG_EPW + 1);
+      const int64_t st = NSYM * q + 9 * r + c;
+      double t = left[jj];
+      if (jj > 0 && ex > 0) t = t + right[jj - 1];
+      E[st * ck.NEcpad + ell] = t;
+      if (ex == g.nx - 1) Rr[st * nr + ell / g.nx] = right[jj];
+      else if (jj == DG_EPW - 1) W[st * dg_nw(ck) + bid] = right[jj];
+    }
+  }
 }
-__global__ void __launch_bounds__(256) mf_pack_batch(const AJob* __restrict__ jobs, int njobs) {
+// Node sums of the merged parts -> full diagonal blocks.  One thread per node
+// and block row (r, r..8): 45 sums per thread would leave the small levels idle.
+__device__ __forceinline__ void mf_diag_gather_body(const Grid& g, const Chunk& ck, const double* __restrict__ E,
+                                                    double* __restrict__ diag64, int bid) {
+  const int rr = bid % NDOF;
+  const int n = ck.n0 + (bid / NDOF) * 256 + threadIdx.x;
+  if (n >= ck.n1) return;
+  double* db = diag64 + (int64_t)(n >> 6) * Lay<double>::SLICE;
+  const int l = n & 63;
+  const int i = n % g.nnx, j = (n / g.nnx) % g.nny, k = n / (g.nnx * g.nny);
+  const double* __restrict__ W = E + dg_w_offset(ck);
+  const double* __restrict__ Rr = E + dg_r_offset(ck);
+  const int nr = ck.NEc / g.nx;
+  const int ez0 = (int)(ck.e0 / ((int64_t)g.nx * g.ny));
+  double s[NDOF];
+#pragma unroll
+  for (int c = 0; c < NDOF; ++c) s[c] = 0.0;
+  if (n < g.N) {
+#pragma unroll
+    for (int q = 3; q >= 0; --q) {
+      const int ey = j - (q & 1), ez = k - (q >> 1);
+      if (ey < 0 || ey >= g.ny || ez < 0 || ez >= g.nz) continue;
+      const int64_t r = ey + (int64_t)g.ny * (ez - ez0);
+#pragma unroll
+      for (int c = 0; c < NDOF; ++c) {
+        if (c < rr) continue;
+        const int64_t st = NSYM * q + sym_index(rr, c);
+        if (i < g.nx) {
+          const int64_t e = i + g.nx * r;
+          double t = E[st * ck.NEcpad + e];
+          if (i > 0 && (e & (DG_EPW - 1)) == 0) t = t + W[st * dg_nw(ck) + e / DG_EPW - 1];
+          s[c] += t;
+        } else {
+          s[c] += Rr[st * nr + r];
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < NDOF; ++c)
+    if (c >= rr) {
+      db[Lay<double>::off(NDOF * rr + c, l)] = s[c];
+      if (c > rr) db[Lay<double>::off(NDOF * c + rr, l)] = s[c];
+    }
+}
+__global__ void __launch_bounds__(256) mf_diag_kernel(Grid g, Chunk ck, const double* __restrict__ D,
+                                                      const DevCard* __restrict__ cd, double* __restrict__ E) {
+  mf_diag_body(g, ck, D, cd, E, blockIdx.x, gridDim.x);
+}
+__global__ void __launch_bounds__(256) mf_diag_gather_kernel(Grid g, Chunk ck, const double* __restrict__ E,
+                                                             double* __restrict__ diag64) {
+  mf_diag_gather_body(g, ck, E, diag64, blockIdx.x);
+}
+__global__ void __launch_bounds__(256) mf_diag_batch(const AJob* __restrict__ jobs, int njobs) {
   int bid;
   const AJob& j = find_job(jobs, njobs, bid);
-  mf_pack_body(j.g, j.ck, j.qp, j.D64, j.D32, j.eb0, j.neb, bid);
+  mf_diag_body(j.g, j.ck, j.D64, j.cd, j.elem, bid, j.nblk);
 }
-void launch_mf_pack_batch(const AJob* jobs, int njobs, int blocks, hipStream_t s) {
-  if (!MF_AVAILABLE) return;
-  mf_pack_batch<<<blocks, 256, 0, s>>>(jobs, njobs);
+__global__ void __launch_bounds__(256) mf_diag_gather_batch(const AJob* __restrict__ jobs, int njobs) {
+  int bid;
+  const AJob& j = find_job(jobs, njobs, bid);
+  mf_diag_gather_body(j.g, j.ck, j.elem, j.diag64, bid);
 }
-int mf_pack_job_blocks(AJob& j) {
-  j.eb0 = j.ck.e0 / 8;
-  j.neb = (j.ck.e0 + j.ck.NEc + 7) / 8 - j.eb0;
-  return (int)((30 * j.neb * 64 + 255) / 256);
+// values of the element buffer a slab of ne elements (padded) in rows of nx uses
+int64_t mf_diag_values(int64_t ne, int nx) { return 4 * NSYM * (ne + ne / DG_EPW + ne / nx + 1); }
+int mf_diag_blocks(const Chunk& ck) { return ck.NEcpad / DG_EPW; }
+int mf_diag_gather_blocks(const Chunk& ck) { return (ck.n1 - ck.n0 + 255) / 256 * NDOF; }
+void launch_mf_diag(const Grid& g, const Chunk& ck, const double* D64, const DevCard* cd, double* elem, double* diag64,
+                    hipStream_t s) {
+  if constexpr (!MF_AVAILABLE) return;
+  mf_diag_kernel<<<mf_diag_blocks(ck), 256, 0, s>>>(g, ck, D64, cd, elem);
+  mf_diag_gather_kernel<<<mf_diag_gather_blocks(ck), 256, 0, s>>>(g, ck, elem, diag64);
+}
+void launch_mf_diag_batch(int op, const AJob* jobs, int njobs, int blocks, hipStream_t s) {
+  if constexpr (!MF_AVAILABLE) return;
+  if (op == AOP_MF_DIAG) mf_diag_batch<<<blocks, 256, 0, s>>>(jobs, njobs);
+  else mf_diag_gather_batch<<<blocks, 256, 0, s>>>(jobs, njobs);
 }
 
-size_t mf_hessian_values(const Grid& g) { return MF_AVAILABLE ? (size_t)120 * 8 * g.NEpad : 0; }
-
-void launch_mf_pack(const Grid& g, const Chunk& ck, const double* qp, double* D64, float* D32, hipStream_t s) {
-  if (!MF_AVAILABLE) return;
-  const int64_t eb0 = ck.e0 / 8, eb1 = (ck.e0 + ck.NEc + 7) / 8;  // element groups of 8 touching the slab
-  const int64_t n = 30 * (eb1 - eb0) * 64;
-  mf_pack_kernel<<<(int)((n + 255) / 256), 256, 0, s>>>(g, ck, qp, D64, D32, eb0, eb1 - eb0);
-}
-
-// Register budgets (measured equal within 1 % for prefetch depths 12 ... 30
+// Register budgets (measured equal within 1 % for prefetch depths 12 and more
 // at 2 ... 4 waves per SIMD): FP32 Hessians 20 vectors ahead at >= 3 waves
 // per SIMD, FP64 16 ahead at >= 2.
 constexpr int MF_PF32 = 20, MF_MINB32 = 3, MF_PF64 = 16, MF_MINB64 = 2;

@@ -10,7 +10,7 @@
 //      the <= 8 element blocks of the elements containing both nodes and
 //      writes the 9x9 block into the tiled half-stencil layout.
 // Summation order is fixed, so results are bitwise reproducible.
-#include "common.h"
+#include "pair.h"
 
 namespace mvpf {
 
@@ -128,6 +128,155 @@ void launch_qp(const Grid& g, const Chunk& ck, const double* state, const DevCar
   }
 }
 
+// Gauss-point gradients and tangents of a matrix-free level, the tangents
+// straight into the matrix-free layout (no pass over a scratch form).  A
+// wavefront holds 8 elements x 8 points (lane = 8 * element + point): lane j
+// loads the 15 state values of corner j of its element and the point's F, eta
+// and eta_n come from three pair interpolations, instead of 120 loads per
+// point.  Bound: FP64 issue at one wavefront per SIMD (~6000 instructions per
+// point); 64^3: 0.81 ms, 1.27 KB written per point (3.3 TB/s), against 2.43 ms
+// for the Hessian in (F, eta) and 1.10 ms for the pass that repacked it.
+struct MfOut {
+  const double* F;
+  double2* D64;   // the wavefront's group of 8 elements
+  float4* D32;    // or null
+  uint32_t slot;  // 8 * point + element
+  double* qp;
+  int64_t qs;     // stride of the gradient components
+  uint32_t qoff;
+  double pend[4];
+  double col[6];
+  __device__ __forceinline__ void vec2(int k, double a, double b) const {
+    (D64 + (int64_t)(k / 2) * 64)[slot] = make_double2(a, b);
+  }
+  __device__ __forceinline__ void vec4(int k, double a, double b, double c, double d) const {
+    vec2(k, a, b);
+    vec2(k + 2, c, d);
+    if (D32) (D32 + (int64_t)(k / 4) * 64)[slot] = make_float4((float)a, (float)b, (float)c, (float)d);
+  }
+  __device__ __forceinline__ void gradient(const double g[NQ], const double*) const {
+#pragma unroll
+    for (int c = 0; c < NQ; ++c) (qp + (int64_t)c * qs)[qoff] = g[c];
+  }
+  __device__ __forceinline__ void strain(const double S[6], const double Dee[21]) const {
+    auto at = [&](int k) {
+      return k < MF_S ? F[k] - (k % 4 == 0 ? 1.0 : 0.0) : k < MF_EE ? S[k - MF_S] : Dee[k - MF_EE];
+    };
+#pragma unroll
+    for (int k = 0; k < MF_EK; k += 4) vec4(k, at(k), at(k + 1), at(k + 2), at(k + 3));
+  }
+  __device__ __forceinline__ void eps_eta(int k, const double d[6]) {
+    const int at = MF_EK + 6 * k;
+    if (k % 2 == 0) {
+#pragma unroll
+      for (int i = 0; i < 6; ++i) col[i] = d[i];
+    } else {
+      vec4(at - 6, col[0], col[1], col[2], col[3]);
+      vec4(at - 2, col[4], col[5], d[0], d[1]);
+      vec4(at + 2, d[2], d[3], d[4], d[5]);
+    }
+  }
+  __device__ __forceinline__ void eta_eta(int k, int l, double v) {
+    const int i = k * (k + 1) / 2 + l;
+    pend[i % 4] = v;
+    if (k == NV - 1 && l == NV - 1) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (j > i % 4) pend[j] = 0.0;
+    }
+    if (i % 4 == 3 || (k == NV - 1 && l == NV - 1))
+      vec4(MF_KK + i / 4 * 4, pend[0], pend[1], pend[2], pend[3]);
+  }
+};
+template <int PD, int MIX>
+__device__ __forceinline__ void qp_mf_body(const Grid& g, const Chunk& ck, const double* __restrict__ state,
+                                           const DevCard* __restrict__ cd, double* __restrict__ qp,
+                                           double* __restrict__ D64, float* __restrict__ D32, int bid) {
+  static_assert(NV == 6 || !MF_AVAILABLE, "entry counts of the matrix-free layout");
+  const int lane = threadIdx.x & 63, gp = lane & 7;
+  // group of 8 elements, uniform over the wavefront
+  const int64_t eg = ck.e0 / 8 + __builtin_amdgcn_readfirstlane(bid * 2 + (threadIdx.x >> 6));
+  const int64_t e = eg * 8 + (lane >> 3), el = e - ck.e0;
+  const bool active = el >= 0 && el < ck.NEc;
+  const bool b0 = gp & 1, b1 = (gp >> 1) & 1, b2 = (gp >> 2) & 1;
+  double F[9], eh[NV], ehn[NV];
+  {
+    double x[3 + 2 * NV];
+#pragma unroll
+    for (int c = 0; c < 3 + 2 * NV; ++c) x[c] = 0.0;
+    if (active) {
+      const int ex = (int)(e % g.nx), ey = (int)((e / g.nx) % g.ny), ez = (int)(e / ((int64_t)g.nx * g.ny));
+      const int node = (ex + b0) + g.nnx * ((ey + b1) + g.nny * (ez + b2));
+#pragma unroll
+      for (int c = 0; c < 3 + 2 * NV; ++c) x[c] = state[(int64_t)c * g.Npad + node];
+    }
+    const double ih = 1.0 / g.h;
+    constexpr int n = 3 + 2 * NV;
+    double s1[n], d1[3], i2[n + 3], s2[n + 3], d2[3], i3[n + 6], s3[n + 6], d3[3];
+    interp_pair<1>(x, MGQ0, b0 ? -ih : ih, s1, d1);
+#pragma unroll
+    for (int c = 0; c < n; ++c) i2[c] = s1[c];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) i2[n + c] = d1[c];
+    interp_pair<2>(i2, MGQ0, b1 ? -ih : ih, s2, d2);
+#pragma unroll
+    for (int c = 0; c < n + 3; ++c) i3[c] = s2[c];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) i3[n + 3 + c] = d2[c];
+    interp_pair<4>(i3, MGQ0, b2 ? -ih : ih, s3, d3);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      F[3 * i] = s3[n + i] + (i == 0 ? 1.0 : 0.0);
+      F[3 * i + 1] = s3[n + 3 + i] + (i == 1 ? 1.0 : 0.0);
+      F[3 * i + 2] = d3[i] + (i == 2 ? 1.0 : 0.0);
+    }
+#pragma unroll
+    for (int k = 0; k < NV; ++k) eh[k] = s3[3 + k], ehn[k] = s3[3 + NV + k];
+  }
+  if (!active) return;  // no lane exchanges from here on
+  MfOut out{F,
+            reinterpret_cast<double2*>(D64) + eg * (MF_NK / 2) * 64,
+            D32 ? reinterpret_cast<float4*>(D32) + eg * (MF_NK / 4) * 64 : nullptr,
+            (uint32_t)(8 * gp + (lane >> 3)),
+            qp,
+            (int64_t)8 * ck.NEcpad,
+            (uint32_t)gp * (uint32_t)ck.NEcpad + (uint32_t)el,
+            {0.0, 0.0, 0.0, 0.0},
+            {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}};
+  local_hessian<PD, MIX>(F, eh, ehn, *cd, out);
+}
+template <int PD, int MIX>
+__global__ void __launch_bounds__(128) qp_mf_kernel(Grid g, Chunk ck, const double* __restrict__ state,
+                                                    const DevCard* __restrict__ cd, double* __restrict__ qp,
+                                                    double* __restrict__ D64, float* __restrict__ D32) {
+  qp_mf_body<PD, MIX>(g, ck, state, cd, qp, D64, D32, blockIdx.x);
+}
+// groups of 8 elements touching the slab, two wavefronts per workgroup
+int qp_mf_blocks(const Chunk& ck) { return (int)(((ck.e0 + ck.NEc + 7) / 8 - ck.e0 / 8 + 1) / 2); }
+template <int PD, int MIX>
+void launch_qp_mf_order(const Grid& g, const Chunk& ck, const double* state, const DevCard* cd, double* qp, double* D64,
+                        float* D32, hipStream_t s) {
+  qp_mf_kernel<PD, MIX><<<qp_mf_blocks(ck), 128, 0, s>>>(g, ck, state, cd, qp, D64, D32);
+}
+void launch_qp_mf(const Grid& g, const Chunk& ck, const double* state, const DevCard* cd, int pade, int mixing,
+                  double* qp, double* D64, float* D32, hipStream_t s) {
+  if constexpr (MF_AVAILABLE) {
+    if (mixing == MVPF_MIX_LOG) {
+      switch (pade) {
+        case 11: launch_qp_mf_order<11, 1>(g, ck, state, cd, qp, D64, D32, s); break;
+        case 33: launch_qp_mf_order<33, 1>(g, ck, state, cd, qp, D64, D32, s); break;
+        default: launch_qp_mf_order<22, 1>(g, ck, state, cd, qp, D64, D32, s); break;
+      }
+      return;
+    }
+    switch (pade) {
+      case 11: launch_qp_mf_order<11, 0>(g, ck, state, cd, qp, D64, D32, s); break;
+      case 33: launch_qp_mf_order<33, 0>(g, ck, state, cd, qp, D64, D32, s); break;
+      default: launch_qp_mf_order<22, 0>(g, ck, state, cd, qp, D64, D32, s); break;
+    }
+  }
+}
+
 __device__ __forceinline__ void residual_gather_body(const Grid& g, const Chunk& ck, const double* __restrict__ state,
                                                      const double* __restrict__ qp, const DevCard* __restrict__ cd,
                                                      double* __restrict__ R, int bid) {
@@ -201,30 +350,24 @@ constexpr int EM_WAVES = 4;
 // 15 unknowns per node take 116 KB of LDS: one workgroup per CU)
 constexpr int EM_MINB = NHP_PAD * 64 * 8 <= 80 * 1024 ? 2 : 1;
 
-// npair = NPAIR: all 36 pairs; npair = 8: the diagonal pairs (a, a) only.
 __device__ __forceinline__ void element_matrix_body(const Grid& g, const Chunk& ck, const double* __restrict__ qp,
-                                                    const DevCard* __restrict__ cd, double* __restrict__ E, int npair,
+                                                    const DevCard* __restrict__ cd, double* __restrict__ E,
                                                     int bid, int nblk) {
   __shared__ double Ds[NHP_PAD * 64];
   // the NPAIR / EM_WAVES pair chunks of one element group are consecutive
   // logical blocks on one XCD, so the group's Hessians are read from HBM once
   // and then hit that XCD's L2
   const int groups = ck.NEcpad / 64;
-  const int chunks = npair / EM_WAVES;
+  constexpr int chunks = NPAIR / EM_WAVES;
   const int Lb = xcd_logical(bid, nblk);
   if (Lb >= groups * chunks) return;  // uniform; before any barrier
   const int eg = Lb / chunks;
   const int pc = Lb % chunks;  // pair chunk
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  int a = 0, b = 0;
-  if (npair == NPAIR) {
-    int rem = pc * EM_WAVES + w;  // pair 0..35
-    while (rem >= 8 - a) { rem -= 8 - a; ++a; }
-    b = a + rem;
-  } else {
-    a = b = pc * EM_WAVES + w;
-  }
-  const int p = pair_index(a, b);
+  const int p = pc * EM_WAVES + w;  // pair 0..35
+  int a = 0, rem = p;
+  while (rem >= 8 - a) { rem -= 8 - a; ++a; }
+  const int b = a + rem;
   const int e = eg * 64 + l;
   const double cuu = g.h * 0.125, cue = g.h * g.h * 0.125, cee = g.h * g.h * g.h * 0.125;
   const int64_t stride = (int64_t)8 * ck.NEcpad;
@@ -301,30 +444,26 @@ __device__ __forceinline__ void element_matrix_body(const Grid& g, const Chunk& 
 __global__ void __launch_bounds__(EM_WAVES * 64, EM_MINB) element_matrix_kernel(Grid g, Chunk ck,
                                                                           const double* __restrict__ qp,
                                                                           const DevCard* __restrict__ cd,
-                                                                          double* __restrict__ E, int npair) {
-  element_matrix_body(g, ck, qp, cd, E, npair, blockIdx.x, gridDim.x);
+                                                                          double* __restrict__ E) {
+  element_matrix_body(g, ck, qp, cd, E, blockIdx.x, gridDim.x);
 }
 
 void launch_element_matrices(const Grid& g, const Chunk& ck, const double* qp, const DevCard* cd, double* elem,
-                             hipStream_t s, bool diag_only) {
-  const int groups = ck.NEcpad / 64;
-  const int npair = diag_only ? 8 : NPAIR;
-  const int nb = groups * (npair / EM_WAVES);
-  element_matrix_kernel<<<(nb + 7) / 8 * 8, EM_WAVES * 64, 0, s>>>(g, ck, qp, cd, elem, npair);
+                             hipStream_t s) {
+  const int nb = ck.NEcpad / 64 * (NPAIR / EM_WAVES);
+  element_matrix_kernel<<<(nb + 7) / 8 * 8, EM_WAVES * 64, 0, s>>>(g, ck, qp, cd, elem);
 }
 
 // Stored block (n, n + off(13 + u)) = sum over the <= 8 elements containing
 // both nodes of their element blocks, in a fixed order (bitwise reproducible).
 // One wavefront per (tile, u): 64 consecutive rows, coalesced element reads
 // and coalesced tiled writes.
-// nup = NUP: every stored block; nup = 1: the diagonal blocks only.
 __device__ __forceinline__ void jacobian_gather_body(const Grid& g, const Chunk& ck, const double* __restrict__ E,
                                                      double* __restrict__ A64, float* __restrict__ A32,
-                                                     double* __restrict__ diag64, int nblocks, int nup, int bid,
-                                                     int nblk) {
+                                                     double* __restrict__ diag64, int nblocks, int bid, int nblk) {
   const int L = xcd_logical(bid, nblk);
   if (L >= nblocks) return;
-  const int t = ck.n0 / TILE + L / nup, u = L % nup;
+  const int t = ck.n0 / TILE + L / NUP, u = L % NUP;
   const int sten = 13 + u;
   const int l = threadIdx.x;
   const int n = t * TILE + l;
@@ -379,29 +518,29 @@ __device__ __forceinline__ void jacobian_gather_body(const Grid& g, const Chunk&
 }
 __global__ void __launch_bounds__(64) jacobian_gather_kernel(Grid g, Chunk ck, const double* __restrict__ E,
                                                              double* __restrict__ A64, float* __restrict__ A32,
-                                                             double* __restrict__ diag64, int nblocks, int nup) {
-  jacobian_gather_body(g, ck, E, A64, A32, diag64, nblocks, nup, blockIdx.x, gridDim.x);
+                                                             double* __restrict__ diag64, int nblocks) {
+  jacobian_gather_body(g, ck, E, A64, A32, diag64, nblocks, blockIdx.x, gridDim.x);
 }
 
 void launch_jacobian_gather(const Grid& g, const Chunk& ck, const double* elem, double* A64, float* A32,
-                            double* diag64, hipStream_t s, bool diag_only) {
+                            double* diag64, hipStream_t s) {
   const int t0 = ck.n0 / TILE, t1 = (ck.n1 + TILE - 1) / TILE;
-  const int nup = diag_only ? 1 : NUP;
-  const int nblocks = (t1 - t0) * nup;
+  const int nblocks = (t1 - t0) * NUP;
   const int nb_pad = (nblocks + 7) / 8 * 8;
-  jacobian_gather_kernel<<<nb_pad, TILE, 0, s>>>(g, ck, elem, diag_only ? nullptr : A64, diag_only ? nullptr : A32,
-                                                 diag64, nblocks, nup);
+  jacobian_gather_kernel<<<nb_pad, TILE, 0, s>>>(g, ck, elem, A64, A32, diag64, nblocks);
 }
 
-// Symmetric elimination on the stored blocks: entries in constrained rows of
+// Symmetric elimination on the stored blocks (nup = NUP; nup = 1: the diagonal
+// blocks of a matrix-free level): entries in constrained rows of
 // node n or constrained columns of node m are zeroed, the diagonal of a
 // constrained dof is 1.
 __device__ __forceinline__ void apply_dirichlet_body(const Grid& g, const uint16_t* __restrict__ mask,
                                                      double* __restrict__ A64, float* __restrict__ A32,
-                                                     double* __restrict__ diag64, int nblocks, int bid, int nblk) {
+                                                     double* __restrict__ diag64, int nblocks, int nup, int bid,
+                                                     int nblk) {
   const int L = xcd_logical(bid, nblk);
   if (L >= nblocks) return;
-  const int t = L / NUP, u = L - t * NUP;
+  const int t = L / nup, u = L - t * nup;
   const int sten = 13 + u;
   const int l = threadIdx.x;
   const int n = t * TILE + l;
@@ -427,15 +566,16 @@ __device__ __forceinline__ void apply_dirichlet_body(const Grid& g, const uint16
 }
 __global__ void __launch_bounds__(64) apply_dirichlet_kernel(Grid g, const uint16_t* __restrict__ mask,
                                                              double* __restrict__ A64, float* __restrict__ A32,
-                                                             double* __restrict__ diag64, int nblocks) {
-  apply_dirichlet_body(g, mask, A64, A32, diag64, nblocks, blockIdx.x, gridDim.x);
+                                                             double* __restrict__ diag64, int nblocks, int nup) {
+  apply_dirichlet_body(g, mask, A64, A32, diag64, nblocks, nup, blockIdx.x, gridDim.x);
 }
 
 void launch_apply_dirichlet(const Grid& g, const uint16_t* mask, double* A64, float* A32, double* diag64,
                             hipStream_t s) {
-  const int nblocks = g.ntiles * NUP;
+  const int nup = (A64 || A32) ? NUP : 1;
+  const int nblocks = g.ntiles * nup;
   const int nb_pad = (nblocks + 7) / 8 * 8;
-  apply_dirichlet_kernel<<<nb_pad, TILE, 0, s>>>(g, mask, A64, A32, diag64, nblocks);
+  apply_dirichlet_kernel<<<nb_pad, TILE, 0, s>>>(g, mask, A64, A32, diag64, nblocks, nup);
 }
 
 // NDOF x NDOF inverse by Gauss-Jordan elimination with partial pivoting (the
@@ -604,20 +744,26 @@ __global__ void __launch_bounds__(128) qp_hess_batch(const AJob* __restrict__ jo
   const AJob& j = find_job(jobs, njobs, bid);
   qp_body<true, PD, MIX>(j.g, j.ck, j.state, j.cd, j.qp, bid);
 }
+template <int PD, int MIX>
+__global__ void __launch_bounds__(128) qp_mf_batch(const AJob* __restrict__ jobs, int njobs) {
+  int bid;
+  const AJob& j = find_job(jobs, njobs, bid);
+  qp_mf_body<PD, MIX>(j.g, j.ck, j.state, j.cd, j.qp, j.D64, j.D32, bid);
+}
 __global__ void __launch_bounds__(EM_WAVES * 64, EM_MINB) element_matrix_batch(const AJob* __restrict__ jobs, int njobs) {
   int bid;
   const AJob& j = find_job(jobs, njobs, bid);
-  element_matrix_body(j.g, j.ck, j.qp, j.cd, j.elem, j.npair, bid, j.nblk);
+  element_matrix_body(j.g, j.ck, j.qp, j.cd, j.elem, bid, j.nblk);
 }
 __global__ void __launch_bounds__(64) jacobian_gather_batch(const AJob* __restrict__ jobs, int njobs) {
   int bid;
   const AJob& j = find_job(jobs, njobs, bid);
-  jacobian_gather_body(j.g, j.ck, j.elem, j.A64, j.A32, j.diag64, j.nblocks, j.nup, bid, j.nblk);
+  jacobian_gather_body(j.g, j.ck, j.elem, j.A64, j.A32, j.diag64, j.nblocks, bid, j.nblk);
 }
 __global__ void __launch_bounds__(64) apply_dirichlet_batch(const AJob* __restrict__ jobs, int njobs) {
   int bid;
   const AJob& j = find_job(jobs, njobs, bid);
-  apply_dirichlet_body(j.g, j.mask, j.A64, j.A32, j.diag64, j.nblocks, bid, j.nblk);
+  apply_dirichlet_body(j.g, j.mask, j.A64, j.A32, j.diag64, j.nblocks, j.nup, bid, j.nblk);
 }
 __global__ void __launch_bounds__(BI_THREADS) block_inverse_batch(const AJob* __restrict__ jobs, int njobs) {
   int bid;
@@ -631,59 +777,69 @@ __global__ void __launch_bounds__(256) residual_gather_batch(const AJob* __restr
 }
 
 // the launch shapes of the single-problem launchers, per job
-int assembly_job_blocks(int op, AJob& j, bool diag_only) {
+int assembly_job_blocks(int op, AJob& j) {
   const Grid& g = j.g;
   const Chunk& ck = j.ck;
   switch (op) {
     case AOP_QP_HESS: return (int)(((int64_t)8 * ck.NEcpad + 127) / 128);
-    case AOP_ELEMENT: {
-      j.npair = diag_only ? 8 : NPAIR;
-      const int nb = (ck.NEcpad / 64) * (j.npair / EM_WAVES);
-      return (nb + 7) / 8 * 8;
-    }
+    case AOP_QP_MF: return qp_mf_blocks(ck);
+    case AOP_ELEMENT: return ((ck.NEcpad / 64) * (NPAIR / EM_WAVES) + 7) / 8 * 8;
     case AOP_GATHER: {
       const int t0 = ck.n0 / TILE, t1 = (ck.n1 + TILE - 1) / TILE;
-      j.nup = diag_only ? 1 : NUP;
-      j.nblocks = (t1 - t0) * j.nup;
+      j.nblocks = (t1 - t0) * NUP;
       return (j.nblocks + 7) / 8 * 8;
     }
+    case AOP_MF_DIAG: return mf_diag_blocks(ck);
+    case AOP_MF_DIAG_GATHER: return mf_diag_gather_blocks(ck);
     case AOP_DIRICHLET:
-      j.nblocks = g.ntiles * NUP;
+      j.nup = (j.A64 || j.A32) ? NUP : 1;
+      j.nblocks = g.ntiles * j.nup;
       return (j.nblocks + 7) / 8 * 8;
     case AOP_BLOCK_INVERSE: return (g.Npad + BI_THREADS - 1) / BI_THREADS;
     case AOP_RESIDUAL: return (ck.n1 - ck.n0 + 255) / 256;
-    case AOP_MF_PACK: return mf_pack_job_blocks(j);
     default: return 0;
   }
+}
+
+// pade = Pade order + QP_LOG_MIX for logarithmic mixing
+struct QpHessBatch {
+  template <int PD, int MIX>
+  static void run(const AJob* jobs, int njobs, int blocks, hipStream_t s) {
+    qp_hess_batch<PD, MIX><<<blocks, 128, 0, s>>>(jobs, njobs);
+  }
+};
+struct QpMfBatch {
+  template <int PD, int MIX>
+  static void run(const AJob* jobs, int njobs, int blocks, hipStream_t s) {
+    qp_mf_batch<PD, MIX><<<blocks, 128, 0, s>>>(jobs, njobs);
+  }
+};
+template <class K>
+void launch_qp_batch(int pade, const AJob* jobs, int njobs, int blocks, hipStream_t s) {
+  const int pd = pade % QP_LOG_MIX;
+  if (pade >= QP_LOG_MIX) {
+    if (pd == 11) K::template run<11, 1>(jobs, njobs, blocks, s);
+    else if (pd == 33) K::template run<33, 1>(jobs, njobs, blocks, s);
+    else K::template run<22, 1>(jobs, njobs, blocks, s);
+  } else if (pd == 11) K::template run<11, 0>(jobs, njobs, blocks, s);
+  else if (pd == 33) K::template run<33, 0>(jobs, njobs, blocks, s);
+  else K::template run<22, 0>(jobs, njobs, blocks, s);
 }
 
 void launch_assembly_batch(int op, int pade, const AJob* jobs, int njobs, int blocks, hipStream_t s) {
   if (njobs <= 0 || blocks <= 0) return;
   switch (op) {
-    case AOP_QP_HESS: {  // pade = Pade order + QP_LOG_MIX for logarithmic mixing
-      const int pd = pade % QP_LOG_MIX;
-      if (pade >= QP_LOG_MIX) {
-        if (pd == 11)
-          qp_hess_batch<11, 1><<<blocks, 128, 0, s>>>(jobs, njobs);
-        else if (pd == 33)
-          qp_hess_batch<33, 1><<<blocks, 128, 0, s>>>(jobs, njobs);
-        else
-          qp_hess_batch<22, 1><<<blocks, 128, 0, s>>>(jobs, njobs);
-      } else if (pd == 11) {
-        qp_hess_batch<11, 0><<<blocks, 128, 0, s>>>(jobs, njobs);
-      } else if (pd == 33) {
-        qp_hess_batch<33, 0><<<blocks, 128, 0, s>>>(jobs, njobs);
-      } else {
-        qp_hess_batch<22, 0><<<blocks, 128, 0, s>>>(jobs, njobs);
-      }
+    case AOP_QP_HESS: launch_qp_batch<QpHessBatch>(pade, jobs, njobs, blocks, s); break;
+    case AOP_QP_MF:
+      if constexpr (MF_AVAILABLE) launch_qp_batch<QpMfBatch>(pade, jobs, njobs, blocks, s);
       break;
-    }
     case AOP_ELEMENT: element_matrix_batch<<<blocks, EM_WAVES * 64, 0, s>>>(jobs, njobs); break;
     case AOP_GATHER: jacobian_gather_batch<<<blocks, TILE, 0, s>>>(jobs, njobs); break;
     case AOP_DIRICHLET: apply_dirichlet_batch<<<blocks, TILE, 0, s>>>(jobs, njobs); break;
     case AOP_BLOCK_INVERSE: block_inverse_batch<<<blocks, BI_THREADS, 0, s>>>(jobs, njobs); break;
     case AOP_RESIDUAL: residual_gather_batch<<<blocks, 256, 0, s>>>(jobs, njobs); break;
-    case AOP_MF_PACK: launch_mf_pack_batch(jobs, njobs, blocks, s); break;
+    case AOP_MF_DIAG:
+    case AOP_MF_DIAG_GATHER: launch_mf_diag_batch(op, jobs, njobs, blocks, s); break;
     default: break;
   }
 }
