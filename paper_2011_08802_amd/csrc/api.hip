@@ -1096,6 +1096,18 @@ int finish_system(mvpf_problem* p, bool coarse_inline) {
   return 0;
 }
 
+// Gauss-point tangents and residual rows of the matrix-free finest level
+void finest_tangents(mvpf_problem* p) {
+  Level& L0 = p->lev[0];
+  for (const Chunk& ck : make_chunks(L0.g, p->ne_use)) {
+    timer_begin(p, p->t_qp);
+    launch_qp_mf(L0.g, ck, L0.state, p->card, p->pade, p->mixing, p->qp, p->Dmf64, p->Dmf32, p->stream);
+    // written: gradient (15) and tangent (93, FP64 and in mixed mode FP32) per Gauss point
+    timer_end(p, p->t_qp, 8.0 * (double)ck.NEc * (8 * NQ + MF_VALUES * (p->Dmf32 ? 1.5 : 1.0)));
+    launch_residual_gather(L0.g, ck, L0.state, p->qp, p->card, p->R, p->stream);
+  }
+}
+
 // diagonal blocks of the matrix-free finest level from its Gauss-point
 // tangents, slab by slab where the element buffer does not hold the whole level
 int mf_diagonal(mvpf_problem* p, double depth) {
@@ -1110,20 +1122,12 @@ int mf_diagonal(mvpf_problem* p, double depth) {
   return 0;
 }
 
-// Galerkin hierarchy (opts.coarse = MVPF_COARSE_GALERKIN, galerkin.hip): the
-// finest tangent's element matrices (all 36 node pairs, contact included)
-// are coarsened slab by slab into level 1's, each level's into the next's;
-// every coarse level's stored blocks are gathered from its element matrices.
-// The coarsest level is finished first so that its inversion overlaps the
-// intermediate levels' gathers and the block inverses.
-int build_system_galerkin(mvpf_problem* p, double depth, bool coarse_inline) {
+// level-1 element matrices of an assembled finest level: its element matrices
+// (all 36 node pairs, contact included) coarsened slab by slab, and its stored
+// blocks
+int galerkin_assembled_finest(mvpf_problem* p, double depth) {
   hipStream_t s = p->stream;
   Level& L0 = p->lev[0];
-  const int Lc = p->L - 1;
-  for (int l = 1; l < p->L; ++l)
-    if (!p->gal[l]) TRY(dalloc(p, &p->gal[l], (size_t)NPAIR * NBLK * p->lev[l].g.NEpad));
-  TRY(system_prelude(p, depth));
-  const bool mf = use_mf(p);
   const Grid& g1 = p->lev[1].g;
   const int64_t nxy = (int64_t)L0.g.nx * L0.g.ny;
   int zdone = 0;  // level-1 element layers coarsened so far
@@ -1131,11 +1135,10 @@ int build_system_galerkin(mvpf_problem* p, double depth, bool coarse_inline) {
     timer_begin(p, p->t_qp);
     launch_qp(L0.g, ck, L0.state, p->card, p->pade, p->mixing, p->qp, true, s);
     timer_end(p, p->t_qp, 8.0 * 8 * QP_HESS * (double)ck.NEc);
-    if (mf) launch_qp_mf(L0.g, ck, L0.state, p->card, p->pade, p->mixing, p->qp, p->Dmf64, p->Dmf32, s);
     launch_residual_gather(L0.g, ck, L0.state, p->qp, p->card, p->R, s);
     launch_element_matrices(L0.g, ck, p->qp, p->card, p->elem, s);
     if (contact(p)) launch_contact_element(L0.g, ck, make_sphere(L0.g, p->load, depth), L0.state, p->elem, s);
-    if (!mf) launch_jacobian_gather(L0.g, ck, p->elem, L0.A64, L0.A32, L0.diag64, s);
+    launch_jacobian_gather(L0.g, ck, p->elem, L0.A64, L0.A32, L0.diag64, s);
     // level-1 layers Z whose child layers 2Z and 2Z + 1 this slab holds (slabs
     // overlap by one element layer, so each layer is met in one of them)
     const int ez0 = (int)(ck.e0 / nxy), ez1 = (int)((ck.e0 + ck.NEc) / nxy);
@@ -1153,7 +1156,42 @@ int build_system_galerkin(mvpf_problem* p, double depth, bool coarse_inline) {
     p->err = "internal: coarse layers left out of the Galerkin product";
     return MVPF_EDEVICE;
   }
-  if (mf) TRY(mf_diagonal(p, depth));
+  return 0;
+}
+
+// the same from a matrix-free finest level: Gauss-point tangents and diagonal
+// blocks; level 1 straight from the tangents except its top layer, whose child
+// layers' element matrices carry the loading's constraints and the contact
+int galerkin_mf_finest(mvpf_problem* p, double depth) {
+  hipStream_t s = p->stream;
+  Level& L0 = p->lev[0];
+  const Grid& g0 = L0.g;
+  const Grid& g1 = p->lev[1].g;
+  finest_tangents(p);
+  const int64_t nxy = (int64_t)g0.nx * g0.ny;
+  const Chunk top{(g0.nz - 2) * nxy, (int)(2 * nxy), (int)((2 * nxy + TILE - 1) / TILE * TILE), 0, 0};
+  launch_qp(g0, top, L0.state, p->card, p->pade, p->mixing, p->qp, true, s);
+  launch_element_matrices(g0, top, p->qp, p->card, p->elem, s);
+  if (contact(p)) launch_contact_element(g0, top, make_sphere(g0, p->load, depth), L0.state, p->elem, s);
+  launch_galerkin_coarsen(g0, top, p->elem, L0.mask, g1, g1.nz - 1, g1.nz, p->gal[1], s);
+  launch_galerkin_direct(g0, p->Dmf64, p->card, g1, 0, g1.nz - 1, p->gal[1], s);
+  return mf_diagonal(p, depth);
+}
+
+// Galerkin hierarchy (opts.coarse = MVPF_COARSE_GALERKIN, galerkin.hip): the
+// finest tangent is coarsened to level 1's element matrices, each level's into
+// the next's; every coarse level's stored blocks are gathered from its element
+// matrices.  The coarsest level is finished first so that its inversion
+// overlaps the intermediate levels' gathers and the block inverses.
+int build_system_galerkin(mvpf_problem* p, double depth, bool coarse_inline) {
+  hipStream_t s = p->stream;
+  Level& L0 = p->lev[0];
+  const int Lc = p->L - 1;
+  for (int l = 1; l < p->L; ++l)
+    if (!p->gal[l]) TRY(dalloc(p, &p->gal[l], (size_t)NPAIR * NBLK * p->lev[l].g.NEpad));
+  TRY(system_prelude(p, depth));
+  const bool mf = use_mf(p);
+  TRY(mf ? galerkin_mf_finest(p, depth) : galerkin_assembled_finest(p, depth));
   TRY(system_rhs(p, depth));
   launch_apply_dirichlet(L0.g, L0.mask, mf ? nullptr : L0.A64, mf ? nullptr : L0.A32, L0.diag64, s);
   auto whole = [](const Grid& g) { return Chunk{0, g.NE, g.NEpad, 0, g.Npad}; };
@@ -1188,22 +1226,21 @@ int build_system(mvpf_problem* p, double depth, bool coarse_inline = true) {
   // finest: residual and unconstrained tangent (on a matrix-free level the
   // Gauss-point tangents and the diagonal blocks)
   const bool mf = use_mf(p);
-  for (const Chunk& ck : make_chunks(L0.g, p->ne_use)) {
-    timer_begin(p, p->t_qp);
-    if (mf)
-      launch_qp_mf(L0.g, ck, L0.state, p->card, p->pade, p->mixing, p->qp, p->Dmf64, p->Dmf32, s);
-    else
+  if (mf) {
+    finest_tangents(p);
+    TRY(mf_diagonal(p, depth));
+  } else {
+    for (const Chunk& ck : make_chunks(L0.g, p->ne_use)) {
+      timer_begin(p, p->t_qp);
       launch_qp(L0.g, ck, L0.state, p->card, p->pade, p->mixing, p->qp, true, s);
-    // written per Gauss point: gradient, and the packed Hessian or its Green-strain form
-    timer_end(p, p->t_qp, 8.0 * (double)ck.NEc *
-                              (mf ? 8 * NQ + MF_VALUES * (p->Dmf32 ? 1.5 : 1.0) : 8.0 * QP_HESS));
-    launch_residual_gather(L0.g, ck, L0.state, p->qp, p->card, p->R, s);
-    if (mf) continue;
-    launch_element_matrices(L0.g, ck, p->qp, p->card, p->elem, s);
-    if (contact(p)) launch_contact_element(L0.g, ck, make_sphere(L0.g, p->load, depth), L0.state, p->elem, s);
-    launch_jacobian_gather(L0.g, ck, p->elem, L0.A64, L0.A32, L0.diag64, s);
+      // written: gradient (15) and packed Hessian (120) per Gauss point
+      timer_end(p, p->t_qp, 8.0 * 8 * QP_HESS * (double)ck.NEc);
+      launch_residual_gather(L0.g, ck, L0.state, p->qp, p->card, p->R, s);
+      launch_element_matrices(L0.g, ck, p->qp, p->card, p->elem, s);
+      if (contact(p)) launch_contact_element(L0.g, ck, make_sphere(L0.g, p->load, depth), L0.state, p->elem, s);
+      launch_jacobian_gather(L0.g, ck, p->elem, L0.A64, L0.A32, L0.diag64, s);
+    }
   }
-  if (mf) TRY(mf_diagonal(p, depth));
   // lifting of the prescribed increment, then symmetric elimination
   TRY(system_rhs(p, depth));
   launch_apply_dirichlet(L0.g, L0.mask, mf ? nullptr : L0.A64, mf ? nullptr : L0.A32, L0.diag64, s);

@@ -324,6 +324,11 @@ void launch_apply_dirichlet(const Grid& g, const uint16_t* mask, double* A64, fl
 // constrained-dof masks; parents go to Ep (whole level, stride gp.NEpad)
 void launch_galerkin_coarsen(const Grid& gc, const Chunk& ckc, const double* Ec, const uint16_t* maskc,
                              const Grid& gp, int Z0, int Z1, double* Ep, hipStream_t s);
+// the same for layers Z0 .. Z1 - 1 from a matrix-free finest level's Gauss-point
+// tangents (layers without constrained child-level unknowns above the plane z = 0,
+// whose u are all constrained, and without contact)
+void launch_galerkin_direct(const Grid& gc, const double* D64, const DevCard* cd, const Grid& gp, int Z0, int Z1,
+                            double* Ep, hipStream_t s);
 // block inverses of the diagonal blocks (outputs may be null; DinvS32: packed
 // upper triangles in FP32)
 void launch_block_inverse(const Grid& g, const double* diag64, double* Dinv64, float* Dinv32, float* DinvS32,

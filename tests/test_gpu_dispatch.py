@@ -4,6 +4,7 @@ from dataclasses import replace
 
 import numpy as np
 import pytest
+import torch
 
 import synth
 from gpu_util import OracleCase, gpu_problem, rel, seeded_state
@@ -42,4 +43,32 @@ def test_coarse_inverse_of_an_indefinite_operator():
     z = gp.precondition(_dev(v)).cpu().numpy()
     zo = oc.mg.precondition(v)
     assert rel(z, zo) < 1e-10, rel(z, zo)
+    gp.close()
+
+
+@pytest.mark.parametrize("nx,ny,nz,kind", [(4, 4, 4, "patch"), (20, 12, 8, "patch"), (34, 6, 6, "cap"),
+                                           (16, 16, 8, "sphere")])
+def test_galerkin_level1_from_gauss_points(nx, ny, nz, kind):
+    """Level 1 of the Galerkin hierarchy summed straight from the Gauss-point
+    tangents (parents per row below, above and at multiples of a workgroup's
+    8; the constrained bottom plane; the top layer through the element
+    matrices, with contact) is the coarsened assembled finest level.  Entries
+    of ~1000 terms summed in another order."""
+    h = 1.0 / nx
+    p = synth.Problem(nx, ny, nz, lx=1.0, ly=ny * h, lz=nz * h, n_levels=2, kind=kind, patch=2, radius=0.2,
+                      depth_increment=0.01)
+    U, En = seeded_state(p, 1e-3)
+    gp = gpu_problem(p, U, En, "fp64", coarse="galerkin")
+    gp.newton_system(p.depth_increment)
+    n1 = (nx // 2 + 1) * (ny // 2 + 1) * (nz // 2 + 1)
+    x = _dev(np.random.default_rng(3).standard_normal(9 * n1))
+    y = gp.jacobian_apply(1, x)
+    ya = gp.jacobian_apply(1, x.abs())
+    gp.set_tuning("matrix_free", 0, 0)
+    gp.newton_system(p.depth_increment)
+    z = gp.jacobian_apply(1, x)
+    assert torch.isfinite(y).all()
+    err = (y - z).reshape(-1, 9)
+    scale = z.reshape(-1, 9).abs().amax(0) + ya.reshape(-1, 9).abs().amax(0)
+    assert float((err.abs().amax(0) / scale).max()) < 1e-12, (err.abs().amax(0) / scale)
     gp.close()
