@@ -918,7 +918,7 @@ int allocate(mvpf_problem* p) {
   {
     // Gauss-point and element-matrix buffers: the whole finest level if that
     // fits ASSEMBLY_FULL_MAX bytes, else slabs of ASSEMBLY_SLAB_BYTES
-    const int64_t per = (int64_t)(QP_HESS_ALLOC * 8 + NPAIR * NBLK) * (int64_t)sizeof(double);
+    const int64_t per = (int64_t)(NHP_PAD * 8 + NPAIR * NBLK) * (int64_t)sizeof(double);
     const int64_t nxy = (int64_t)g0.nx * g0.ny;
     if ((int64_t)g0.NEpad * per <= ASSEMBLY_FULL_MAX)
       p->ne_cap = g0.NEpad;
@@ -926,7 +926,7 @@ int allocate(mvpf_problem* p) {
       p->ne_cap = std::max<int64_t>(ASSEMBLY_SLAB_BYTES / per, 2 * nxy + TILE) / TILE * TILE;
     p->ne_cap = std::min<int64_t>(p->ne_cap, g0.NEpad);
     p->ne_use = p->ne_cap;
-    TRY(dalloc(p, &p->qp, (size_t)QP_HESS_ALLOC * 8 * p->ne_cap));
+    TRY(dalloc(p, &p->qp, (size_t)NHP_PAD * 8 * p->ne_cap));
     TRY(dalloc(p, &p->elem, (size_t)NPAIR * NBLK * p->ne_cap));
   }
   {
@@ -986,13 +986,20 @@ int free_norm(mvpf_problem* p, const double* v, double* out) {
 // residual at the current state into p->R (masks of `depth` for the norm)
 bool contact(const mvpf_problem* p) { return p->load.kind == MVPF_LOAD_SPHERE; }
 
+// residual rows at the current state, without contact, into p->R; Cbuf holds
+// the element outputs of the whole level (36 or 60 merged values per element
+// and their leftovers, fewer than its 13 NDOF values per node or
+// mf_out_values(g))
+void residual_rows(mvpf_problem* p) {
+  Level& L0 = p->lev[0];
+  launch_residual(L0.g, Chunk{0, L0.g.NE, L0.g.NEpad, 0, L0.g.Npad}, L0.state, p->card, p->pade, p->mixing,
+                  (double*)p->Cbuf, p->R, p->stream);
+}
+
 int compute_residual(mvpf_problem* p, double depth, double* norm_free) {
   Level& L0 = p->lev[0];
   launch_dirichlet_masks(L0.g, p->load, depth, L0.mask, L0.target, p->stream);
-  for (const Chunk& ck : make_chunks(L0.g, p->ne_use)) {
-    launch_qp(L0.g, ck, L0.state, p->card, p->pade, p->mixing, p->qp, false, p->stream);
-    launch_residual_gather(L0.g, ck, L0.state, p->qp, p->card, p->R, p->stream);
-  }
+  residual_rows(p);
   if (contact(p)) launch_contact_residual(L0.g, make_sphere(L0.g, p->load, depth), L0.state, p->R, p->stream);
   TRY(launch_check(p, "residual"));
   if (norm_free) TRY(free_norm(p, p->R, norm_free));
@@ -1004,7 +1011,7 @@ int compute_residual(mvpf_problem* p, double depth, double* norm_free) {
 void assemble_coarse_level(mvpf_problem* p, int l, double depth) {
   Level& C = p->lev[l];
   for (const Chunk& ck : make_chunks(C.g, p->ne_use)) {
-    launch_qp(C.g, ck, C.state, p->card, p->pade, p->mixing, p->qp, true, p->stream);
+    launch_qp(C.g, ck, C.state, p->card, p->pade, p->mixing, p->qp, p->stream);
     launch_element_matrices(C.g, ck, p->qp, p->card, p->elem, p->stream);
     if (contact(p)) launch_contact_element(C.g, ck, make_sphere(C.g, p->load, depth), C.state, p->elem, p->stream);
     launch_jacobian_gather(C.g, ck, p->elem, C.A64, C.A32, C.diag64, p->stream);
@@ -1096,16 +1103,14 @@ int finish_system(mvpf_problem* p, bool coarse_inline) {
   return 0;
 }
 
-// Gauss-point tangents and residual rows of the matrix-free finest level
+// Gauss-point tangents of the matrix-free finest level
 void finest_tangents(mvpf_problem* p) {
   Level& L0 = p->lev[0];
-  for (const Chunk& ck : make_chunks(L0.g, p->ne_use)) {
-    timer_begin(p, p->t_qp);
-    launch_qp_mf(L0.g, ck, L0.state, p->card, p->pade, p->mixing, p->qp, p->Dmf64, p->Dmf32, p->stream);
-    // written: gradient (15) and tangent (93, FP64 and in mixed mode FP32) per Gauss point
-    timer_end(p, p->t_qp, 8.0 * (double)ck.NEc * (8 * NQ + MF_VALUES * (p->Dmf32 ? 1.5 : 1.0)));
-    launch_residual_gather(L0.g, ck, L0.state, p->qp, p->card, p->R, p->stream);
-  }
+  timer_begin(p, p->t_qp);
+  launch_qp_mf(L0.g, Chunk{0, L0.g.NE, L0.g.NEpad, 0, L0.g.Npad}, L0.state, p->card, p->pade, p->mixing, p->Dmf64,
+               p->Dmf32, p->stream);
+  // written per Gauss point: 93 values, FP64 and in mixed mode FP32
+  timer_end(p, p->t_qp, 8.0 * (double)L0.g.NE * MF_VALUES * (p->Dmf32 ? 1.5 : 1.0));
 }
 
 // diagonal blocks of the matrix-free finest level from its Gauss-point
@@ -1133,9 +1138,8 @@ int galerkin_assembled_finest(mvpf_problem* p, double depth) {
   int zdone = 0;  // level-1 element layers coarsened so far
   for (const Chunk& ck : make_chunks(L0.g, p->ne_use)) {
     timer_begin(p, p->t_qp);
-    launch_qp(L0.g, ck, L0.state, p->card, p->pade, p->mixing, p->qp, true, s);
-    timer_end(p, p->t_qp, 8.0 * 8 * QP_HESS * (double)ck.NEc);
-    launch_residual_gather(L0.g, ck, L0.state, p->qp, p->card, p->R, s);
+    launch_qp(L0.g, ck, L0.state, p->card, p->pade, p->mixing, p->qp, s);
+    timer_end(p, p->t_qp, 8.0 * 8 * NHP * (double)ck.NEc);
     launch_element_matrices(L0.g, ck, p->qp, p->card, p->elem, s);
     if (contact(p)) launch_contact_element(L0.g, ck, make_sphere(L0.g, p->load, depth), L0.state, p->elem, s);
     launch_jacobian_gather(L0.g, ck, p->elem, L0.A64, L0.A32, L0.diag64, s);
@@ -1170,7 +1174,7 @@ int galerkin_mf_finest(mvpf_problem* p, double depth) {
   finest_tangents(p);
   const int64_t nxy = (int64_t)g0.nx * g0.ny;
   const Chunk top{(g0.nz - 2) * nxy, (int)(2 * nxy), (int)((2 * nxy + TILE - 1) / TILE * TILE), 0, 0};
-  launch_qp(g0, top, L0.state, p->card, p->pade, p->mixing, p->qp, true, s);
+  launch_qp(g0, top, L0.state, p->card, p->pade, p->mixing, p->qp, s);
   launch_element_matrices(g0, top, p->qp, p->card, p->elem, s);
   if (contact(p)) launch_contact_element(g0, top, make_sphere(g0, p->load, depth), L0.state, p->elem, s);
   launch_galerkin_coarsen(g0, top, p->elem, L0.mask, g1, g1.nz - 1, g1.nz, p->gal[1], s);
@@ -1191,6 +1195,7 @@ int build_system_galerkin(mvpf_problem* p, double depth, bool coarse_inline) {
     if (!p->gal[l]) TRY(dalloc(p, &p->gal[l], (size_t)NPAIR * NBLK * p->lev[l].g.NEpad));
   TRY(system_prelude(p, depth));
   const bool mf = use_mf(p);
+  residual_rows(p);
   TRY(mf ? galerkin_mf_finest(p, depth) : galerkin_assembled_finest(p, depth));
   TRY(system_rhs(p, depth));
   launch_apply_dirichlet(L0.g, L0.mask, mf ? nullptr : L0.A64, mf ? nullptr : L0.A32, L0.diag64, s);
@@ -1225,6 +1230,7 @@ int build_system(mvpf_problem* p, double depth, bool coarse_inline = true) {
   for (int l = Lc - 1; l >= 1; --l) assemble_coarse_level(p, l, depth);
   // finest: residual and unconstrained tangent (on a matrix-free level the
   // Gauss-point tangents and the diagonal blocks)
+  residual_rows(p);
   const bool mf = use_mf(p);
   if (mf) {
     finest_tangents(p);
@@ -1232,10 +1238,9 @@ int build_system(mvpf_problem* p, double depth, bool coarse_inline = true) {
   } else {
     for (const Chunk& ck : make_chunks(L0.g, p->ne_use)) {
       timer_begin(p, p->t_qp);
-      launch_qp(L0.g, ck, L0.state, p->card, p->pade, p->mixing, p->qp, true, s);
+      launch_qp(L0.g, ck, L0.state, p->card, p->pade, p->mixing, p->qp, s);
       // written: gradient (15) and packed Hessian (120) per Gauss point
-      timer_end(p, p->t_qp, 8.0 * 8 * QP_HESS * (double)ck.NEc);
-      launch_residual_gather(L0.g, ck, L0.state, p->qp, p->card, p->R, s);
+      timer_end(p, p->t_qp, 8.0 * 8 * NHP * (double)ck.NEc);
       launch_element_matrices(L0.g, ck, p->qp, p->card, p->elem, s);
       if (contact(p)) launch_contact_element(L0.g, ck, make_sphere(L0.g, p->load, depth), L0.state, p->elem, s);
       launch_jacobian_gather(L0.g, ck, p->elem, L0.A64, L0.A32, L0.diag64, s);
@@ -2155,6 +2160,7 @@ int batch_assemble(mvpf_batch* b, const double* depths, hipStream_t s) {
     j.cd = p->card;
     j.qp = p->qp;
     j.elem = p->elem;
+    j.out = (double*)p->Cbuf;
     j.A64 = L.A64;
     j.A32 = L.A32;
     j.diag64 = L.diag64;
@@ -2243,7 +2249,8 @@ int batch_assemble(mvpf_batch* b, const double* depths, hipStream_t s) {
     }
     qp_steps(AOP_QP_MF, mp, mj);
     qp_steps(AOP_QP_HESS, ap, aj);
-    add(AOP_RESIDUAL, 0, js);
+    qp_steps(AOP_RESIDUAL, b->probs, js);
+    add(AOP_RESIDUAL_NODES, 0, js);
     add(AOP_MF_DIAG, 0, mj);
     add(AOP_ELEMENT, 0, aj);
     add(AOP_MF_DIAG_GATHER, 0, mj);

@@ -22,7 +22,7 @@
 //    36 node pairs p = (a <= b) of element el.
 //  * diagonal blocks and their inverses: slice t = D + t * Lay<T>::SLICE, same
 //    entry layout.
-//  * per-Gauss-point scratch: qp[(comp * 8 + g) * NEpad + e].
+//  * packed Gauss-point Hessians during assembly: qp[(comp * 8 + g) * NEpad + e].
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -69,13 +69,10 @@ __device__ __forceinline__ double read_lane(double v, int lane) {
 constexpr int NPAIR = 36;            // element node pairs a <= b
 constexpr int NBLK = NDOF * NDOF;
 constexpr int TILE = 64;
-constexpr int QP_GRAD = NQ;          // gradient components per Gauss point
-constexpr int QP_HESS = NQ + NHP;    // gradient + packed Hessian
 // packed Hessian entries rounded up to whole 8-component groups: the
 // element-matrix kernel stages them 8 at a time, so the Gauss-point buffer
-// holds NQ + NHP_PAD components (the padding is never used)
+// holds NHP_PAD components (the padding is never used)
 constexpr int NHP_PAD = (NHP + 7) / 8 * 8;
-constexpr int QP_HESS_ALLOC = NQ + NHP_PAD;
 constexpr int MAX_LEVELS = 8;
 constexpr int MAX_RESTART = 64;
 constexpr int SMALL_GRID_NODES = 10000;  // default size limit of the small-grid kernels
@@ -253,9 +250,9 @@ struct mvpf_problem {
   mvpf::DevCard* card = nullptr;     // device copy
   int pade = 22;                     // Pade order of the Hencky strain (11, 22, 33)
   int mixing = 0;                    // MVPF_MIX_LINEAR or MVPF_MIX_LOG
-  double* qp = nullptr;              // per-Gauss-point scratch (finest size)
+  double* qp = nullptr;              // packed Gauss-point Hessians (assembly scratch)
   double* elem = nullptr;            // element matrices, upper node pairs (finest size)
-  void* Cbuf = nullptr;              // lower-half contributions, 13 * NDOF * Npad doubles (finest size)
+  void* Cbuf = nullptr;              // lower-half contributions, 13 * NDOF * Npad doubles (finest size), or element outputs
   // matrix-free finest level (tuning key "matrix_free"): Gauss-point Hessians
   // in the matrix-free layout, FP64 (outer product, FP64 mode) and FP32
   // (mixed-mode smoother); element outputs go to Cbuf
@@ -308,9 +305,10 @@ namespace mvpf {
 // ---- launchers (all asynchronous on `s`) ----------------------------------
 // quadrature / assembly
 void launch_qp(const Grid& g, const Chunk& ck, const double* state, const DevCard* cd, int pade, int mixing,
-               double* qp, bool hess, hipStream_t s);
-void launch_residual_gather(const Grid& g, const Chunk& ck, const double* state, const double* qp, const DevCard* cd,
-                            double* R, hipStream_t s);
+               double* qp, hipStream_t s);
+// residual rows n0 .. n1 - 1 of a slab; E: scratch of slab_values(ck, nx, NDOF) values (pair.h)
+void launch_residual(const Grid& g, const Chunk& ck, const double* state, const DevCard* cd, int pade, int mixing,
+                     double* E, double* R, hipStream_t s);
 void launch_element_matrices(const Grid& g, const Chunk& ck, const double* qp, const DevCard* cd, double* elem,
                              hipStream_t s);
 void launch_jacobian_gather(const Grid& g, const Chunk& ck, const double* elem, double* A64, float* A32, double* diag64,
@@ -352,10 +350,9 @@ void launch_contact_apply(const Grid& g, const Sphere* sp, const double* state, 
 // matrix-free finest level (mf.hip): laid out for the six-variant card
 constexpr bool MF_AVAILABLE = NV == 6;
 size_t mf_hessian_values(const Grid& g);
-// Gauss-point tangents of a slab in Green-strain form, FP64 and (unless null)
-// FP32, and the gradients into qp (as launch_qp)
+// Gauss-point tangents of a slab in Green-strain form, FP64 and (unless null) FP32
 void launch_qp_mf(const Grid& g, const Chunk& ck, const double* state, const DevCard* cd, int pade, int mixing,
-                  double* qp, double* D64, float* D32, hipStream_t s);
+                  double* D64, float* D32, hipStream_t s);
 // diagonal blocks of a slab's node rows from the tangents; elem: scratch of
 // mf_diag_values(NEcpad, nx) values
 void launch_mf_diag(const Grid& g, const Chunk& ck, const double* D64, const DevCard* cd, double* elem, double* diag64,
@@ -549,6 +546,7 @@ struct AJob {
   const DevCard* cd;
   double* qp;                // Gauss-point scratch
   double* elem;              // element matrices
+  double* out;               // element outputs of the residual
   double *A64, *diag64, *Dinv64, *R, *D64;
   float *A32, *Dinv32, *D32, *DinvS32;
   const uint16_t* mask;
@@ -558,7 +556,7 @@ struct AJob {
 };
 constexpr int QP_LOG_MIX = 1000;  // added to the Pade order of a batched Hessian launch: logarithmic mixing
 enum AssemblyOp {
-  AOP_QP_HESS,        // Gauss-point gradients and Hessians (Pade order, + QP_LOG_MIX for log mixing)
+  AOP_QP_HESS,        // Gauss-point Hessians (Pade order, + QP_LOG_MIX for log mixing)
   AOP_QP_MF,          // the same into the matrix-free layout
   AOP_ELEMENT,        // element matrices
   AOP_GATHER,         // stored blocks
@@ -566,7 +564,8 @@ enum AssemblyOp {
   AOP_MF_DIAG_GATHER, // diagonal blocks from them
   AOP_DIRICHLET,      // symmetric elimination on the stored blocks (A64 / A32 null: diagonal only)
   AOP_BLOCK_INVERSE,  // 9x9 diagonal-block inverses
-  AOP_RESIDUAL,       // residual rows from the Gauss-point gradients
+  AOP_RESIDUAL,       // element parts of the residual (Pade order, + QP_LOG_MIX)
+  AOP_RESIDUAL_NODES, // residual rows from them
 };
 // fills the job's derived fields (nblocks, nup) and returns its workgroups
 int assembly_job_blocks(int op, AJob& j);

@@ -555,23 +555,18 @@ __device__ __forceinline__ void to_strain(const double G[9], const double q[6], 
   }
 }
 
-// Gradient and second derivatives of the local density in (eps, eta), handed
-// to out as soon as they are known (so that few stay live): out.strain(g, S,
-// D_ee) with the gradient, the stress and the upper triangle, out.eps_eta(k, d)
-// with the six entries D_(.)k, out.eta_eta(k, l, val) for l <= k.
+// Second derivatives of the local density in (eps, eta), handed to out as soon
+// as they are known (so that few stay live): out.strain(S, D_ee) with the stress
+// and the upper triangle, out.eps_eta(k, d) with the six entries D_(.)k,
+// out.eta_eta(k, l, val) for l <= k.
 template <int PD, int MIX, class Out>
-__device__ __forceinline__ void local_hessian(const double F[9], const double eh[NV], const double ehn[NV],
-                                              const DevCard& cd, Out&& out) {
+__device__ __forceinline__ void local_hessian(const double F[9], const double eh[NV], const DevCard& cd, Out&& out) {
   using P = Pade<PD>;
   LocalBase<PD> b;
   MixDerivative<MIX> dm;
-  double S[6], phi[6], g[NQ];
+  double S[6], phi[6];
   local_base<PD, MIX>(F, eh, cd, b, dm);
   local_first<PD>(b, S, phi);
-  first_piola(F, S, g);
-  eta_gradient<MIX>(eh, ehn, cd, b.Jt, b.wEta, dm, phi, g + 9);
-  out.gradient(g, S);
-  
   // ---- second derivatives in C-space -------------------------------------
   double dh[6][6];  // engineering components of dH along E_v
   double wCC[21];   // upper triangle
@@ -723,7 +718,6 @@ __device__ __forceinline__ void local_hessian(const double F[9], const double eh
     }
     out.strain(S, Dee);
   }
-  
   // ---- F^t space ---------------------------------------------------------------
   double X[21];     // second derivative along F^t at fixed L, / J_t
   double Te[6][6];  // [v][w]: mixed (F^t_v, eps_w), / J_t
@@ -863,11 +857,6 @@ struct PackedOut {
   double* D;
   int64_t ds;
   uint32_t off;
-  double* g;
-  __device__ __forceinline__ void gradient(const double gr[NQ], const double*) const {
-#pragma unroll
-    for (int i = 0; i < NQ; ++i) g[i] = gr[i];
-  }
   __device__ __forceinline__ void eps_eta(int k, const double d[6]) const {
 #pragma unroll
     for (int i = 0; i < 3; ++i)
@@ -900,12 +889,5 @@ struct PackedOut {
       }
   }
 };
-
-template <int PD, int MIX = 0>
-__device__ __forceinline__ void local_hessian_packed(const double F[9], const double eh[NV], const double ehn[NV],
-                                                     const DevCard& cd, double g[NQ], double* __restrict__ D,
-                                                     int64_t ds, uint32_t off) {
-  local_hessian<PD, MIX>(F, eh, ehn, cd, PackedOut{F, D, ds, off, g});
-}
 
 }  // namespace mvpf

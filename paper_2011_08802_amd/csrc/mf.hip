@@ -261,38 +261,8 @@ __device__ __forceinline__ void mf_element_body(const Grid& g, const TD* __restr
 #pragma unroll
   for (int c = 0; c < 9; ++c) a1[c] = r2[c], bx[c] = r2[9 + c];
   interp_pair_t<1>(a1, bx, hi, lo, out);
-  // Element outputs through LDS: a lane holds corner gp's 9 values; staged
-  // per stream (gp, c), the workgroup merges each element's left corners
-  // with the right corners of its predecessor in the same row and stores
-  // one contiguous, aligned run of each merged stream (whole 128-byte lines
-  // at 32 elements in FP32), plus the right corners that no element of the
-  // workgroup takes (its last element's, row ends).  Every lane of the
-  // workgroup reaches the barrier.
   __shared__ T eo[72 * (MF_MAX_EPW + 1)];
-  const int epw = blockDim.x >> 3;
-  const int jw = threadIdx.x >> 3;  // element within the workgroup
-#pragma unroll
-  for (int c = 0; c < 9; ++c) eo[(gp * 9 + c) * (epw + 1) + jw] = out[c];
-  __syncthreads();
-  const int64_t ew = (int64_t)bid * epw;  // the workgroup's first element
-  const int ex0 = (int)(ew % g.nx);
-  T* __restrict__ W = E + mf_w_offset(g);
-  T* __restrict__ Rr = E + mf_r_offset(g);
-  for (int idx = threadIdx.x; idx < 36 * epw; idx += blockDim.x) {
-    const int s = idx / epw, jj = idx - s * epw;  // merged stream s = 9 q + c
-    const int64_t e = ew + jj;
-    if (e >= g.NE) continue;
-    const int q = s / 9, c = s - 9 * q;
-    int ex = ex0 + jj;
-    while (ex >= g.nx) ex -= g.nx;
-    const T* left = eo + (18 * q + c) * (epw + 1);      // corner 2q
-    const T* right = eo + (18 * q + 9 + c) * (epw + 1);  // corner 2q + 1
-    T v = left[jj];
-    if (jj > 0 && ex > 0) v = v + right[jj - 1];
-    E[(int64_t)s * g.NEpad + e] = v;
-    if (ex == g.nx - 1) Rr[(int64_t)s * mf_nr(g) + e / g.nx] = right[jj];
-    else if (jj == epw - 1) W[(int64_t)s * mf_nw(g) + bid] = right[jj];
-  }
+  store_corners<T, 9>(eo, out, gp, threadIdx.x >> 3, blockDim.x >> 3, bid, g.nx, g.NE, E, g.NEpad, mf_nw(g), mf_nr(g));
 }
 template <typename TD, typename TX, typename T, int MINB, int PF, bool SPARSE>
 __global__ void __launch_bounds__(256, MINB) mf_element_kernel(Grid g, const TD* __restrict__ D, const TX* __restrict__ x,
@@ -431,10 +401,7 @@ __device__ __forceinline__ double pair_sum(double a, const PairWeights& w) {
 // of 9.  Bound: FP64 issue (~2000 instructions per point) and the tangents'
 // 0.77 KB per point, read once; 64^3: 0.58 ms, and 0.18
 // ms for the node sums.
-constexpr int DG_EPW = 32;
-__host__ __device__ inline int64_t dg_nw(const Chunk& ck) { return ck.NEcpad / DG_EPW; }
-__host__ __device__ inline int64_t dg_w_offset(const Chunk& ck) { return (int64_t)4 * NSYM * ck.NEcpad; }
-__host__ __device__ inline int64_t dg_r_offset(const Chunk& ck) { return dg_w_offset(ck) + 4 * NSYM * dg_nw(ck); }
+constexpr int DG_EPW = SLAB_EPW;
 
 __device__ __forceinline__ void mf_diag_body(const Grid& g, const Chunk& ck, const double* __restrict__ D,
                                              const DevCard* __restrict__ cd, double* __restrict__ E, int wg, int nb) {
@@ -525,33 +492,15 @@ __device__ __forceinline__ void mf_diag_body(const Grid& g, const Chunk& ck, con
             pair_sum<1, PAIR_VV>(pair_sum<2, PAIR_VV>(pair_sum<4, PAIR_VV>(d, wz), wy), wx) + h / 3.0 * cd->Mg[l][m];
       }
   }
-  // merge along x and store, nine entries at a time through LDS
-  double* __restrict__ W = E + dg_w_offset(ck);
-  double* __restrict__ Rr = E + dg_r_offset(ck);
-  const int nr = ck.NEc / g.nx;
-  const int ex0 = (bid * DG_EPW) % g.nx;
+  // nine entries at a time: streams 9 r + c of each q
 #pragma unroll
   for (int r = 0; r < 5; ++r) {
     if (r > 0) __syncthreads();
+    double part[9];
 #pragma unroll
-    for (int c = 0; c < 9; ++c) eo[(gp * 9 + c) * (DG_EPW + 1) + jw] = out[9 * r + c];
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < 36 * DG_EPW; idx += 256) {
-      const int s = idx / DG_EPW, jj = idx & (DG_EPW - 1);
-      const int q = s / 9, c = s - 9 * q;
-      const int ell = bid * DG_EPW + jj;
-      if (ell >= ck.NEc) continue;
-      int ex = ex0 + jj;
-      while (ex >= g.nx) ex -= g.nx;
-      const double* left = eo + (18 * q + c) * (DG_EPW + 1);
-      const double* right = eo + (18 * q + 9 + c) * (DG_EPW + 1);
-      const int64_t st = NSYM * q + 9 * r + c;
-      double t = left[jj];
-      if (jj > 0 && ex > 0) t = t + right[jj - 1];
-      E[st * ck.NEcpad + ell] = t;
-      if (ex == g.nx - 1) Rr[st * nr + ell / g.nx] = right[jj];
-      else if (jj == DG_EPW - 1) W[st * dg_nw(ck) + bid] = right[jj];
-    }
+    for (int c = 0; c < 9; ++c) part[c] = out[9 * r + c];
+    store_corners<double, 9>(eo, part, gp, jw, DG_EPW, bid, g.nx, ck.NEc, E + r * slab_values(ck, g.nx, 9), ck.NEcpad,
+                             slab_nw(ck), ck.NEc / g.nx);
   }
 }
 // Node sums of the merged parts -> full diagonal blocks.  One thread per node
@@ -564,32 +513,16 @@ __device__ __forceinline__ void mf_diag_gather_body(const Grid& g, const Chunk& 
   double* db = diag64 + (int64_t)(n >> 6) * Lay<double>::SLICE;
   const int l = n & 63;
   const int i = n % g.nnx, j = (n / g.nnx) % g.nny, k = n / (g.nnx * g.nny);
-  const double* __restrict__ W = E + dg_w_offset(ck);
-  const double* __restrict__ Rr = E + dg_r_offset(ck);
-  const int nr = ck.NEc / g.nx;
   const int ez0 = (int)(ck.e0 / ((int64_t)g.nx * g.ny));
   double s[NDOF];
 #pragma unroll
   for (int c = 0; c < NDOF; ++c) s[c] = 0.0;
   if (n < g.N) {
 #pragma unroll
-    for (int q = 3; q >= 0; --q) {
-      const int ey = j - (q & 1), ez = k - (q >> 1);
-      if (ey < 0 || ey >= g.ny || ez < 0 || ez >= g.nz) continue;
-      const int64_t r = ey + (int64_t)g.ny * (ez - ez0);
-#pragma unroll
-      for (int c = 0; c < NDOF; ++c) {
-        if (c < rr) continue;
-        const int64_t st = NSYM * q + sym_index(rr, c);
-        if (i < g.nx) {
-          const int64_t e = i + g.nx * r;
-          double t = E[st * ck.NEcpad + e];
-          if (i > 0 && (e & (DG_EPW - 1)) == 0) t = t + W[st * dg_nw(ck) + e / DG_EPW - 1];
-          s[c] += t;
-        } else {
-          s[c] += Rr[st * nr + r];
-        }
-      }
+    for (int c = 0; c < NDOF; ++c) {
+      if (c < rr) continue;
+      const int t = sym_index(rr, c);
+      s[c] = slab_node_sum(g, ck, E + t / 9 * slab_values(ck, g.nx, 9), 9, t % 9, i, j, k - ez0);
     }
   }
 #pragma unroll
@@ -618,7 +551,7 @@ __global__ void __launch_bounds__(256) mf_diag_gather_batch(const AJob* __restri
   mf_diag_gather_body(j.g, j.ck, j.elem, j.diag64, bid);
 }
 // values of the element buffer a slab of ne elements (padded) in rows of nx uses
-int64_t mf_diag_values(int64_t ne, int nx) { return 4 * NSYM * (ne + ne / DG_EPW + ne / nx + 1); }
+int64_t mf_diag_values(int64_t ne, int nx) { return 4 * NSYM * (ne + ne / SLAB_EPW + ne / nx + 1); }
 int mf_diag_blocks(const Chunk& ck) { return ck.NEcpad / DG_EPW; }
 int mf_diag_gather_blocks(const Chunk& ck) { return (ck.n1 - ck.n0 + 255) / 256 * NDOF; }
 void launch_mf_diag(const Grid& g, const Chunk& ck, const double* D64, const DevCard* cd, double* elem, double* diag64,

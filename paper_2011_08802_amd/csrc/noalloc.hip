@@ -1,7 +1,7 @@
 // mvpf_residual_noalloc: the residual of mvpf_residual with no device memory
 // allocated by the call or by the library on its behalf.  Its scratch -- the
-// per-Gauss-point gradients of one slab of element layers and the partial
-// sums of the free-dof norm -- lives in a file-scope device array of fixed
+// element outputs of one slab of element layers and the partial sums of the
+// free-dof norm -- lives in a file-scope device array of fixed
 // size; each GPU holds its own copy of the array (at its own address) until
 // the process ends.
 #include <cmath>
@@ -15,14 +15,16 @@ using namespace mvpf;
 namespace {
 
 // Scratch layout (doubles): [0, RED) partial sums of the norm, [RED, QP0)
-// the reduced value, [QP0, end) Gauss-point gradients of one slab,
-// QP_GRAD * 8 values per element.
+// the reduced value, [QP0, end) element outputs of one slab: 4 NDOF merged
+// values per element, 1/32 of that per workgroup and 4 NDOF per row of at
+// least two elements, fewer than the 8 NQ per element counted.
 constexpr int64_t SCRATCH_DOUBLES = (int64_t)8 << 20;  // 64 MiB
 constexpr int64_t RED = MAX_RED_BLOCKS;
 constexpr int64_t QP0 = RED + 4096;
-constexpr int64_t NE_CAP = ((SCRATCH_DOUBLES - QP0) / (QP_GRAD * 8)) / TILE * TILE;
+constexpr int64_t NE_CAP = ((SCRATCH_DOUBLES - QP0) / (NQ * 8)) / TILE * TILE;
 
-static_assert(QP0 % 32 == 0, "the Gauss-point slab starts 256-byte aligned");
+static_assert(QP0 % 32 == 0, "the slab starts 256-byte aligned");
+static_assert(4 * NDOF * (64 + 2 + 32) <= NQ * 8 * 64, "a slab's element outputs fit");
 
 static __device__ __align__(256) double scratch[SCRATCH_DOUBLES];
 
@@ -85,15 +87,14 @@ int mvpf_residual_noalloc(mvpf_problem* p, double* R, double* norm_free) {
   if (rc) return rc;
   double* part = base;
   double* red = base + RED;
-  double* qp = base + QP0;
+  double* out = base + QP0;
   hipStream_t s = p->stream;
   const double depth = p->have_system ? p->sys_depth : p->depth;
   // the same kernels and slab logic as mvpf_residual; every scratch value
   // read is written earlier in the same call, so nothing needs clearing
   launch_dirichlet_masks(g, p->load, depth, L0.mask, L0.target, s);
   for (const Chunk& ck : make_chunks(g, NE_CAP)) {
-    launch_qp(g, ck, L0.state, p->card, p->pade, p->mixing, qp, false, s);
-    launch_residual_gather(g, ck, L0.state, qp, p->card, p->R, s);
+    launch_residual(g, ck, L0.state, p->card, p->pade, p->mixing, out, p->R, s);
   }
   if (p->load.kind == MVPF_LOAD_SPHERE)
     launch_contact_residual(g, make_sphere(g, p->load, depth), L0.state, p->R, s);

@@ -56,4 +56,74 @@ __device__ __forceinline__ void interp_pair_t(const T (&a)[n], const T (&bs)[n],
   }
 }
 
+// Element outputs through LDS: a lane holds NC values of corner gp of element jw
+// of its workgroup (lane = 8 * element + corner).  Staged per stream (corner, c),
+// the workgroup merges each element's left corners with the right corners of its
+// predecessor in the same row and stores one contiguous, aligned run of each
+// merged stream (whole 128-byte lines at 32 elements in FP32), plus the right
+// corners that no element of the workgroup takes (its last element's, row ends):
+//   E[(NC q + c) se + e], then W[(NC q + c) nw + bid], Rr[(NC q + c) nr + row]
+// (q = by + 2 bz; W and Rr follow E's 4 NC streams).  Every lane of the
+// workgroup reaches the barrier.  eo: 8 NC (epw + 1) values; the workgroup's
+// elements are e = bid epw ..., ne of them exist, a row holds nx and e = 0 starts one.
+template <typename T, int NC>
+__device__ __forceinline__ void store_corners(T* eo, const T (&out)[NC], int gp, int jw, int epw, int bid, int nx,
+                                              int64_t ne, T* __restrict__ E, int64_t se, int64_t nw, int64_t nr) {
+#pragma unroll
+  for (int c = 0; c < NC; ++c) eo[(gp * NC + c) * (epw + 1) + jw] = out[c];
+  __syncthreads();
+  const int64_t ew = (int64_t)bid * epw;  // the workgroup's first element
+  const int ex0 = (int)(ew % nx);
+  T* __restrict__ W = E + 4 * NC * se;
+  T* __restrict__ Rr = W + 4 * NC * nw;
+  for (int idx = threadIdx.x; idx < 4 * NC * epw; idx += blockDim.x) {
+    const int s = idx / epw, jj = idx - s * epw;  // merged stream s = NC q + c
+    const int64_t e = ew + jj;
+    if (e >= ne) continue;
+    const int q = s / NC, c = s - NC * q;
+    int ex = ex0 + jj;
+    while (ex >= nx) ex -= nx;
+    const T* left = eo + (2 * NC * q + c) * (epw + 1);      // corner 2q
+    const T* right = eo + (2 * NC * q + NC + c) * (epw + 1);  // corner 2q + 1
+    T v = left[jj];
+    if (jj > 0 && ex > 0) v = v + right[jj - 1];
+    E[(int64_t)s * se + e] = v;
+    if (ex == nx - 1) Rr[(int64_t)s * nr + e / nx] = right[jj];
+    else if (jj == epw - 1) W[(int64_t)s * nw + bid] = right[jj];
+  }
+}
+
+// Merged element outputs of one assembly slab (whole element layers, chunk-local
+// elements, SLAB_EPW per workgroup), NC values per corner: values in all, and the
+// node sum of value c at node (i, j) and node layer k counted from the slab's
+// first element layer.
+constexpr int SLAB_EPW = 32;
+__host__ __device__ inline int64_t slab_nw(const Chunk& ck) { return ck.NEcpad / SLAB_EPW; }
+__host__ __device__ inline int64_t slab_values(const Chunk& ck, int nx, int nc) {
+  return 4 * (int64_t)nc * (ck.NEcpad + slab_nw(ck) + ck.NEc / nx);
+}
+__device__ __forceinline__ double slab_node_sum(const Grid& g, const Chunk& ck, const double* __restrict__ E, int nc,
+                                                int c, int i, int j, int k) {
+  const int nz = ck.NEc / (g.nx * g.ny);
+  const int64_t nw = slab_nw(ck), nr = ck.NEc / g.nx;
+  const double* __restrict__ W = E + 4 * (int64_t)nc * ck.NEcpad;
+  const double* __restrict__ Rr = W + 4 * (int64_t)nc * nw;
+  double s = 0.0;
+#pragma unroll
+  for (int q = 3; q >= 0; --q) {  // element row (j - by, k - bz) holds the node at (by, bz)
+    const int ey = j - (q & 1), ez = k - (q >> 1);
+    if (ey < 0 || ey >= g.ny || ez < 0 || ez >= nz) continue;
+    const int64_t r = ey + (int64_t)g.ny * ez, st = nc * q + c;
+    if (i < g.nx) {
+      const int64_t e = i + g.nx * r;
+      double t = E[st * ck.NEcpad + e];
+      if (i > 0 && (e & (SLAB_EPW - 1)) == 0) t = t + W[st * nw + e / SLAB_EPW - 1];
+      s += t;
+    } else {
+      s += Rr[st * nr + r];
+    }
+  }
+  return s;
+}
+
 }  // namespace mvpf

@@ -1,9 +1,11 @@
 // Quadrature and assembly kernels (Sec. 3.3-3.4): residual R = dPi/dU and
 // tangent K = d^2 Pi / dU^2 of the discrete potential on Q1 hexahedra with
 // 2x2x2 Gauss points, assembled without atomics:
-//   1. qp_kernel: one thread per (Gauss point, element) evaluates the local
-//      gradient (and Hessian) of the density and stores it (SoA, coalesced);
-//   2. residual_gather: one thread per node sums its <= 8 elements;
+//   1. residual_element, residual_nodes: the elements' residual parts and their
+//      node sums;
+//   2. qp_kernel: one thread per (Gauss point, element) evaluates the local
+//      Hessian of the density and stores it (SoA, coalesced); qp_mf_kernel: the
+//      same into the matrix-free layout;
 //   3. element_matrix: element blocks for the 36 node pairs a <= b, with the
 //      Gauss-point Hessians shared through LDS;
 //   4. jacobian_gather: one thread per (node row, stored stencil block) sums
@@ -51,7 +53,8 @@ __device__ __forceinline__ double lap_ref(int a, int b) {
   return 0.125 * s;
 }
 
-template <bool HESS, int PD, int MIX>
+// Packed Hessians of a slab's Gauss points, one thread per (point, element).
+template <int PD, int MIX>
 __device__ __forceinline__ void qp_body(const Grid& g, const Chunk& ck, const double* __restrict__ state,
                                         const DevCard* __restrict__ cd, double* __restrict__ qp, int bid) {
   const int64_t tid = (int64_t)bid * 128 + threadIdx.x;
@@ -62,9 +65,9 @@ __device__ __forceinline__ void qp_body(const Grid& g, const Chunk& ck, const do
   const int ex = (int)(e % g.nx), ey = (int)((e / g.nx) % g.ny), ez = (int)(e / ((int64_t)g.nx * g.ny));
   const double ih = 1.0 / g.h;
   double F[9] = {1, 0, 0, 0, 1, 0, 0, 0, 1};
-  double eh[NV], ehn[NV];
+  double eh[NV];
 #pragma unroll
-  for (int k = 0; k < NV; ++k) eh[k] = ehn[k] = 0.0;
+  for (int k = 0; k < NV; ++k) eh[k] = 0.0;
 #pragma unroll
   for (int a = 0; a < 8; ++a) {
     const int node = (ex + (a & 1)) + g.nnx * ((ey + ((a >> 1) & 1)) + g.nny * (ez + ((a >> 2) & 1)));
@@ -76,60 +79,168 @@ __device__ __forceinline__ void qp_body(const Grid& g, const Chunk& ck, const do
       for (int j = 0; j < 3; ++j) F[3 * i + j] += u * s.dN[j] * ih;
     }
 #pragma unroll
-    for (int k = 0; k < NV; ++k) {
-      eh[k] += s.N * state[(int64_t)(3 + k) * g.Npad + node];
-      ehn[k] += s.N * state[(int64_t)(3 + NV + k) * g.Npad + node];
-    }
+    for (int k = 0; k < NV; ++k) eh[k] += s.N * state[(int64_t)(3 + k) * g.Npad + node];
   }
-  const int64_t stride = (int64_t)8 * ck.NEcpad;
   const uint32_t off = (uint32_t)gp * (uint32_t)ck.NEcpad + (uint32_t)el;  // < 8 NEcpad
-  double gr[NQ];
-  if (HESS) {
-    local_hessian_packed<PD, MIX>(F, eh, ehn, *cd, gr, qp + (int64_t)NQ * stride, stride, off);
-  } else {
-    local_gradient<PD, MIX>(F, eh, ehn, *cd, gr);
-  }
-#pragma unroll
-  for (int c = 0; c < NQ; ++c) (qp + (int64_t)c * stride)[off] = gr[c];
+  local_hessian<PD, MIX>(F, eh, *cd, PackedOut{F, qp, (int64_t)8 * ck.NEcpad, off});
 }
-template <bool HESS, int PD, int MIX>
+template <int PD, int MIX>
 __global__ void __launch_bounds__(128) qp_kernel(Grid g, Chunk ck, const double* __restrict__ state,
                                                  const DevCard* __restrict__ cd, double* __restrict__ qp) {
-  qp_body<HESS, PD, MIX>(g, ck, state, cd, qp, blockIdx.x);
+  qp_body<PD, MIX>(g, ck, state, cd, qp, blockIdx.x);
 }
 
-template <int PD, int MIX>
-void launch_qp_order(const Grid& g, const Chunk& ck, const double* state, const DevCard* cd, double* qp, bool hess,
-                     hipStream_t s) {
-  const int64_t n = (int64_t)8 * ck.NEcpad;
-  const int bs = 128;
-  const int nb = (int)((n + bs - 1) / bs);
-  if (hess)
-    qp_kernel<true, PD, MIX><<<nb, bs, 0, s>>>(g, ck, state, cd, qp);
-  else
-    qp_kernel<false, PD, MIX><<<nb, bs, 0, s>>>(g, ck, state, cd, qp);
-}
-
-// pade: 11, 22 or 33; mixing: MVPF_MIX_LINEAR or MVPF_MIX_LOG (validated at creation)
-void launch_qp(const Grid& g, const Chunk& ck, const double* state, const DevCard* cd, int pade, int mixing,
-               double* qp, bool hess, hipStream_t s) {
+// Kernel K::run<order, mixing>(args...) of a card: pade 11, 22 or 33, mixing
+// MVPF_MIX_LINEAR or MVPF_MIX_LOG (validated at creation).
+template <class K, class... A>
+void run_card(int pade, int mixing, A... a) {
   if (mixing == MVPF_MIX_LOG) {
     switch (pade) {
-      case 11: launch_qp_order<11, 1>(g, ck, state, cd, qp, hess, s); break;
-      case 33: launch_qp_order<33, 1>(g, ck, state, cd, qp, hess, s); break;
-      default: launch_qp_order<22, 1>(g, ck, state, cd, qp, hess, s); break;
+      case 11: K::template run<11, 1>(a...); break;
+      case 33: K::template run<33, 1>(a...); break;
+      default: K::template run<22, 1>(a...); break;
     }
     return;
   }
   switch (pade) {
-    case 11: launch_qp_order<11, 0>(g, ck, state, cd, qp, hess, s); break;
-    case 33: launch_qp_order<33, 0>(g, ck, state, cd, qp, hess, s); break;
-    default: launch_qp_order<22, 0>(g, ck, state, cd, qp, hess, s); break;
+    case 11: K::template run<11, 0>(a...); break;
+    case 33: K::template run<33, 0>(a...); break;
+    default: K::template run<22, 0>(a...); break;
   }
 }
+struct QpRun {
+  template <int PD, int MIX>
+  static void run(const Grid& g, const Chunk& ck, const double* state, const DevCard* cd, double* qp, hipStream_t s) {
+    qp_kernel<PD, MIX><<<(int)(((int64_t)8 * ck.NEcpad + 127) / 128), 128, 0, s>>>(g, ck, state, cd, qp);
+  }
+};
+void launch_qp(const Grid& g, const Chunk& ck, const double* state, const DevCard* cd, int pade, int mixing,
+               double* qp, hipStream_t s) {
+  run_card<QpRun>(pade, mixing, g, ck, state, cd, qp, s);
+}
 
-// Gauss-point gradients and tangents of a matrix-free level, the tangents
-// straight into the matrix-free layout (no pass over a scratch form).  A
+// ---- residual ---------------------------------------------------------------
+// One pass over the elements: a wavefront holds 8 elements x 8 points (lane = 8 *
+// element + point); lane j loads the state of corner j, the point's F, eta,
+// grad eta and eta_n come from three pair interpolations, and the density's
+// gradient (and the gradient energy's) goes back to the corners through the
+// transposed stages.  The corner values are merged along x in the workgroup and
+// a node sum of at most 4 merged rows follows.  Bound: FP64 issue of the local
+// gradient (~1300 instructions per point); 64^3: 0.19 ms and 0.03 ms for the
+// node sums, against 0.30 ms for gradients stored per point and 0.35 ms for a
+// node gather that read each of them eight times.
+template <int PD, int MIX>
+__device__ __forceinline__ void residual_element_body(const Grid& g, const Chunk& ck, const double* __restrict__ state,
+                                                      const DevCard* __restrict__ cd, double* __restrict__ E, int wg,
+                                                      int nb) {
+  __shared__ double eo[8 * NDOF * (SLAB_EPW + 1)];
+  const int xcd = wg & 7;  // one contiguous range of elements per XCD
+  const int bid = xcd * (nb >> 3) + min(xcd, nb & 7) + (wg >> 3);
+  const int gp = threadIdx.x & 7, jw = threadIdx.x >> 3;
+  const int el = bid * SLAB_EPW + jw;
+  const bool b0 = gp & 1, b1 = (gp >> 1) & 1, b2 = (gp >> 2) & 1;
+  constexpr int NS = 3 + 2 * NV;
+  double F[9], eh[NV], ehn[NV], ge[3 * NV];
+  {
+    double x[NS];
+#pragma unroll
+    for (int c = 0; c < NS; ++c) x[c] = 0.0;
+    if (el < ck.NEc) {
+      const int64_t e = ck.e0 + el;
+      const int ex = (int)(e % g.nx), ey = (int)((e / g.nx) % g.ny), ez = (int)(e / ((int64_t)g.nx * g.ny));
+      const int node = (ex + b0) + g.nnx * ((ey + b1) + g.nny * (ez + b2));
+#pragma unroll
+      for (int c = 0; c < NS; ++c) x[c] = state[(int64_t)c * g.Npad + node];
+    }
+    double s1[NS], d1[NDOF], i2[NS + NDOF], s2[NS + NDOF], d2[NDOF], i3[NS + 2 * NDOF], s3[NS + 2 * NDOF], d3[NDOF];
+    interp_pair<1>(x, MGQ0, b0 ? -1.0 : 1.0, s1, d1);
+#pragma unroll
+    for (int c = 0; c < NS; ++c) i2[c] = s1[c];
+#pragma unroll
+    for (int c = 0; c < NDOF; ++c) i2[NS + c] = d1[c];
+    interp_pair<2>(i2, MGQ0, b1 ? -1.0 : 1.0, s2, d2);
+#pragma unroll
+    for (int c = 0; c < NS + NDOF; ++c) i3[c] = s2[c];
+#pragma unroll
+    for (int c = 0; c < NDOF; ++c) i3[NS + NDOF + c] = d2[c];
+    interp_pair<4>(i3, MGQ0, b2 ? -1.0 : 1.0, s3, d3);
+    const double ih = 1.0 / g.h;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      F[3 * i] = s3[NS + i] * ih + (i == 0 ? 1.0 : 0.0);
+      F[3 * i + 1] = s3[NS + NDOF + i] * ih + (i == 1 ? 1.0 : 0.0);
+      F[3 * i + 2] = d3[i] * ih + (i == 2 ? 1.0 : 0.0);
+    }
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      eh[k] = s3[3 + k], ehn[k] = s3[3 + NV + k];
+      ge[3 * k] = s3[NS + 3 + k], ge[3 * k + 1] = s3[NS + NDOF + 3 + k], ge[3 * k + 2] = d3[3 + k];
+    }
+  }
+  double gr[NQ];
+  local_gradient<PD, MIX>(F, eh, ehn, *cd, gr);
+  // coefficients of the values and of the x, y, z reference derivatives, each
+  // derivative's with the transposed stage's sign of its direction
+  const double h = g.h, cu = 0.125 * h * h, cg = 0.125 * h;
+  const double sx = b0 ? 1.0 : -1.0, sy = b1 ? 1.0 : -1.0, sz = b2 ? 1.0 : -1.0;
+  double a3[3 * NDOF], bz[3 * NDOF], r3[3 * NDOF];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    a3[i] = 0.0, a3[NDOF + i] = sx * cu * gr[3 * i], a3[2 * NDOF + i] = sy * cu * gr[3 * i + 1];
+    bz[i] = sz * cu * gr[3 * i + 2];
+  }
+#pragma unroll
+  for (int m = 0; m < NV; ++m) {
+    double z[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int m2 = 0; m2 < NV; ++m2)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) z[j] += cd->Mg[m][m2] * ge[3 * m2 + j];
+    a3[3 + m] = h * cu * gr[9 + m], a3[NDOF + 3 + m] = sx * cg * z[0], a3[2 * NDOF + 3 + m] = sy * cg * z[1];
+    bz[3 + m] = sz * cg * z[2];
+  }
+#pragma unroll
+  for (int c = NDOF; c < 3 * NDOF; ++c) bz[c] = 0.0;
+  interp_pair_t<4>(a3, bz, MGQ1, MGQ0, r3);
+  double a2[2 * NDOF], by[2 * NDOF], r2[2 * NDOF], a1[NDOF], bx[NDOF], out[NDOF];
+#pragma unroll
+  for (int c = 0; c < 2 * NDOF; ++c) a2[c] = r3[c], by[c] = c < NDOF ? r3[2 * NDOF + c] : 0.0;
+  interp_pair_t<2>(a2, by, MGQ1, MGQ0, r2);
+#pragma unroll
+  for (int c = 0; c < NDOF; ++c) a1[c] = r2[c], bx[c] = r2[NDOF + c];
+  interp_pair_t<1>(a1, bx, MGQ1, MGQ0, out);
+  store_corners<double, NDOF>(eo, out, gp, jw, SLAB_EPW, bid, g.nx, ck.NEc, E, ck.NEcpad, slab_nw(ck), ck.NEc / g.nx);
+}
+__device__ __forceinline__ void residual_nodes_body(const Grid& g, const Chunk& ck, const double* __restrict__ E,
+                                                    double* __restrict__ R, int bid) {
+  // one value per thread (8^3: 19 -> 4.6 us against a node per thread)
+  const int c = bid % NDOF, n = ck.n0 + bid / NDOF * 256 + threadIdx.x;
+  if (n >= ck.n1) return;
+  const int i = n % g.nnx, j = (n / g.nnx) % g.nny, k = n / (g.nnx * g.nny) - (int)(ck.e0 / ((int64_t)g.nx * g.ny));
+  R[(int64_t)c * g.Npad + n] = n < g.N ? slab_node_sum(g, ck, E, NDOF, c, i, j, k) : 0.0;
+}
+template <int PD, int MIX>
+__global__ void __launch_bounds__(256) residual_element_kernel(Grid g, Chunk ck, const double* __restrict__ state,
+                                                               const DevCard* __restrict__ cd, double* __restrict__ E) {
+  residual_element_body<PD, MIX>(g, ck, state, cd, E, blockIdx.x, gridDim.x);
+}
+__global__ void __launch_bounds__(256) residual_nodes_kernel(Grid g, Chunk ck, const double* __restrict__ E,
+                                                             double* __restrict__ R) {
+  residual_nodes_body(g, ck, E, R, blockIdx.x);
+}
+struct ResidualRun {
+  template <int PD, int MIX>
+  static void run(const Grid& g, const Chunk& ck, const double* state, const DevCard* cd, double* E, hipStream_t s) {
+    residual_element_kernel<PD, MIX><<<ck.NEcpad / SLAB_EPW, 256, 0, s>>>(g, ck, state, cd, E);
+  }
+};
+void launch_residual(const Grid& g, const Chunk& ck, const double* state, const DevCard* cd, int pade, int mixing,
+                     double* E, double* R, hipStream_t s) {
+  run_card<ResidualRun>(pade, mixing, g, ck, state, cd, E, s);
+  residual_nodes_kernel<<<(ck.n1 - ck.n0 + 255) / 256 * NDOF, 256, 0, s>>>(g, ck, E, R);
+}
+
+// Gauss-point tangents of a matrix-free level, straight into the matrix-free layout (no pass over a scratch form).  A
 // wavefront holds 8 elements x 8 points (lane = 8 * element + point): lane j
 // loads the 15 state values of corner j of its element and the point's F, eta
 // and eta_n come from three pair interpolations, instead of 120 loads per
@@ -141,9 +252,6 @@ struct MfOut {
   double2* D64;   // the wavefront's group of 8 elements
   float4* D32;    // or null
   uint32_t slot;  // 8 * point + element
-  double* qp;
-  int64_t qs;     // stride of the gradient components
-  uint32_t qoff;
   double pend[4];
   double col[6];
   __device__ __forceinline__ void vec2(int k, double a, double b) const {
@@ -153,10 +261,6 @@ struct MfOut {
     vec2(k, a, b);
     vec2(k + 2, c, d);
     if (D32) (D32 + (int64_t)(k / 4) * 64)[slot] = make_float4((float)a, (float)b, (float)c, (float)d);
-  }
-  __device__ __forceinline__ void gradient(const double g[NQ], const double*) const {
-#pragma unroll
-    for (int c = 0; c < NQ; ++c) (qp + (int64_t)c * qs)[qoff] = g[c];
   }
   __device__ __forceinline__ void strain(const double S[6], const double Dee[21]) const {
     auto at = [&](int k) {
@@ -190,8 +294,8 @@ struct MfOut {
 };
 template <int PD, int MIX>
 __device__ __forceinline__ void qp_mf_body(const Grid& g, const Chunk& ck, const double* __restrict__ state,
-                                           const DevCard* __restrict__ cd, double* __restrict__ qp,
-                                           double* __restrict__ D64, float* __restrict__ D32, int bid) {
+                                           const DevCard* __restrict__ cd, double* __restrict__ D64,
+                                           float* __restrict__ D32, int bid) {
   static_assert(NV == 6 || !MF_AVAILABLE, "entry counts of the matrix-free layout");
   const int lane = threadIdx.x & 63, gp = lane & 7;
   // group of 8 elements, uniform over the wavefront
@@ -199,19 +303,19 @@ __device__ __forceinline__ void qp_mf_body(const Grid& g, const Chunk& ck, const
   const int64_t e = eg * 8 + (lane >> 3), el = e - ck.e0;
   const bool active = el >= 0 && el < ck.NEc;
   const bool b0 = gp & 1, b1 = (gp >> 1) & 1, b2 = (gp >> 2) & 1;
-  double F[9], eh[NV], ehn[NV];
+  double F[9], eh[NV];
   {
-    double x[3 + 2 * NV];
+    double x[NDOF];
 #pragma unroll
-    for (int c = 0; c < 3 + 2 * NV; ++c) x[c] = 0.0;
+    for (int c = 0; c < NDOF; ++c) x[c] = 0.0;
     if (active) {
       const int ex = (int)(e % g.nx), ey = (int)((e / g.nx) % g.ny), ez = (int)(e / ((int64_t)g.nx * g.ny));
       const int node = (ex + b0) + g.nnx * ((ey + b1) + g.nny * (ez + b2));
 #pragma unroll
-      for (int c = 0; c < 3 + 2 * NV; ++c) x[c] = state[(int64_t)c * g.Npad + node];
+      for (int c = 0; c < NDOF; ++c) x[c] = state[(int64_t)c * g.Npad + node];
     }
     const double ih = 1.0 / g.h;
-    constexpr int n = 3 + 2 * NV;
+    constexpr int n = NDOF;
     double s1[n], d1[3], i2[n + 3], s2[n + 3], d2[3], i3[n + 6], s3[n + 6], d3[3];
     interp_pair<1>(x, MGQ0, b0 ? -ih : ih, s1, d1);
 #pragma unroll
@@ -231,112 +335,36 @@ __device__ __forceinline__ void qp_mf_body(const Grid& g, const Chunk& ck, const
       F[3 * i + 2] = d3[i] + (i == 2 ? 1.0 : 0.0);
     }
 #pragma unroll
-    for (int k = 0; k < NV; ++k) eh[k] = s3[3 + k], ehn[k] = s3[3 + NV + k];
+    for (int k = 0; k < NV; ++k) eh[k] = s3[3 + k];
   }
   if (!active) return;  // no lane exchanges from here on
   MfOut out{F,
             reinterpret_cast<double2*>(D64) + eg * (MF_NK / 2) * 64,
             D32 ? reinterpret_cast<float4*>(D32) + eg * (MF_NK / 4) * 64 : nullptr,
             (uint32_t)(8 * gp + (lane >> 3)),
-            qp,
-            (int64_t)8 * ck.NEcpad,
-            (uint32_t)gp * (uint32_t)ck.NEcpad + (uint32_t)el,
             {0.0, 0.0, 0.0, 0.0},
             {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}};
-  local_hessian<PD, MIX>(F, eh, ehn, *cd, out);
+  local_hessian<PD, MIX>(F, eh, *cd, out);
 }
 template <int PD, int MIX>
 __global__ void __launch_bounds__(128) qp_mf_kernel(Grid g, Chunk ck, const double* __restrict__ state,
-                                                    const DevCard* __restrict__ cd, double* __restrict__ qp,
-                                                    double* __restrict__ D64, float* __restrict__ D32) {
-  qp_mf_body<PD, MIX>(g, ck, state, cd, qp, D64, D32, blockIdx.x);
+                                                    const DevCard* __restrict__ cd, double* __restrict__ D64,
+                                                    float* __restrict__ D32) {
+  qp_mf_body<PD, MIX>(g, ck, state, cd, D64, D32, blockIdx.x);
 }
 // groups of 8 elements touching the slab, two wavefronts per workgroup
 int qp_mf_blocks(const Chunk& ck) { return (int)(((ck.e0 + ck.NEc + 7) / 8 - ck.e0 / 8 + 1) / 2); }
-template <int PD, int MIX>
-void launch_qp_mf_order(const Grid& g, const Chunk& ck, const double* state, const DevCard* cd, double* qp, double* D64,
-                        float* D32, hipStream_t s) {
-  qp_mf_kernel<PD, MIX><<<qp_mf_blocks(ck), 128, 0, s>>>(g, ck, state, cd, qp, D64, D32);
-}
+struct QpMfRun {
+  template <int PD, int MIX>
+  static void run(const Grid& g, const Chunk& ck, const double* state, const DevCard* cd, double* D64, float* D32,
+                  hipStream_t s) {
+    qp_mf_kernel<PD, MIX><<<qp_mf_blocks(ck), 128, 0, s>>>(g, ck, state, cd, D64, D32);
+  }
+};
 void launch_qp_mf(const Grid& g, const Chunk& ck, const double* state, const DevCard* cd, int pade, int mixing,
-                  double* qp, double* D64, float* D32, hipStream_t s) {
-  if constexpr (MF_AVAILABLE) {
-    if (mixing == MVPF_MIX_LOG) {
-      switch (pade) {
-        case 11: launch_qp_mf_order<11, 1>(g, ck, state, cd, qp, D64, D32, s); break;
-        case 33: launch_qp_mf_order<33, 1>(g, ck, state, cd, qp, D64, D32, s); break;
-        default: launch_qp_mf_order<22, 1>(g, ck, state, cd, qp, D64, D32, s); break;
-      }
-      return;
-    }
-    switch (pade) {
-      case 11: launch_qp_mf_order<11, 0>(g, ck, state, cd, qp, D64, D32, s); break;
-      case 33: launch_qp_mf_order<33, 0>(g, ck, state, cd, qp, D64, D32, s); break;
-      default: launch_qp_mf_order<22, 0>(g, ck, state, cd, qp, D64, D32, s); break;
-    }
-  }
+                  double* D64, float* D32, hipStream_t s) {
+  if constexpr (MF_AVAILABLE) run_card<QpMfRun>(pade, mixing, g, ck, state, cd, D64, D32, s);
 }
-
-__device__ __forceinline__ void residual_gather_body(const Grid& g, const Chunk& ck, const double* __restrict__ state,
-                                                     const double* __restrict__ qp, const DevCard* __restrict__ cd,
-                                                     double* __restrict__ R, int bid) {
-  const int n = ck.n0 + bid * 256 + threadIdx.x;
-  if (n >= ck.n1 || n >= g.Npad) return;
-  double r[NDOF];
-#pragma unroll
-  for (int c = 0; c < NDOF; ++c) r[c] = 0.0;
-  if (n < g.N) {
-    const int i = n % g.nnx, j = (n / g.nnx) % g.nny, k = n / (g.nnx * g.nny);
-    const double cu = g.h * g.h * 0.125, ce = g.h * g.h * g.h * 0.125;
-    const int64_t stride = (int64_t)8 * ck.NEcpad;
-    for (int a = 0; a < 8; ++a) {
-      const int ax = a & 1, ay = (a >> 1) & 1, az = (a >> 2) & 1;
-      const int ex = i - ax, ey = j - ay, ez = k - az;
-      if (ex < 0 || ex >= g.nx || ey < 0 || ey >= g.ny || ez < 0 || ez >= g.nz) continue;
-      const int64_t el = ex + (int64_t)g.nx * (ey + (int64_t)g.ny * ez) - ck.e0;  // in [0, NEc) by construction
-#pragma unroll
-      for (int gp = 0; gp < 8; ++gp) {
-        const Shape s = shape(gp, a);
-        const double* q = qp + (int64_t)gp * ck.NEcpad + el;
-#pragma unroll
-        for (int i3 = 0; i3 < 3; ++i3)
-          r[i3] += cu * (s.dN[0] * q[(3 * i3 + 0) * stride] + s.dN[1] * q[(3 * i3 + 1) * stride] +
-                         s.dN[2] * q[(3 * i3 + 2) * stride]);
-#pragma unroll
-        for (int m = 0; m < NV; ++m) r[3 + m] += ce * s.N * q[(9 + m) * stride];
-      }
-      // gradient energy 1/2 Mg_kl grad eta_k . grad eta_l: h * Lap_ab * Mg * eta_b
-      for (int b = 0; b < 8; ++b) {
-        const int nb = (ex + (b & 1)) + g.nnx * ((ey + ((b >> 1) & 1)) + g.nny * (ez + ((b >> 2) & 1)));
-        const double lap = g.h * lap_ref(a, b);
-        double eb[NV];
-#pragma unroll
-        for (int l = 0; l < NV; ++l) eb[l] = state[(int64_t)(3 + l) * g.Npad + nb];
-#pragma unroll
-        for (int m = 0; m < NV; ++m) {
-          double s2 = 0.0;
-#pragma unroll
-          for (int l = 0; l < NV; ++l) s2 += cd->Mg[m][l] * eb[l];
-          r[3 + m] += lap * s2;
-        }
-      }
-    }
-  }
-#pragma unroll
-  for (int c = 0; c < NDOF; ++c) R[(int64_t)c * g.Npad + n] = r[c];
-}
-__global__ void __launch_bounds__(256) residual_gather_kernel(Grid g, Chunk ck, const double* __restrict__ state,
-                                                              const double* __restrict__ qp,
-                                                              const DevCard* __restrict__ cd,
-                                                              double* __restrict__ R) {
-  residual_gather_body(g, ck, state, qp, cd, R, blockIdx.x);
-}
-
-void launch_residual_gather(const Grid& g, const Chunk& ck, const double* state, const double* qp, const DevCard* cd,
-                            double* R, hipStream_t s) {
-  residual_gather_kernel<<<(ck.n1 - ck.n0 + 255) / 256, 256, 0, s>>>(g, ck, state, qp, cd, R);
-}
-
 
 // Element matrices K_e = sum_g w_g B_g^T D_g B_g + h Lap (x) Mg for the 36
 // node pairs a <= b.  A workgroup of EM_WAVES wavefronts covers 64
@@ -381,7 +409,7 @@ __device__ __forceinline__ void element_matrix_body(const Grid& g, const Chunk& 
       // instruction moves two Hessian components of the group's 64 elements,
       // lanes 0-31 component c and lanes 32-63 component c + 1, 16 B (two
       // elements) per lane, landing at LDS base + 16 * lane
-      const double* src = qp + (int64_t)(QP_GRAD + 2 * w + (l >> 5)) * stride + (int64_t)gp * ck.NEcpad + eg * 64 +
+      const double* src = qp + (int64_t)(2 * w + (l >> 5)) * stride + (int64_t)gp * ck.NEcpad + eg * 64 +
                           2 * (l & 31);
 #pragma unroll
       for (int r = 0; r < NHP_PAD / (2 * EM_WAVES); ++r) {
@@ -742,13 +770,13 @@ template <int PD, int MIX>
 __global__ void __launch_bounds__(128) qp_hess_batch(const AJob* __restrict__ jobs, int njobs) {
   int bid;
   const AJob& j = find_job(jobs, njobs, bid);
-  qp_body<true, PD, MIX>(j.g, j.ck, j.state, j.cd, j.qp, bid);
+  qp_body<PD, MIX>(j.g, j.ck, j.state, j.cd, j.qp, bid);
 }
 template <int PD, int MIX>
 __global__ void __launch_bounds__(128) qp_mf_batch(const AJob* __restrict__ jobs, int njobs) {
   int bid;
   const AJob& j = find_job(jobs, njobs, bid);
-  qp_mf_body<PD, MIX>(j.g, j.ck, j.state, j.cd, j.qp, j.D64, j.D32, bid);
+  qp_mf_body<PD, MIX>(j.g, j.ck, j.state, j.cd, j.D64, j.D32, bid);
 }
 __global__ void __launch_bounds__(EM_WAVES * 64, EM_MINB) element_matrix_batch(const AJob* __restrict__ jobs, int njobs) {
   int bid;
@@ -770,10 +798,16 @@ __global__ void __launch_bounds__(BI_THREADS) block_inverse_batch(const AJob* __
   const AJob& j = find_job(jobs, njobs, bid);
   block_inverse_body(j.g, j.diag64, j.Dinv64, j.Dinv32, BI_REGS ? j.DinvS32 : nullptr, j.status, bid);
 }
-__global__ void __launch_bounds__(256) residual_gather_batch(const AJob* __restrict__ jobs, int njobs) {
+template <int PD, int MIX>
+__global__ void __launch_bounds__(256) residual_element_batch(const AJob* __restrict__ jobs, int njobs) {
   int bid;
   const AJob& j = find_job(jobs, njobs, bid);
-  residual_gather_body(j.g, j.ck, j.state, j.qp, j.cd, j.R, bid);
+  residual_element_body<PD, MIX>(j.g, j.ck, j.state, j.cd, j.out, bid, j.nblk);
+}
+__global__ void __launch_bounds__(256) residual_nodes_batch(const AJob* __restrict__ jobs, int njobs) {
+  int bid;
+  const AJob& j = find_job(jobs, njobs, bid);
+  residual_nodes_body(j.g, j.ck, j.out, j.R, bid);
 }
 
 // the launch shapes of the single-problem launchers, per job
@@ -796,12 +830,12 @@ int assembly_job_blocks(int op, AJob& j) {
       j.nblocks = g.ntiles * j.nup;
       return (j.nblocks + 7) / 8 * 8;
     case AOP_BLOCK_INVERSE: return (g.Npad + BI_THREADS - 1) / BI_THREADS;
-    case AOP_RESIDUAL: return (ck.n1 - ck.n0 + 255) / 256;
+    case AOP_RESIDUAL: return ck.NEcpad / SLAB_EPW;
+    case AOP_RESIDUAL_NODES: return (ck.n1 - ck.n0 + 255) / 256 * NDOF;
     default: return 0;
   }
 }
 
-// pade = Pade order + QP_LOG_MIX for logarithmic mixing
 struct QpHessBatch {
   template <int PD, int MIX>
   static void run(const AJob* jobs, int njobs, int blocks, hipStream_t s) {
@@ -814,30 +848,28 @@ struct QpMfBatch {
     qp_mf_batch<PD, MIX><<<blocks, 128, 0, s>>>(jobs, njobs);
   }
 };
-template <class K>
-void launch_qp_batch(int pade, const AJob* jobs, int njobs, int blocks, hipStream_t s) {
-  const int pd = pade % QP_LOG_MIX;
-  if (pade >= QP_LOG_MIX) {
-    if (pd == 11) K::template run<11, 1>(jobs, njobs, blocks, s);
-    else if (pd == 33) K::template run<33, 1>(jobs, njobs, blocks, s);
-    else K::template run<22, 1>(jobs, njobs, blocks, s);
-  } else if (pd == 11) K::template run<11, 0>(jobs, njobs, blocks, s);
-  else if (pd == 33) K::template run<33, 0>(jobs, njobs, blocks, s);
-  else K::template run<22, 0>(jobs, njobs, blocks, s);
-}
+struct ResidualBatch {
+  template <int PD, int MIX>
+  static void run(const AJob* jobs, int njobs, int blocks, hipStream_t s) {
+    residual_element_batch<PD, MIX><<<blocks, 256, 0, s>>>(jobs, njobs);
+  }
+};
 
+// pade = Pade order + QP_LOG_MIX for logarithmic mixing
 void launch_assembly_batch(int op, int pade, const AJob* jobs, int njobs, int blocks, hipStream_t s) {
   if (njobs <= 0 || blocks <= 0) return;
+  const int order = pade % QP_LOG_MIX, mixing = pade >= QP_LOG_MIX ? MVPF_MIX_LOG : MVPF_MIX_LINEAR;
   switch (op) {
-    case AOP_QP_HESS: launch_qp_batch<QpHessBatch>(pade, jobs, njobs, blocks, s); break;
+    case AOP_QP_HESS: run_card<QpHessBatch>(order, mixing, jobs, njobs, blocks, s); break;
     case AOP_QP_MF:
-      if constexpr (MF_AVAILABLE) launch_qp_batch<QpMfBatch>(pade, jobs, njobs, blocks, s);
+      if constexpr (MF_AVAILABLE) run_card<QpMfBatch>(order, mixing, jobs, njobs, blocks, s);
       break;
+    case AOP_RESIDUAL: run_card<ResidualBatch>(order, mixing, jobs, njobs, blocks, s); break;
+    case AOP_RESIDUAL_NODES: residual_nodes_batch<<<blocks, 256, 0, s>>>(jobs, njobs); break;
     case AOP_ELEMENT: element_matrix_batch<<<blocks, EM_WAVES * 64, 0, s>>>(jobs, njobs); break;
     case AOP_GATHER: jacobian_gather_batch<<<blocks, TILE, 0, s>>>(jobs, njobs); break;
     case AOP_DIRICHLET: apply_dirichlet_batch<<<blocks, TILE, 0, s>>>(jobs, njobs); break;
     case AOP_BLOCK_INVERSE: block_inverse_batch<<<blocks, BI_THREADS, 0, s>>>(jobs, njobs); break;
-    case AOP_RESIDUAL: residual_gather_batch<<<blocks, 256, 0, s>>>(jobs, njobs); break;
     case AOP_MF_DIAG:
     case AOP_MF_DIAG_GATHER: launch_mf_diag_batch(op, jobs, njobs, blocks, s); break;
     default: break;
