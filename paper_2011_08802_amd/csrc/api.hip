@@ -549,6 +549,15 @@ void precondition(mvpf_problem* p, const double* v, TZ* z) {
   launch_precond_finish<T, TZ>(L0.g, (const T*)L0.x, v, L0.mask, z, p->stream);
 }
 
+// the same between the callers' node-interleaved vectors
+template <typename T>
+void precondition_interleaved(mvpf_problem* p, const double* v, double* z) {
+  Level& L0 = p->lev[0];
+  launch_interleaved_to_soa<T>(L0.g, v, NDOF, 0, (T*)L0.b, p->stream, L0.mask);
+  vcycle<T>(p, 0);
+  launch_soa_to_interleaved<T>(L0.g, (const T*)L0.x, NDOF, 0, z, p->stream, L0.mask, v);
+}
+
 // ---- FGMRES ---------------------------------------------------------------------
 int fetch(mvpf_problem* p, const double* dsrc, int count) {
   HIPCHK(hipMemcpyAsync(p->hhost, dsrc, sizeof(double) * count, hipMemcpyDeviceToHost, p->stream));
@@ -2523,9 +2532,9 @@ int mvpf_set_opts(mvpf_problem* p, const mvpf_opts* o) {
 int mvpf_set_state(mvpf_problem* p, const double* u, const double* eta, const double* eta_prev, double depth) {
   if (!p) return MVPF_EINVAL;
   const Grid& g = p->lev[0].g;
-  if (u) launch_interleaved_to_soa(g, u, 3, 0, 3, p->lev[0].state, p->stream);
-  if (eta) launch_interleaved_to_soa(g, eta, NV, 3, NV, p->lev[0].state, p->stream);
-  if (eta_prev) launch_interleaved_to_soa(g, eta_prev, NV, 3 + NV, NV, p->lev[0].state, p->stream);
+  if (u) launch_interleaved_to_soa(g, u, 3, 0, p->lev[0].state, p->stream);
+  if (eta) launch_interleaved_to_soa(g, eta, NV, 3, p->lev[0].state, p->stream);
+  if (eta_prev) launch_interleaved_to_soa(g, eta_prev, NV, 3 + NV, p->lev[0].state, p->stream);
   p->depth = depth;
   p->have_system = p->have_solution = false;
   TRY(launch_check(p, "set_state"));
@@ -2536,9 +2545,9 @@ int mvpf_set_state(mvpf_problem* p, const double* u, const double* eta, const do
 int mvpf_get_state(mvpf_problem* p, double* u, double* eta, double* eta_prev, double* depth) {
   if (!p) return MVPF_EINVAL;
   const Grid& g = p->lev[0].g;
-  if (u) launch_soa_to_interleaved(g, p->lev[0].state, 3, 0, 3, u, p->stream);
-  if (eta) launch_soa_to_interleaved(g, p->lev[0].state, NV, 3, NV, eta, p->stream);
-  if (eta_prev) launch_soa_to_interleaved(g, p->lev[0].state, NV, 3 + NV, NV, eta_prev, p->stream);
+  if (u) launch_soa_to_interleaved(g, p->lev[0].state, 3, 0, u, p->stream);
+  if (eta) launch_soa_to_interleaved(g, p->lev[0].state, NV, 3, eta, p->stream);
+  if (eta_prev) launch_soa_to_interleaved(g, p->lev[0].state, NV, 3 + NV, eta_prev, p->stream);
   if (depth) *depth = p->depth;
   TRY(launch_check(p, "get_state"));
   HIPCHK(hipStreamSynchronize(p->stream));
@@ -2557,10 +2566,11 @@ int mvpf_init_random(mvpf_problem* p, uint64_t seed) {
 
 int mvpf_residual(mvpf_problem* p, double* R, double* norm_free) {
   if (!p) return MVPF_EINVAL;
-  TRY(compute_residual(p, p->have_system ? p->sys_depth : p->depth, norm_free));
-  if (R) launch_soa_to_interleaved(p->lev[0].g, p->R, NDOF, 0, NDOF, R, p->stream);
+  TRY(compute_residual(p, p->have_system ? p->sys_depth : p->depth, nullptr));
+  if (R) launch_soa_to_interleaved(p->lev[0].g, p->R, NDOF, 0, R, p->stream);
   TRY(launch_check(p, "residual"));
-  HIPCHK(hipStreamSynchronize(p->stream));
+  if (norm_free) TRY(free_norm(p, p->R, norm_free));  // waits for the stream
+  else HIPCHK(hipStreamSynchronize(p->stream));
   return 0;
 }
 
@@ -2577,7 +2587,7 @@ int mvpf_newton_system(mvpf_problem* p, double depth) {
 int mvpf_get_rhs(mvpf_problem* p, double* b) {
   if (!p || !b) return MVPF_EINVAL;
   if (!p->have_system) { p->err = "no Newton system"; return MVPF_ESTATE; }
-  launch_soa_to_interleaved(p->lev[0].g, p->rhs, NDOF, 0, NDOF, b, p->stream);
+  launch_soa_to_interleaved(p->lev[0].g, p->rhs, NDOF, 0, b, p->stream);
   TRY(launch_check(p, "get_rhs"));
   HIPCHK(hipStreamSynchronize(p->stream));
   return 0;
@@ -2589,20 +2599,21 @@ int mvpf_jacobian_apply(mvpf_problem* p, int level, int precision, const double*
   Level& L = p->lev[level];
   const Grid& g = L.g;
   hipStream_t s = p->stream;
-  launch_interleaved_to_soa(g, x, NDOF, 0, NDOF, p->tmp, s);
   const bool mf = level == 0 && use_mf(p);
   if (precision == MVPF_FP64) {
+    if (!mf && !L.A64) { p->err = "no FP64 operator on this level"; return MVPF_EINVAL; }
+    launch_interleaved_to_soa(g, x, NDOF, 0, p->tmp, s);
     if (mf) {
       mf_elements<double, double>(p, p->tmp, true);
       launch_mf_gather<0, double, double, double>(g, (const double*)p->Cbuf, contact(p), p->mf_epw, L.mask, p->tmp,
                                                   nullptr, nullptr, 0.0, p->tmp2, s);
     } else {
-      if (!L.A64) { p->err = "no FP64 operator on this level"; return MVPF_EINVAL; }
       launch_spmv<double, double, double>(g, L.A64, p->tmp, p->tmp2, p->Cbuf, s);
     }
+    launch_soa_to_interleaved(g, p->tmp2, NDOF, 0, y, s);
   } else if (precision == MVPF_MIXED) {
     if (mf ? !p->Dmf32 : !L.A32) { p->err = "no FP32 operator on this level"; return MVPF_EINVAL; }
-    launch_convert<double, float>(nvec(g), p->tmp, (float*)L.x, s);
+    launch_interleaved_to_soa(g, x, NDOF, 0, (float*)L.x, s);
     if (mf) {
       mf_elements<float, float>(p, (const float*)L.x, true);
       launch_mf_gather<0, float, float, float>(g, (const float*)p->Cbuf, contact(p), p->mf_epw, L.mask,
@@ -2610,11 +2621,10 @@ int mvpf_jacobian_apply(mvpf_problem* p, int level, int precision, const double*
     } else {
       launch_spmv<float, float, float>(g, L.A32, (const float*)L.x, (float*)L.r, p->Cbuf, s);
     }
-    launch_convert<float, double>(nvec(g), (const float*)L.r, p->tmp2, s);
+    launch_soa_to_interleaved(g, (const float*)L.r, NDOF, 0, y, s);
   } else {
     return MVPF_EINVAL;
   }
-  launch_soa_to_interleaved(g, p->tmp2, NDOF, 0, NDOF, y, s);
   TRY(launch_check(p, "jacobian_apply"));
   HIPCHK(hipStreamSynchronize(s));
   return 0;
@@ -2623,13 +2633,10 @@ int mvpf_jacobian_apply(mvpf_problem* p, int level, int precision, const double*
 int mvpf_precondition(mvpf_problem* p, const double* v, double* z) {
   if (!p || !v || !z) return MVPF_EINVAL;
   if (!p->have_system) { p->err = "no Newton system"; return MVPF_ESTATE; }
-  const Grid& g = p->lev[0].g;
-  launch_interleaved_to_soa(g, v, NDOF, 0, NDOF, p->tmp, p->stream);
   if (p->mixed)
-    precondition<float, double>(p, p->tmp, p->tmp2);
+    precondition_interleaved<float>(p, v, z);
   else
-    precondition<double, double>(p, p->tmp, p->tmp2);
-  launch_soa_to_interleaved(g, p->tmp2, NDOF, 0, NDOF, z, p->stream);
+    precondition_interleaved<double>(p, v, z);
   TRY(launch_check(p, "precondition"));
   HIPCHK(hipStreamSynchronize(p->stream));
   return 0;
@@ -2643,13 +2650,13 @@ int mvpf_solve(mvpf_problem* p, const double* b, double* x, mvpf_solve_stats* st
   const Grid& g = p->lev[0].g;
   const double* bb = p->rhs;
   if (b) {
-    launch_interleaved_to_soa(g, b, NDOF, 0, NDOF, p->tmp2, p->stream);
+    launch_interleaved_to_soa(g, b, NDOF, 0, p->tmp2, p->stream);
     bb = p->tmp2;
   }
   int rc = solve_internal(p, bb, p->dx, st);
   if (rc < 0) return rc;
   if (x) {
-    launch_soa_to_interleaved(g, p->dx, NDOF, 0, NDOF, x, p->stream);
+    launch_soa_to_interleaved(g, p->dx, NDOF, 0, x, p->stream);
     TRY(launch_check(p, "solve output"));
     HIPCHK(hipStreamSynchronize(p->stream));
   }

@@ -420,10 +420,14 @@ int dense_invert_pivoted(int n, const double* a, double* inv, double* work, int*
 template <typename T>
 void launch_coarse_solve(const Grid& g, const double* Ainv, const T* b, T* x, hipStream_t s);
 // vectors
-void launch_interleaved_to_soa(const Grid& g, const double* in, int ncomp, int comp0, int ldc,
-                               double* out, hipStream_t s);
-void launch_soa_to_interleaved(const Grid& g, const double* in, int ncomp, int comp0, int ldc,
-                               double* out, hipStream_t s);
+// mask: constrained dofs become zero (needs all NDOF components)
+template <typename T>
+void launch_interleaved_to_soa(const Grid& g, const double* in, int ncomp, int comp0, T* out, hipStream_t s,
+                               const uint16_t* mask = nullptr);
+// mask: constrained dofs are taken from v, which out may be
+template <typename T>
+void launch_soa_to_interleaved(const Grid& g, const T* in, int ncomp, int comp0, double* out, hipStream_t s,
+                               const uint16_t* mask = nullptr, const double* v = nullptr);
 template <typename TI, typename TO>
 void launch_convert_masked(const Grid& g, const TI* in, const uint16_t* mask, TO* out, hipStream_t s);
 void launch_set_constrained(const Grid& g, const uint16_t* mask, const double* src, double* dst,
@@ -458,8 +462,6 @@ void launch_axpby(int64_t n, double a, const double* x, double b, const double* 
                   hipStream_t s);
 template <typename T>
 void launch_zero(int64_t n, T* p, hipStream_t s);
-template <typename TI, typename TO>
-void launch_convert(int64_t n, const TI* in, TO* out, hipStream_t s);
 template <typename T, typename TZ>
 void launch_precond_finish(const Grid& g, const T* x, const double* v, const uint16_t* mask, TZ* z, hipStream_t s);
 

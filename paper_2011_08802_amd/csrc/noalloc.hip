@@ -112,7 +112,7 @@ int mvpf_residual_noalloc(mvpf_problem* p, double* R, double* norm_free) {
     }
     *norm_free = std::sqrt(p->hhost[0]);
   }
-  if (R) launch_soa_to_interleaved(g, p->R, NDOF, 0, NDOF, R, s);
+  if (R) launch_soa_to_interleaved(g, p->R, NDOF, 0, R, s);
   if ((rc = check(p, "residual_noalloc"))) return rc;
   const hipError_t e = hipStreamSynchronize(s);
   if (e != hipSuccess) {
