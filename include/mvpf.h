@@ -422,7 +422,7 @@ int mvpf_indent(mvpf_problem* p, const mvpf_indent_opts* o, mvpf_indent_callback
  * cache reach of each other); "outer_blocks": the same for the outer FP64
  * operator product (level ignored); "small_grid_nodes": levels with at most
  * this many nodes use the latency-oriented small-grid smoother and defect
- * kernels (27 threads per row; default 10000; level ignored).  The two kernel
+ * kernels (27 threads per row; default 40000; level ignored).  The two kernel
  * families sum the 27 block products in different orders, so this key alone
  * changes results at rounding level; the others never do.  "coarse_overlap":
  * 1 = the coarsest level's dense inversion runs on a second (default
@@ -446,7 +446,8 @@ int mvpf_indent(mvpf_problem* p, const mvpf_indent_opts* o, mvpf_indent_callback
  * level ignored.  row_blocks on level 0 and outer_blocks apply to the
  * assembled finest level only.  "mf_elements_per_block": elements per
  * workgroup of the matrix-free element kernel, 8, 16 or 32 (64, 128 or 256
- * threads; default 32; level ignored; results bitwise unchanged).
+ * threads; default 8 up to 8192 elements, else 32; level ignored; results
+ * bitwise unchanged).
  * "autotune_cache": 1 (default) = mvpf_autotune reuses the results of earlier
  * tuning runs for the same GPU architecture, multigrid precision,
  * finest-level mode (matrix-free or assembled) and level shape (elements per
@@ -488,8 +489,7 @@ int mvpf_kernel_stats(mvpf_problem* p, const char* name, int* launches, double* 
  * one launch covering all problems, whatever their sizes: each problem is a
  * job of the launch, owning a range of its workgroups.  Each problem's
  * numbers are bitwise those of solving it alone with mvpf_solve (under the
- * same tuning: the problems of a batch start with small_grid_nodes = 0, the
- * small-grid kernels pay only in narrow single-problem launches).  Every problem is a full handle (mvpf_batch_problem)
+ * same tuning).  Every problem is a full handle (mvpf_batch_problem)
  * on which the single-problem calls work; the batch owns them. */
 
 /* Create n (1..MVPF_MAX_BATCH) problems: meshes[i], mats[i], loads[i] as for

@@ -488,7 +488,16 @@ void mf_elements(mvpf_problem* p, const TX* x, bool masked, bool sparse = false)
   if (contact(p)) launch_contact_apply<T, TX>(L0.g, p->sphere, L0.state, mask, x, (T*)p->Cbuf, p->stream);
 }
 
+// block inverses of the finest level's sweep from a zero guess: the
+// matrix-free gather's, whose FP32 form is packed
+template <typename T>
+bool zero_packed(const mvpf_problem* p) {
+  return use_mf(p) && sizeof(T) == 4;
+}
+
 // ---- V-cycle ------------------------------------------------------------------
+// one sweep on level l; zero: the finest level's first one, from a zero guess
+// (the coarser levels' is written by the restriction)
 template <typename T>
 void sweep(mvpf_problem* p, int l, bool zero) {
   Level& L = p->lev[l];
@@ -499,10 +508,13 @@ void sweep(mvpf_problem* p, int l, bool zero) {
     mf_elements<T, T>(p, (const T*)L.x, true);
     launch_mf_gather<2, T, T, T>(L.g, (const T*)p->Cbuf, contact(p), p->mf_epw, L.mask, (const T*)L.x, (const T*)L.b,
                                  mfDinv<T>(L), om, (T*)L.x2, p->stream);
-  } else if (!zero && L.g.N <= p->small_nodes)
+  } else if (zero)
+    launch_pbj_zero<T>(L.g, use_mf(p) ? mfDinv<T>(L) : opD<T>(L), zero_packed<T>(p), (const T*)L.b, (T*)L.x2, om,
+                       p->stream, p->row_G[l]);
+  else if (L.g.N <= p->small_nodes)
     launch_row_small<T>(L.g, opA<T>(L), opD<T>(L), (const T*)L.x, (const T*)L.b, (T*)L.x2, om, true, p->stream);
   else
-    launch_pbj<T>(L.g, opA<T>(L), opD<T>(L), (const T*)L.x, (const T*)L.b, (T*)L.x2, om, zero, p->Cbuf, p->stream,
+    launch_pbj<T>(L.g, opA<T>(L), opD<T>(L), (const T*)L.x, (const T*)L.b, (T*)L.x2, om, p->Cbuf, p->stream,
                   p->row_G[l]);
   if (timed) timer_end(p, p->t_sweep, sweep_bytes<T>(L.g, use_mf(p)));
   std::swap(L.x, L.x2);
@@ -517,7 +529,7 @@ void vcycle(mvpf_problem* p, int l) {
     return;
   }
   if (p->opts.nu_pre > 0) {
-    sweep<T>(p, l, true);
+    if (l == 0) sweep<T>(p, l, true);
     for (int k = 1; k < p->opts.nu_pre; ++k) sweep<T>(p, l, false);
   } else {
     launch_zero<T>(nvec(L.g), (T*)L.x, s);
@@ -535,7 +547,9 @@ void vcycle(mvpf_problem* p, int l) {
     timer_end(p, p->t_resid,
               sizeof(T) * ((use_mf(p) ? MF_VALUES * L.g.NE : stored_blocks(L.g) * NBLK) + (double)L.g.N * 3 * NDOF));
   Level& C = p->lev[l + 1];
-  launch_restrict<T>(L.g, C.g, (const T*)L.r, C.mask, (T*)C.b, s);
+  const bool presmooth = l + 1 < p->L - 1 && p->opts.nu_pre > 0;
+  launch_restrict<T>(L.g, C.g, (const T*)L.r, C.mask, (T*)C.b, presmooth ? opD<T>(C) : nullptr, (T*)C.x,
+                     (T)p->opts.omega, s);
   vcycle<T>(p, l + 1);
   launch_prolong_add<T>(L.g, C.g, (const T*)C.x, L.mask, (T*)L.x, s);
   for (int k = 0; k < p->opts.nu_post; ++k) sweep<T>(p, l, false);
@@ -885,6 +899,7 @@ int allocate(mvpf_problem* p) {
     const int f = 1 << l;
     Level& L = p->lev[l];
     L.g = make_grid(M.nx / f, M.ny / f, M.nz / f, M.h * f);
+    if (l == 0) p->mf_epw = mf_default_epw(L.g.NE);
     const bool coarsest = (l == p->L - 1);
     const int64_t nv = nvec(L.g);
     const int64_t nA64 = (int64_t)L.g.ntiles * NUP * Lay<double>::SLICE;
@@ -1446,7 +1461,7 @@ void autotune_levels(mvpf_problem* p, int* tuned) {
     int bestG = 0;
     for (int G : launch_candidates(L.g)) {
       const double ms = time_launches(p, 5, [&] {
-        launch_pbj<T>(L.g, opA<T>(L), opD<T>(L), (const T*)L.x, (const T*)L.b, (T*)L.x2, (T)p->opts.omega, false,
+        launch_pbj<T>(L.g, opA<T>(L), opD<T>(L), (const T*)L.x, (const T*)L.b, (T*)L.x2, (T)p->opts.omega,
                       p->Cbuf, p->stream, G);
       });
       if (ms < best * 0.98) { best = ms; bestG = G; }
@@ -1645,6 +1660,8 @@ void plan_sweep(Planner& pl, const std::vector<mvpf_problem*>& ps, int l, bool z
     j.b = L.b;
     j.y = L.x2;
     if (zero) {
+      if (use_mf(p)) j.D = mfDinv<T>(L);
+      j.packed = zero_packed<T>(p);
       z.push_back(j);
     } else if (l == 0 && use_mf(p)) {
       mf.push_back(p);
@@ -1740,7 +1757,7 @@ void plan_vcycle(Planner& pl, const std::vector<mvpf_problem*>& ps, int l) {
       pl.solo([x, n](hipStream_t s) { launch_zero<T>(n, x, s); });
     }
   }
-  plan_sweep<T>(pl, act, l, true);
+  if (l == 0) plan_sweep<T>(pl, act, l, true);  // the coarser levels': written by the restriction
   for (int k = 1; k < nu_pre; ++k) {
     act.clear();
     for (mvpf_problem* p : fine)
@@ -1757,6 +1774,9 @@ void plan_vcycle(Planner& pl, const std::vector<mvpf_problem*>& ps, int l) {
     j.x = L.r;
     j.mask = C.mask;
     j.y = C.b;
+    if (l + 1 < p->L - 1 && p->opts.nu_pre > 0) j.D = opD<T>(C);
+    j.C = C.x;
+    j.omega = p->opts.omega;
     rs.push_back(j);
   }
   pl.add(BOP_RESTRICT, std::move(rs));
@@ -3118,7 +3138,6 @@ int mvpf_create_batch(int n, const mvpf_mesh* meshes, const mvpf_material* mats,
     // a batched launch is wide even where each problem's level is small: the
     // two-pass kernels (every stored block read once) beat the small-grid
     // ones there (batched solve 336 -> 314 ms on the 32-problem workload)
-    b->probs[i]->small_nodes = BATCH_SMALL_GRID_NODES;
     const int64_t nv = nvec(b->probs[i]->lev[0].g);
     if (hipMalloc((void**)&b->vin[i], sizeof(double) * nv) != hipSuccess ||
         hipMalloc(&b->zout[i], (b->mixed ? sizeof(float) : sizeof(double)) * nv) != hipSuccess ||

@@ -18,8 +18,8 @@ int batch_job_blocks(int op, const BJob& j, int threads) {
     case BOP_DEFECT_LOWER:
     case BOP_ROW_SMALL_PBJ:
     case BOP_ROW_SMALL_DEFECT: return bsr_job_blocks(op, j.g);
-    case BOP_RESTRICT: return (j.g2.Npad + 255) / 256;
-    case BOP_PROLONG: return (j.g.Npad + 255) / 256;
+    case BOP_RESTRICT:
+    case BOP_PROLONG: return transfer_job_blocks(op, j);
     case BOP_COARSE: return (int)(((int64_t)NDOF * j.g.N + 3) / 4);
     case BOP_MF_ELEMENT:
     case BOP_MF_GATHER_PBJ:

@@ -297,31 +297,51 @@ template void launch_defect<double>(const Grid&, const double*, const double*, c
 
 // Damped point-block Jacobi sweep (Sec. 3.4): xo = x + omega D^-1 (b - A x).
 // Pass 1 leaves the partial residual in xo; pass 2 completes it and updates.
-// With a zero initial guess the product with A vanishes: xo = omega D^-1 b.
-template <typename T>
-__device__ __forceinline__ void pbj_zero_body(const Grid& g, const T* __restrict__ Dinv, const T* __restrict__ b,
-                                              T* __restrict__ xo, T omega, int bid, int nblk) {
-  ROW_LOOP_B(g, bid, nblk) {
-    if (n >= g.Npad) continue;
-    const int t = n >> 6, l = n & 63;
-    const T* Db = Dinv + (int64_t)t * Lay<T>::SLICE;
-    T bv[NDOF];
+// With a zero initial guess the product with A vanishes: xo = omega D^-1 b
+// (packed: D holds the upper triangles of the matrix-free level's inverses,
+// 45 instead of 81 values per row of the stream that bounds this kernel).
+template <typename T, bool PACKED>
+__device__ __forceinline__ void pbj_zero_row(const Grid& g, const T* __restrict__ Dinv, const T* __restrict__ b,
+                                             T* __restrict__ xo, T omega, int n) {
+  const int t = n >> 6, l = n & 63;
+  const T* Db = Dinv + (int64_t)t * (PACKED ? LaySym<T>::SLICE : Lay<T>::SLICE);
+  T bv[NDOF];
 #pragma unroll
-    for (int c = 0; c < NDOF; ++c) bv[c] = b[(int64_t)c * g.Npad + n];
+  for (int c = 0; c < NDOF; ++c) bv[c] = b[(int64_t)c * g.Npad + n];
 #pragma unroll
-    for (int r = 0; r < NDOF; ++r) {
-      T s = 0;
+  for (int r = 0; r < NDOF; ++r) {
+    T s = 0;
 #pragma unroll
-      for (int c = 0; c < NDOF; ++c) s += Db[Lay<T>::off(r * NDOF + c, l)] * bv[c];
-      xo[(int64_t)r * g.Npad + n] = (n < g.N) ? omega * s : (T)0;
-    }
+    for (int c = 0; c < NDOF; ++c)
+      s += Db[PACKED ? LaySym<T>::off(sym_index(r, c), l) : Lay<T>::off(r * NDOF + c, l)] * bv[c];
+    xo[(int64_t)r * g.Npad + n] = (n < g.N) ? omega * s : (T)0;
   }
 }
 template <typename T>
-__global__ void __launch_bounds__(256) pbj_zero_kernel(Grid g, const T* __restrict__ Dinv, const T* __restrict__ b,
-                                                       T* __restrict__ xo, T omega) {
-  pbj_zero_body<T>(g, Dinv, b, xo, omega, blockIdx.x, gridDim.x);
+__device__ __forceinline__ void pbj_zero_body(const Grid& g, const T* __restrict__ Dinv, bool packed,
+                                              const T* __restrict__ b, T* __restrict__ xo, T omega, int bid,
+                                              int nblk) {
+  ROW_LOOP_B(g, bid, nblk) {
+    if (n >= g.Npad) continue;
+    if (packed)
+      pbj_zero_row<T, true>(g, Dinv, b, xo, omega, n);
+    else
+      pbj_zero_row<T, false>(g, Dinv, b, xo, omega, n);
+  }
 }
+template <typename T>
+__global__ void __launch_bounds__(256) pbj_zero_kernel(Grid g, const T* __restrict__ Dinv, bool packed,
+                                                       const T* __restrict__ b, T* __restrict__ xo, T omega) {
+  pbj_zero_body<T>(g, Dinv, packed, b, xo, omega, blockIdx.x, gridDim.x);
+}
+
+template <typename T>
+void launch_pbj_zero(const Grid& g, const T* Dinv, bool packed, const T* b, T* xo, T omega, hipStream_t s, int G) {
+  pbj_zero_kernel<T><<<row_grid(g, G), 256, 0, s>>>(g, Dinv, packed, b, xo, omega);
+}
+template void launch_pbj_zero<float>(const Grid&, const float*, bool, const float*, float*, float, hipStream_t, int);
+template void launch_pbj_zero<double>(const Grid&, const double*, bool, const double*, double*, double, hipStream_t,
+                                      int);
 
 template <typename T>
 __device__ __forceinline__ void pbj_lower_body(const Grid& g, const T* __restrict__ Dinv, const T* __restrict__ x,
@@ -351,13 +371,9 @@ __global__ void __launch_bounds__(256) pbj_lower_kernel(Grid g, const T* __restr
 }
 
 template <typename T>
-void launch_pbj(const Grid& g, const T* A, const T* Dinv, const T* x, const T* b, T* xo, T omega, bool zero_guess,
-                void* C, hipStream_t s, int G) {
+void launch_pbj(const Grid& g, const T* A, const T* Dinv, const T* x, const T* b, T* xo, T omega, void* C,
+                hipStream_t s, int G) {
   const int nb = row_grid(g, G);
-  if (zero_guess) {
-    pbj_zero_kernel<T><<<nb, 256, 0, s>>>(g, Dinv, b, xo, omega);
-    return;
-  }
   if (G <= 0)
     defect_upper_split_kernel<T><<<split_grid(g), 256, 0, s>>>(g, A, x, b, xo, (T*)C);
   else
@@ -365,29 +381,57 @@ void launch_pbj(const Grid& g, const T* A, const T* Dinv, const T* x, const T* b
   pbj_lower_kernel<T><<<nb, 256, 0, s>>>(g, Dinv, x, xo, (const T*)C, omega);
 }
 template void launch_pbj<float>(const Grid&, const float*, const float*, const float*, const float*, float*, float,
-                                bool, void*, hipStream_t, int);
+                                void*, hipStream_t, int);
 template void launch_pbj<double>(const Grid&, const double*, const double*, const double*, const double*, double*,
-                                 double, bool, void*, hipStream_t, int);
+                                 double, void*, hipStream_t, int);
 
 // ---- small grids --------------------------------------------------------------
 // On coarse levels the one-thread-per-row kernels are latency bound (27 rounds
 // of dependent loads per thread).  Here 27 threads share a row, one per
 // stencil block; each does one round of loads and the 27 partial products are
-// summed through LDS in a fixed order.  9 rows per 256-thread workgroup,
-// thread index = s * 9 + local row.
-constexpr int SMALL_ROWS = 9;
+// summed through LDS in a fixed order.  SMALL_ROWS rows per workgroup, thread
+// index = s * SMALL_ROWS + local row, so a load takes the 16-byte words of 8
+// consecutive rows, a cache line; up to SMALL_CHUNK of them and the epilogue's
+// operands are in flight together.  A row reads the 13 blocks below its
+// diagonal from its neighbours' rows; consecutive workgroups share an XCD
+// (ROW_LOOP's numbering), so these come from its L2.
+// Per sweep, before (9 rows, scalar loads, workgroups dealt to all XCDs) and
+// now: FP64 9261 nodes 41.6 -> 23.3 us (85 MB of operator: 3.6 TB/s), 1331
+// nodes 9.8 -> 5.4, 125 nodes 6.0 -> 4.7; FP32 4913 nodes 16.2 -> 7.5 us.
+constexpr int SMALL_ROWS = 8;
+constexpr int SMALL_CHUNK = 21;  // 16-byte loads in flight per thread (an FP32 block of 9 x 9; half an FP64 one)
+#define SMALL_OCC __attribute__((amdgpu_waves_per_eu(3, 3)))  // registers for them
+constexpr int SMALL_THREADS = (SMALL_ROWS * NSTEN + 63) / 64 * 64;
+int small_blocks(const Grid& g) { return ((g.N + SMALL_ROWS - 1) / SMALL_ROWS + 7) / 8 * 8; }
 
 template <typename T, bool PBJ>
 __device__ __forceinline__ void row_small_body(const Grid& g, const T* __restrict__ A, const T* __restrict__ Dinv,
                                                const T* __restrict__ x, const T* __restrict__ b, T* __restrict__ out,
-                                               T omega, int bid) {
+                                               T omega, int bid, int nblk) {
   __shared__ T part[SMALL_ROWS][NSTEN][NDOF];
   __shared__ T res[SMALL_ROWS][NDOF];
+  using VT = typename Vec16<T>::type;
+  constexpr int V = Lay<T>::V;
   const int tid = threadIdx.x;
   const int s = tid / SMALL_ROWS, ln = tid % SMALL_ROWS;
-  const int n = bid * SMALL_ROWS + ln;
+  const int n0 = ((bid & 7) * (nblk >> 3) + (bid >> 3)) * SMALL_ROWS;
+  const int n = n0 + ln;
+  // the epilogue's operands (thread = local row x component), in flight from the start
+  const int ln2 = tid / NDOF, r2 = tid % NDOF;
+  const int n2 = n0 + ln2;
+  const bool own = tid < SMALL_ROWS * NDOF && n2 < g.N;
+  T b2 = 0, x2 = 0, d2[NDOF];
+  if (own) {
+    b2 = b[(int64_t)r2 * g.Npad + n2];
+    if (PBJ) {
+      x2 = x[(int64_t)r2 * g.Npad + n2];
+      const T* Db = Dinv + (int64_t)(n2 >> 6) * Lay<T>::SLICE;
+#pragma unroll
+      for (int c = 0; c < NDOF; ++c) d2[c] = Db[Lay<T>::off(r2 * NDOF + c, n2 & 63)];
+    }
+  }
   T pr[NDOF] = {};
-  if (tid < SMALL_ROWS * NSTEN && n < g.N) {
+  if (s < NSTEN && n < g.N) {
     const int i = n % g.nnx, j = (n / g.nnx) % g.nny, k = n / (g.nnx * g.nny);
     const int dx = s % 3 - 1, dy = (s / 3) % 3 - 1, dz = s / 9 - 1;
     if (i + dx >= 0 && i + dx < g.nnx && j + dy >= 0 && j + dy < g.nny && k + dz >= 0 && k + dz < g.nnz) {
@@ -395,69 +439,74 @@ __device__ __forceinline__ void row_small_body(const Grid& g, const T* __restric
       T xv[NDOF];
 #pragma unroll
       for (int c = 0; c < NDOF; ++c) xv[c] = x[(int64_t)c * g.Npad + m];
-      if (s >= 13) {
-        const T* Ab = A + ((int64_t)(n >> 6) * NUP + (s - 13)) * Lay<T>::SLICE;
-        const int ll = n & 63;
+      const bool upper = s >= 13;
+      const int o = upper ? n : m;  // the row that stores the block
+      const VT* Ab =
+          reinterpret_cast<const VT*>(A + ((int64_t)(o >> 6) * NUP + (upper ? s - 13 : 13 - s)) * Lay<T>::SLICE) +
+          (o & 63);
 #pragma unroll
-        for (int r = 0; r < NDOF; ++r) {
-          T acc = 0;
+      for (int q0 = 0; q0 < Lay<T>::NQ; q0 += SMALL_CHUNK) {
+        VT vq[SMALL_CHUNK];
 #pragma unroll
-          for (int c = 0; c < NDOF; ++c) acc += Ab[Lay<T>::off(r * NDOF + c, ll)] * xv[c];
-          pr[r] = acc;
-        }
-      } else {
-        const T* Ab = A + ((int64_t)(m >> 6) * NUP + (13 - s)) * Lay<T>::SLICE;
-        const int ll = m & 63;
+        for (int q = 0; q < SMALL_CHUNK; ++q)
+          if (q0 + q < Lay<T>::NQ) vq[q] = Ab[(q0 + q) * TILE];
+        // one branch per chunk: the stored block, or its transpose
+        auto add = [&](auto up) {
 #pragma unroll
-        for (int r = 0; r < NDOF; ++r) {
-          T acc = 0;
+          for (int q = 0; q < SMALL_CHUNK; ++q) {
+            T av[V];
+            __builtin_memcpy(av, &vq[q], sizeof(VT));
 #pragma unroll
-          for (int c = 0; c < NDOF; ++c) acc += Ab[Lay<T>::off(c * NDOF + r, ll)] * xv[c];
-          pr[r] = acc;
-        }
+            for (int v = 0; v < V; ++v) {
+              const int e = (q0 + q) * V + v;
+              if (e < NBLK) {
+                const int r = e / NDOF, c = e % NDOF;
+                pr[up.value ? r : c] += av[v] * xv[up.value ? c : r];
+              }
+            }
+          }
+        };
+        if (upper) add(std::true_type{}); else add(std::false_type{});
       }
     }
   }
-  if (tid < SMALL_ROWS * NSTEN)
+  if (s < NSTEN)
 #pragma unroll
     for (int r = 0; r < NDOF; ++r) part[ln][s][r] = pr[r];
   __syncthreads();
-  const int ln2 = tid / NDOF, r2 = tid % NDOF;
-  const int n2 = bid * SMALL_ROWS + ln2;
-  const bool own = tid < SMALL_ROWS * NDOF && n2 < g.N;
   if (own) {
-    T acc = b[(int64_t)r2 * g.Npad + n2];
+    T acc = b2;
+#pragma unroll
     for (int ss = 0; ss < NSTEN; ++ss) acc -= part[ln2][ss][r2];
-    res[ln2][r2] = acc;
+    if (PBJ)
+      res[ln2][r2] = acc;
+    else
+      out[(int64_t)r2 * g.Npad + n2] = acc;
   }
+  if (!PBJ) return;
   __syncthreads();
   if (own) {
-    if (!PBJ) {
-      out[(int64_t)r2 * g.Npad + n2] = res[ln2][r2];
-    } else {
-      const T* Db = Dinv + (int64_t)(n2 >> 6) * Lay<T>::SLICE;
-      T acc = 0;
+    T acc = 0;
 #pragma unroll
-      for (int c = 0; c < NDOF; ++c) acc += Db[Lay<T>::off(r2 * NDOF + c, n2 & 63)] * res[ln2][c];
-      out[(int64_t)r2 * g.Npad + n2] = x[(int64_t)r2 * g.Npad + n2] + omega * acc;
-    }
+    for (int c = 0; c < NDOF; ++c) acc += d2[c] * res[ln2][c];
+    out[(int64_t)r2 * g.Npad + n2] = x2 + omega * acc;
   }
 }
 template <typename T, bool PBJ>
-__global__ void __launch_bounds__(256) row_small_kernel(Grid g, const T* __restrict__ A, const T* __restrict__ Dinv,
-                                                        const T* __restrict__ x, const T* __restrict__ b,
-                                                        T* __restrict__ out, T omega) {
-  row_small_body<T, PBJ>(g, A, Dinv, x, b, out, omega, blockIdx.x);
+__global__ void __launch_bounds__(SMALL_THREADS) SMALL_OCC
+    row_small_kernel(Grid g, const T* __restrict__ A, const T* __restrict__ Dinv, const T* __restrict__ x,
+                     const T* __restrict__ b, T* __restrict__ out, T omega) {
+  row_small_body<T, PBJ>(g, A, Dinv, x, b, out, omega, blockIdx.x, gridDim.x);
 }
 
 template <typename T>
 void launch_row_small(const Grid& g, const T* A, const T* Dinv, const T* x, const T* b, T* out, T omega, bool pbj,
                       hipStream_t s) {
-  const int nb = (g.N + SMALL_ROWS - 1) / SMALL_ROWS;
+  const int nb = small_blocks(g);
   if (pbj)
-    row_small_kernel<T, true><<<nb, 256, 0, s>>>(g, A, Dinv, x, b, out, omega);
+    row_small_kernel<T, true><<<nb, SMALL_THREADS, 0, s>>>(g, A, Dinv, x, b, out, omega);
   else
-    row_small_kernel<T, false><<<nb, 256, 0, s>>>(g, A, Dinv, x, b, out, omega);
+    row_small_kernel<T, false><<<nb, SMALL_THREADS, 0, s>>>(g, A, Dinv, x, b, out, omega);
 }
 template void launch_row_small<float>(const Grid&, const float*, const float*, const float*, const float*, float*,
                                       float, bool, hipStream_t);
@@ -469,7 +518,7 @@ template <typename T>
 __global__ void __launch_bounds__(256) pbj_zero_batch(const BJob* __restrict__ jobs, int njobs) {
   int bid;
   const BJob& j = find_job(jobs, njobs, bid);
-  pbj_zero_body<T>(j.g, (const T*)j.D, (const T*)j.b, (T*)j.y, (T)j.omega, bid, j.nblk);
+  pbj_zero_body<T>(j.g, (const T*)j.D, j.packed, (const T*)j.b, (T*)j.y, (T)j.omega, bid, j.nblk);
 }
 template <typename T>
 __global__ void __launch_bounds__(256) defect_upper_split_batch(const BJob* __restrict__ jobs, int njobs) {
@@ -490,10 +539,11 @@ __global__ void __launch_bounds__(256) defect_lower_batch(const BJob* __restrict
   defect_lower_body<T>(j.g, (T*)j.y, (const T*)j.C, bid, j.nblk);
 }
 template <typename T, bool PBJ>
-__global__ void __launch_bounds__(256) row_small_batch(const BJob* __restrict__ jobs, int njobs) {
+__global__ void __launch_bounds__(SMALL_THREADS) SMALL_OCC row_small_batch(const BJob* __restrict__ jobs, int njobs) {
   int bid;
   const BJob& j = find_job(jobs, njobs, bid);
-  row_small_body<T, PBJ>(j.g, (const T*)j.A, (const T*)j.D, (const T*)j.x, (const T*)j.b, (T*)j.y, (T)j.omega, bid);
+  row_small_body<T, PBJ>(j.g, (const T*)j.A, (const T*)j.D, (const T*)j.x, (const T*)j.b, (T*)j.y, (T)j.omega, bid,
+                         j.nblk);
 }
 
 template <typename T>
@@ -503,8 +553,8 @@ void launch_bsr_batch(int op, const BJob* jobs, int njobs, int blocks, hipStream
     case BOP_DEFECT_SPLIT: defect_upper_split_batch<T><<<blocks, 256, 0, s>>>(jobs, njobs); break;
     case BOP_PBJ_LOWER: pbj_lower_batch<T><<<blocks, 256, 0, s>>>(jobs, njobs); break;
     case BOP_DEFECT_LOWER: defect_lower_batch<T><<<blocks, 256, 0, s>>>(jobs, njobs); break;
-    case BOP_ROW_SMALL_PBJ: row_small_batch<T, true><<<blocks, 256, 0, s>>>(jobs, njobs); break;
-    case BOP_ROW_SMALL_DEFECT: row_small_batch<T, false><<<blocks, 256, 0, s>>>(jobs, njobs); break;
+    case BOP_ROW_SMALL_PBJ: row_small_batch<T, true><<<blocks, SMALL_THREADS, 0, s>>>(jobs, njobs); break;
+    case BOP_ROW_SMALL_DEFECT: row_small_batch<T, false><<<blocks, SMALL_THREADS, 0, s>>>(jobs, njobs); break;
     default: break;
   }
 }
@@ -520,7 +570,7 @@ int bsr_job_blocks(int op, const Grid& g) {
     case BOP_DEFECT_LOWER: return row_grid(g, 0);
     case BOP_DEFECT_SPLIT: return split_grid(g);
     case BOP_ROW_SMALL_PBJ:
-    case BOP_ROW_SMALL_DEFECT: return (g.N + SMALL_ROWS - 1) / SMALL_ROWS;
+    case BOP_ROW_SMALL_DEFECT: return small_blocks(g);
     default: return 0;
   }
 }

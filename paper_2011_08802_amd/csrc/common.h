@@ -75,8 +75,12 @@ constexpr int TILE = 64;
 constexpr int NHP_PAD = (NHP + 7) / 8 * 8;
 constexpr int MAX_LEVELS = 8;
 constexpr int MAX_RESTART = 64;
-constexpr int SMALL_GRID_NODES = 10000;  // default size limit of the small-grid kernels
-constexpr int BATCH_SMALL_GRID_NODES = 0;  // its default for the problems of a batch
+// default size limit of the small-grid kernels: a V-cycle is faster with them
+// on levels of 35937 nodes (FP32 1051 -> 1045 us, FP64 2052 -> 2008, 15
+// unknowns per node 856 -> 760), slower on the next larger ones (71825 nodes,
+// FP64: 3942 -> 4101 us; 139425, FP32: 3914 -> 4055), whose blocks, read twice,
+// no longer come out of an L2; a batch gains as well (92.8 -> 87 ms)
+constexpr int SMALL_GRID_NODES = 40000;
 
 struct Grid {
   int nx, ny, nz;      // elements
@@ -147,6 +151,10 @@ constexpr int MF_G = 0, MF_S = 9, MF_EE = 15, MF_EK = 36, MF_KK = 72, MF_NK = 96
 // node meet in one addition, in the kernel or in the gather, so the sums do
 // not depend on epw.
 __host__ __device__ inline int mf_epw_of(int epw) { return (epw == 8 || epw == 16) ? epw : 32; }
+// default: one wavefront per workgroup where 8 NE lanes fill at most one
+// wavefront per SIMD, so that every CU streams its share (a solve on 8^3: 4.0
+// -> 3.5 ms, on 16^3 5.1 -> 4.7); beyond (20^3 ... 40^3) within 1 %
+inline int mf_default_epw(int64_t NE) { return NE <= 8 * 1024 ? 8 : 32; }
 __host__ __device__ inline int64_t mf_nw(const Grid& g) { return (int64_t)g.NEpad / 8; }
 __host__ __device__ inline int64_t mf_nr(const Grid& g) { return ((int64_t)g.ny * g.nz + 63) / 64 * 64; }
 __host__ __device__ inline int64_t mf_nf(const Grid& g) { return ((int64_t)g.nx * g.ny + 63) / 64 * 64; }
@@ -377,18 +385,22 @@ void launch_spmv(const Grid& g, const TA* A, const TX* x, TY* y, void* C, hipStr
 template <typename T>
 void launch_defect(const Grid& g, const T* A, const T* x, const T* b, T* r, void* C, hipStream_t s, int G = 0);
 template <typename T>
-void launch_pbj(const Grid& g, const T* A, const T* Dinv, const T* x, const T* b, T* xo, T omega,
-                bool zero_guess, void* C, hipStream_t s, int G = 0);
+void launch_pbj(const Grid& g, const T* A, const T* Dinv, const T* x, const T* b, T* xo, T omega, void* C,
+                hipStream_t s, int G = 0);
+// its sweep from a zero guess, xo = omega Dinv b (packed: Dinv in LaySym form)
+template <typename T>
+void launch_pbj_zero(const Grid& g, const T* Dinv, bool packed, const T* b, T* xo, T omega, hipStream_t s, int G = 0);
 // coarse-level variant (27 threads per row); out = b - A x, or the damped
 // point-block Jacobi update when pbj is set.  Used on levels with at most
 // small_grid_nodes nodes (default SMALL_GRID_NODES, a tuning key).
 template <typename T>
 void launch_row_small(const Grid& g, const T* A, const T* Dinv, const T* x, const T* b, T* out, T omega, bool pbj,
                       hipStream_t s);
-// transfers
+// transfers; with the coarse level's block inverses Dinv the restriction also
+// writes its first sweep from a zero guess, xc = omega Dinv bc
 template <typename T>
-void launch_restrict(const Grid& fine, const Grid& coarse, const T* rf, const uint16_t* cmask, T* bc,
-                     hipStream_t s);
+void launch_restrict(const Grid& fine, const Grid& coarse, const T* rf, const uint16_t* cmask, T* bc, const T* Dinv,
+                     T* xc, T omega, hipStream_t s);
 template <typename T>
 void launch_prolong_add(const Grid& fine, const Grid& coarse, const T* ec, const uint16_t* fmask, T* xf,
                         hipStream_t s);
@@ -473,17 +485,18 @@ struct BJob {
   Grid g;                  // the level (finest grid of a transfer)
   Grid g2;                 // coarse grid of a transfer
   const void* A;           // half-stencil operator, Gauss-point Hessians or dense coarse inverse
-  const void* D;           // block inverses
+  const void* D;           // block inverses (restriction: the coarse level's, null without its zero-guess sweep)
   const void* x;           // input vector
   const void* b;           // right-hand side; FP64 vector v at the preconditioner's ends
   void* y;                 // output vector
-  void* C;                 // scratch: transposed contributions or element outputs
+  void* C;                 // scratch: transposed contributions or element outputs; coarse x of a restriction
   const uint16_t* mask;    // constrained-dof masks of the output's level
   const DevCard* cd;       // material card (matrix-free element kernel)
   double omega;            // damping of the Jacobi sweeps
   int block0, nblk;
   int epw;                 // matrix-free gathers: elements per workgroup of the element launch
   int contact;             // matrix-free gathers: add the contact face outputs
+  int packed;              // zero-guess sweep: D holds packed upper triangles
 };
 // job of this workgroup in a batched launch; bid = its workgroup index within the job
 template <typename J>
@@ -591,6 +604,7 @@ template <typename T>
 void launch_bsr_batch(int op, const BJob* jobs, int njobs, int blocks, hipStream_t s);
 template <typename T>
 void launch_transfer_batch(int op, const BJob* jobs, int njobs, int blocks, hipStream_t s);
+int transfer_job_blocks(int op, const BJob& j);
 template <typename T>
 void launch_coarse_solve_batch(const BJob* jobs, int njobs, int blocks, hipStream_t s);
 template <typename T>

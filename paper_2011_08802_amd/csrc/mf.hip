@@ -369,6 +369,95 @@ __global__ void __launch_bounds__(256) mf_gather_kernel(Grid g, const T* __restr
   mf_gather_body<MODE, T, TX, TY>(g, E, Cf, epw, mask, x, b, Dinv, omega, y, blockIdx.x);
 }
 
+// The same for grids of at most a tile of 64 nodes per CU, where a thread per
+// node leaves most of the chip idle and walks its loads in turn: a workgroup
+// takes a tile, one wavefront per component, with the tile's block inverses
+// staged in LDS while the element outputs arrive.  Sums and rounding as above.
+// FP64 Jacobi update: 9^3 nodes 8.2 -> 5.6 us; above the limit every block
+// inverse passes through LDS for no gain (41^3 nodes: 16.4 us by node, 28.6
+// by tile; 65^3, FP32: 21 and 55).
+constexpr int GT = 9 * TILE;
+template <int MODE, typename T, typename TX, typename TY>
+__global__ void __launch_bounds__(GT) mf_gather_tile_kernel(Grid g, const T* __restrict__ E, const T* __restrict__ Cf,
+                                                            int epw, const uint16_t* __restrict__ mask,
+                                                            const TX* __restrict__ x, const T* __restrict__ b,
+                                                            const T* __restrict__ Dinv, T omega, TY* __restrict__ y) {
+  using LD = std::conditional_t<sizeof(T) == 4, LaySym<T>, Lay<T>>;
+  using VT = typename Vec16<T>::type;
+  constexpr int ND = MODE == 2 && MF_AVAILABLE ? LD::NE / LD::V * TILE : 1, ROUNDS = (ND + GT - 1) / GT;
+  __shared__ VT sd[ND];
+  __shared__ T sr[9][TILE];
+  const int t = blockIdx.x, l = threadIdx.x & 63, c = threadIdx.x >> 6;
+  const int n = t * TILE + l;
+  VT dv[ROUNDS];
+  if constexpr (MODE == 2) {
+    const VT* Db = reinterpret_cast<const VT*>(Dinv + (int64_t)t * LD::SLICE);
+#pragma unroll
+    for (int u = 0; u < ROUNDS; ++u) {
+      const int i = u * GT + threadIdx.x;
+      if (i < ND) dv[u] = Db[i];
+    }
+  }
+  const T* __restrict__ W = E + mf_w_offset(g);
+  const T* __restrict__ Rr = E + mf_r_offset(g);
+  T xv = 0, r = 0;
+  if (n < g.N) {
+    xv = (T)x[(int64_t)c * g.Npad + n];
+    const T bv = MODE == 0 ? (T)0 : b[(int64_t)c * g.Npad + n];
+    const unsigned mb = mask ? mask[n] : 0u;
+    const int i = n % g.nnx, j = (n / g.nnx) % g.nny, k = n / (g.nnx * g.nny);
+    T a[4], w[4];
+    bool in[4];
+#pragma unroll
+    for (int q = 3; q >= 0; --q) {
+      const int ey = j - (q & 1), ez = k - (q >> 1);
+      in[q] = ey >= 0 && ey < g.ny && ez >= 0 && ez < g.nz;
+      const int64_t row = in[q] ? ey + (int64_t)g.ny * ez : 0;
+      const int64_t e = i + g.nx * row;
+      a[q] = *(i < g.nx ? E + (int64_t)(9 * q + c) * g.NEpad + e : Rr + (int64_t)(9 * q + c) * mf_nr(g) + row);
+      w[q] = 0;
+      if (i > 0 && i < g.nx && (e & (epw - 1)) == 0) w[q] = W[(int64_t)(9 * q + c) * mf_nw(g) + e / epw - 1];
+    }
+    T s = 0;
+#pragma unroll
+    for (int q = 3; q >= 0; --q)
+      if (in[q]) s += a[q] + w[q];
+    if (Cf && c < 3 && k == g.nz) {
+      const int64_t nf = mf_nf(g);
+#pragma unroll
+      for (int q = 3; q >= 0; --q) {
+        const int fi = i - (q & 1), fj = j - (q >> 1);
+        if (fi < 0 || fi >= g.nx || fj < 0 || fj >= g.ny) continue;
+        s += Cf[(3 * q + c) * nf + fi + (int64_t)g.nx * fj];
+      }
+    }
+    const T kx = ((mb >> c) & 1) ? xv : s;
+    r = (MODE == 0) ? kx : bv - kx;
+  }
+  if constexpr (MODE == 2) {
+    sr[c][l] = r;
+#pragma unroll
+    for (int u = 0; u < ROUNDS; ++u) {
+      const int i = u * GT + threadIdx.x;
+      if (i < ND) sd[i] = dv[u];
+    }
+    __syncthreads();
+    const T* D = reinterpret_cast<const T*>(sd);
+    T acc = 0;
+#pragma unroll
+    for (int d = 0; d < 9; ++d) {
+      int o;
+      if constexpr (sizeof(T) == 4)
+        o = (int)LD::off(c <= d ? c * NDOF - c * (c - 1) / 2 + (d - c) : d * NDOF - d * (d - 1) / 2 + (c - d), l);
+      else
+        o = (int)LD::off(9 * c + d, l);
+      acc += D[o] * sr[d][l];
+    }
+    r = n < g.N ? xv + omega * acc : (T)0;
+  }
+  y[(int64_t)c * g.Npad + n] = (TY)r;
+}
+
 size_t mf_hessian_values(const Grid& g) { return MF_AVAILABLE ? (size_t)MF_NK * 8 * g.NEpad : 0; }
 
 // ---- diagonal blocks from the Gauss-point tangents ----------------------------
@@ -585,12 +674,17 @@ void launch_mf_element(const Grid& g, const TD* D, const TX* x, const uint16_t* 
     mf_element_kernel<TD, TX, T, MINB, PF, false><<<blocks, wg, 0, s>>>(g, D, x, mask, cd, E);
 }
 
+constexpr int MF_GATHER_TILE_NODES = 256 * TILE;  // a tile per CU (measured at mf_gather_tile_kernel)
 template <int MODE, typename T, typename TX, typename TY>
 void launch_mf_gather(const Grid& g, const T* E, bool contact, int elems_per_wg, const uint16_t* mask, const TX* x,
                       const T* b, const T* Dinv, T omega, TY* y, hipStream_t s) {
   if constexpr (!MF_AVAILABLE) return;
-  mf_gather_kernel<MODE, T, TX, TY><<<(g.Npad + 255) / 256, 256, 0, s>>>(
-      g, E, contact ? E + mf_cf_offset(g) : nullptr, mf_epw_of(elems_per_wg), mask, x, b, Dinv, omega, y);
+  const T* Cf = contact ? E + mf_cf_offset(g) : nullptr;
+  const int epw = mf_epw_of(elems_per_wg);
+  if (g.Npad <= MF_GATHER_TILE_NODES)
+    mf_gather_tile_kernel<MODE, T, TX, TY><<<g.ntiles, GT, 0, s>>>(g, E, Cf, epw, mask, x, b, Dinv, omega, y);
+  else
+    mf_gather_kernel<MODE, T, TX, TY><<<(g.Npad + 255) / 256, 256, 0, s>>>(g, E, Cf, epw, mask, x, b, Dinv, omega, y);
 }
 
 template void launch_mf_element<float, float, float>(const Grid&, const float*, const float*, const uint16_t*,

@@ -18,8 +18,10 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
   return r;  // valid in thread 0
 }
 
+// 1024 values per block, fewer on short vectors: a row per thread until there
+// is a block for every CU (a vector of 6561 values: 7 blocks leave the chip idle)
 int red_blocks(int64_t n) {
-  const int64_t b = (n + 1023) / 1024;
+  const int64_t b = std::max<int64_t>((n + 1023) / 1024, std::min<int64_t>((n + RB - 1) / RB, 256));
   return (int)std::max<int64_t>(1, std::min<int64_t>(b, MAX_RED_BLOCKS));
 }
 
@@ -30,13 +32,13 @@ constexpr int MD_G = 8;
 constexpr int MD_U = 4;
 __device__ __forceinline__ void multidot_body(int64_t n, const double* __restrict__ V, int64_t ldv, int k,
                                               const double* __restrict__ w, double* __restrict__ part, int bid,
-                                              int nblk) {
+                                              int nblk, int first = 0, int step = MD_G) {
   __shared__ double sh[MD_G][RB / 64];
   const int64_t chunk = (n + nblk - 1) / nblk;
   const int64_t lo = (int64_t)bid * chunk;
   const int64_t hi = std::min<int64_t>(n, lo + chunk);
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  for (int j0 = 0; j0 < k; j0 += MD_G) {
+  for (int j0 = first; j0 < k; j0 += step) {
     const int g_n = std::min(MD_G, k - j0);  // uniform
     double s[MD_G];
 #pragma unroll
@@ -83,11 +85,14 @@ __device__ __forceinline__ void multidot_body(int64_t n, const double* __restric
 }
 __global__ void __launch_bounds__(RB) multidot_kernel(int64_t n, const double* __restrict__ V, int64_t ldv, int k,
                                                       const double* __restrict__ w, double* __restrict__ part) {
-  multidot_body(n, V, ldv, k, w, part, blockIdx.x, gridDim.x);
+  multidot_body(n, V, ldv, k, w, part, blockIdx.x, gridDim.x, blockIdx.y * MD_G, gridDim.y * MD_G);
 }
 
+// On short vectors the groups go to blocks of their own: a block per CU or
+// fewer would take them one after the other, a memory round trip each.
 void launch_multidot(int64_t n, const double* V, int64_t ldv, int k, const double* w, double* part, hipStream_t s) {
-  multidot_kernel<<<red_blocks(n), RB, 0, s>>>(n, V, ldv, k, w, part);
+  const int nb = red_blocks(n);
+  multidot_kernel<<<dim3(nb, nb <= 256 ? (k + MD_G - 1) / MD_G : 1), RB, 0, s>>>(n, V, ldv, k, w, part);
 }
 
 // out[j] (+)= sum_b part[j * nblk + b]
@@ -243,7 +248,7 @@ void launch_multiaxpy_dot(int64_t n, const double* V, int64_t ldv, int k, const 
                           hipStream_t s) {
   if (launch_multiaxpy_reg<true>(n, V, ldv, k, h, w, part, s)) return;
   launch_multiaxpy(n, V, ldv, k, h, w, nullptr, s);
-  multidot_kernel<<<red_blocks(n), RB, 0, s>>>(n, V, ldv, k, w, part);
+  launch_multidot(n, V, ldv, k, w, part, s);
 }
 
 __global__ void __launch_bounds__(RB) scale_kernel(int64_t n, const double* __restrict__ w, const double* beta,

@@ -72,3 +72,30 @@ def test_galerkin_level1_from_gauss_points(nx, ny, nz, kind):
     scale = z.reshape(-1, 9).abs().amax(0) + ya.reshape(-1, 9).abs().amax(0)
     assert float((err.abs().amax(0) / scale).max()) < 1e-12, (err.abs().amax(0) / scale)
     gp.close()
+
+
+@pytest.mark.parametrize("precision,tol", [("fp64", 1e-12), ("mixed", 1e-4)])
+@pytest.mark.parametrize("nx,ny,nz,levels", [(4, 4, 4, 2), (6, 10, 2, 2), (16, 4, 12, 3), (24, 24, 24, 3), (28, 24, 24, 3)])
+def test_vcycle_of_both_level_kernel_families(nx, ny, nz, levels, precision, tol):
+    """A V-cycle with the small-grid row kernel on every level (row counts that
+    leave a remainder of its 8 rows and of a tile, 125 to 18125 rows), and with
+    the two-pass kernels: the same 27 x 9 products per entry, summed in another
+    order, over 9 sweeps whose factors are below 3 (FP64 243 * 1.1e-16 * 9 * 3;
+    FP32 the square root of the terms).  The matrix-free finest level is on
+    either side of the node gather's limit of 256 tiles."""
+    h = 1.0 / max(nx, ny, nz)
+    p = synth.Problem(nx, ny, nz, lx=nx * h, ly=ny * h, lz=nz * h, n_levels=levels, patch=2, depth_increment=0.01)
+    U, En = seeded_state(p, 1e-3)
+    gp = gpu_problem(p, U, En, precision)
+    x = _dev(np.random.default_rng(5).standard_normal(9 * (nx + 1) * (ny + 1) * (nz + 1)))
+    for mf in (1, 0):
+        gp.set_tuning("matrix_free", 0, mf)
+        gp.newton_system(p.depth_increment)
+        gp.set_tuning("small_grid_nodes", 0, 40000)
+        z = gp.precondition(x)
+        gp.set_tuning("small_grid_nodes", 0, 0)
+        z2 = gp.precondition(x)
+        assert torch.isfinite(z).all()
+        err = float((z - z2).norm() / z2.norm())
+        assert err < tol, (mf, err)
+    gp.close()
