@@ -2049,6 +2049,7 @@ int batch_fgmres(mvpf_batch* b, mvpf_solve_stats* st) {
       outer.add(BOP_MF_OUTER_GATHER, og, bblocks);
       // classical Gram-Schmidt twice, norm, Hessenberg columns
       std::vector<KJob> md, rd1, ax1, rd2, ax2, rdn, cp;
+      int kmax = 0;
       for (int i = 0; i < nprob; ++i) {
         auto& k = K[i];
         if (k.phase != KP::ARNOLDI) continue;
@@ -2059,6 +2060,7 @@ int batch_fgmres(mvpf_batch* b, mvpf_solve_stats* st) {
         j.w = p->V + (int64_t)(k.j + 1) * k.n;
         j.part = p->red;
         j.k = k.j + 1;
+        kmax = std::max(kmax, j.k);
         j.nb = k.nb;
         md.push_back(j);
         KJob r = j;
@@ -2084,8 +2086,7 @@ int batch_fgmres(mvpf_batch* b, mvpf_solve_stats* st) {
       post.used = pre.used;
       post.add(KOP_MULTIDOT, md, kblocks);
       post.add(KOP_REDUCE, rd1, kblocks);
-      post.add(KOP_MULTIAXPY, ax1, kblocks);
-      post.add(KOP_MULTIDOT, md, kblocks);
+      post.add(KOP_MULTIAXPY_DOT, ax1, kblocks);
       post.add(KOP_REDUCE, rd2, kblocks);
       post.add(KOP_MULTIAXPY, ax2, kblocks);
       post.add(KOP_REDUCE, rdn, kblocks);
@@ -2098,7 +2099,7 @@ int batch_fgmres(mvpf_batch* b, mvpf_solve_stats* st) {
       BCHK(hipMemcpyAsync(b->jobs_dev + b->fin_off, b->gjobs_host + nprob, sizeof(BJob) * nprob,
                           hipMemcpyHostToDevice, s));
       for (size_t q = 0; q < pre.op.size(); ++q)
-        launch_krylov_batch(pre.op[q], b->kjobs_dev + pre.first[q], pre.count[q], pre.blocks[q], s);
+        launch_krylov_batch(pre.op[q], b->kjobs_dev + pre.first[q], pre.count[q], pre.blocks[q], 0, s);
       BCHK(hipGraphLaunch(b->exec, s));
       // element launches, then the per-problem contact and product launches, then the gather
       size_t q = 0;
@@ -2110,7 +2111,7 @@ int batch_fgmres(mvpf_batch* b, mvpf_solve_stats* st) {
         launch_batch<T, TZ>(outer.op[q], b->ojobs_dev + outer.first[q], outer.count[q], outer.blocks[q], s,
                             outer.threads[q]);
       for (size_t q = 0; q < post.op.size(); ++q)
-        launch_krylov_batch(post.op[q], b->kjobs_dev + post.first[q], post.count[q], post.blocks[q], s);
+        launch_krylov_batch(post.op[q], b->kjobs_dev + post.first[q], post.count[q], post.blocks[q], kmax, s);
       BCHK(hipGetLastError());
       BCHK(hipMemcpyAsync(b->bcol_host, b->bcol_dev, sizeof(double) * HCOL * nprob, hipMemcpyDeviceToHost, s));
     }

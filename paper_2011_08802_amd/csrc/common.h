@@ -548,6 +548,7 @@ enum KrylovOp {
   KOP_MULTIDOT,   // part[j][blk] = V_j . w over the block's chunk, j < k
   KOP_REDUCE,     // out[j] (+)= sum_b part[j][b], j < k
   KOP_MULTIAXPY,  // w -= sum_j h_j V_j (norm partials of w into part)
+  KOP_MULTIAXPY_DOT,  // the same, and part[j][blk] = V_j . w of the new w, j < k
   KOP_SCALE,      // w = a w
   KOP_COPY,       // out[0..k) = src[0..k)
 };
@@ -588,7 +589,7 @@ void launch_assembly_batch(int op, int pade, const AJob* jobs, int njobs, int bl
 void launch_mf_diag_batch(int op, const AJob* jobs, int njobs, int blocks, hipStream_t s);
 int mf_diag_blocks(const Chunk& ck);
 int mf_diag_gather_blocks(const Chunk& ck);
-void launch_krylov_batch(int op, const KJob* jobs, int njobs, int blocks, hipStream_t s);
+void launch_krylov_batch(int op, const KJob* jobs, int njobs, int blocks, int kmax, hipStream_t s);
 template <typename TZ>
 void launch_mf_outer_batch(int op, const BJob* jobs, int njobs, int blocks, hipStream_t s, int threads = 256);
 // workgroups one job of op needs (threads: workgroup size of the

@@ -151,15 +151,14 @@ __global__ void __launch_bounds__(RB) multiaxpy_kernel(int64_t n, const double* 
 // and every sum its terms, in the order of multiaxpy_body and multidot_body,
 // so the results are bitwise theirs.
 template <int KB, int KD>
-__global__ void __launch_bounds__(RB) multiaxpy_reg_kernel(int64_t n, const double* __restrict__ V, int64_t ldv,
-                                                           int k, const double* __restrict__ h,
-                                                           double* __restrict__ w, double* __restrict__ part) {
+__device__ __forceinline__ void multiaxpy_reg_body(int64_t n, const double* __restrict__ V, int64_t ldv, int k,
+                                                   const double* __restrict__ h, double* __restrict__ w,
+                                                   double* __restrict__ part, int bid, int nblk) {
   constexpr int NA = KD > 0 ? KD : 1;
   __shared__ double sh[NA][RB / 64];
   __shared__ double hs[KB];
   for (int j = threadIdx.x; j < k; j += RB) hs[j] = h[j];
   __syncthreads();
-  const int bid = blockIdx.x, nblk = gridDim.x;
   const int64_t chunk = (n + nblk - 1) / nblk;
   const int64_t lo = (int64_t)bid * chunk;
   const int64_t hi = std::min<int64_t>(n, lo + chunk);
@@ -215,6 +214,13 @@ __global__ void __launch_bounds__(RB) multiaxpy_reg_kernel(int64_t n, const doub
     const double nrm = block_sum(acc[0], &sh[0][0]);
     if (threadIdx.x == 0) part[bid] = nrm;
   }
+}
+
+template <int KB, int KD>
+__global__ void __launch_bounds__(RB) multiaxpy_reg_kernel(int64_t n, const double* __restrict__ V, int64_t ldv,
+                                                           int k, const double* __restrict__ h,
+                                                           double* __restrict__ w, double* __restrict__ part) {
+  multiaxpy_reg_body<KB, KD>(n, V, ldv, k, h, w, part, blockIdx.x, gridDim.x);
 }
 
 // register tiers k <= 8, 16, 24, 32 (false above), the projections on all k
@@ -627,11 +633,33 @@ __global__ void __launch_bounds__(RB) krylov_batch_kernel(int op, const KJob* __
     default: break;
   }
 }
+// the updates in the single problems' register tiers (every job's k <= KB)
+template <int KB, int KD>
+__global__ void __launch_bounds__(RB) multiaxpy_reg_batch(const KJob* __restrict__ jobs, int njobs) {
+  int bid;
+  const KJob& j = find_job(jobs, njobs, bid);
+  multiaxpy_reg_body<KB, KD>(j.n, j.V, j.n, j.k, j.h, j.w, KD > 0 || j.flag ? j.part : nullptr, bid, j.nblk);
+}
+template <bool DOT>
+static bool launch_multiaxpy_reg_batch(const KJob* jobs, int njobs, int blocks, int kmax, hipStream_t s) {
+  if (kmax <= 8)
+    multiaxpy_reg_batch<8, DOT ? 8 : 0><<<blocks, RB, 0, s>>>(jobs, njobs);
+  else if (kmax <= 16)
+    multiaxpy_reg_batch<16, DOT ? 16 : 0><<<blocks, RB, 0, s>>>(jobs, njobs);
+  else if (kmax <= 24)
+    multiaxpy_reg_batch<24, DOT ? 24 : 0><<<blocks, RB, 0, s>>>(jobs, njobs);
+  else if (kmax <= 32)
+    multiaxpy_reg_batch<32, DOT ? 32 : 0><<<blocks, RB, 0, s>>>(jobs, njobs);
+  else
+    return false;
+  return true;
+}
 
 int krylov_job_blocks(int op, const KJob& j) {
   switch (op) {
     case KOP_MULTIDOT:
-    case KOP_MULTIAXPY: return red_blocks(j.n);
+    case KOP_MULTIAXPY:
+    case KOP_MULTIAXPY_DOT: return red_blocks(j.n);
     case KOP_REDUCE: return j.k;
     case KOP_SCALE: return (int)std::min<int64_t>(1024, (j.n + RB - 1) / RB);
     case KOP_COPY: return 1;
@@ -639,8 +667,20 @@ int krylov_job_blocks(int op, const KJob& j) {
   }
 }
 
-void launch_krylov_batch(int op, const KJob* jobs, int njobs, int blocks, hipStream_t s) {
-  if (njobs > 0 && blocks > 0) krylov_batch_kernel<<<blocks, RB, 0, s>>>(op, jobs, njobs);
+// kmax: the largest k of the jobs.  A batch of ten up to 48^3, Gram-Schmidt
+// and norms of a solve: 11.6 -> 7.5 ms against one basis entry in flight per
+// thread and separate projections.
+void launch_krylov_batch(int op, const KJob* jobs, int njobs, int blocks, int kmax, hipStream_t s) {
+  if (njobs <= 0 || blocks <= 0) return;
+  if (op == KOP_MULTIAXPY_DOT) {
+    if (launch_multiaxpy_reg_batch<true>(jobs, njobs, blocks, kmax, s)) return;
+    // these jobs carry no flag: the update without norm partials, then the projections
+    krylov_batch_kernel<<<blocks, RB, 0, s>>>(KOP_MULTIAXPY, jobs, njobs);
+    krylov_batch_kernel<<<blocks, RB, 0, s>>>(KOP_MULTIDOT, jobs, njobs);
+    return;
+  }
+  if (op == KOP_MULTIAXPY && launch_multiaxpy_reg_batch<false>(jobs, njobs, blocks, kmax, s)) return;
+  krylov_batch_kernel<<<blocks, RB, 0, s>>>(op, jobs, njobs);
 }
 
 }  // namespace mvpf
