@@ -8,7 +8,7 @@
 //      same into the matrix-free layout;
 //   3. element_matrix: element blocks for the 36 node pairs a <= b, with the
 //      Gauss-point Hessians shared through LDS;
-//   4. jacobian_gather: one thread per (node row, stored stencil block) sums
+//   4. jacobian_gather: a workgroup per (64 node rows, stored stencil block) sums
 //      the <= 8 element blocks of the elements containing both nodes and
 //      writes the 9x9 block into the tiled half-stencil layout.
 // Summation order is fixed, so results are bitwise reproducible.
@@ -483,9 +483,19 @@ void launch_element_matrices(const Grid& g, const Chunk& ck, const double* qp, c
 }
 
 // Stored block (n, n + off(13 + u)) = sum over the <= 8 elements containing
-// both nodes of their element blocks, in a fixed order (bitwise reproducible).
-// One wavefront per (tile, u): 64 consecutive rows, coalesced element reads
-// and coalesced tiled writes.
+// both nodes of their element blocks, in a fixed order (bitwise reproducible);
+// the second node never precedes the first, nor does its corner, so every
+// element block is read as stored.
+// Bound by reading the element blocks once and writing the rows.  A workgroup
+// takes a (tile, u): coalesced element reads of 64 consecutive rows, each
+// wavefront JG_E block entries, written as 16-byte words.  (One wavefront for
+// the whole block, three rows of it at a time, is a chain of up to 24 rounds
+// of loads.)  33^3 nodes: 470 -> 207 us (1.25 GB, 6 TB/s), 17^3 204 -> 27,
+// 5^3 162 -> below 16; 15 unknowns per node, 10648 nodes: 1084 -> 286.
+constexpr int JG_E = 12;  // whole 16-byte words of either type
+constexpr int JG_CHUNKS = Lay<float>::NE / JG_E;
+constexpr int JG_WAVES = JG_CHUNKS <= 16 ? JG_CHUNKS : (JG_CHUNKS + 1) / 2;
+static_assert(Lay<float>::NE % JG_E == 0 && JG_E % 4 == 0 && JG_WAVES <= 16);
 __device__ __forceinline__ void jacobian_gather_body(const Grid& g, const Chunk& ck, const double* __restrict__ E,
                                                      double* __restrict__ A64, float* __restrict__ A32,
                                                      double* __restrict__ diag64, int nblocks, int bid, int nblk) {
@@ -493,60 +503,52 @@ __device__ __forceinline__ void jacobian_gather_body(const Grid& g, const Chunk&
   if (L >= nblocks) return;
   const int t = ck.n0 / TILE + L / NUP, u = L % NUP;
   const int sten = 13 + u;
-  const int l = threadIdx.x;
+  const int l = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = t * TILE + l;
   if (n < ck.n0 || n >= ck.n1) return;  // rows of other slabs (no barriers below)
   const int dx = sten % 3 - 1, dy = (sten / 3) % 3 - 1, dz = sten / 9 - 1;
   const bool inside = n < g.N;
   const int i = n % g.nnx, j = (n / g.nnx) % g.nny, k = n / (g.nnx * g.nny);
-  const int64_t base64 = (int64_t)(t * NUP + u) * Lay<double>::SLICE;
-  const int64_t base32 = (int64_t)(t * NUP + u) * Lay<float>::SLICE;
-  const int64_t db = (int64_t)t * Lay<double>::SLICE;
-  // chunks of three block rows keep 3 NDOF accumulators live
-  for (int r0 = 0; r0 < NDOF; r0 += 3) {
-    double K[3 * NDOF];
+  const int64_t es = ck.NEcpad;
+  for (int ch = w; ch < JG_CHUNKS; ch += JG_WAVES) {
+    const int q0 = ch * JG_E;
+    double K[JG_E];
 #pragma unroll
-    for (int q = 0; q < 3 * NDOF; ++q) K[q] = 0.0;
-    if (inside) {
-      for (int a = 0; a < 8; ++a) {
-        const int ax = a & 1, ay = (a >> 1) & 1, az = (a >> 2) & 1;
-        const int bx = ax + dx, by = ay + dy, bz = az + dz;
-        if (bx < 0 || bx > 1 || by < 0 || by > 1 || bz < 0 || bz > 1) continue;  // wave-uniform
-        const int ex = i - ax, ey = j - ay, ez = k - az;
-        if (ex < 0 || ex >= g.nx || ey < 0 || ey >= g.ny || ez < 0 || ez >= g.nz) continue;
-        const int b = bx + 2 * by + 4 * bz;
-        const int64_t e = ex + (int64_t)g.nx * (ey + (int64_t)g.ny * ez) - ck.e0;  // local, in [0, NEc)
-        const int64_t es = ck.NEcpad;
-        if (a <= b) {
-          const double* src = E + (int64_t)pair_index(a, b) * NBLK * es + e;
+    for (int q = 0; q < JG_E; ++q) K[q] = 0.0;
+    for (int a = 0; a < 8; ++a) {
+      const int ax = a & 1, ay = (a >> 1) & 1, az = (a >> 2) & 1;
+      const int bx = ax + dx, by = ay + dy, bz = az + dz;
+      if (bx < 0 || bx > 1 || by < 0 || by > 1 || bz < 0 || bz > 1) continue;  // wave-uniform
+      const int ex = i - ax, ey = j - ay, ez = k - az;
+      if (!inside || ex < 0 || ex >= g.nx || ey < 0 || ey >= g.ny || ez < 0 || ez >= g.nz) continue;
+      const int b = bx + 2 * by + 4 * bz;
+      const int64_t e = ex + (int64_t)g.nx * (ey + (int64_t)g.ny * ez) - ck.e0;  // local, in [0, NEc)
+      const double* src = E + ((int64_t)pair_index(a, b) * NBLK + q0) * es + e;
 #pragma unroll
-          for (int q = 0; q < 3 * NDOF; ++q) K[q] += src[(int64_t)(NDOF * r0 + q) * es];
-        } else {
-          const double* src = E + (int64_t)pair_index(b, a) * NBLK * es + e;
-#pragma unroll
-          for (int rr = 0; rr < 3; ++rr)
-#pragma unroll
-            for (int c = 0; c < NDOF; ++c) K[NDOF * rr + c] += src[(int64_t)(NDOF * c + r0 + rr) * es];
-        }
-      }
+      for (int q = 0; q < JG_E; ++q)
+        if (q0 + q < NBLK) K[q] += src[q * es];
     }
-    if (A64) {
+    auto put64 = [&](double* D) {
 #pragma unroll
-      for (int q = 0; q < 3 * NDOF; ++q) A64[base64 + Lay<double>::off(NDOF * r0 + q, l)] = K[q];
-    }
+      for (int q = 0; q < JG_E; q += 2)
+        if (q0 + q < Lay<double>::NE) *reinterpret_cast<double2*>(D + Lay<double>::off(q0 + q, l)) = double2{K[q], K[q + 1]};
+    };
+    if (A64) put64(A64 + (int64_t)(t * NUP + u) * Lay<double>::SLICE);
+    if (u == 0 && diag64) put64(diag64 + (int64_t)t * Lay<double>::SLICE);
     if (A32) {
+      float* D = A32 + (int64_t)(t * NUP + u) * Lay<float>::SLICE;
 #pragma unroll
-      for (int q = 0; q < 3 * NDOF; ++q) A32[base32 + Lay<float>::off(NDOF * r0 + q, l)] = (float)K[q];
-    }
-    if (u == 0 && diag64) {
-#pragma unroll
-      for (int q = 0; q < 3 * NDOF; ++q) diag64[db + Lay<double>::off(NDOF * r0 + q, l)] = K[q];
+      for (int q = 0; q < JG_E; q += 4)
+        *reinterpret_cast<float4*>(D + Lay<float>::off(q0 + q, l)) =
+            float4{(float)K[q], (float)K[q + 1], (float)K[q + 2], (float)K[q + 3]};
     }
   }
 }
-__global__ void __launch_bounds__(64) jacobian_gather_kernel(Grid g, Chunk ck, const double* __restrict__ E,
-                                                             double* __restrict__ A64, float* __restrict__ A32,
-                                                             double* __restrict__ diag64, int nblocks) {
+__global__ void __launch_bounds__(64 * JG_WAVES) jacobian_gather_kernel(Grid g, Chunk ck, const double* __restrict__ E,
+                                                                        double* __restrict__ A64,
+                                                                        float* __restrict__ A32,
+                                                                        double* __restrict__ diag64, int nblocks) {
   jacobian_gather_body(g, ck, E, A64, A32, diag64, nblocks, blockIdx.x, gridDim.x);
 }
 
@@ -555,7 +557,7 @@ void launch_jacobian_gather(const Grid& g, const Chunk& ck, const double* elem, 
   const int t0 = ck.n0 / TILE, t1 = (ck.n1 + TILE - 1) / TILE;
   const int nblocks = (t1 - t0) * NUP;
   const int nb_pad = (nblocks + 7) / 8 * 8;
-  jacobian_gather_kernel<<<nb_pad, TILE, 0, s>>>(g, ck, elem, A64, A32, diag64, nblocks);
+  jacobian_gather_kernel<<<nb_pad, 64 * JG_WAVES, 0, s>>>(g, ck, elem, A64, A32, diag64, nblocks);
 }
 
 // Symmetric elimination on the stored blocks (nup = NUP; nup = 1: the diagonal
@@ -783,7 +785,7 @@ __global__ void __launch_bounds__(EM_WAVES * 64, EM_MINB) element_matrix_batch(c
   const AJob& j = find_job(jobs, njobs, bid);
   element_matrix_body(j.g, j.ck, j.qp, j.cd, j.elem, bid, j.nblk);
 }
-__global__ void __launch_bounds__(64) jacobian_gather_batch(const AJob* __restrict__ jobs, int njobs) {
+__global__ void __launch_bounds__(64 * JG_WAVES) jacobian_gather_batch(const AJob* __restrict__ jobs, int njobs) {
   int bid;
   const AJob& j = find_job(jobs, njobs, bid);
   jacobian_gather_body(j.g, j.ck, j.elem, j.A64, j.A32, j.diag64, j.nblocks, bid, j.nblk);
@@ -867,7 +869,7 @@ void launch_assembly_batch(int op, int pade, const AJob* jobs, int njobs, int bl
     case AOP_RESIDUAL: run_card<ResidualBatch>(order, mixing, jobs, njobs, blocks, s); break;
     case AOP_RESIDUAL_NODES: residual_nodes_batch<<<blocks, 256, 0, s>>>(jobs, njobs); break;
     case AOP_ELEMENT: element_matrix_batch<<<blocks, EM_WAVES * 64, 0, s>>>(jobs, njobs); break;
-    case AOP_GATHER: jacobian_gather_batch<<<blocks, TILE, 0, s>>>(jobs, njobs); break;
+    case AOP_GATHER: jacobian_gather_batch<<<blocks, 64 * JG_WAVES, 0, s>>>(jobs, njobs); break;
     case AOP_DIRICHLET: apply_dirichlet_batch<<<blocks, TILE, 0, s>>>(jobs, njobs); break;
     case AOP_BLOCK_INVERSE: block_inverse_batch<<<blocks, BI_THREADS, 0, s>>>(jobs, njobs); break;
     case AOP_MF_DIAG:
