@@ -712,25 +712,30 @@ int dense_invert_pivoted(int n, const double* a, double* inv, double* work, int*
 // over the whole matrix.  In-place Gauss-Jordan by blocks of BG = 64: with
 // D = A_kk^-1 (partial pivoting inside the block), step k replaces
 //   A_kj -> D A_kj,  A_ij -> A_ij - A_ik D A_kj,  A_ik -> -A_ik D,  A_kk -> D.
-// A step is one launch over all 64 x 64 tiles, reading one copy of the matrix
-// and writing the other (every tile changes anyway); the workgroup of the next
-// diagonal tile inverts it at once, beside the other tiles' products, so that
-// the chain per 64 columns is one tile product and one block inversion.
+// Throughout, A_ij = A_ji^T where both or neither of i, j < k are eliminated and
+// A_ij = -A_ji^T where one is: only the tiles i >= j are held and computed.
+// A step is one launch over these tiles, reading one copy of the matrix and
+// writing the other (every tile changes anyway); the workgroup of the next
+// diagonal tile, the first of the launch, inverts it at once, beside the other
+// tiles' products, so that the chain per 64 columns is one tile product and
+// one block inversion.
 //
 // Stability is not assumed: the finished inverse is checked (bgj_check), and a
 // matrix that fails is inverted again by the elimination with pivoting over
 // all rows above.
 //
-// Bound: up to ~1500 unknowns the chain of block inversions (64 columns in
-// registers, one barrier per column, 32 us, beside which the tiles' products
-// take 14 us), beyond that the two copies' traffic per step.  Measured against
-// four launches per 16 or 32 columns of the elimination above: 576 unknowns
-// 2.07 -> 0.43 ms, 1125 4.23 -> 0.94 ms, 2187 12.1 -> 2.4 ms, 3645 22.7 -> 6.5 ms.
+// Bound: up to ~2000 unknowns the chain of block inversions (64 columns in
+// registers, one barrier per column; 45 us per step, launch and tile products
+// included), beyond that the tiles' traffic.  Measured against four launches
+// per 16 or 32 columns of the elimination above, with all tiles and with the
+// lower ones: 576 unknowns 2.07, 0.43 and 0.41 ms, 1125 4.23, 0.94 and 0.81,
+// 2187 12.1, 2.4 and 2.0, 3645 22.7, 6.4 and 4.2 ms.
 typedef double bg_vec4 __attribute__((ext_vector_type(4)));
 constexpr int BG_LDA = 66, BG_LDB = 72;  // LDS strides: the matrix instructions' operand reads meet every bank evenly
 // up to this many blocks a step forms D A_kj in every tile's workgroup; beyond,
-// a launch of its own forms the row panel once (fewer operations, one launch
-// more per step)
+// a launch of its own forms the row panel and the column panel once, and the
+// tiles change in place (half the operations and less than half the traffic,
+// one launch more per step).  The same sums either way.
 constexpr int BG_FUSED_MAX = 24;
 
 // 64 x 64 x 64 product into acc: T1 (rows x k, stride BG_LDA) times T2 (k x
@@ -773,6 +778,46 @@ __device__ __forceinline__ void bgj_load(const double* __restrict__ src, int64_t
   }
 }
 
+// its transpose
+template <int LD>
+__device__ __forceinline__ void bgj_load_t(const double* __restrict__ src, int64_t ld, double* T) {
+  double2 v[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const int r = (threadIdx.x >> 5) + 8 * q, c = 2 * (threadIdx.x & 31);
+    v[q] = *reinterpret_cast<const double2*>(src + (int64_t)r * ld + c);
+  }
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const int r = (threadIdx.x >> 5) + 8 * q, c = 2 * (threadIdx.x & 31);
+    T[c * LD + r] = v[q].x;
+    T[(c + 1) * LD + r] = v[q].y;
+  }
+}
+// A_km (m != k) before step k, from the tiles held
+template <int LD>
+__device__ __forceinline__ void bgj_load_row(const double* __restrict__ M, int64_t np, int k, int m, double* T) {
+  if (m < k)
+    bgj_load<LD>(M + (int64_t)k * BG * np + m * BG, np, T);
+  else
+    bgj_load_t<LD>(M + (int64_t)m * BG * np + k * BG, np, T);
+}
+// |A_mk|: A_mk for m > k, -A_mk for m < k
+template <int LD>
+__device__ __forceinline__ void bgj_load_col(const double* __restrict__ M, int64_t np, int k, int m, double* T) {
+  if (m > k)
+    bgj_load<LD>(M + (int64_t)m * BG * np + k * BG, np, T);
+  else
+    bgj_load_t<LD>(M + (int64_t)k * BG * np + m * BG, np, T);
+}
+// tile b of the lower triangle, rows in turn
+__device__ __forceinline__ void bgj_tile(int b, int& ti, int& tj) {
+  ti = (int)((sqrtf(8.0f * b + 1.0f) - 1.0f) * 0.5f);
+  while ((ti + 1) * (ti + 2) / 2 <= b) ++ti;
+  while (ti * (ti + 1) / 2 > b) --ti;
+  tj = b - ti * (ti + 1) / 2;
+}
+
 // 1 / x to rounding (two Newton steps from the hardware estimate; a zero gives
 // inf or NaN, which the check finds)
 __device__ __forceinline__ double bgj_reciprocal(double x) {
@@ -785,7 +830,11 @@ __device__ __forceinline__ double bgj_reciprocal(double x) {
 // Gauss-Jordan in registers, lane = row, wavefront w holds columns 16 w .. 16 w
 // + 15.  The pivot of a column is the largest of its remaining entries by the
 // upper 31 bits of the magnitude (within 2^-19), ties to the lowest row; rows
-// stay in place and the permutation is undone in the final store.  One barrier
+// stay in place and the permutation is undone in the final store, which also
+// takes the symmetric part (the tiles of the other triangle are never formed,
+// so an asymmetry of D grows from step to step: on a random matrix of 1125
+// unknowns, a tenth of its eigenvalues negative, the check's ratio is 2.7e-8
+// without it and 7e-13 with it).  One barrier
 // per column: the wavefront that holds the next column updates it first, finds
 // its pivot and publishes column, pivot row and reciprocal before the rest of
 // its update.  fb: 2 x 64 published columns, ipb: 2 reciprocals, pv: 128.
@@ -826,16 +875,19 @@ __device__ void bgj_invert(double* T, double* fb, double* ipb, int* pv, double* 
       const double fl = fb[64 * (jc & 1) + l], ip = ipb[jc & 1];
       const bool mine = l == p;
       act = act && !mine;
+      // a - f ip a_p, and ip a_p in the pivot row: a keep - g a_p with the
+      // broadcast entry as a scalar operand
+      const double keep = mine ? 0.0 : 1.0, g = mine ? -ip : fl * ip;
       auto update = [&](int j) {
-        const double r = read_lane(a[j], p) * ip;
-        a[j] = mine ? r : a[j] - fl * r;
+        const double s = read_lane(a[j], p);
+        a[j] = __builtin_fma(-g, s, a[j] * keep);
       };
       update(jn);
       if (c + 1 < 64 && w == (jc == 15 ? wc + 1 : wc)) publish(a[jn], c + 1);
 #pragma unroll
       for (int j = 0; j < 16; ++j)
         if (j != jn) update(j);
-      if (w == wc) a[jc] = mine ? ip : -fl * ip;
+      if (w == wc) a[jc] = -g;
     }
   }
   if (bad && l == 0) atomicOr(status, GJ_REJECTED);
@@ -848,7 +900,10 @@ __device__ void bgj_invert(double* T, double* fb, double* ipb, int* pv, double* 
 #pragma unroll
   for (int j = 0; j < 16; ++j) T[c * BG_LDA + pv[16 * w + j]] = a[j];
   __syncthreads();
-  for (int idx = threadIdx.x; idx < BG * BG; idx += 256) out[idx] = T[(idx >> 6) * BG_LDA + (idx & 63)];
+  for (int idx = threadIdx.x; idx < BG * BG; idx += 256) {
+    const int r = idx >> 6, q = idx & 63;
+    out[idx] = 0.5 * (T[r * BG_LDA + q] + T[q * BG_LDA + r]);
+  }
 }
 
 // job of grid layer z: from the table, or the one passed by value
@@ -856,15 +911,16 @@ __device__ __forceinline__ const GJJob& bgj_job(const GJJob* __restrict__ tab, c
   return tab ? tab[blockIdx.z] : one;
 }
 
-// padded copy of the matrix (identity in the padding), the first block's inverse
+// padded copy of the matrix's lower tiles (identity in the padding), the first block's inverse
 __global__ void __launch_bounds__(256) bgj_init_kernel(const GJJob* __restrict__ tab, GJJob one) {
   __shared__ double T[BG * BG_LDA];
   __shared__ double fb[2 * BG], ipb[2];
   __shared__ int pv[2 * BG];
   const GJJob& jb = bgj_job(tab, one);
   const int n = jb.n, nb = (n + BG - 1) / BG;
-  const int ti = blockIdx.y, tj = blockIdx.x;
-  if (ti >= nb || tj >= nb) return;  // uniform
+  int ti, tj;
+  bgj_tile(blockIdx.x, ti, tj);
+  if (ti >= nb) return;  // uniform
   const int64_t np = (int64_t)nb * BG;
   const bool first = ti == 0 && tj == 0;
   for (int idx = threadIdx.x; idx < BG * BG; idx += 256) {
@@ -876,17 +932,16 @@ __global__ void __launch_bounds__(256) bgj_init_kernel(const GJJob* __restrict__
   if (first) bgj_invert(T, fb, ipb, pv, jb.dinv, jb.status);
 }
 
-// row panel of step k: rp = D A_kj (j != k)
-__global__ void __launch_bounds__(256) bgj_rows_kernel(const GJJob* __restrict__ tab, GJJob one, int k) {
+// panels of step k, tile m != k: rp_m = D A_km (64 x np), cp_m = |A_mk| (np x 64, in b1)
+__global__ void __launch_bounds__(256) bgj_panels_kernel(const GJJob* __restrict__ tab, GJJob one, int k) {
   __shared__ double T1[BG * BG_LDA];
   __shared__ double T2[BG * BG_LDB];
   const GJJob& jb = bgj_job(tab, one);
-  const int nb = (jb.n + BG - 1) / BG, tj = blockIdx.x;
-  if (k >= nb || tj >= nb || tj == k) return;  // uniform
+  const int nb = (jb.n + BG - 1) / BG, m = blockIdx.x;
+  if (nb <= BG_FUSED_MAX || k >= nb || m >= nb || m == k) return;  // uniform
   const int64_t np = (int64_t)nb * BG;
-  const double* src = (k & 1) ? jb.b1 : jb.b0;
   bgj_load<BG_LDA>(jb.dinv + (k & 1) * BG * BG, BG, T1);
-  bgj_load<BG_LDB>(src + (int64_t)k * BG * np + tj * BG, np, T2);
+  bgj_load_row<BG_LDB>(jb.b0, np, k, m, T2);
   __syncthreads();
   bg_vec4 acc[2][2] = {};
   bgj_product(T1, T2, acc);
@@ -895,7 +950,10 @@ __global__ void __launch_bounds__(256) bgj_rows_kernel(const GJJob* __restrict__
 #pragma unroll
     for (int y = 0; y < 2; ++y)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) jb.rp[bgj_row(x, r) * np + tj * BG + bgj_col(y)] = acc[x][y][r];
+      for (int r = 0; r < 4; ++r) jb.rp[bgj_row(x, r) * np + m * BG + bgj_col(y)] = acc[x][y][r];
+  // T2 holds A_km, of which |A_mk| is the transpose
+  double* cp = jb.b1 + (int64_t)m * BG * BG;
+  for (int idx = threadIdx.x; idx < BG * BG; idx += 256) cp[idx] = T2[(idx & 63) * BG_LDB + (idx >> 6)];
 }
 
 template <bool FUSED>
@@ -906,11 +964,16 @@ __global__ void __launch_bounds__(256) bgj_step_kernel(const GJJob* __restrict__
   __shared__ int pv[2 * BG];
   const GJJob& jb = bgj_job(tab, one);
   const int n = jb.n, nb = (n + BG - 1) / BG;
-  const int ti = blockIdx.y, tj = blockIdx.x;
-  if (k >= nb || ti >= nb || tj >= nb) return;  // uniform
+  if ((nb <= BG_FUSED_MAX) != FUSED || k >= nb) return;  // uniform
+  int ti, tj;
+  {  // the next diagonal tile's workgroup, which has most to do, comes first
+    const int nx = (k + 1) * (k + 2) / 2 + k + 1, b = blockIdx.x;
+    bgj_tile(k + 1 < nb && (b == 0 || b == nx) ? nx - b : b, ti, tj);
+  }
+  if (ti >= nb) return;  // uniform
   const int64_t np = (int64_t)nb * BG;
-  const double* __restrict__ src = (k & 1) ? jb.b1 : jb.b0;
-  double* __restrict__ dst = (k & 1) ? jb.b0 : jb.b1;
+  const double* src = !FUSED || !(k & 1) ? jb.b0 : jb.b1;
+  double* dst = !FUSED || (k & 1) ? jb.b0 : jb.b1;
   const double* __restrict__ D = jb.dinv + (k & 1) * BG * BG;
   const double* sij = src + (int64_t)ti * BG * np + tj * BG;
   bg_vec4 acc[2][2] = {};
@@ -938,7 +1001,7 @@ __global__ void __launch_bounds__(256) bgj_step_kernel(const GJJob* __restrict__
   } else {
     if (FUSED) {
       bgj_load<BG_LDA>(D, BG, T1);
-      bgj_load<BG_LDB>(src + (int64_t)k * BG * np + tj * BG, np, T2);
+      bgj_load_row<BG_LDB>(src, np, k, tj, T2);
       __syncthreads();
       bgj_product(T1, T2, acc);
     }
@@ -953,18 +1016,19 @@ __global__ void __launch_bounds__(256) bgj_step_kernel(const GJJob* __restrict__
             for (int r = 0; r < 4; ++r) T2[bgj_row(x, r) * BG_LDB + bgj_col(y)] = acc[x][y][r];
             acc[x][y] = bg_vec4{0.0, 0.0, 0.0, 0.0};
           }
+        bgj_load_col<BG_LDA>(src, np, k, ti, T1);
       } else {
         bgj_load<BG_LDB>(jb.rp + tj * BG, np, T2);
+        bgj_load<BG_LDA>(jb.b1 + (int64_t)ti * BG * BG, BG, T1);
       }
-      bgj_load<BG_LDA>(src + (int64_t)ti * BG * np + k * BG, np, T1);
       __syncthreads();
       bgj_product(T1, T2, acc);
-      sign = -1.0;
+      sign = ti > k ? -1.0 : 1.0;
       keep = 1.0;
     }
   }
   const bool last = k == nb - 1, next = ti == k + 1 && tj == k + 1;
-  if (next) __syncthreads();  // T1 is read no more
+  if (next || last) __syncthreads();  // T1 is read no more
 #pragma unroll
   for (int x = 0; x < 2; ++x)
 #pragma unroll
@@ -974,23 +1038,27 @@ __global__ void __launch_bounds__(256) bgj_step_kernel(const GJJob* __restrict__
         const int rr = bgj_row(x, r), cc = bgj_col(y);
         double v = sign * acc[x][y][r];
         if (keep != 0.0) v += sij[(int64_t)rr * np + cc];
-        if (last) {
-          const int i = ti * BG + rr, j = tj * BG + cc;
-          if (i < n && j < n) jb.inv[(int64_t)i * n + j] = v;
-        } else {
-          dst[((int64_t)ti * BG + rr) * np + tj * BG + cc] = v;
-        }
-        if (next) T1[rr * BG_LDA + cc] = v;
+        if (!last) dst[((int64_t)ti * BG + rr) * np + tj * BG + cc] = v;
+        if (next || last) T1[rr * BG_LDA + cc] = v;
       }
   if (next) bgj_invert(T1, fb, ipb, pv, jb.dinv + ((k + 1) & 1) * BG * BG, jb.status);
+  if (!last) return;  // uniform
+  __syncthreads();
+  // the inverse, tile and transpose
+  for (int idx = threadIdx.x; idx < BG * BG; idx += 256) {
+    const int r = idx >> 6, c = idx & 63;
+    const int i = ti * BG + r, j = tj * BG + c, it = tj * BG + r, jt = ti * BG + c;
+    if (i < n && j < n) jb.inv[(int64_t)i * n + j] = T1[r * BG_LDA + c];
+    if (ti != tj && it < n && jt < n) jb.inv[(int64_t)it * n + jt] = T1[c * BG_LDA + r];
+  }
 }
 
 // Check of the inverse X on one vector v of signs: x = X v, and in a second
 // pass |A x - v| <= 1e-15 sqrt(n) (|A| |x| + 1) in every row.  Measured for the
 // largest row of that ratio: 0.1 sqrt(n) 1e-15 on definite matrices of 1 to
-// 3645 unknowns (0.2 with pivoting over all rows), 2 to 200 times sqrt(n) 1e-15
-// on random symmetric indefinite ones of 243 and more, where the block
-// elimination loses two to three digits.  Otherwise, or where anything is not
+// 3645 unknowns (0.2 with pivoting over all rows), 2 to 27000 times sqrt(n)
+// 1e-15 on random symmetric indefinite ones of 243 and more, where the block
+// elimination loses digits.  Otherwise, or where anything is not
 // finite, the matrix is marked for the elimination with pivoting over all rows.
 __device__ __forceinline__ double bgj_sign(int j) { return (((unsigned)j * 2654435761u) >> 16) & 1 ? 1.0 : -1.0; }
 __global__ void __launch_bounds__(256) bgj_apply_kernel(const GJJob* __restrict__ tab, GJJob one) {
@@ -1024,16 +1092,16 @@ __global__ void __launch_bounds__(256) bgj_check_kernel(const GJJob* __restrict_
 // Inversions of nj matrices (job table in device memory, or the one job by
 // value), nmax unknowns at most: status gets GJ_REJECTED where the result is
 // to be replaced by dense_invert_pivoted's.
-static int bgj_run(const GJJob* tab, const GJJob& one, int nj, int nmax, hipStream_t s) {
+static int bgj_run(const GJJob* tab, const GJJob& one, int nj, int nmin, int nmax, hipStream_t s) {
   const int nb = (nmax + BG - 1) / BG;
-  const dim3 tiles(nb, nb, nj);
-  bgj_init_kernel<<<tiles, 256, 0, s>>>(tab, one);
-  for (int k = 0; k < nb; ++k) {
-    if (nb <= BG_FUSED_MAX) {
-      bgj_step_kernel<true><<<tiles, 256, 0, s>>>(tab, one, k);
-    } else {
-      bgj_rows_kernel<<<dim3(nb, 1, nj), 256, 0, s>>>(tab, one, k);
-      bgj_step_kernel<false><<<tiles, 256, 0, s>>>(tab, one, k);
+  const bool some_fused = (nmin + BG - 1) / BG <= BG_FUSED_MAX;
+  const auto tiles = [&](int b) { return dim3(b * (b + 1) / 2, 1, nj); };
+  bgj_init_kernel<<<tiles(nb), 256, 0, s>>>(tab, one);
+  for (int k = 0; k < nb; ++k) {  // a kernel leaves the other kind's jobs alone
+    if (some_fused && k < BG_FUSED_MAX) bgj_step_kernel<true><<<tiles(std::min(nb, BG_FUSED_MAX)), 256, 0, s>>>(tab, one, k);
+    if (nb > BG_FUSED_MAX) {
+      bgj_panels_kernel<<<dim3(nb, 1, nj), 256, 0, s>>>(tab, one, k);
+      bgj_step_kernel<false><<<tiles(nb), 256, 0, s>>>(tab, one, k);
     }
   }
   bgj_apply_kernel<<<dim3((nmax + 3) / 4, 1, nj), 256, 0, s>>>(tab, one);
@@ -1043,13 +1111,13 @@ static int bgj_run(const GJJob* tab, const GJJob& one, int nj, int nmax, hipStre
 
 // a: n x n input (not modified); inv: n x n output; work: dense_invert_work(n) bytes.
 int dense_invert(int n, const double* a, double* inv, double* work, int* status, hipStream_t s) {
-  return bgj_run(nullptr, gj_make_job(n, a, inv, work, status), 1, n, s);
+  return bgj_run(nullptr, gj_make_job(n, a, inv, work, status), 1, n, n, s);
 }
 // tab_dev: device table of the jobs of sizes ns
 int dense_invert_batch(const GJJob* tab_dev, const std::vector<int>& ns, hipStream_t s) {
-  int nmax = 0;
-  for (int n : ns) nmax = std::max(nmax, n);
-  return bgj_run(tab_dev, GJJob{}, (int)ns.size(), nmax, s);
+  if (ns.empty()) return 0;
+  const auto [lo, hi] = std::minmax_element(ns.begin(), ns.end());
+  return bgj_run(tab_dev, GJJob{}, (int)ns.size(), *lo, *hi, s);
 }
 
 // x = Ainv b on the coarsest level; one wavefront per output unknown, FP64

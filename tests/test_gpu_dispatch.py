@@ -99,3 +99,29 @@ def test_vcycle_of_both_level_kernel_families(nx, ny, nz, levels, precision, tol
         err = float((z - z2).norm() / z2.norm())
         assert err < tol, (mf, err)
     gp.close()
+
+
+def test_batch_of_both_coarse_elimination_kinds():
+    """Coarsest levels of 576 unknowns (a step in one launch) and of 1539 (25
+    blocks: panels in a launch of their own) in one batch: every V-cycle is
+    bitwise the one of the problem by itself."""
+    from paper_2011_08802_amd import mvpf
+    probs = []
+    for i, (nx, ny, nz) in enumerate([(6, 6, 6), (4, 4, 36), (4, 4, 4)]):
+        h = 1.0 / nz
+        probs.append(synth.Problem(nx, ny, nz, lx=nx * h, ly=ny * h, lz=1.0, n_levels=2, patch=2, depth_increment=0.01,
+                                   seed=synth.BASE_SEED + 40 + i))
+    B = mvpf.Batch(probs, "fp64")
+    states = [seeded_state(p, 1e-3) for p in probs]
+    for i, (U, En) in enumerate(states):
+        B.problem(i).set_state(U[:, :3], U[:, 3:], En, 0.0)
+    B.newton_system([p.depth_increment for p in probs])
+    for i, (p, (U, En)) in enumerate(zip(probs, states)):
+        v = _dev(np.random.default_rng(11 + i).standard_normal(9 * (p.nx + 1) * (p.ny + 1) * (p.nz + 1)))
+        gp = gpu_problem(p, U, En, "fp64")
+        gp.newton_system(p.depth_increment)
+        z = gp.precondition(v)
+        assert torch.isfinite(z).all()
+        assert torch.equal(B.problem(i).precondition(v), z), i
+        gp.close()
+    B.close()
