@@ -421,8 +421,8 @@ int mvpf_indent(mvpf_problem* p, const mvpf_indent_opts* o, mvpf_indent_callback
  * workgroup loop over rows in rounds, which keeps the rows in flight within
  * cache reach of each other); "outer_blocks": the same for the outer FP64
  * operator product (level ignored); "small_grid_nodes": levels with at most
- * this many nodes use the latency-oriented small-grid smoother and defect
- * kernels (27 threads per row; default 40000; level ignored).  The two kernel
+ * this many nodes use the latency-oriented small-grid smoother, defect and
+ * product kernels (27 threads per row; default 40000; level ignored).  The two kernel
  * families sum the 27 block products in different orders, so this key alone
  * changes results at rounding level; the others never do.  "coarse_overlap":
  * 1 = the coarsest level's dense inversion runs on a second (default

@@ -688,7 +688,7 @@ struct Krylov {
       launch_mf_gather<0, double, TZ, double>(g, (const double*)p->Cbuf, contact(p), p->mf_epw, p->lev[0].mask, zj(),
                                               nullptr, nullptr, 0.0, w, s);
     } else {
-      launch_spmv<double, TZ, double>(g, p->lev[0].A64, zj(), w, p->Cbuf, s, p->outer_G);
+      launch_spmv<double, TZ, double>(g, p->lev[0].A64, zj(), w, p->Cbuf, s, p->small_nodes, p->outer_G);
     }
     if (p->timing)
       timer_end(p, p->t_outer, 8.0 * (use_mf(p) ? MF_VALUES * g.NE : stored_blocks(g) * NBLK) +
@@ -757,7 +757,7 @@ struct Krylov {
       launch_mf_gather<0, double, double, double>(g, (const double*)p->Cbuf, contact(p), p->mf_epw, p->lev[0].mask, x,
                                                   nullptr, nullptr, 0.0, p->tmp, s);
     } else {
-      launch_spmv<double, double, double>(g, p->lev[0].A64, x, p->tmp, p->Cbuf, s, p->outer_G);
+      launch_spmv<double, double, double>(g, p->lev[0].A64, x, p->tmp, p->Cbuf, s, p->small_nodes, p->outer_G);
     }
     launch_axpby(n, 1.0, b, -1.0, p->tmp, p->tmp, s);
     launch_multidot(n, p->tmp, n, 1, p->tmp, p->red, s);
@@ -1080,7 +1080,7 @@ int system_rhs(mvpf_problem* p, double depth) {
     launch_mf_gather<0, double, double, double>(L0.g, (const double*)p->Cbuf, contact(p), p->mf_epw, nullptr, p->gvec,
                                                 nullptr, nullptr, 0.0, p->tmp, s);
   } else {
-    launch_spmv<double, double, double>(L0.g, L0.A64, p->gvec, p->tmp, p->Cbuf, s);
+    launch_spmv<double, double, double>(L0.g, L0.A64, p->gvec, p->tmp, p->Cbuf, s, p->small_nodes);
   }
   launch_newton_rhs(L0.g, L0.mask, p->R, p->tmp, p->gvec, p->rhs, s);
   return 0;
@@ -1471,7 +1471,7 @@ void autotune_levels(mvpf_problem* p, int* tuned) {
     tune_store(tune_key(p, "row_blocks", L.g), bestG);
   }
   const Grid& g = p->lev[0].g;
-  if (use_mf(p)) return;
+  if (use_mf(p) || g.N <= p->small_nodes) return;
   if (cached && tune_lookup(tune_key(p, "outer_blocks", g), &hit)) {
     p->outer_G = hit;
     tuned[p->L - 1] = hit;
@@ -1482,9 +1482,11 @@ void autotune_levels(mvpf_problem* p, int* tuned) {
   for (int G : launch_candidates(g)) {
     const double ms = time_launches(p, 5, [&] {
       if (p->mixed)
-        launch_spmv<double, float, double>(g, p->lev[0].A64, (const float*)p->Z, p->tmp, p->Cbuf, p->stream, G);
+        launch_spmv<double, float, double>(g, p->lev[0].A64, (const float*)p->Z, p->tmp, p->Cbuf, p->stream,
+                                           p->small_nodes, G);
       else
-        launch_spmv<double, double, double>(g, p->lev[0].A64, p->tmp2, p->tmp, p->Cbuf, p->stream, G);
+        launch_spmv<double, double, double>(g, p->lev[0].A64, p->tmp2, p->tmp, p->Cbuf, p->stream, p->small_nodes,
+                                            G);
     });
     if (ms < best * 0.98) { best = ms; bestG = G; }
   }
@@ -2040,7 +2042,7 @@ int batch_fgmres(mvpf_batch* b, mvpf_solve_stats* st) {
             });
         } else {
           solos.push_back([p, z, w](hipStream_t st_) {
-            launch_spmv<double, TZ, double>(p->lev[0].g, p->lev[0].A64, z, w, p->Cbuf, st_, p->outer_G);
+            launch_spmv<double, TZ, double>(p->lev[0].g, p->lev[0].A64, z, w, p->Cbuf, st_, p->small_nodes, p->outer_G);
           });
         }
       }
@@ -2629,7 +2631,7 @@ int mvpf_jacobian_apply(mvpf_problem* p, int level, int precision, const double*
       launch_mf_gather<0, double, double, double>(g, (const double*)p->Cbuf, contact(p), p->mf_epw, L.mask, p->tmp,
                                                   nullptr, nullptr, 0.0, p->tmp2, s);
     } else {
-      launch_spmv<double, double, double>(g, L.A64, p->tmp, p->tmp2, p->Cbuf, s);
+      launch_spmv<double, double, double>(g, L.A64, p->tmp, p->tmp2, p->Cbuf, s, p->small_nodes);
     }
     launch_soa_to_interleaved(g, p->tmp2, NDOF, 0, y, s);
   } else if (precision == MVPF_MIXED) {
@@ -2640,7 +2642,7 @@ int mvpf_jacobian_apply(mvpf_problem* p, int level, int precision, const double*
       launch_mf_gather<0, float, float, float>(g, (const float*)p->Cbuf, contact(p), p->mf_epw, L.mask,
                                                (const float*)L.x, nullptr, nullptr, 0.0f, (float*)L.r, s);
     } else {
-      launch_spmv<float, float, float>(g, L.A32, (const float*)L.x, (float*)L.r, p->Cbuf, s);
+      launch_spmv<float, float, float>(g, L.A32, (const float*)L.x, (float*)L.r, p->Cbuf, s, p->small_nodes);
     }
     launch_soa_to_interleaved(g, (const float*)L.r, NDOF, 0, y, s);
   } else {

@@ -192,8 +192,149 @@ __global__ void __launch_bounds__(256) spmv_upper_split_kernel(Grid g, const TA*
   }
 }
 
+// ---- small grids --------------------------------------------------------------
+// On coarse levels the one-thread-per-row kernels are latency bound (27 rounds
+// of dependent loads per thread).  Here 27 threads share a row, one per
+// stencil block; each does one round of loads and the 27 partial products are
+// summed through LDS in a fixed order.  SMALL_ROWS rows per workgroup, thread
+// index = s * SMALL_ROWS + local row, so a load takes the 16-byte words of 8
+// consecutive rows, a cache line; up to SMALL_CHUNK of them and the epilogue's
+// operands are in flight together.  A row reads the 13 blocks below its
+// diagonal from its neighbours' rows; consecutive workgroups share an XCD
+// (ROW_LOOP's numbering), so these come from its L2.
+// Per sweep, before (9 rows, scalar loads, workgroups dealt to all XCDs) and
+// now: FP64 9261 nodes 41.6 -> 23.3 us (85 MB of operator: 3.6 TB/s), 1331
+// nodes 9.8 -> 5.4, 125 nodes 6.0 -> 4.7; FP32 4913 nodes 16.2 -> 7.5 us.
+constexpr int SMALL_ROWS = 8;
+constexpr int SMALL_CHUNK = 21;  // 16-byte loads in flight per thread (an FP32 block of 9 x 9; half an FP64 one)
+#define SMALL_OCC __attribute__((amdgpu_waves_per_eu(3, 3)))  // registers for them
+constexpr int SMALL_THREADS = (SMALL_ROWS * NSTEN + 63) / 64 * 64;
+// the padding included (a product leaves zeros there)
+static int small_blocks(const Grid& g) { return (g.Npad / SMALL_ROWS + 7) / 8 * 8; }
+static_assert(TILE % SMALL_ROWS == 0);
+
+enum RowMode { ROW_PRODUCT, ROW_DEFECT, ROW_PBJ };  // out = A x, b - A x, x + omega Dinv (b - A x)
+template <typename TA, typename TX, typename T, RowMode MODE>
+__device__ __forceinline__ void row_small_body(const Grid& g, const TA* __restrict__ A, const T* __restrict__ Dinv,
+                                               const TX* __restrict__ x, const T* __restrict__ b,
+                                               T* __restrict__ out, T omega, int bid, int nblk) {
+  constexpr bool PBJ = MODE == ROW_PBJ;
+  __shared__ T part[SMALL_ROWS][NSTEN][NDOF];
+  __shared__ T res[SMALL_ROWS][NDOF];
+  using VT = typename Vec16<TA>::type;
+  constexpr int V = Lay<TA>::V;
+  const int tid = threadIdx.x;
+  const int s = tid / SMALL_ROWS, ln = tid % SMALL_ROWS;
+  const int n0 = ((bid & 7) * (nblk >> 3) + (bid >> 3)) * SMALL_ROWS;
+  const int n = n0 + ln;
+  // the epilogue's operands (thread = local row x component), in flight from the start
+  const int ln2 = tid / NDOF, r2 = tid % NDOF;
+  const int n2 = n0 + ln2;
+  const bool own = tid < SMALL_ROWS * NDOF && n2 < g.N;
+  T b2 = 0, x2 = 0, d2[NDOF];
+  if (own) {
+    if (MODE != ROW_PRODUCT) b2 = b[(int64_t)r2 * g.Npad + n2];
+    if (PBJ) {
+      x2 = (T)x[(int64_t)r2 * g.Npad + n2];
+      const T* Db = Dinv + (int64_t)(n2 >> 6) * Lay<T>::SLICE;
+#pragma unroll
+      for (int c = 0; c < NDOF; ++c) d2[c] = Db[Lay<T>::off(r2 * NDOF + c, n2 & 63)];
+    }
+  }
+  T pr[NDOF] = {};
+  if (s < NSTEN && n < g.N) {
+    const int i = n % g.nnx, j = (n / g.nnx) % g.nny, k = n / (g.nnx * g.nny);
+    const int dx = s % 3 - 1, dy = (s / 3) % 3 - 1, dz = s / 9 - 1;
+    if (i + dx >= 0 && i + dx < g.nnx && j + dy >= 0 && j + dy < g.nny && k + dz >= 0 && k + dz < g.nnz) {
+      const int m = n + dx + g.nnx * (dy + g.nny * dz);
+      T xv[NDOF];
+#pragma unroll
+      for (int c = 0; c < NDOF; ++c) xv[c] = (T)x[(int64_t)c * g.Npad + m];
+      const bool upper = s >= 13;
+      const int o = upper ? n : m;  // the row that stores the block
+      const VT* Ab =
+          reinterpret_cast<const VT*>(A + ((int64_t)(o >> 6) * NUP + (upper ? s - 13 : 13 - s)) * Lay<TA>::SLICE) +
+          (o & 63);
+#pragma unroll
+      for (int q0 = 0; q0 < Lay<TA>::NQ; q0 += SMALL_CHUNK) {
+        VT vq[SMALL_CHUNK];
+#pragma unroll
+        for (int q = 0; q < SMALL_CHUNK; ++q)
+          if (q0 + q < Lay<TA>::NQ) vq[q] = Ab[(q0 + q) * TILE];
+        // one branch per chunk: the stored block, or its transpose
+        auto add = [&](auto up) {
+#pragma unroll
+          for (int q = 0; q < SMALL_CHUNK; ++q) {
+            TA av[V];
+            __builtin_memcpy(av, &vq[q], sizeof(VT));
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+              const int e = (q0 + q) * V + v;
+              if (e < NBLK) {
+                const int r = e / NDOF, c = e % NDOF;
+                pr[up.value ? r : c] += (T)av[v] * xv[up.value ? c : r];
+              }
+            }
+          }
+        };
+        if (upper) add(std::true_type{}); else add(std::false_type{});
+      }
+    }
+  }
+  if (s < NSTEN)
+#pragma unroll
+    for (int r = 0; r < NDOF; ++r) part[ln][s][r] = pr[r];
+  __syncthreads();
+  if (own) {
+    T acc = b2;
+#pragma unroll
+    for (int ss = 0; ss < NSTEN; ++ss) acc += MODE == ROW_PRODUCT ? part[ln2][ss][r2] : -part[ln2][ss][r2];
+    if (PBJ)
+      res[ln2][r2] = acc;
+    else
+      out[(int64_t)r2 * g.Npad + n2] = acc;
+  }
+  if (MODE == ROW_PRODUCT && tid < SMALL_ROWS * NDOF && n2 >= g.N && n2 < g.Npad) out[(int64_t)r2 * g.Npad + n2] = 0;
+  if (!PBJ) return;
+  __syncthreads();
+  if (own) {
+    T acc = 0;
+#pragma unroll
+    for (int c = 0; c < NDOF; ++c) acc += d2[c] * res[ln2][c];
+    out[(int64_t)r2 * g.Npad + n2] = x2 + omega * acc;
+  }
+}
+template <typename TA, typename TX, typename T, RowMode MODE>
+__global__ void __launch_bounds__(SMALL_THREADS) SMALL_OCC
+    row_small_kernel(Grid g, const TA* __restrict__ A, const T* __restrict__ Dinv, const TX* __restrict__ x,
+                     const T* __restrict__ b, T* __restrict__ out, T omega) {
+  row_small_body<TA, TX, T, MODE>(g, A, Dinv, x, b, out, omega, blockIdx.x, gridDim.x);
+}
+
+template <typename T>
+void launch_row_small(const Grid& g, const T* A, const T* Dinv, const T* x, const T* b, T* out, T omega, bool pbj,
+                      hipStream_t s) {
+  const int nb = small_blocks(g);
+  if (pbj)
+    row_small_kernel<T, T, T, ROW_PBJ><<<nb, SMALL_THREADS, 0, s>>>(g, A, Dinv, x, b, out, omega);
+  else
+    row_small_kernel<T, T, T, ROW_DEFECT><<<nb, SMALL_THREADS, 0, s>>>(g, A, Dinv, x, b, out, omega);
+}
+template void launch_row_small<float>(const Grid&, const float*, const float*, const float*, const float*, float*,
+                                      float, bool, hipStream_t);
+template void launch_row_small<double>(const Grid&, const double*, const double*, const double*, const double*,
+                                       double*, double, bool, hipStream_t);
+
+// ---- products -------------------------------------------------------------------
 template <typename TA, typename TX, typename TY>
-void launch_spmv(const Grid& g, const TA* A, const TX* x, TY* y, void* C, hipStream_t s, int G) {
+void launch_spmv(const Grid& g, const TA* A, const TX* x, TY* y, void* C, hipStream_t s, int small_nodes, int G) {
+  // FP64, 15 unknowns per node, 10648 nodes: 508 us in two passes (one thread per
+  // row, 42 workgroups), 95 here (270 MB of operator)
+  if (g.N <= small_nodes) {
+    row_small_kernel<TA, TX, TY, ROW_PRODUCT><<<small_blocks(g), SMALL_THREADS, 0, s>>>(g, A, nullptr, x, nullptr, y,
+                                                                                       (TY)0);
+    return;
+  }
   const int nb = row_grid(g, G);
   // FP64 operators keep one wavefront per tile (2 waves per SIMD fit either
   // way and the split measured slower); FP32 ones split
@@ -204,11 +345,11 @@ void launch_spmv(const Grid& g, const TA* A, const TX* x, TY* y, void* C, hipStr
   spmv_lower_kernel<TY><<<nb, 256, 0, s>>>(g, y, (const TY*)C);
 }
 template void launch_spmv<double, double, double>(const Grid&, const double*, const double*, double*, void*,
-                                                  hipStream_t, int);
+                                                  hipStream_t, int, int);
 template void launch_spmv<double, float, double>(const Grid&, const double*, const float*, double*, void*,
-                                                 hipStream_t, int);
+                                                 hipStream_t, int, int);
 template void launch_spmv<float, float, float>(const Grid&, const float*, const float*, float*, void*, hipStream_t,
-                                               int);
+                                               int, int);
 
 // r = b - A x
 template <typename T>
@@ -385,134 +526,6 @@ template void launch_pbj<float>(const Grid&, const float*, const float*, const f
 template void launch_pbj<double>(const Grid&, const double*, const double*, const double*, const double*, double*,
                                  double, void*, hipStream_t, int);
 
-// ---- small grids --------------------------------------------------------------
-// On coarse levels the one-thread-per-row kernels are latency bound (27 rounds
-// of dependent loads per thread).  Here 27 threads share a row, one per
-// stencil block; each does one round of loads and the 27 partial products are
-// summed through LDS in a fixed order.  SMALL_ROWS rows per workgroup, thread
-// index = s * SMALL_ROWS + local row, so a load takes the 16-byte words of 8
-// consecutive rows, a cache line; up to SMALL_CHUNK of them and the epilogue's
-// operands are in flight together.  A row reads the 13 blocks below its
-// diagonal from its neighbours' rows; consecutive workgroups share an XCD
-// (ROW_LOOP's numbering), so these come from its L2.
-// Per sweep, before (9 rows, scalar loads, workgroups dealt to all XCDs) and
-// now: FP64 9261 nodes 41.6 -> 23.3 us (85 MB of operator: 3.6 TB/s), 1331
-// nodes 9.8 -> 5.4, 125 nodes 6.0 -> 4.7; FP32 4913 nodes 16.2 -> 7.5 us.
-constexpr int SMALL_ROWS = 8;
-constexpr int SMALL_CHUNK = 21;  // 16-byte loads in flight per thread (an FP32 block of 9 x 9; half an FP64 one)
-#define SMALL_OCC __attribute__((amdgpu_waves_per_eu(3, 3)))  // registers for them
-constexpr int SMALL_THREADS = (SMALL_ROWS * NSTEN + 63) / 64 * 64;
-int small_blocks(const Grid& g) { return ((g.N + SMALL_ROWS - 1) / SMALL_ROWS + 7) / 8 * 8; }
-
-template <typename T, bool PBJ>
-__device__ __forceinline__ void row_small_body(const Grid& g, const T* __restrict__ A, const T* __restrict__ Dinv,
-                                               const T* __restrict__ x, const T* __restrict__ b, T* __restrict__ out,
-                                               T omega, int bid, int nblk) {
-  __shared__ T part[SMALL_ROWS][NSTEN][NDOF];
-  __shared__ T res[SMALL_ROWS][NDOF];
-  using VT = typename Vec16<T>::type;
-  constexpr int V = Lay<T>::V;
-  const int tid = threadIdx.x;
-  const int s = tid / SMALL_ROWS, ln = tid % SMALL_ROWS;
-  const int n0 = ((bid & 7) * (nblk >> 3) + (bid >> 3)) * SMALL_ROWS;
-  const int n = n0 + ln;
-  // the epilogue's operands (thread = local row x component), in flight from the start
-  const int ln2 = tid / NDOF, r2 = tid % NDOF;
-  const int n2 = n0 + ln2;
-  const bool own = tid < SMALL_ROWS * NDOF && n2 < g.N;
-  T b2 = 0, x2 = 0, d2[NDOF];
-  if (own) {
-    b2 = b[(int64_t)r2 * g.Npad + n2];
-    if (PBJ) {
-      x2 = x[(int64_t)r2 * g.Npad + n2];
-      const T* Db = Dinv + (int64_t)(n2 >> 6) * Lay<T>::SLICE;
-#pragma unroll
-      for (int c = 0; c < NDOF; ++c) d2[c] = Db[Lay<T>::off(r2 * NDOF + c, n2 & 63)];
-    }
-  }
-  T pr[NDOF] = {};
-  if (s < NSTEN && n < g.N) {
-    const int i = n % g.nnx, j = (n / g.nnx) % g.nny, k = n / (g.nnx * g.nny);
-    const int dx = s % 3 - 1, dy = (s / 3) % 3 - 1, dz = s / 9 - 1;
-    if (i + dx >= 0 && i + dx < g.nnx && j + dy >= 0 && j + dy < g.nny && k + dz >= 0 && k + dz < g.nnz) {
-      const int m = n + dx + g.nnx * (dy + g.nny * dz);
-      T xv[NDOF];
-#pragma unroll
-      for (int c = 0; c < NDOF; ++c) xv[c] = x[(int64_t)c * g.Npad + m];
-      const bool upper = s >= 13;
-      const int o = upper ? n : m;  // the row that stores the block
-      const VT* Ab =
-          reinterpret_cast<const VT*>(A + ((int64_t)(o >> 6) * NUP + (upper ? s - 13 : 13 - s)) * Lay<T>::SLICE) +
-          (o & 63);
-#pragma unroll
-      for (int q0 = 0; q0 < Lay<T>::NQ; q0 += SMALL_CHUNK) {
-        VT vq[SMALL_CHUNK];
-#pragma unroll
-        for (int q = 0; q < SMALL_CHUNK; ++q)
-          if (q0 + q < Lay<T>::NQ) vq[q] = Ab[(q0 + q) * TILE];
-        // one branch per chunk: the stored block, or its transpose
-        auto add = [&](auto up) {
-#pragma unroll
-          for (int q = 0; q < SMALL_CHUNK; ++q) {
-            T av[V];
-            __builtin_memcpy(av, &vq[q], sizeof(VT));
-#pragma unroll
-            for (int v = 0; v < V; ++v) {
-              const int e = (q0 + q) * V + v;
-              if (e < NBLK) {
-                const int r = e / NDOF, c = e % NDOF;
-                pr[up.value ? r : c] += av[v] * xv[up.value ? c : r];
-              }
-            }
-          }
-        };
-        if (upper) add(std::true_type{}); else add(std::false_type{});
-      }
-    }
-  }
-  if (s < NSTEN)
-#pragma unroll
-    for (int r = 0; r < NDOF; ++r) part[ln][s][r] = pr[r];
-  __syncthreads();
-  if (own) {
-    T acc = b2;
-#pragma unroll
-    for (int ss = 0; ss < NSTEN; ++ss) acc -= part[ln2][ss][r2];
-    if (PBJ)
-      res[ln2][r2] = acc;
-    else
-      out[(int64_t)r2 * g.Npad + n2] = acc;
-  }
-  if (!PBJ) return;
-  __syncthreads();
-  if (own) {
-    T acc = 0;
-#pragma unroll
-    for (int c = 0; c < NDOF; ++c) acc += d2[c] * res[ln2][c];
-    out[(int64_t)r2 * g.Npad + n2] = x2 + omega * acc;
-  }
-}
-template <typename T, bool PBJ>
-__global__ void __launch_bounds__(SMALL_THREADS) SMALL_OCC
-    row_small_kernel(Grid g, const T* __restrict__ A, const T* __restrict__ Dinv, const T* __restrict__ x,
-                     const T* __restrict__ b, T* __restrict__ out, T omega) {
-  row_small_body<T, PBJ>(g, A, Dinv, x, b, out, omega, blockIdx.x, gridDim.x);
-}
-
-template <typename T>
-void launch_row_small(const Grid& g, const T* A, const T* Dinv, const T* x, const T* b, T* out, T omega, bool pbj,
-                      hipStream_t s) {
-  const int nb = small_blocks(g);
-  if (pbj)
-    row_small_kernel<T, true><<<nb, SMALL_THREADS, 0, s>>>(g, A, Dinv, x, b, out, omega);
-  else
-    row_small_kernel<T, false><<<nb, SMALL_THREADS, 0, s>>>(g, A, Dinv, x, b, out, omega);
-}
-template void launch_row_small<float>(const Grid&, const float*, const float*, const float*, const float*, float*,
-                                      float, bool, hipStream_t);
-template void launch_row_small<double>(const Grid&, const double*, const double*, const double*, const double*,
-                                       double*, double, bool, hipStream_t);
-
 // ---- batched launches (one launch for the jobs of many problems) ------------
 template <typename T>
 __global__ void __launch_bounds__(256) pbj_zero_batch(const BJob* __restrict__ jobs, int njobs) {
@@ -538,11 +551,11 @@ __global__ void __launch_bounds__(256) defect_lower_batch(const BJob* __restrict
   const BJob& j = find_job(jobs, njobs, bid);
   defect_lower_body<T>(j.g, (T*)j.y, (const T*)j.C, bid, j.nblk);
 }
-template <typename T, bool PBJ>
+template <typename T, RowMode MODE>
 __global__ void __launch_bounds__(SMALL_THREADS) SMALL_OCC row_small_batch(const BJob* __restrict__ jobs, int njobs) {
   int bid;
   const BJob& j = find_job(jobs, njobs, bid);
-  row_small_body<T, PBJ>(j.g, (const T*)j.A, (const T*)j.D, (const T*)j.x, (const T*)j.b, (T*)j.y, (T)j.omega, bid,
+  row_small_body<T, T, T, MODE>(j.g, (const T*)j.A, (const T*)j.D, (const T*)j.x, (const T*)j.b, (T*)j.y, (T)j.omega, bid,
                          j.nblk);
 }
 
@@ -553,8 +566,8 @@ void launch_bsr_batch(int op, const BJob* jobs, int njobs, int blocks, hipStream
     case BOP_DEFECT_SPLIT: defect_upper_split_batch<T><<<blocks, 256, 0, s>>>(jobs, njobs); break;
     case BOP_PBJ_LOWER: pbj_lower_batch<T><<<blocks, 256, 0, s>>>(jobs, njobs); break;
     case BOP_DEFECT_LOWER: defect_lower_batch<T><<<blocks, 256, 0, s>>>(jobs, njobs); break;
-    case BOP_ROW_SMALL_PBJ: row_small_batch<T, true><<<blocks, SMALL_THREADS, 0, s>>>(jobs, njobs); break;
-    case BOP_ROW_SMALL_DEFECT: row_small_batch<T, false><<<blocks, SMALL_THREADS, 0, s>>>(jobs, njobs); break;
+    case BOP_ROW_SMALL_PBJ: row_small_batch<T, ROW_PBJ><<<blocks, SMALL_THREADS, 0, s>>>(jobs, njobs); break;
+    case BOP_ROW_SMALL_DEFECT: row_small_batch<T, ROW_DEFECT><<<blocks, SMALL_THREADS, 0, s>>>(jobs, njobs); break;
     default: break;
   }
 }

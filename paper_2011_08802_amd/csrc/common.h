@@ -381,7 +381,7 @@ void launch_mf_gather(const Grid& g, const T* E, bool contact, int elems_per_wg,
 // C: scratch for the transposed lower-half contributions, >= 13 * 9 * Npad
 // values of the accumulation type (TY for spmv, T otherwise).
 template <typename TA, typename TX, typename TY>
-void launch_spmv(const Grid& g, const TA* A, const TX* x, TY* y, void* C, hipStream_t s, int G = 0);
+void launch_spmv(const Grid& g, const TA* A, const TX* x, TY* y, void* C, hipStream_t s, int small_nodes, int G = 0);
 template <typename T>
 void launch_defect(const Grid& g, const T* A, const T* x, const T* b, T* r, void* C, hipStream_t s, int G = 0);
 template <typename T>

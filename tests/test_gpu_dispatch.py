@@ -74,15 +74,16 @@ def test_galerkin_level1_from_gauss_points(nx, ny, nz, kind):
     gp.close()
 
 
-@pytest.mark.parametrize("precision,tol", [("fp64", 1e-12), ("mixed", 1e-4)])
+@pytest.mark.parametrize("precision,tol,ptol", [("fp64", 1e-12, 3e-14), ("mixed", 1e-4, 2e-5)])
 @pytest.mark.parametrize("nx,ny,nz,levels", [(4, 4, 4, 2), (6, 10, 2, 2), (16, 4, 12, 3), (24, 24, 24, 3), (28, 24, 24, 3)])
-def test_vcycle_of_both_level_kernel_families(nx, ny, nz, levels, precision, tol):
+def test_vcycle_of_both_level_kernel_families(nx, ny, nz, levels, precision, tol, ptol):
     """A V-cycle with the small-grid row kernel on every level (row counts that
     leave a remainder of its 8 rows and of a tile, 125 to 18125 rows), and with
     the two-pass kernels: the same 27 x 9 products per entry, summed in another
     order, over 9 sweeps whose factors are below 3 (FP64 243 * 1.1e-16 * 9 * 3;
     FP32 the square root of the terms).  The matrix-free finest level is on
-    either side of the node gather's limit of 256 tiles."""
+    either side of the node gather's limit of 256 tiles.  The assembled
+    product by itself, relative to |A x| + |A |x||: 243 roundings per entry."""
     h = 1.0 / max(nx, ny, nz)
     p = synth.Problem(nx, ny, nz, lx=nx * h, ly=ny * h, lz=nz * h, n_levels=levels, patch=2, depth_increment=0.01)
     U, En = seeded_state(p, 1e-3)
@@ -98,6 +99,11 @@ def test_vcycle_of_both_level_kernel_families(nx, ny, nz, levels, precision, tol
         assert torch.isfinite(z).all()
         err = float((z - z2).norm() / z2.norm())
         assert err < tol, (mf, err)
+    kind = 0 if precision == "fp64" else 1
+    y2, ya = gp.jacobian_apply(0, x, kind), gp.jacobian_apply(0, x.abs(), kind)
+    gp.set_tuning("small_grid_nodes", 0, 40000)
+    y = gp.jacobian_apply(0, x, kind)
+    assert float((y - y2).norm() / (y2.norm() + ya.norm())) < ptol
     gp.close()
 
 
