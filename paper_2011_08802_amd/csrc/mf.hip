@@ -487,10 +487,18 @@ __device__ __forceinline__ double pair_sum(double a, const PairWeights& w) {
 // summed by three pair exchanges per coefficient (297 in all) instead of one
 // 9x9 product per corner and point.  Elements of one slab (whole layers),
 // chunk-local index el; streams as for the element outputs, 45 values instead
-// of 9.  Bound: FP64 issue (~2000 instructions per point) and the tangents'
-// 0.77 KB per point, read once; 64^3: 0.58 ms, and 0.18
-// ms for the node sums.
+// of 9, each group of nine stored as soon as it is complete.  Bound: the
+// tangents' 0.77 KB per point, read once (64^3: 1.6 GB), at the 3 wavefronts
+// per SIMD that 168 registers allow: 698 -> 442 us against one wavefront with
+// all 45 results live.
 constexpr int DG_EPW = SLAB_EPW;
+constexpr int DG_ENTRIES = 45;
+// position of entry (r, c) of the symmetric block among the 45: u-u, then u-eta by
+// eta component, then eta-eta
+__host__ __device__ constexpr int diag_stream(int r, int c) {
+  if (r > c) { const int x = r; r = c; c = x; }
+  return c < 3 ? c * (c + 1) / 2 + r : r < 3 ? 6 + 3 * (c - 3) + r : 24 + (c - 3) * (c - 2) / 2 + r - 3;
+}
 
 __device__ __forceinline__ void mf_diag_body(const Grid& g, const Chunk& ck, const double* __restrict__ D,
                                              const DevCard* __restrict__ cd, double* __restrict__ E, int wg, int nb) {
@@ -504,7 +512,18 @@ __device__ __forceinline__ void mf_diag_body(const Grid& g, const Chunk& ck, con
   const double2* Dp = reinterpret_cast<const double2*>(D) + ((e >> 3) * (MF_NK / 2) * 64 + gp * 8 + (e & 7));
   const PairWeights wx = pair_weights(gp & 1), wy = pair_weights((gp >> 1) & 1), wz = pair_weights((gp >> 2) & 1);
   const double h = g.h, cuu = 0.125 * h, cue = 0.125 * h * h, cee = 0.125 * h * h * h;
-  double out[NSYM];
+  // entry `next` (order of diag_stream), nine to a stream group: a full group
+  // leaves at once, so that nine results, not 45, are live
+  double part[9];
+  int next = 0;
+  auto emit = [&](double v) {
+    part[next % 9] = v;
+    if (++next % 9) return;
+    const int r = next / 9 - 1;
+    if (r > 0) __syncthreads();
+    store_corners<double, 9>(eo, part, gp, jw, DG_EPW, bid, g.nx, ck.NEc, E + r * slab_values(ck, g.nx, 9), ck.NEcpad,
+                             slab_nw(ck), ck.NEc / g.nx);
+  };
   double F[9];
   {
     double2 v[(MF_EK) / 2];
@@ -542,8 +561,8 @@ __device__ __forceinline__ void mf_diag_body(const Grid& g, const Chunk& ck, con
         const double yz = pair_sum<2, PAIR_VD>(pair_sum<4, PAIR_VD>(d[3], wz), wy);
         const double xz = pair_sum<2, PAIR_VV>(pair_sum<4, PAIR_VD>(d[4], wz), wy);
         const double xy = pair_sum<2, PAIR_VD>(pair_sum<4, PAIR_VV>(d[5], wz), wy);
-        out[sym_index(i, k)] = pair_sum<1, PAIR_DD>(xx, wx) + pair_sum<1, PAIR_VV>(yy + zz + yz, wx) +
-                               pair_sum<1, PAIR_VD>(xz + xy, wx);
+        emit(pair_sum<1, PAIR_DD>(xx, wx) + pair_sum<1, PAIR_VV>(yy + zz + yz, wx) +
+             pair_sum<1, PAIR_VD>(xz + xy, wx));
       }
     }
   }
@@ -564,7 +583,7 @@ __device__ __forceinline__ void mf_diag_body(const Grid& g, const Chunk& ck, con
       const double x = pair_sum<2, PAIR_VV>(pair_sum<4, PAIR_VV>(c[0], wz), wy);
       const double y = pair_sum<2, PAIR_VD>(pair_sum<4, PAIR_VV>(c[1], wz), wy);
       const double z = pair_sum<2, PAIR_VV>(pair_sum<4, PAIR_VD>(c[2], wz), wy);
-      out[sym_index(i, 3 + m)] = pair_sum<1, PAIR_VD>(x, wx) + pair_sum<1, PAIR_VV>(y + z, wx);
+      emit(pair_sum<1, PAIR_VD>(x, wx) + pair_sum<1, PAIR_VV>(y + z, wx));
     }
   }
   {
@@ -577,82 +596,100 @@ __device__ __forceinline__ void mf_diag_body(const Grid& g, const Chunk& ck, con
 #pragma unroll
       for (int l = 0; l <= m; ++l, ++k) {
         const double d = cee * ((k & 1) ? v[k >> 1].y : v[k >> 1].x);
-        out[sym_index(3 + l, 3 + m)] =
-            pair_sum<1, PAIR_VV>(pair_sum<2, PAIR_VV>(pair_sum<4, PAIR_VV>(d, wz), wy), wx) + h / 3.0 * cd->Mg[l][m];
+        emit(pair_sum<1, PAIR_VV>(pair_sum<2, PAIR_VV>(pair_sum<4, PAIR_VV>(d, wz), wy), wx) + h / 3.0 * cd->Mg[l][m]);
       }
   }
-  // nine entries at a time: streams 9 r + c of each q
-#pragma unroll
-  for (int r = 0; r < 5; ++r) {
-    if (r > 0) __syncthreads();
-    double part[9];
-#pragma unroll
-    for (int c = 0; c < 9; ++c) part[c] = out[9 * r + c];
-    store_corners<double, 9>(eo, part, gp, jw, DG_EPW, bid, g.nx, ck.NEc, E + r * slab_values(ck, g.nx, 9), ck.NEcpad,
-                             slab_nw(ck), ck.NEc / g.nx);
-  }
 }
-// Node sums of the merged parts -> full diagonal blocks.  One thread per node
-// and block row (r, r..8): 45 sums per thread would leave the small levels idle.
+// Node sums of the merged parts -> full diagonal blocks.  A workgroup takes a
+// tile of 64 nodes, each wavefront five of the 45 entries with all their loads
+// in flight; the tile's blocks then leave LDS in whole 16-byte words.  (A thread
+// per node and block row, single values stored: 250 -> 153 us at 65^3 nodes, 560 MB.)
+constexpr int DG_WAVES = 9, DG_PER = DG_ENTRIES / DG_WAVES;
 __device__ __forceinline__ void mf_diag_gather_body(const Grid& g, const Chunk& ck, const double* __restrict__ E,
                                                     double* __restrict__ diag64, int bid) {
-  const int rr = bid % NDOF;
-  const int n = ck.n0 + (bid / NDOF) * 256 + threadIdx.x;
-  if (n >= ck.n1) return;
-  double* db = diag64 + (int64_t)(n >> 6) * Lay<double>::SLICE;
-  const int l = n & 63;
-  const int i = n % g.nnx, j = (n / g.nnx) % g.nny, k = n / (g.nnx * g.nny);
-  const int ez0 = (int)(ck.e0 / ((int64_t)g.nx * g.ny));
-  double s[NDOF];
+  __shared__ double sh[DG_ENTRIES * TILE];
+  const int t = ck.n0 / TILE + bid;
+  {
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = t * TILE + l;
+    double s[DG_PER];
 #pragma unroll
-  for (int c = 0; c < NDOF; ++c) s[c] = 0.0;
-  if (n < g.N) {
+    for (int u = 0; u < DG_PER; ++u) s[u] = 0.0;
+    if (n >= ck.n0 && n < ck.n1 && n < g.N) {
+      const int nz = ck.NEc / (g.nx * g.ny);
+      const int64_t nw = slab_nw(ck), nr = ck.NEc / g.nx, se = ck.NEcpad;
+      const int i = n % g.nnx, j = (n / g.nnx) % g.nny, k = n / (g.nnx * g.nny) - (int)(ck.e0 / ((int64_t)g.nx * g.ny));
+      double a[4][DG_PER], b[4][DG_PER];
+      bool in[4];
 #pragma unroll
-    for (int c = 0; c < NDOF; ++c) {
-      if (c < rr) continue;
-      const int t = sym_index(rr, c);
-      s[c] = slab_node_sum(g, ck, E + t / 9 * slab_values(ck, g.nx, 9), 9, t % 9, i, j, k - ez0);
+      for (int q = 3; q >= 0; --q) {  // element row (j - by, k - bz) holds the node at (by, bz)
+        const int ey = j - (q & 1), ez = k - (q >> 1);
+        in[q] = ey >= 0 && ey < g.ny && ez >= 0 && ez < nz;
+        const int64_t r = in[q] ? ey + (int64_t)g.ny * ez : 0, e = i + g.nx * r;
+        const bool cut = i > 0 && i < g.nx && (e & (DG_EPW - 1)) == 0;  // element e - 1 ended a workgroup
+#pragma unroll
+        for (int u = 0; u < DG_PER; ++u) {
+          const int x = w + DG_WAVES * u;  // stream x / 9 * 9 + x % 9
+          const double* G = E + x / 9 * slab_values(ck, g.nx, 9);
+          const int64_t st = 9 * q + x % 9;
+          const double* W = G + 36 * se;
+          a[q][u] = *(i < g.nx ? G + st * se + e : W + 36 * nw + st * nr + r);
+          b[q][u] = 0.0;
+          if (cut) b[q][u] = W[st * nw + e / DG_EPW - 1];
+        }
+      }
+#pragma unroll
+      for (int q = 3; q >= 0; --q)
+        if (in[q]) {
+#pragma unroll
+          for (int u = 0; u < DG_PER; ++u) s[u] += a[q][u] + b[q][u];
+        }
     }
+#pragma unroll
+    for (int u = 0; u < DG_PER; ++u) sh[(w + DG_WAVES * u) * TILE + l] = s[u];
   }
-#pragma unroll
-  for (int c = 0; c < NDOF; ++c)
-    if (c >= rr) {
-      db[Lay<double>::off(NDOF * rr + c, l)] = s[c];
-      if (c > rr) db[Lay<double>::off(NDOF * c + rr, l)] = s[c];
-    }
+  __syncthreads();
+  double2* db = reinterpret_cast<double2*>(diag64 + (int64_t)t * Lay<double>::SLICE);
+  for (int x = threadIdx.x; x < (82 / 2) * TILE; x += DG_WAVES * 64) {
+    const int e = x / TILE * 2, l = x % TILE, n = t * TILE + l;
+    if (n < ck.n0 || n >= ck.n1) continue;
+    double2 v;
+    v.x = sh[diag_stream(e / 9, e % 9) * TILE + l];
+    v.y = e + 1 < 81 ? sh[diag_stream((e + 1) / 9, (e + 1) % 9) * TILE + l] : 0.0;
+    db[x] = v;
+  }
 }
-__global__ void __launch_bounds__(256) mf_diag_kernel(Grid g, Chunk ck, const double* __restrict__ D,
+__global__ void __launch_bounds__(256, 3) mf_diag_kernel(Grid g, Chunk ck, const double* __restrict__ D,
                                                       const DevCard* __restrict__ cd, double* __restrict__ E) {
   mf_diag_body(g, ck, D, cd, E, blockIdx.x, gridDim.x);
 }
-__global__ void __launch_bounds__(256) mf_diag_gather_kernel(Grid g, Chunk ck, const double* __restrict__ E,
+__global__ void __launch_bounds__(64 * DG_WAVES) mf_diag_gather_kernel(Grid g, Chunk ck, const double* __restrict__ E,
                                                              double* __restrict__ diag64) {
   mf_diag_gather_body(g, ck, E, diag64, blockIdx.x);
 }
-__global__ void __launch_bounds__(256) mf_diag_batch(const AJob* __restrict__ jobs, int njobs) {
+__global__ void __launch_bounds__(256, 3) mf_diag_batch(const AJob* __restrict__ jobs, int njobs) {
   int bid;
   const AJob& j = find_job(jobs, njobs, bid);
   mf_diag_body(j.g, j.ck, j.D64, j.cd, j.elem, bid, j.nblk);
 }
-__global__ void __launch_bounds__(256) mf_diag_gather_batch(const AJob* __restrict__ jobs, int njobs) {
+__global__ void __launch_bounds__(64 * DG_WAVES) mf_diag_gather_batch(const AJob* __restrict__ jobs, int njobs) {
   int bid;
   const AJob& j = find_job(jobs, njobs, bid);
   mf_diag_gather_body(j.g, j.ck, j.elem, j.diag64, bid);
 }
 // values of the element buffer a slab of ne elements (padded) in rows of nx uses
-int64_t mf_diag_values(int64_t ne, int nx) { return 4 * NSYM * (ne + ne / SLAB_EPW + ne / nx + 1); }
+int64_t mf_diag_values(int64_t ne, int nx) { return 4 * DG_ENTRIES * (ne + ne / SLAB_EPW + ne / nx + 1); }
 int mf_diag_blocks(const Chunk& ck) { return ck.NEcpad / DG_EPW; }
-int mf_diag_gather_blocks(const Chunk& ck) { return (ck.n1 - ck.n0 + 255) / 256 * NDOF; }
+int mf_diag_gather_blocks(const Chunk& ck) { return (ck.n1 + TILE - 1) / TILE - ck.n0 / TILE; }
 void launch_mf_diag(const Grid& g, const Chunk& ck, const double* D64, const DevCard* cd, double* elem, double* diag64,
                     hipStream_t s) {
   if constexpr (!MF_AVAILABLE) return;
   mf_diag_kernel<<<mf_diag_blocks(ck), 256, 0, s>>>(g, ck, D64, cd, elem);
-  mf_diag_gather_kernel<<<mf_diag_gather_blocks(ck), 256, 0, s>>>(g, ck, elem, diag64);
+  mf_diag_gather_kernel<<<mf_diag_gather_blocks(ck), 64 * DG_WAVES, 0, s>>>(g, ck, elem, diag64);
 }
 void launch_mf_diag_batch(int op, const AJob* jobs, int njobs, int blocks, hipStream_t s) {
   if constexpr (!MF_AVAILABLE) return;
   if (op == AOP_MF_DIAG) mf_diag_batch<<<blocks, 256, 0, s>>>(jobs, njobs);
-  else mf_diag_gather_batch<<<blocks, 256, 0, s>>>(jobs, njobs);
+  else mf_diag_gather_batch<<<blocks, 64 * DG_WAVES, 0, s>>>(jobs, njobs);
 }
 
 // Register budgets (measured equal within 1 % for prefetch depths 12 and more
