@@ -725,12 +725,15 @@ int dense_invert_pivoted(int n, const double* a, double* inv, double* work, int*
 // all rows above.
 //
 // Bound: up to ~2000 unknowns the chain of block inversions (64 columns in
-// registers, one barrier per column; 45 us per step, launch and tile products
-// included), beyond that the tiles' traffic.  Measured against four launches
-// per 16 or 32 columns of the elimination above, with all tiles and with the
-// lower ones: 576 unknowns 2.07, 0.43 and 0.41 ms, 1125 4.23, 0.94 and 0.81,
-// 2187 12.1, 2.4 and 2.0, 3645 22.7, 6.4 and 4.2 ms.
+// registers, one barrier per column; 37 us per step, launch and tile products
+// included), beyond that the tiles' traffic.  8 wavefronts per tile: the one
+// that publishes the next column has half the columns to update after it
+// (against 4 wavefronts: 1125 unknowns 0.81 -> 0.66 ms, 3645 4.2 -> 3.1 ms).
+// Measured against four launches per 16 or 32 columns of the elimination
+// above: 576 unknowns 2.07 -> 0.33 ms, 1125 4.23 -> 0.66, 2187 12.1 -> 1.6,
+// 3645 22.7 -> 3.1 ms.
 typedef double bg_vec4 __attribute__((ext_vector_type(4)));
+constexpr int BGT = 512;  // threads of a tile's workgroup
 constexpr int BG_LDA = 66, BG_LDB = 72;  // LDS strides: the matrix instructions' operand reads meet every bank evenly
 // up to this many blocks a step forms D A_kj in every tile's workgroup; beyond,
 // a launch of its own forms the row panel and the column panel once, and the
@@ -739,41 +742,39 @@ constexpr int BG_LDA = 66, BG_LDB = 72;  // LDS strides: the matrix instructions
 constexpr int BG_FUSED_MAX = 24;
 
 // 64 x 64 x 64 product into acc: T1 (rows x k, stride BG_LDA) times T2 (k x
-// columns, stride BG_LDB); 4 wavefronts, 32 x 32 each as 2 x 2 matrix
+// columns, stride BG_LDB); 8 wavefronts, 32 x 16 each as two matrix
 // instructions of 16 x 16 x 4 (lane l: A row l % 16, k l / 16; B k l / 16,
 // column l % 16; result rows 4 r + l / 16, column l % 16)
-__device__ __forceinline__ void bgj_product(const double* T1, const double* T2, bg_vec4 (&acc)[2][2]) {
+__device__ __forceinline__ void bgj_product(const double* T1, const double* T2, bg_vec4 (&acc)[2]) {
   const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const double* pa = T1 + (32 * (w >> 1) + (l & 15)) * BG_LDA + (l >> 4);
-  const double* pb = T2 + (l >> 4) * BG_LDB + 32 * (w & 1) + (l & 15);
+  const double* pa = T1 + (32 * (w >> 2) + (l & 15)) * BG_LDA + (l >> 4);
+  const double* pb = T2 + (l >> 4) * BG_LDB + 16 * (w & 3) + (l & 15);
 #pragma unroll
   for (int k = 0; k < 16; ++k) {
     const double a0 = pa[4 * k], a1 = pa[16 * BG_LDA + 4 * k];
-    const double b0 = pb[4 * k * BG_LDB], b1 = pb[4 * k * BG_LDB + 16];
-    acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0][0], 0, 0, 0);
-    acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc[0][1], 0, 0, 0);
-    acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1][0], 0, 0, 0);
-    acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc[1][1], 0, 0, 0);
+    const double b0 = pb[4 * k * BG_LDB];
+    acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0], 0, 0, 0);
+    acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1], 0, 0, 0);
   }
 }
-// row and column of entry r of acc[x][y] in this lane
+// row and column of entry r of acc[x] in this lane
 __device__ __forceinline__ int bgj_row(int x, int r) {
-  return 32 * (threadIdx.x >> 7) + 16 * x + 4 * r + ((threadIdx.x & 63) >> 4);
+  return 32 * (threadIdx.x >> 8) + 16 * x + 4 * r + ((threadIdx.x & 63) >> 4);
 }
-__device__ __forceinline__ int bgj_col(int y) { return 32 * ((threadIdx.x >> 6) & 1) + 16 * y + (threadIdx.x & 15); }
+__device__ __forceinline__ int bgj_col() { return 16 * ((threadIdx.x >> 6) & 3) + (threadIdx.x & 15); }
 
 // a 64 x 64 tile from global memory (row stride ld) to LDS
 template <int LD>
 __device__ __forceinline__ void bgj_load(const double* __restrict__ src, int64_t ld, double* T) {
-  double2 v[8];
+  double2 v[4];
 #pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const int r = (threadIdx.x >> 5) + 8 * q, c = 2 * (threadIdx.x & 31);
+  for (int q = 0; q < 4; ++q) {
+    const int r = (threadIdx.x >> 5) + 16 * q, c = 2 * (threadIdx.x & 31);
     v[q] = *reinterpret_cast<const double2*>(src + (int64_t)r * ld + c);
   }
 #pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const int r = (threadIdx.x >> 5) + 8 * q, c = 2 * (threadIdx.x & 31);
+  for (int q = 0; q < 4; ++q) {
+    const int r = (threadIdx.x >> 5) + 16 * q, c = 2 * (threadIdx.x & 31);
     *reinterpret_cast<double2*>(T + r * LD + c) = v[q];
   }
 }
@@ -781,15 +782,15 @@ __device__ __forceinline__ void bgj_load(const double* __restrict__ src, int64_t
 // its transpose
 template <int LD>
 __device__ __forceinline__ void bgj_load_t(const double* __restrict__ src, int64_t ld, double* T) {
-  double2 v[8];
+  double2 v[4];
 #pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const int r = (threadIdx.x >> 5) + 8 * q, c = 2 * (threadIdx.x & 31);
+  for (int q = 0; q < 4; ++q) {
+    const int r = (threadIdx.x >> 5) + 16 * q, c = 2 * (threadIdx.x & 31);
     v[q] = *reinterpret_cast<const double2*>(src + (int64_t)r * ld + c);
   }
 #pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const int r = (threadIdx.x >> 5) + 8 * q, c = 2 * (threadIdx.x & 31);
+  for (int q = 0; q < 4; ++q) {
+    const int r = (threadIdx.x >> 5) + 16 * q, c = 2 * (threadIdx.x & 31);
     T[c * LD + r] = v[q].x;
     T[(c + 1) * LD + r] = v[q].y;
   }
@@ -827,8 +828,8 @@ __device__ __forceinline__ double bgj_reciprocal(double x) {
 }
 
 // Inverse of the 64 x 64 block in T (stride BG_LDA) to out (row-major): in-place
-// Gauss-Jordan in registers, lane = row, wavefront w holds columns 16 w .. 16 w
-// + 15.  The pivot of a column is the largest of its remaining entries by the
+// Gauss-Jordan in registers, lane = row, wavefront w holds columns 8 w .. 8 w
+// + 7.  The pivot of a column is the largest of its remaining entries by the
 // upper 31 bits of the magnitude (within 2^-19), ties to the lowest row; rows
 // stay in place and the permutation is undone in the final store, which also
 // takes the symmetric part (the tiles of the other triangle are never formed,
@@ -840,10 +841,10 @@ __device__ __forceinline__ double bgj_reciprocal(double x) {
 // its update.  fb: 2 x 64 published columns, ipb: 2 reciprocals, pv: 128.
 __device__ void bgj_invert(double* T, double* fb, double* ipb, int* pv, double* __restrict__ out, int* status) {
   const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
-  double a[16];
+  double a[8];
   __syncthreads();
 #pragma unroll
-  for (int j = 0; j < 16; ++j) a[j] = T[l * BG_LDA + 16 * w + j];
+  for (int j = 0; j < 8; ++j) a[j] = T[l * BG_LDA + 8 * w + j];
   bool act = true, bad = false;
   auto publish = [&](double v, int c) {  // column c, held by this wavefront
     const unsigned hi = (unsigned)(__builtin_bit_cast(unsigned long long, v) >> 32) & 0x7FFFFFFFu;
@@ -866,11 +867,11 @@ __device__ void bgj_invert(double* T, double* fb, double* ipb, int* pv, double* 
   };
   if (w == 0) publish(a[0], 0);
 #pragma unroll 1
-  for (int wc = 0; wc < 4; ++wc) {
+  for (int wc = 0; wc < 8; ++wc) {
 #pragma unroll
-    for (int jc = 0; jc < 16; ++jc) {
+    for (int jc = 0; jc < 8; ++jc) {
       __syncthreads();
-      const int c = 16 * wc + jc, jn = (jc + 1) & 15;
+      const int c = 8 * wc + jc, jn = (jc + 1) & 7;
       const int p = __builtin_amdgcn_readfirstlane(pv[c]);
       const double fl = fb[64 * (jc & 1) + l], ip = ipb[jc & 1];
       const bool mine = l == p;
@@ -883,9 +884,9 @@ __device__ void bgj_invert(double* T, double* fb, double* ipb, int* pv, double* 
         a[j] = __builtin_fma(-g, s, a[j] * keep);
       };
       update(jn);
-      if (c + 1 < 64 && w == (jc == 15 ? wc + 1 : wc)) publish(a[jn], c + 1);
+      if (c + 1 < 64 && w == (jc == 7 ? wc + 1 : wc)) publish(a[jn], c + 1);
 #pragma unroll
-      for (int j = 0; j < 16; ++j)
+      for (int j = 0; j < 8; ++j)
         if (j != jn) update(j);
       if (w == wc) a[jc] = -g;
     }
@@ -898,9 +899,9 @@ __device__ void bgj_invert(double* T, double* fb, double* ipb, int* pv, double* 
   __syncthreads();
   const int c = pos[l];
 #pragma unroll
-  for (int j = 0; j < 16; ++j) T[c * BG_LDA + pv[16 * w + j]] = a[j];
+  for (int j = 0; j < 8; ++j) T[c * BG_LDA + pv[8 * w + j]] = a[j];
   __syncthreads();
-  for (int idx = threadIdx.x; idx < BG * BG; idx += 256) {
+  for (int idx = threadIdx.x; idx < BG * BG; idx += BGT) {
     const int r = idx >> 6, q = idx & 63;
     out[idx] = 0.5 * (T[r * BG_LDA + q] + T[q * BG_LDA + r]);
   }
@@ -912,7 +913,7 @@ __device__ __forceinline__ const GJJob& bgj_job(const GJJob* __restrict__ tab, c
 }
 
 // padded copy of the matrix's lower tiles (identity in the padding), the first block's inverse
-__global__ void __launch_bounds__(256) bgj_init_kernel(const GJJob* __restrict__ tab, GJJob one) {
+__global__ void __launch_bounds__(BGT) bgj_init_kernel(const GJJob* __restrict__ tab, GJJob one) {
   __shared__ double T[BG * BG_LDA];
   __shared__ double fb[2 * BG], ipb[2];
   __shared__ int pv[2 * BG];
@@ -923,7 +924,7 @@ __global__ void __launch_bounds__(256) bgj_init_kernel(const GJJob* __restrict__
   if (ti >= nb) return;  // uniform
   const int64_t np = (int64_t)nb * BG;
   const bool first = ti == 0 && tj == 0;
-  for (int idx = threadIdx.x; idx < BG * BG; idx += 256) {
+  for (int idx = threadIdx.x; idx < BG * BG; idx += BGT) {
     const int r = idx >> 6, c = idx & 63, i = ti * BG + r, j = tj * BG + c;
     const double v = (i < n && j < n) ? jb.a[(int64_t)i * n + j] : (i == j ? 1.0 : 0.0);
     jb.b0[i * np + j] = v;
@@ -933,7 +934,7 @@ __global__ void __launch_bounds__(256) bgj_init_kernel(const GJJob* __restrict__
 }
 
 // panels of step k, tile m != k: rp_m = D A_km (64 x np), cp_m = |A_mk| (np x 64, in b1)
-__global__ void __launch_bounds__(256) bgj_panels_kernel(const GJJob* __restrict__ tab, GJJob one, int k) {
+__global__ void __launch_bounds__(BGT) bgj_panels_kernel(const GJJob* __restrict__ tab, GJJob one, int k) {
   __shared__ double T1[BG * BG_LDA];
   __shared__ double T2[BG * BG_LDB];
   const GJJob& jb = bgj_job(tab, one);
@@ -943,21 +944,19 @@ __global__ void __launch_bounds__(256) bgj_panels_kernel(const GJJob* __restrict
   bgj_load<BG_LDA>(jb.dinv + (k & 1) * BG * BG, BG, T1);
   bgj_load_row<BG_LDB>(jb.b0, np, k, m, T2);
   __syncthreads();
-  bg_vec4 acc[2][2] = {};
+  bg_vec4 acc[2] = {};
   bgj_product(T1, T2, acc);
 #pragma unroll
   for (int x = 0; x < 2; ++x)
 #pragma unroll
-    for (int y = 0; y < 2; ++y)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) jb.rp[bgj_row(x, r) * np + m * BG + bgj_col(y)] = acc[x][y][r];
+      for (int r = 0; r < 4; ++r) jb.rp[bgj_row(x, r) * np + m * BG + bgj_col()] = acc[x][r];
   // T2 holds A_km, of which |A_mk| is the transpose
   double* cp = jb.b1 + (int64_t)m * BG * BG;
-  for (int idx = threadIdx.x; idx < BG * BG; idx += 256) cp[idx] = T2[(idx & 63) * BG_LDB + (idx >> 6)];
+  for (int idx = threadIdx.x; idx < BG * BG; idx += BGT) cp[idx] = T2[(idx & 63) * BG_LDB + (idx >> 6)];
 }
 
 template <bool FUSED>
-__global__ void __launch_bounds__(256) bgj_step_kernel(const GJJob* __restrict__ tab, GJJob one, int k) {
+__global__ void __launch_bounds__(BGT) bgj_step_kernel(const GJJob* __restrict__ tab, GJJob one, int k) {
   __shared__ double T1[BG * BG_LDA];
   __shared__ double T2[BG * BG_LDB];
   __shared__ double fb[2 * BG], ipb[2];
@@ -976,15 +975,19 @@ __global__ void __launch_bounds__(256) bgj_step_kernel(const GJJob* __restrict__
   double* dst = !FUSED || (k & 1) ? jb.b0 : jb.b1;
   const double* __restrict__ D = jb.dinv + (k & 1) * BG * BG;
   const double* sij = src + (int64_t)ti * BG * np + tj * BG;
-  bg_vec4 acc[2][2] = {};
-  double sign = 1.0, keep = 0.0;  // result = sign * acc + keep * old tile
+  bg_vec4 acc[2] = {}, old[2] = {};
+  double sign = 1.0;  // result = sign * acc + old
+  if (ti != k && tj != k) {  // the old tile, in flight during the products
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) old[x][r] = sij[(int64_t)bgj_row(x, r) * np + bgj_col()];
+  }
   if (ti == k && tj == k) {
 #pragma unroll
     for (int x = 0; x < 2; ++x)
 #pragma unroll
-      for (int y = 0; y < 2; ++y)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[x][y][r] = D[bgj_row(x, r) * BG + bgj_col(y)];
+        for (int r = 0; r < 4; ++r) acc[x][r] = D[bgj_row(x, r) * BG + bgj_col()];
   } else if (tj == k) {
     bgj_load<BG_LDA>(sij, np, T1);
     bgj_load<BG_LDB>(D, BG, T2);
@@ -995,9 +998,7 @@ __global__ void __launch_bounds__(256) bgj_step_kernel(const GJJob* __restrict__
 #pragma unroll
     for (int x = 0; x < 2; ++x)
 #pragma unroll
-      for (int y = 0; y < 2; ++y)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[x][y][r] = jb.rp[bgj_row(x, r) * np + tj * BG + bgj_col(y)];
+        for (int r = 0; r < 4; ++r) acc[x][r] = jb.rp[bgj_row(x, r) * np + tj * BG + bgj_col()];
   } else {
     if (FUSED) {
       bgj_load<BG_LDA>(D, BG, T1);
@@ -1009,13 +1010,11 @@ __global__ void __launch_bounds__(256) bgj_step_kernel(const GJJob* __restrict__
       if (FUSED) {
         __syncthreads();
 #pragma unroll
-        for (int x = 0; x < 2; ++x)
+        for (int x = 0; x < 2; ++x) {
 #pragma unroll
-          for (int y = 0; y < 2; ++y) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) T2[bgj_row(x, r) * BG_LDB + bgj_col(y)] = acc[x][y][r];
-            acc[x][y] = bg_vec4{0.0, 0.0, 0.0, 0.0};
-          }
+          for (int r = 0; r < 4; ++r) T2[bgj_row(x, r) * BG_LDB + bgj_col()] = acc[x][r];
+          acc[x] = bg_vec4{0.0, 0.0, 0.0, 0.0};
+        }
         bgj_load_col<BG_LDA>(src, np, k, ti, T1);
       } else {
         bgj_load<BG_LDB>(jb.rp + tj * BG, np, T2);
@@ -1024,7 +1023,6 @@ __global__ void __launch_bounds__(256) bgj_step_kernel(const GJJob* __restrict__
       __syncthreads();
       bgj_product(T1, T2, acc);
       sign = ti > k ? -1.0 : 1.0;
-      keep = 1.0;
     }
   }
   const bool last = k == nb - 1, next = ti == k + 1 && tj == k + 1;
@@ -1032,12 +1030,9 @@ __global__ void __launch_bounds__(256) bgj_step_kernel(const GJJob* __restrict__
 #pragma unroll
   for (int x = 0; x < 2; ++x)
 #pragma unroll
-    for (int y = 0; y < 2; ++y)
-#pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int rr = bgj_row(x, r), cc = bgj_col(y);
-        double v = sign * acc[x][y][r];
-        if (keep != 0.0) v += sij[(int64_t)rr * np + cc];
+        const int rr = bgj_row(x, r), cc = bgj_col();
+        const double v = sign * acc[x][r] + old[x][r];
         if (!last) dst[((int64_t)ti * BG + rr) * np + tj * BG + cc] = v;
         if (next || last) T1[rr * BG_LDA + cc] = v;
       }
@@ -1045,7 +1040,7 @@ __global__ void __launch_bounds__(256) bgj_step_kernel(const GJJob* __restrict__
   if (!last) return;  // uniform
   __syncthreads();
   // the inverse, tile and transpose
-  for (int idx = threadIdx.x; idx < BG * BG; idx += 256) {
+  for (int idx = threadIdx.x; idx < BG * BG; idx += BGT) {
     const int r = idx >> 6, c = idx & 63;
     const int i = ti * BG + r, j = tj * BG + c, it = tj * BG + r, jt = ti * BG + c;
     if (i < n && j < n) jb.inv[(int64_t)i * n + j] = T1[r * BG_LDA + c];
@@ -1096,12 +1091,12 @@ static int bgj_run(const GJJob* tab, const GJJob& one, int nj, int nmin, int nma
   const int nb = (nmax + BG - 1) / BG;
   const bool some_fused = (nmin + BG - 1) / BG <= BG_FUSED_MAX;
   const auto tiles = [&](int b) { return dim3(b * (b + 1) / 2, 1, nj); };
-  bgj_init_kernel<<<tiles(nb), 256, 0, s>>>(tab, one);
+  bgj_init_kernel<<<tiles(nb), BGT, 0, s>>>(tab, one);
   for (int k = 0; k < nb; ++k) {  // a kernel leaves the other kind's jobs alone
-    if (some_fused && k < BG_FUSED_MAX) bgj_step_kernel<true><<<tiles(std::min(nb, BG_FUSED_MAX)), 256, 0, s>>>(tab, one, k);
+    if (some_fused && k < BG_FUSED_MAX) bgj_step_kernel<true><<<tiles(std::min(nb, BG_FUSED_MAX)), BGT, 0, s>>>(tab, one, k);
     if (nb > BG_FUSED_MAX) {
-      bgj_panels_kernel<<<dim3(nb, 1, nj), 256, 0, s>>>(tab, one, k);
-      bgj_step_kernel<false><<<tiles(nb), 256, 0, s>>>(tab, one, k);
+      bgj_panels_kernel<<<dim3(nb, 1, nj), BGT, 0, s>>>(tab, one, k);
+      bgj_step_kernel<false><<<tiles(nb), BGT, 0, s>>>(tab, one, k);
     }
   }
   bgj_apply_kernel<<<dim3((nmax + 3) / 4, 1, nj), 256, 0, s>>>(tab, one);
