@@ -380,9 +380,11 @@ __device__ __forceinline__ void convert_masked_body(const Grid& g, const TI* __r
   const int n = bid * RB + threadIdx.x;
   if (n >= g.Npad) return;
   const unsigned m = (n < g.N) ? mask[n] : (1u << NDOF) - 1u;
+  TI v[NDOF];  // loaded beside the mask, not after it
 #pragma unroll
-  for (int c = 0; c < NDOF; ++c)
-    out[(int64_t)c * g.Npad + n] = ((m >> c) & 1) ? (TO)0 : (TO)in[(int64_t)c * g.Npad + n];
+  for (int c = 0; c < NDOF; ++c) v[c] = in[(int64_t)c * g.Npad + n];
+#pragma unroll
+  for (int c = 0; c < NDOF; ++c) out[(int64_t)c * g.Npad + n] = ((m >> c) & 1) ? (TO)0 : (TO)v[c];
 }
 template <typename TI, typename TO>
 __global__ void __launch_bounds__(RB) convert_masked_kernel(Grid g, const TI* __restrict__ in,
@@ -567,10 +569,13 @@ __device__ __forceinline__ void precond_finish_body(const Grid& g, const T* __re
   const int n = bid * RB + threadIdx.x;
   if (n >= g.Npad) return;
   const unsigned m = (n < g.N) ? mask[n] : 0;
+  T xv[NDOF];  // loaded beside the mask, not after it
+#pragma unroll
+  for (int c = 0; c < NDOF; ++c) xv[c] = x[(int64_t)c * g.Npad + n];
 #pragma unroll
   for (int c = 0; c < NDOF; ++c) {
     const int64_t q = (int64_t)c * g.Npad + n;
-    z[q] = ((m >> c) & 1) ? (TZ)v[q] : (TZ)x[q];
+    z[q] = ((m >> c) & 1) ? (TZ)v[q] : (TZ)xv[c];
   }
 }
 template <typename T, typename TZ>
