@@ -437,7 +437,7 @@ int mvpf_indent(mvpf_problem* p, const mvpf_indent_opts* o, mvpf_indent_callback
  * capacity; level ignored; results bitwise unchanged.
  * "matrix_free": 1 (default for problems with two or more levels) = the
  * finest-level tangent is never assembled: its Gauss-point Hessians (Sec.
- * 3.4; 8 x 120 per element, FP64 and, in mixed mode, FP32) are stored and
+ * 3.4; 8 x 96 values per element, FP64 and, in mixed mode, FP32) are stored and
  * applied directly in the smoother, the defect and the outer product, and
  * only the diagonal blocks the smoother inverts are assembled; 0 = the
  * finest level is assembled into half-stencil blocks like the others (the
