@@ -12,8 +12,14 @@
 // depends on F through F^T F only): D v costs the same number of operations as
 // with the 120 packed entries of D_g, and the product is bound by streaming
 // them.  64^3, FP32: 188 -> 156 us per product (0.81 GB, 5.2 TB/s); 128x128x64:
-// FP32 750 -> 611 us, FP64 1513 -> 1212 us (5.3 TB/s).  Error of the FP32
-// product against 64 bits 6.1e-8 -> 6.4e-8.
+// FP32 750 -> 611 us, FP64 1513 -> 1212 us (5.3 TB/s).
+// eps and sigma are intermediate results that a product with the packed entries
+// does not round.  So the sums of D v are taken in 64 bits for either storage
+// type: a vector instruction costs the same in both, the product is bound by
+// its stream, and only 12 instead of 20 vectors are in flight (registers).
+// Error of the FP32 product against 64 bits at 64^3: 6.1e-8 with the packed
+// entries, 6.4e-8 in this form with 32-bit sums, 5.7e-8 with 64-bit ones
+// (219 and 216 us with the layout conversions around the product).
 // Stored per element: 3 KB in FP32 instead of the half-stencil blocks of its
 // node (4.7 KB) plus the assembled path's transposed contributions (0.9 KB
 // written and read per sweep).
@@ -136,7 +142,8 @@ __device__ __forceinline__ void mf_element_body(const Grid& g, const TD* __restr
   }
   // w = D v: with F = I + G, eps = sym(F^T dF) (engineering shears),
   // sigma = D_ee eps + D_ek eta, t = D_ek^T eps + D_kk eta, and back through
-  // dF: F sigma + dF S
+  // dF: F sigma + dF S.  All sums in 64 bits (see the head of the file); G and
+  // S wait in the storage type for their use at the end.
   T w[15];
 #pragma unroll
   for (int k = 0; k < 15; ++k) w[k] = 0;
@@ -155,40 +162,33 @@ __device__ __forceinline__ void mf_element_body(const Grid& g, const TD* __restr
   if (load) {
     // entry k of the stream (each taken once, in order): its vector's first
     // entry issues the load PF vectors ahead
-    auto entry = [&](int k) -> T {
+    auto entry = [&](int k) -> TD {
       if (!SPARSE && k % V == 0 && k / V + PF < NV) dq[k / V + PF] = __builtin_nontemporal_load(Dp + (k / V + PF) * ks);
-      return (T)dq[k / V][k % V];
+      return dq[k / V][k % V];
     };
-    T G[9], eps[6], sig[6];
+    TD G[9], S[6];
+    double eps[6], sig[6], t[6];
 #pragma unroll
     for (int k = 0; k < 9; ++k) G[k] = entry(MF_G + k);
 #pragma unroll
     for (int u = 0; u < 6; ++u) {
       const int j = BA(u), l = BB(u);
-      T s = j == l ? v[4 * j] : v[3 * j + l] + v[3 * l + j];
+      double s = j == l ? (double)v[4 * j] : (double)v[3 * j + l] + (double)v[3 * l + j];
 #pragma unroll
       for (int i = 0; i < 3; ++i) {
-        s += G[3 * i + j] * v[3 * i + l];
-        if (j != l) s += G[3 * i + l] * v[3 * i + j];
+        s += (double)G[3 * i + j] * (double)v[3 * i + l];
+        if (j != l) s += (double)G[3 * i + l] * (double)v[3 * i + j];
       }
       eps[u] = s;
-      sig[u] = 0;
+      sig[u] = t[u] = 0;
     }
 #pragma unroll
-    for (int u = 0; u < 6; ++u) {
-      const T d = entry(MF_S + u);
-      const int j = BA(u), l = BB(u);
-#pragma unroll
-      for (int i = 0; i < 3; ++i) {
-        w[3 * i + j] += d * v[3 * i + l];
-        if (j != l) w[3 * i + l] += d * v[3 * i + j];
-      }
-    }
+    for (int u = 0; u < 6; ++u) S[u] = entry(MF_S + u);
 #pragma unroll
     for (int p = 0, k = MF_EE; p < 6; ++p)
 #pragma unroll
       for (int q = p; q < 6; ++q, ++k) {
-        const T d = entry(k);
+        const double d = entry(k);
         sig[p] += d * eps[q];
         if (q != p) sig[q] += d * eps[p];
       }
@@ -196,26 +196,29 @@ __device__ __forceinline__ void mf_element_body(const Grid& g, const TD* __restr
     for (int m = 0; m < 6; ++m)
 #pragma unroll
       for (int u = 0; u < 6; ++u) {
-        const T d = entry(MF_EK + 6 * m + u);
-        sig[u] += d * v[9 + m];
-        w[9 + m] += d * eps[u];
+        const double d = entry(MF_EK + 6 * m + u);
+        sig[u] += d * (double)v[9 + m];
+        t[m] += d * eps[u];
       }
 #pragma unroll
     for (int m = 0, k = MF_KK; m < 6; ++m)
 #pragma unroll
       for (int l = 0; l <= m; ++l, ++k) {
-        const T d = entry(k);
-        w[9 + m] += d * v[9 + l];
-        if (l != m) w[9 + l] += d * v[9 + m];
+        const double d = entry(k);
+        t[m] += d * (double)v[9 + l];
+        if (l != m) t[l] += d * (double)v[9 + m];
       }
+#pragma unroll
+    for (int m = 0; m < 6; ++m) w[9 + m] = (T)t[m];
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
-        T s = sig[SI(i, j)];
+        double s = sig[SI(i, j)];
 #pragma unroll
-        for (int l = 0; l < 3; ++l) s += G[3 * i + l] * sig[SI(l, j)];
-        w[3 * i + j] += s;
+        for (int l = 0; l < 3; ++l)
+          s += (double)G[3 * i + l] * sig[SI(l, j)] + (double)S[SI(l, j)] * (double)v[3 * i + l];
+        w[3 * i + j] = (T)s;
       }
   }
   // gradient energy: z = (Mg (x) I) grad_ref eta
@@ -693,9 +696,9 @@ void launch_mf_diag_batch(int op, const AJob* jobs, int njobs, int blocks, hipSt
 }
 
 // Register budgets (measured equal within 1 % for prefetch depths 12 and more
-// at 2 ... 4 waves per SIMD): FP32 Hessians 20 vectors ahead at >= 3 waves
-// per SIMD, FP64 16 ahead at >= 2.
-constexpr int MF_PF32 = 20, MF_MINB32 = 3, MF_PF64 = 16, MF_MINB64 = 2;
+// at 2 ... 4 waves per SIMD): FP32 tangents 12 vectors ahead at >= 3 waves
+// per SIMD (162 registers; 14 spill), FP64 16 ahead at >= 2.
+constexpr int MF_PF32 = 12, MF_MINB32 = 3, MF_PF64 = 16, MF_MINB64 = 2;
 template <typename TD, typename TX, typename T>
 void launch_mf_element(const Grid& g, const TD* D, const TX* x, const uint16_t* mask, const DevCard* cd, T* E,
                        hipStream_t s, bool sparse_x, int elems_per_wg) {

@@ -144,3 +144,30 @@ def test_mf_merged_outputs_independent_of_workgroup_size(name):
     for o in outs[1:]:
         for a, b in zip(o, outs[0]):
             assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("amp,bound,bound_eta", [(2e-4, 6.71e-8, 8.96e-8), (5e-3, 6.73e-8, 8.34e-8)])
+def test_mf_fp32_product_rounds_no_more_than_packed_hessians(amp, bound, bound_eta):
+    """Error of the FP32 product against the FP64 one, for an input that FP32
+    holds, on the free unknowns of a 16^3 patch problem.  The bounds are the
+    errors of a product from the 120 packed FP32 Hessian entries of each point
+    on the same input, all sums in FP32 with fused multiply-adds in the
+    kernel's order, evaluated on the CPU (all unknowns; order parameters); the
+    strain form with its sums in FP32 exceeds them by 4 % and more."""
+    from paper_2011_08802_amd import mvpf
+    from oracle import solver as S
+    from oracle.fem import Mesh
+    p = synth.Problem(16, 16, 16, n_levels=3, patch=4, depth_increment=0.01)
+    U, En = seeded_state(p, amp)
+    mask, _ = S.dirichlet(Mesh.from_problem(p), p.kind, p.patch, p.radius, depth=p.depth_increment, ndof=9)
+    x = np.random.default_rng(17).standard_normal(U.shape).astype(np.float32).astype(float)
+    x[mask] = 0.0
+    gp = _mf_problem(p, U, En, p.depth_increment, "mixed")
+    free = torch.as_tensor(~mask.ravel()).cuda()
+    y64 = torch.where(free, gp.jacobian_apply(0, _dev(x), mvpf.FP64), 0.0).reshape(-1, 9)
+    d = torch.where(free, gp.jacobian_apply(0, _dev(x), mvpf.MIXED), 0.0).reshape(-1, 9) - y64
+    gp.close()
+    err = float(d.norm() / y64.norm())
+    err_eta = float(d[:, 3:].norm() / y64[:, 3:].norm())
+    say(f"    FP32 product against FP64: {err:.3e}, order parameters {err_eta:.3e}")
+    assert err <= bound and err_eta <= bound_eta, (err, err_eta)
