@@ -493,9 +493,9 @@ void launch_element_matrices(const Grid& g, const Chunk& ck, const double* qp, c
 // of loads.)  33^3 nodes: 470 -> 207 us (1.25 GB, 6 TB/s), 17^3 204 -> 27,
 // 5^3 162 -> below 16; 15 unknowns per node, 10648 nodes: 1084 -> 286.
 constexpr int JG_E = 12;  // whole 16-byte words of either type
-constexpr int JG_CHUNKS = Lay<float>::NE / JG_E;
+constexpr int JG_CHUNKS = (Lay<float>::NE + JG_E - 1) / JG_E;  // the last one may be short
 constexpr int JG_WAVES = JG_CHUNKS <= 16 ? JG_CHUNKS : (JG_CHUNKS + 1) / 2;
-static_assert(Lay<float>::NE % JG_E == 0 && JG_E % 4 == 0 && JG_WAVES <= 16);
+static_assert(JG_E % Lay<float>::V == 0 && JG_E % Lay<double>::V == 0 && JG_WAVES <= 16);
 __device__ __forceinline__ void jacobian_gather_body(const Grid& g, const Chunk& ck, const double* __restrict__ E,
                                                      double* __restrict__ A64, float* __restrict__ A32,
                                                      double* __restrict__ diag64, int nblocks, int bid, int nblk) {
@@ -540,8 +540,9 @@ __device__ __forceinline__ void jacobian_gather_body(const Grid& g, const Chunk&
       float* D = A32 + (int64_t)(t * NUP + u) * Lay<float>::SLICE;
 #pragma unroll
       for (int q = 0; q < JG_E; q += 4)
-        *reinterpret_cast<float4*>(D + Lay<float>::off(q0 + q, l)) =
-            float4{(float)K[q], (float)K[q + 1], (float)K[q + 2], (float)K[q + 3]};
+        if (q0 + q < Lay<float>::NE)
+          *reinterpret_cast<float4*>(D + Lay<float>::off(q0 + q, l)) =
+              float4{(float)K[q], (float)K[q + 1], (float)K[q + 2], (float)K[q + 3]};
     }
   }
 }
