@@ -428,7 +428,13 @@ int mvpf_indent(mvpf_problem* p, const mvpf_indent_opts* o, mvpf_indent_callback
  * 1 = the coarsest level's dense inversion runs on a second (default
  * priority) stream, overlapping the assembly of the finer levels; 0 = in
  * order on the problem's stream before them (default 1; level ignored;
- * results unchanged).
+ * results unchanged).  "coarse_pivoting": 1 = the coarsest level's dense
+ * matrix is inverted with pivoting over all rows at once; 0 (default) = by
+ * block elimination with pivoting inside 64 x 64 blocks, whose result is
+ * checked, and with pivoting over all rows only where the check rejects it
+ * (an indefinite operator); level ignored; the two inverses agree to rounding.
+ * "coarse_pivoted" (read only): 1 if the last Newton system's coarsest inverse
+ * came from pivoting over all rows.
  * "assembly_slab_elements": elements per assembly slab (0 = the capacity
  * allocated by mvpf_create: the whole finest level if its Gauss-point and
  * element-matrix buffers take at most 96 GiB, else slabs of 40 GiB).  Levels

@@ -1044,6 +1044,10 @@ void assemble_coarse_level(mvpf_problem* p, int l, double depth) {
 }
 
 int* setup_status(mvpf_problem* p) { return (int*)p->red; }  // first word of the reduction scratch
+int* setup_rejected(mvpf_problem* p) { return setup_status(p) + 1; }  // GJJob::rejected of a single inversion
+// their pinned host copies
+int* host_status(mvpf_problem* p) { return (int*)(p->hhost + 3 * (MAX_RESTART + 2)); }
+int* host_rejected(mvpf_problem* p) { return host_status(p) + 1; }
 
 // The coarsest operator is assembled first; its dense gather and inversion
 // then run on the side stream while the main stream assembles the finer
@@ -1055,7 +1059,7 @@ int* setup_status(mvpf_problem* p) { return (int*)p->red; }  // first word of th
 int system_prelude(mvpf_problem* p, double depth) {
   hipStream_t s = p->stream;
   Level& L0 = p->lev[0];
-  HIPCHK(hipMemsetAsync(setup_status(p), 0, sizeof(int), s));
+  HIPCHK(hipMemsetAsync(setup_status(p), 0, 2 * sizeof(int), s));
   launch_dirichlet_masks(L0.g, p->load, depth, L0.mask, L0.target, s);
   for (int l = 1; l < p->L; ++l) {
     launch_inject_mask(p->lev[l - 1].g, p->lev[l].g, p->lev[l - 1].mask, p->lev[l].mask, s);
@@ -1087,6 +1091,15 @@ int system_rhs(mvpf_problem* p, double depth) {
 }
 
 double* coarse_dense(mvpf_problem* p) { return p->coarse_work ? p->coarse_work : p->V; }
+// the coarsest level's inversion: input its dense operator, workspace behind it
+GJJob coarse_job(mvpf_problem* p, int* rejected) {
+  Level& C = p->lev[p->L - 1];
+  double* work = coarse_dense(p);
+  return gj_make_job(C.ndense, work, C.Ainv, work + (int64_t)C.ndense * C.ndense, setup_status(p), rejected);
+}
+bool coarse_overlaps(const mvpf_problem* p) {
+  return p->coarse_overlap < 0 ? p->lev[p->L - 1].ndense <= COARSE_OVERLAP_MAX : p->coarse_overlap != 0;
+}
 
 // the coarsest level's eliminated operator -> dense matrix; marks it ready
 int coarse_fork(mvpf_problem* p, bool coarse_inline) {
@@ -1108,20 +1121,19 @@ int finish_system(mvpf_problem* p, bool coarse_inline) {
   }
   TRY(launch_check(p, "assembly"));
   if (coarse_inline) {
-    Level& C = p->lev[p->L - 1];
-    const int nd = C.ndense;
-    double* work = coarse_dense(p);
-    const bool overlap = p->coarse_overlap < 0 ? nd <= COARSE_OVERLAP_MAX : p->coarse_overlap != 0;
+    const bool overlap = coarse_overlaps(p);
     hipStream_t cs = overlap ? p->side : s;
     if (overlap) HIPCHK(hipStreamWaitEvent(p->side, p->ev_fork, 0));
-    if (dense_invert(nd, work, C.Ainv, work + (int64_t)nd * nd, setup_status(p), cs) != 0) {
+    const GJJob job = coarse_job(p, setup_rejected(p));
+    p->coarse_pivoted = p->coarse_pivoting != 0;
+    if ((p->coarse_pivoted ? dense_invert_pivoted(job, cs) : dense_invert(job, cs)) != 0) {
       p->err = "coarse inversion launch failed";
       return MVPF_EDEVICE;
     }
-    if (overlap) {
-      HIPCHK(hipEventRecord(p->ev_join, p->side));
-      p->coarse_pending = true;
-    }
+    // setup_solver waits for this copy (and for the main stream only after it)
+    HIPCHK(hipMemcpyAsync(host_rejected(p), setup_rejected(p), sizeof(int), hipMemcpyDeviceToHost, cs));
+    HIPCHK(hipEventRecord(p->ev_join, cs));
+    p->coarse_pending = overlap;
     TRY(launch_check(p, "coarse inversion"));
   }
   return 0;
@@ -1276,9 +1288,6 @@ int build_system(mvpf_problem* p, double depth, bool coarse_inline = true) {
   return finish_system(p, coarse_inline);
 }
 
-// pinned host slot of the setup status
-int* host_status(mvpf_problem* p) { return (int*)(p->hhost + 3 * (MAX_RESTART + 2)); }
-
 // joins the coarse inversion; status -> host (build_system enqueued the
 // smoother's block inverses)
 int setup_enqueue(mvpf_problem* p) {
@@ -1295,21 +1304,6 @@ int setup_enqueue(mvpf_problem* p) {
 
 // after the problem's stream has been synchronised
 int setup_finish(mvpf_problem* p) {
-  if (*host_status(p) == GJ_REJECTED) {
-    // the coarsest operator's block elimination failed its check: invert it
-    // with pivoting over all rows (its dense copy is untouched)
-    hipStream_t s = p->stream;
-    Level& C = p->lev[p->L - 1];
-    const int nd = C.ndense;
-    double* work = coarse_dense(p);
-    HIPCHK(hipMemsetAsync(setup_status(p), 0, sizeof(int), s));
-    if (dense_invert_pivoted(nd, work, C.Ainv, work + (int64_t)nd * nd, setup_status(p), s) != 0) {
-      p->err = "coarse inversion launch failed";
-      return MVPF_EDEVICE;
-    }
-    HIPCHK(hipMemcpyAsync(host_status(p), setup_status(p), sizeof(int), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-  }
   if (*host_status(p)) {
     p->err = "singular 9x9 diagonal block or coarse operator";
     return MVPF_ESINGULAR;
@@ -1317,8 +1311,29 @@ int setup_finish(mvpf_problem* p) {
   return 0;
 }
 
+// The check of the coarse inversion is looked at as soon as the inversion is
+// done, while the main stream still assembles: an operator that fails it is
+// inverted again with pivoting over all rows (its dense copy is untouched) on
+// the same stream, beside the rest of the assembly.  The main stream is made to
+// wait for that chain of several hundred short launches only when it is done: a
+// barrier pending in one queue slows the other's dispatch (1125 unknowns, 16^3:
+// a system of 5.45 ms so, 5.16 ms with the host waiting).
 int setup_solver(mvpf_problem* p) {
   TRY(setup_enqueue(p));
+  HIPCHK(hipEventSynchronize(p->ev_join));
+  if (*host_rejected(p)) {
+    const bool overlap = coarse_overlaps(p);
+    hipStream_t cs = overlap ? p->side : p->stream;
+    if (dense_invert_pivoted(coarse_job(p, setup_rejected(p)), cs) != 0) {
+      p->err = "coarse inversion launch failed";
+      return MVPF_EDEVICE;
+    }
+    p->coarse_pivoted = true;
+    HIPCHK(hipEventRecord(p->ev_join, cs));
+    HIPCHK(hipEventSynchronize(p->ev_join));
+    p->coarse_pending = overlap;
+    TRY(setup_enqueue(p));
+  }
   HIPCHK(hipStreamSynchronize(p->stream));
   return setup_finish(p);
 }
@@ -1530,6 +1545,10 @@ struct mvpf_batch {
   // the coarsest-level inversions of all problems as one batched inversion
   mvpf::GJJob* gj_tab = nullptr;
   std::vector<int> gj_n;
+  // their check's results (device and pinned copy), and the table of those to
+  // be inverted again with pivoting over all rows
+  int *gj_rejected = nullptr, *gj_rejected_host = nullptr;
+  mvpf::GJJob* gj_again = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   std::vector<int> graph_version;  // config_version of each problem at capture
@@ -2159,6 +2178,46 @@ struct AsmStep {
   std::function<int()> host;
 };
 
+// all coarsest-level inversions at once, on the batch's work stream
+int batch_invert(mvpf_batch* b) {
+  BCHK(hipMemsetAsync(b->gj_rejected, 0, sizeof(int) * b->n, b->work));
+  if (dense_invert_batch(b->gj_tab, b->gj_n, b->work) != 0) {
+    b->err = "batched coarse inversion launch failed";
+    return MVPF_EDEVICE;
+  }
+  BCHK(hipMemcpyAsync(b->gj_rejected_host, b->gj_rejected, sizeof(int) * b->n, hipMemcpyDeviceToHost, b->work));
+  return 0;
+}
+
+// The operators that failed the check, again at once and with pivoting over
+// all rows, beside what the other streams still assemble; the streams are
+// synchronised and every problem's status is on the host when it returns.
+int batch_invert_again(mvpf_batch* b, const std::vector<hipStream_t>& streams) {
+  BCHK(hipStreamSynchronize(b->work));
+  std::vector<GJJob> tab;
+  std::vector<int> ns, which;
+  for (int i = 0; i < b->n; ++i) {
+    mvpf_problem* p = b->probs[i];
+    p->coarse_pivoted = p->coarse_pivoting || b->gj_rejected_host[i];
+    if (!p->coarse_pivoted) continue;
+    tab.push_back(coarse_job(p, b->gj_rejected + i));
+    ns.push_back(tab.back().n);
+    which.push_back(i);
+  }
+  if (!tab.empty()) {
+    BCHK(hipMemcpyAsync(b->gj_again, tab.data(), sizeof(GJJob) * tab.size(), hipMemcpyHostToDevice, b->work));
+    if (dense_invert_pivoted_batch(b->gj_again, ns, b->work) != 0) {
+      b->err = "batched coarse inversion launch failed";
+      return MVPF_EDEVICE;
+    }
+  }
+  for (hipStream_t st : streams) BCHK(hipStreamSynchronize(st));
+  BCHK(hipStreamSynchronize(b->work));
+  for (int i : which)
+    BCHK(hipMemcpy(host_status(b->probs[i]), setup_status(b->probs[i]), sizeof(int), hipMemcpyDeviceToHost));
+  return 0;
+}
+
 int batch_assemble(mvpf_batch* b, const double* depths, hipStream_t s) {
   std::vector<AsmStep> steps;
   std::vector<AJob> all;
@@ -2328,10 +2387,7 @@ int batch_assemble(mvpf_batch* b, const double* depths, hipStream_t s) {
     // after the assembly so that the host feeds the assembly stream first
     host([b]() -> int {
       BCHK(hipStreamWaitEvent(b->work, b->fork, 0));
-      if (dense_invert_batch(b->gj_tab, b->gj_n, b->work) != 0) {
-        b->err = "batched coarse inversion launch failed";
-        return MVPF_EDEVICE;
-      }
+      TRY(batch_invert(b));
       BCHK(hipEventRecord(b->leave, b->work));
       return 0;
     });
@@ -2386,7 +2442,9 @@ void batch_free(mvpf_batch* b) {
   if (b->fork) (void)hipEventDestroy(b->fork);
   if (b->enter) (void)hipEventDestroy(b->enter);
   if (b->leave) (void)hipEventDestroy(b->leave);
-  if (b->gj_tab) (void)hipFree(b->gj_tab);
+  for (void* d : {(void*)b->gj_tab, (void*)b->gj_again, (void*)b->gj_rejected})
+    if (d) (void)hipFree(d);
+  if (b->gj_rejected_host) (void)hipHostFree(b->gj_rejected_host);
   if (b->jobs_dev) (void)hipFree(b->jobs_dev);
   b->jobs_dev = nullptr;
   b->jobs_cap = 0;
@@ -2403,7 +2461,8 @@ void batch_free(mvpf_batch* b) {
   b->ojobs_host = nullptr;
   b->gjobs_host = nullptr;
   b->bcol_host = nullptr;
-  b->gj_tab = nullptr;
+  b->gj_tab = b->gj_again = nullptr;
+  b->gj_rejected = b->gj_rejected_host = nullptr;
   if (b->work) {
     (void)hipStreamSynchronize(b->work);
     (void)hipStreamDestroy(b->work);
@@ -2714,15 +2773,14 @@ int mvpf_newton_step(mvpf_problem* p, double depth, mvpf_solve_stats* stats) {
 
 namespace {
 
-struct EventPair {
-  hipEvent_t a = nullptr, b = nullptr;
-  EventPair() {
-    (void)hipEventCreate(&a);
-    (void)hipEventCreate(&b);
+struct Events {
+  hipEvent_t a = nullptr, b = nullptr, c = nullptr;
+  Events() {
+    for (hipEvent_t* e : {&a, &b, &c}) (void)hipEventCreate(e);
   }
-  ~EventPair() {
-    if (a) (void)hipEventDestroy(a);
-    if (b) (void)hipEventDestroy(b);
+  ~Events() {
+    for (hipEvent_t e : {a, b, c})
+      if (e) (void)hipEventDestroy(e);
   }
 };
 
@@ -2735,7 +2793,7 @@ struct EventPair {
 // iterations without success (*ok false, return 0); other errors are
 // returned.  Timings and iteration counts accumulate into st; *its = the
 // solves made.
-int newton_iterate(mvpf_problem* p, double trial, mvpf_step_stats* st, int* its, bool* ok, EventPair& ev) {
+int newton_iterate(mvpf_problem* p, double trial, mvpf_step_stats* st, int* its, bool* ok, Events& ev) {
   Level& L0 = p->lev[0];
   double b0 = 0.0;
   for (int it = 0; it <= p->opts.newton_max; ++it) {
@@ -2751,13 +2809,11 @@ int newton_iterate(mvpf_problem* p, double trial, mvpf_step_stats* st, int* its,
     (void)hipEventRecord(ev.a, p->stream);
     TRY(build_system(p, trial));
     (void)hipEventRecord(ev.b, p->stream);
-    (void)hipEventSynchronize(ev.b);
-    st->assemble_ms += elapsed_ms(ev.a, ev.b);
-    (void)hipEventRecord(ev.a, p->stream);
     const int srs = setup_solver(p);
-    (void)hipEventRecord(ev.b, p->stream);
-    (void)hipEventSynchronize(ev.b);
-    st->setup_ms += elapsed_ms(ev.a, ev.b);
+    (void)hipEventRecord(ev.c, p->stream);
+    (void)hipEventSynchronize(ev.c);
+    st->assemble_ms += elapsed_ms(ev.a, ev.b);
+    st->setup_ms += elapsed_ms(ev.b, ev.c);
     if (srs == MVPF_ESINGULAR) return 0;  // a failed attempt: the caller halves the increment
     TRY(srs);
     p->sys_depth = trial;
@@ -2786,7 +2842,7 @@ int newton_iterate(mvpf_problem* p, double trial, mvpf_step_stats* st, int* its,
 int newton_attempt(mvpf_problem* p, double trial, mvpf_step_stats* st, int* its, bool* ok) {
   Level& L0 = p->lev[0];
   const size_t sbytes = sizeof(double) * NSTATE * L0.g.Npad;
-  EventPair ev;
+  Events ev;
   *ok = false;
   *its = 0;
   const double depth0 = p->depth;  // the updates move it with the state
@@ -3004,6 +3060,9 @@ int mvpf_set_tuning(mvpf_problem* p, const char* key, int level, int value) {
     p->small_nodes = value;
   } else if (!std::strcmp(key, "coarse_overlap")) {
     p->coarse_overlap = value;
+  } else if (!std::strcmp(key, "coarse_pivoting")) {
+    if (value > 1) { p->err = "coarse_pivoting is 0 or 1"; return MVPF_EINVAL; }
+    p->coarse_pivoting = value;
   } else if (!std::strcmp(key, "autotune_cache")) {
     if (value > 1) { p->err = "autotune_cache is 0 or 1"; return MVPF_EINVAL; }
     p->tune_cache_use = value;
@@ -3058,8 +3117,11 @@ int mvpf_get_tuning(const mvpf_problem* p, const char* key, int level, int* valu
   } else if (!std::strcmp(key, "autotune_cache")) {
     *value = p->tune_cache_use;
   } else if (!std::strcmp(key, "coarse_overlap")) {
-    const int nd = p->lev[p->L - 1].ndense;
-    *value = p->coarse_overlap < 0 ? (nd <= COARSE_OVERLAP_MAX ? 1 : 0) : (p->coarse_overlap != 0);
+    *value = coarse_overlaps(p);
+  } else if (!std::strcmp(key, "coarse_pivoting")) {
+    *value = p->coarse_pivoting;
+  } else if (!std::strcmp(key, "coarse_pivoted")) {
+    *value = p->coarse_pivoted;
   } else {
     return MVPF_EINVAL;
   }
@@ -3161,16 +3223,18 @@ int mvpf_create_batch(int n, const mvpf_mesh* meshes, const mvpf_material* mats,
     // job table of the batched coarse inversion (workspaces fixed per problem)
     std::vector<GJJob> tab(n);
     b->gj_n.resize(n);
-    for (int i = 0; i < n; ++i) {
-      mvpf_problem* p = b->probs[i];
-      Level& C = p->lev[p->L - 1];
-      const int nd = C.ndense;
-      double* work = p->coarse_work ? p->coarse_work : p->V;
-      tab[i] = gj_make_job(nd, work, C.Ainv, work + (int64_t)nd * nd, setup_status(p));
-      b->gj_n[i] = nd;
+    if (hipMalloc((void**)&b->gj_rejected, sizeof(int) * n) != hipSuccess) {
+      g_create_err = "batch job tables failed";
+      rc = MVPF_ENOMEM;
     }
-    if (hipMalloc((void**)&b->gj_tab, sizeof(GJJob) * n) != hipSuccess ||
-        hipMemcpy(b->gj_tab, tab.data(), sizeof(GJJob) * n, hipMemcpyHostToDevice) != hipSuccess) {
+    for (int i = 0; i < n && rc == 0; ++i) {
+      tab[i] = coarse_job(b->probs[i], b->gj_rejected + i);
+      b->gj_n[i] = tab[i].n;
+    }
+    if (rc == 0 && (hipMalloc((void**)&b->gj_tab, sizeof(GJJob) * n) != hipSuccess ||
+        hipMalloc((void**)&b->gj_again, sizeof(GJJob) * n) != hipSuccess ||
+        hipHostMalloc((void**)&b->gj_rejected_host, sizeof(int) * n) != hipSuccess ||
+        hipMemcpy(b->gj_tab, tab.data(), sizeof(GJJob) * n, hipMemcpyHostToDevice) != hipSuccess)) {
       g_create_err = "batch job tables failed";
       rc = MVPF_ENOMEM;
     }
@@ -3223,6 +3287,7 @@ int mvpf_batch_newton_system(mvpf_batch* b, const double* depths) {
     }
     rc = batch_assemble(b, depths, s);
     for (mvpf_problem* p : b->probs) p->stream = b->stream;
+    if (rc == 0) rc = batch_invert_again(b, {s});
     (void)hipStreamSynchronize(s);
     (void)hipStreamSynchronize(b->work);
     if (rc) return rc;
@@ -3248,10 +3313,7 @@ int mvpf_batch_newton_system(mvpf_batch* b, const double* depths) {
     // every problem's dense coarse matrix is ready; each problem's setup waits
     if (rc == 0) {
       for (int i = 0; i < b->n; ++i) BCHK(hipStreamWaitEvent(b->work, b->probs[i]->ev_fork, 0));
-      if (dense_invert_batch(b->gj_tab, b->gj_n, b->work) != 0) {
-        b->err = "batched coarse inversion launch failed";
-        rc = MVPF_EDEVICE;
-      }
+      rc = batch_invert(b);
       for (int i = 0; i < b->n && rc == 0; ++i) BCHK(hipEventRecord(b->probs[i]->ev_join, b->work));
     }
     for (int oi = 0; oi < b->n && rc == 0; ++oi) {
@@ -3262,9 +3324,11 @@ int mvpf_batch_newton_system(mvpf_batch* b, const double* depths) {
       p->stream = b->stream;
       if (rc) bad = i;
     }
+    if (rc == 0) rc = batch_invert_again(b, b->branch);
     for (int i = 0; i < b->n; ++i) (void)hipStreamSynchronize(b->branch[i]);
+    (void)hipStreamSynchronize(b->work);
     if (rc) {
-      b->err = "problem " + std::to_string(bad) + ": " + b->probs[bad]->err;
+      if (bad >= 0) b->err = "problem " + std::to_string(bad) + ": " + b->probs[bad]->err;
       return rc;
     }
   }

@@ -81,10 +81,32 @@ constexpr int GJB = 32;   // widest sub-panel
 constexpr int GJ_NB = 128;  // outer panel width
 constexpr int GJ_THREADS = 512;
 
+// Several inversions can run as one: every kernel of either elimination works on
+// job z of a device table, or on the one job passed by value (a type of its own:
+// a choice at run time puts the job's pointers behind vector loads, 1125
+// unknowns with pivoting over all rows 4.4 -> 4.8 ms).  Each job keeps its own
+// panel widths and kernel variants, so it computes the same numbers alone or in
+// a batch.
+struct GJOne {
+  GJJob job;
+  __device__ __forceinline__ const GJJob& get() const { return job; }
+};
+struct GJTab {
+  const GJJob* tab;
+  __device__ __forceinline__ const GJJob& get() const { return tab[blockIdx.z]; }
+};
+
 // sub-panel width: up to 4 rows per thread the sub-panel is factored in one
 // workgroup's registers, beyond that by tournament pivoting
 __host__ __device__ inline int gj_pbw(int n) { return (n > 4 * GJ_THREADS || n <= 2 * GJ_THREADS) ? GJB : 16; }
-// the sub-panel at (c0, s0), if there is one: outer-panel width nbw, width B
+// how a job's sub-panels are factored: gj_panel_kernel with 1 to 4 rows per
+// thread (0 ... 3) or 5 rows per thread of a half-size workgroup (4), or by
+// tournament pivoting (5); a launch leaves the jobs of other variants alone
+constexpr int GJ_VARIANTS = 6;
+__host__ __device__ inline int gj_variant(int n) {
+  return n > 4 * GJ_THREADS ? 5 : n > 2 * GJ_THREADS && n <= 5 * 256 ? 4 : (n - 1) / GJ_THREADS;
+}
+// the job's sub-panel at (c0, s0), if it has one: outer-panel width nbw, width B
 __device__ __forceinline__ bool gj_step(int n, int c0, int s0, int& nbw, int& B) {
   if (c0 >= n) return false;
   nbw = min(GJ_NB, n - c0);
@@ -263,11 +285,12 @@ __device__ int window_eliminate(double (&W)[RPT][PB], bool (&act)[RPT], const in
 // A column costs every wavefront the same pivot search whatever its row
 // count, so fewer, fuller wavefronts (NT = 256, 5 rows per thread) take less
 // time per column than 512 threads with 3 rows each.
-template <int RPT, int PB, int NT>
-__global__ void __launch_bounds__(NT) gj_panel_kernel(GJJob jb, int oc0, int c0) {
+template <int RPT, int PB, int NT, class Jobs>
+__global__ void __launch_bounds__(NT) gj_panel_kernel(Jobs jobs, int variant, int oc0, int c0) {
+  const GJJob& jb = jobs.get();
   const int n = jb.n;
   int nbw_, B;
-  if (!gj_step(n, oc0, c0, nbw_, B)) return;  // uniform
+  if (gj_variant(n) != variant || !gj_step(n, oc0, c0, nbw_, B)) return;  // uniform
   double* __restrict__ M = jb.M;
   const double* __restrict__ F = jb.F;
   const double* __restrict__ Wc = jb.Wc;
@@ -327,7 +350,9 @@ __device__ __forceinline__ int64_t gj_col(int n, int c0, int nbw, int j) {
 }
 
 // R[a][j] = sum_b Pinv[a][b] M[prow[s0 + b]][col(j)] over the active columns
-__global__ void __launch_bounds__(256) gj_rows_kernel(GJJob jb, int c0, int s0) {
+template <class Jobs>
+__global__ void __launch_bounds__(256) gj_rows_kernel(Jobs jobs, int c0, int s0) {
+  const GJJob& jb = jobs.get();
   const int n = jb.n;
   int nbw, B;
   if (!gj_step(n, c0, s0, nbw, B)) return;
@@ -353,7 +378,9 @@ __global__ void __launch_bounds__(256) gj_rows_kernel(GJJob jb, int c0, int s0) 
 // Over the active columns: rows pivoted in this sub-panel become R, every
 // other row i becomes M[i] - F[i, :] R.  Block: UPR rows x 256 columns.
 constexpr int UPR = 8;
-__global__ void __launch_bounds__(256) gj_update_kernel(GJJob jb, int c0, int s0) {
+template <class Jobs>
+__global__ void __launch_bounds__(256) gj_update_kernel(Jobs jobs, int c0, int s0) {
+  const GJJob& jb = jobs.get();
   __shared__ double Fs[UPR][GJB];
   __shared__ int sub[UPR];  // sub-panel position of each row, or -1
   const int n = jb.n;
@@ -430,7 +457,9 @@ __global__ void __launch_bounds__(256) gj_update_kernel(GJJob jb, int c0, int s0
 // rounding.  Two launches per sub-panel instead of one per column.
 
 // F[i][b] = Wc[b][i] = M[i][s0 + b]
-__global__ void __launch_bounds__(256) gj_fetch_kernel(GJJob jb, int c0, int s0) {
+template <class Jobs>
+__global__ void __launch_bounds__(256) gj_fetch_kernel(Jobs jobs, int c0, int s0) {
+  const GJJob& jb = jobs.get();
   const int n = jb.n;
   int nbw, B;
   if (!gj_step(n, c0, s0, nbw, B)) return;
@@ -446,14 +475,16 @@ __global__ void __launch_bounds__(256) gj_fetch_kernel(GJJob jb, int c0, int s0)
   Wc[(int64_t)b * n + i] = v;
 }
 
-__global__ void __launch_bounds__(GJ_THREADS) gj_tourn0_kernel(GJJob jb, int c0, int s0) {
+template <class Jobs>
+__global__ void __launch_bounds__(GJ_THREADS) gj_tourn0_kernel(Jobs jobs, int c0, int s0) {
+  const GJJob& jb = jobs.get();
   __shared__ double cv[2][NWV];
   __shared__ int ci[2][NWV];
   __shared__ double crow[2][NWV][GJB];
   __shared__ int pv[GJB];  // the block's pivot rows (written to global memory after the elimination)
   const int n = jb.n;
   int nbw, B;
-  if (!gj_step(n, c0, s0, nbw, B)) return;  // uniform
+  if (gj_variant(n) != 5 || !gj_step(n, c0, s0, nbw, B)) return;  // uniform
   const double* __restrict__ Wc = jb.Wc;
   const int* __restrict__ done = jb.done;
   int* __restrict__ cand = jb.cand;
@@ -472,7 +503,9 @@ __global__ void __launch_bounds__(GJ_THREADS) gj_tourn0_kernel(GJJob jb, int c0,
   for (int jj = threadIdx.x; jj < GJB; jj += blockDim.x) mine[jj] = jj < got ? pv[jj] : -1;
 }
 
-__global__ void __launch_bounds__(GJ_THREADS) gj_tourn1_kernel(GJJob jb, int c0, int s0) {
+template <class Jobs>
+__global__ void __launch_bounds__(GJ_THREADS) gj_tourn1_kernel(Jobs jobs, int c0, int s0) {
+  const GJJob& jb = jobs.get();
   __shared__ double Mp[GJB][2 * GJB];
   __shared__ double fr[GJB];
   __shared__ double rowc[2 * GJB];
@@ -482,7 +515,7 @@ __global__ void __launch_bounds__(GJ_THREADS) gj_tourn1_kernel(GJJob jb, int c0,
   __shared__ double crow[2][NWV][GJB];
   const int n = jb.n;
   int nbw, B;
-  if (!gj_step(n, c0, s0, nbw, B)) return;  // uniform
+  if (gj_variant(n) != 5 || !gj_step(n, c0, s0, nbw, B)) return;  // uniform
   const int nblk = (n + GJ_THREADS - 1) / GJ_THREADS;
   double* __restrict__ M = jb.M;
   const double* __restrict__ F = jb.F;
@@ -517,7 +550,9 @@ __global__ void __launch_bounds__(GJ_THREADS) gj_tourn1_kernel(GJJob jb, int c0,
 }
 
 // Yo[i][k] = M[i][n + c0 + k] - [i == p_{c0+k}];  Rb[k][j] = M[p_{c0+k}][c0 + nbw + j]
-__global__ void __launch_bounds__(256) gj_gather_kernel(GJJob jb, int c0) {
+template <class Jobs>
+__global__ void __launch_bounds__(256) gj_gather_kernel(Jobs jobs, int c0) {
+  const GJJob& jb = jobs.get();
   const int n = jb.n;
   if (c0 >= n) return;
   const int nbw = min(GJ_NB, n - c0);
@@ -546,7 +581,9 @@ __global__ void __launch_bounds__(256) gj_gather_kernel(GJJob jb, int c0) {
 // M[i][c0 + nbw + j] += sum_k Yo[i][k] Rb[k][j]  (i < n, j < n - nbw).
 // 64 x 64 output tile per workgroup, 4 x 4 per thread, K staged in LDS by 16.
 constexpr int GT = 64, GK = 16;
-__global__ void __launch_bounds__(256) gj_gemm_kernel(GJJob jb, int c0) {
+template <class Jobs>
+__global__ void __launch_bounds__(256) gj_gemm_kernel(Jobs jobs, int c0) {
+  const GJJob& jb = jobs.get();
   __shared__ double Ys[GK][GT + 1];
   __shared__ double Rs[GK][GT + 1];
   const int n = jb.n;
@@ -599,7 +636,9 @@ __global__ void __launch_bounds__(256) gj_gemm_kernel(GJJob jb, int c0) {
   }
 }
 
-__global__ void __launch_bounds__(256) gj_init_kernel(GJJob jb) {
+template <class Jobs>
+__global__ void __launch_bounds__(256) gj_init_kernel(Jobs jobs) {
+  const GJJob& jb = jobs.get();
   const int n = jb.n;
   const double* __restrict__ a = jb.a;
   double* __restrict__ M = jb.M;
@@ -620,7 +659,9 @@ __global__ void __launch_bounds__(256) gj_init_kernel(GJJob jb) {
 }
 
 // A^-1[k][p_m] = M[p_k][n + m]
-__global__ void __launch_bounds__(256) gj_extract_kernel(GJJob jb) {
+template <class Jobs>
+__global__ void __launch_bounds__(256) gj_extract_kernel(Jobs jobs) {
+  const GJJob& jb = jobs.get();
   const int n = jb.n;
   const double* __restrict__ M = jb.M;
   const int* __restrict__ prow = jb.prow;
@@ -649,13 +690,14 @@ size_t dense_invert_work(int n) {
   return std::max(pivoted, block);
 }
 
-GJJob gj_make_job(int n, const double* a, double* inv, double* work, int* status) {
+GJJob gj_make_job(int n, const double* a, double* inv, double* work, int* status, int* rejected) {
   GJJob j;
   const int64_t np = bgj_pad(n);
   j.n = n;
   j.a = a;
   j.inv = inv;
   j.status = status;
+  j.rejected = rejected;
   j.b0 = (double*)(((uintptr_t)work + 15) / 16 * 16);  // 16-byte loads
   j.b1 = j.b0 + np * np;
   j.dinv = j.b1 + np * np;
@@ -674,37 +716,49 @@ GJJob gj_make_job(int n, const double* a, double* inv, double* work, int* status
   return j;
 }
 
-// Inversion with partial pivoting over all rows, for the matrices the block
-// elimination's check rejects.  n <= 16 GJ_THREADS (MVPF_MAX_COARSE_DOF).
-int dense_invert_pivoted(int n, const double* a, double* inv, double* work, int* status, hipStream_t s) {
-  if (n > 16 * GJ_THREADS) return -1;  // at most 16 tournament blocks
-  const GJJob jb = gj_make_job(n, a, inv, work, status);
-  gj_init_kernel<<<1024, 256, 0, s>>>(jb);
-  const int step = gj_pbw(n);
-  for (int c0 = 0; c0 < n; c0 += GJ_NB) {
-    for (int s0 = c0; s0 < std::min(n, c0 + GJ_NB); s0 += step) {
-      gj_fetch_kernel<<<(n * GJB + 255) / 256, 256, 0, s>>>(jb, c0, s0);
-      if (n > 4 * GJ_THREADS) {
-        gj_tourn0_kernel<<<(n + GJ_THREADS - 1) / GJ_THREADS, GJ_THREADS, 0, s>>>(jb, c0, s0);
-        gj_tourn1_kernel<<<1, GJ_THREADS, 0, s>>>(jb, c0, s0);
-      } else if (n > 2 * GJ_THREADS && n <= 5 * 256) {
-        gj_panel_kernel<5, 16, 256><<<1, 256, 0, s>>>(jb, c0, s0);
-      } else {
-        switch ((n - 1) / GJ_THREADS) {
-          case 0: gj_panel_kernel<1, 32, GJ_THREADS><<<1, GJ_THREADS, 0, s>>>(jb, c0, s0); break;
-          case 1: gj_panel_kernel<2, 32, GJ_THREADS><<<1, GJ_THREADS, 0, s>>>(jb, c0, s0); break;
-          case 2: gj_panel_kernel<3, 16, GJ_THREADS><<<1, GJ_THREADS, 0, s>>>(jb, c0, s0); break;
-          default: gj_panel_kernel<4, 16, GJ_THREADS><<<1, GJ_THREADS, 0, s>>>(jb, c0, s0);
+// Inversions with partial pivoting over all rows, for the matrices the block
+// elimination's check rejects: jobs of sizes ns, n <= 16 GJ_THREADS
+// (MVPF_MAX_COARSE_DOF).
+template <class Jobs>
+static int gj_run(const Jobs& jobs, const std::vector<int>& ns, hipStream_t s) {
+  const int nj = (int)ns.size();
+  const int nmax = *std::max_element(ns.begin(), ns.end());
+  if (nmax > 16 * GJ_THREADS) return -1;  // at most 16 tournament blocks
+  bool have[GJ_VARIANTS] = {};
+  for (int n : ns) have[gj_variant(n)] = true;
+  gj_init_kernel<<<dim3(1024, 1, nj), 256, 0, s>>>(jobs);
+  for (int c0 = 0; c0 < nmax; c0 += GJ_NB) {
+    for (int s0 = c0; s0 < std::min(nmax, c0 + GJ_NB); s0 += 16) {  // every sub-panel width is a multiple
+      bool any = false;
+      for (int n : ns) any = any || (c0 < n && s0 < std::min(n, c0 + GJ_NB) && (s0 - c0) % gj_pbw(n) == 0);
+      if (!any) continue;
+      gj_fetch_kernel<<<dim3((nmax * GJB + 255) / 256, 1, nj), 256, 0, s>>>(jobs, c0, s0);
+      for (int v = 0; v < GJ_VARIANTS; ++v) {
+        if (!have[v]) continue;
+        const dim3 z(1, 1, nj);
+        switch (v) {
+          case 0: gj_panel_kernel<1, 32, GJ_THREADS><<<z, GJ_THREADS, 0, s>>>(jobs, v, c0, s0); break;
+          case 1: gj_panel_kernel<2, 32, GJ_THREADS><<<z, GJ_THREADS, 0, s>>>(jobs, v, c0, s0); break;
+          case 2: gj_panel_kernel<3, 16, GJ_THREADS><<<z, GJ_THREADS, 0, s>>>(jobs, v, c0, s0); break;
+          case 3: gj_panel_kernel<4, 16, GJ_THREADS><<<z, GJ_THREADS, 0, s>>>(jobs, v, c0, s0); break;
+          case 4: gj_panel_kernel<5, 16, 256><<<z, 256, 0, s>>>(jobs, v, c0, s0); break;
+          default:
+            gj_tourn0_kernel<<<dim3((nmax + GJ_THREADS - 1) / GJ_THREADS, 1, nj), GJ_THREADS, 0, s>>>(jobs, c0, s0);
+            gj_tourn1_kernel<<<z, GJ_THREADS, 0, s>>>(jobs, c0, s0);
         }
       }
-      gj_rows_kernel<<<dim3((2 * GJ_NB + 255) / 256, GJB), 256, 0, s>>>(jb, c0, s0);
-      gj_update_kernel<<<dim3((2 * GJ_NB + 255) / 256, (n + UPR - 1) / UPR), 256, 0, s>>>(jb, c0, s0);
+      gj_rows_kernel<<<dim3((2 * GJ_NB + 255) / 256, GJB, nj), 256, 0, s>>>(jobs, c0, s0);
+      gj_update_kernel<<<dim3((2 * GJ_NB + 255) / 256, (nmax + UPR - 1) / UPR, nj), 256, 0, s>>>(jobs, c0, s0);
     }
-    gj_gather_kernel<<<1024, 256, 0, s>>>(jb, c0);
-    gj_gemm_kernel<<<dim3((n + GT - 1) / GT, (n + GT - 1) / GT), 256, 0, s>>>(jb, c0);
+    gj_gather_kernel<<<dim3(1024, 1, nj), 256, 0, s>>>(jobs, c0);
+    gj_gemm_kernel<<<dim3((nmax + GT - 1) / GT, (nmax + GT - 1) / GT, nj), 256, 0, s>>>(jobs, c0);
   }
-  gj_extract_kernel<<<1024, 256, 0, s>>>(jb);
+  gj_extract_kernel<<<dim3(1024, 1, nj), 256, 0, s>>>(jobs);
   return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+int dense_invert_pivoted(const GJJob& job, hipStream_t s) { return gj_run(GJOne{job}, {job.n}, s); }
+int dense_invert_pivoted_batch(const GJJob* tab_dev, const std::vector<int>& ns, hipStream_t s) {
+  return ns.empty() ? 0 : gj_run(GJTab{tab_dev}, ns, s);
 }
 
 // ---- block elimination with pivoting inside the diagonal blocks -----------
@@ -839,7 +893,7 @@ __device__ __forceinline__ double bgj_reciprocal(double x) {
 // per column: the wavefront that holds the next column updates it first, finds
 // its pivot and publishes column, pivot row and reciprocal before the rest of
 // its update.  fb: 2 x 64 published columns, ipb: 2 reciprocals, pv: 128.
-__device__ void bgj_invert(double* T, double* fb, double* ipb, int* pv, double* __restrict__ out, int* status) {
+__device__ void bgj_invert(double* T, double* fb, double* ipb, int* pv, double* __restrict__ out, int* rejected) {
   const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
   double a[8];
   __syncthreads();
@@ -891,7 +945,7 @@ __device__ void bgj_invert(double* T, double* fb, double* ipb, int* pv, double* 
       if (w == wc) a[jc] = -g;
     }
   }
-  if (bad && l == 0) atomicOr(status, GJ_REJECTED);
+  if (bad && l == 0) atomicOr(rejected, 1);
   __syncthreads();  // pv complete
   // A^-1[c][p_m] sits in row p_c, column m
   int* pos = pv + 64;
@@ -907,17 +961,13 @@ __device__ void bgj_invert(double* T, double* fb, double* ipb, int* pv, double* 
   }
 }
 
-// job of grid layer z: from the table, or the one passed by value
-__device__ __forceinline__ const GJJob& bgj_job(const GJJob* __restrict__ tab, const GJJob& one) {
-  return tab ? tab[blockIdx.z] : one;
-}
-
 // padded copy of the matrix's lower tiles (identity in the padding), the first block's inverse
-__global__ void __launch_bounds__(BGT) bgj_init_kernel(const GJJob* __restrict__ tab, GJJob one) {
+template <class Jobs>
+__global__ void __launch_bounds__(BGT) bgj_init_kernel(Jobs jobs) {
   __shared__ double T[BG * BG_LDA];
   __shared__ double fb[2 * BG], ipb[2];
   __shared__ int pv[2 * BG];
-  const GJJob& jb = bgj_job(tab, one);
+  const GJJob& jb = jobs.get();
   const int n = jb.n, nb = (n + BG - 1) / BG;
   int ti, tj;
   bgj_tile(blockIdx.x, ti, tj);
@@ -930,14 +980,15 @@ __global__ void __launch_bounds__(BGT) bgj_init_kernel(const GJJob* __restrict__
     jb.b0[i * np + j] = v;
     if (first) T[r * BG_LDA + c] = v;
   }
-  if (first) bgj_invert(T, fb, ipb, pv, jb.dinv, jb.status);
+  if (first) bgj_invert(T, fb, ipb, pv, jb.dinv, jb.rejected);
 }
 
 // panels of step k, tile m != k: rp_m = D A_km (64 x np), cp_m = |A_mk| (np x 64, in b1)
-__global__ void __launch_bounds__(BGT) bgj_panels_kernel(const GJJob* __restrict__ tab, GJJob one, int k) {
+template <class Jobs>
+__global__ void __launch_bounds__(BGT) bgj_panels_kernel(Jobs jobs, int k) {
   __shared__ double T1[BG * BG_LDA];
   __shared__ double T2[BG * BG_LDB];
-  const GJJob& jb = bgj_job(tab, one);
+  const GJJob& jb = jobs.get();
   const int nb = (jb.n + BG - 1) / BG, m = blockIdx.x;
   if (nb <= BG_FUSED_MAX || k >= nb || m >= nb || m == k) return;  // uniform
   const int64_t np = (int64_t)nb * BG;
@@ -955,13 +1006,13 @@ __global__ void __launch_bounds__(BGT) bgj_panels_kernel(const GJJob* __restrict
   for (int idx = threadIdx.x; idx < BG * BG; idx += BGT) cp[idx] = T2[(idx & 63) * BG_LDB + (idx >> 6)];
 }
 
-template <bool FUSED>
-__global__ void __launch_bounds__(BGT) bgj_step_kernel(const GJJob* __restrict__ tab, GJJob one, int k) {
+template <bool FUSED, class Jobs>
+__global__ void __launch_bounds__(BGT) bgj_step_kernel(Jobs jobs, int k) {
   __shared__ double T1[BG * BG_LDA];
   __shared__ double T2[BG * BG_LDB];
   __shared__ double fb[2 * BG], ipb[2];
   __shared__ int pv[2 * BG];
-  const GJJob& jb = bgj_job(tab, one);
+  const GJJob& jb = jobs.get();
   const int n = jb.n, nb = (n + BG - 1) / BG;
   if ((nb <= BG_FUSED_MAX) != FUSED || k >= nb) return;  // uniform
   int ti, tj;
@@ -1036,7 +1087,7 @@ __global__ void __launch_bounds__(BGT) bgj_step_kernel(const GJJob* __restrict__
         if (!last) dst[((int64_t)ti * BG + rr) * np + tj * BG + cc] = v;
         if (next || last) T1[rr * BG_LDA + cc] = v;
       }
-  if (next) bgj_invert(T1, fb, ipb, pv, jb.dinv + ((k + 1) & 1) * BG * BG, jb.status);
+  if (next) bgj_invert(T1, fb, ipb, pv, jb.dinv + ((k + 1) & 1) * BG * BG, jb.rejected);
   if (!last) return;  // uniform
   __syncthreads();
   // the inverse, tile and transpose
@@ -1056,8 +1107,9 @@ __global__ void __launch_bounds__(BGT) bgj_step_kernel(const GJJob* __restrict__
 // elimination loses digits.  Otherwise, or where anything is not
 // finite, the matrix is marked for the elimination with pivoting over all rows.
 __device__ __forceinline__ double bgj_sign(int j) { return (((unsigned)j * 2654435761u) >> 16) & 1 ? 1.0 : -1.0; }
-__global__ void __launch_bounds__(256) bgj_apply_kernel(const GJJob* __restrict__ tab, GJJob one) {
-  const GJJob& jb = bgj_job(tab, one);
+template <class Jobs>
+__global__ void __launch_bounds__(256) bgj_apply_kernel(Jobs jobs) {
+  const GJJob& jb = jobs.get();
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (row >= jb.n) return;
   const double* X = jb.inv + (int64_t)row * jb.n;
@@ -1066,8 +1118,9 @@ __global__ void __launch_bounds__(256) bgj_apply_kernel(const GJJob* __restrict_
   for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
   if (lane == 0) jb.xv[row] = s;
 }
-__global__ void __launch_bounds__(256) bgj_check_kernel(const GJJob* __restrict__ tab, GJJob one) {
-  const GJJob& jb = bgj_job(tab, one);
+template <class Jobs>
+__global__ void __launch_bounds__(256) bgj_check_kernel(Jobs jobs) {
+  const GJJob& jb = jobs.get();
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (row >= jb.n) return;
   const double* A = jb.a + (int64_t)row * jb.n;
@@ -1081,38 +1134,36 @@ __global__ void __launch_bounds__(256) bgj_check_kernel(const GJJob* __restrict_
     s += __shfl_down(s, off, 64);
     m += __shfl_down(m, off, 64);
   }
-  if (lane == 0 && !(fabs(s - bgj_sign(row)) <= 1e-15 * sqrt((double)jb.n) * (m + 1.0))) atomicOr(jb.status, GJ_REJECTED);
+  if (lane == 0 && !(fabs(s - bgj_sign(row)) <= 1e-15 * sqrt((double)jb.n) * (m + 1.0))) atomicOr(jb.rejected, 1);
 }
 
 // Inversions of nj matrices (job table in device memory, or the one job by
-// value), nmax unknowns at most: status gets GJ_REJECTED where the result is
-// to be replaced by dense_invert_pivoted's.
-static int bgj_run(const GJJob* tab, const GJJob& one, int nj, int nmin, int nmax, hipStream_t s) {
+// value), nmin to nmax unknowns: a job's `rejected` (zero before) is set where
+// the result is to be replaced by the elimination with pivoting over all rows.
+template <class Jobs>
+static int bgj_run(const Jobs& jobs, int nj, int nmin, int nmax, hipStream_t s) {
   const int nb = (nmax + BG - 1) / BG;
   const bool some_fused = (nmin + BG - 1) / BG <= BG_FUSED_MAX;
   const auto tiles = [&](int b) { return dim3(b * (b + 1) / 2, 1, nj); };
-  bgj_init_kernel<<<tiles(nb), BGT, 0, s>>>(tab, one);
+  bgj_init_kernel<<<tiles(nb), BGT, 0, s>>>(jobs);
   for (int k = 0; k < nb; ++k) {  // a kernel leaves the other kind's jobs alone
-    if (some_fused && k < BG_FUSED_MAX) bgj_step_kernel<true><<<tiles(std::min(nb, BG_FUSED_MAX)), BGT, 0, s>>>(tab, one, k);
+    if (some_fused && k < BG_FUSED_MAX) bgj_step_kernel<true><<<tiles(std::min(nb, BG_FUSED_MAX)), BGT, 0, s>>>(jobs, k);
     if (nb > BG_FUSED_MAX) {
-      bgj_panels_kernel<<<dim3(nb, 1, nj), BGT, 0, s>>>(tab, one, k);
-      bgj_step_kernel<false><<<tiles(nb), BGT, 0, s>>>(tab, one, k);
+      bgj_panels_kernel<<<dim3(nb, 1, nj), BGT, 0, s>>>(jobs, k);
+      bgj_step_kernel<false><<<tiles(nb), BGT, 0, s>>>(jobs, k);
     }
   }
-  bgj_apply_kernel<<<dim3((nmax + 3) / 4, 1, nj), 256, 0, s>>>(tab, one);
-  bgj_check_kernel<<<dim3((nmax + 3) / 4, 1, nj), 256, 0, s>>>(tab, one);
+  bgj_apply_kernel<<<dim3((nmax + 3) / 4, 1, nj), 256, 0, s>>>(jobs);
+  bgj_check_kernel<<<dim3((nmax + 3) / 4, 1, nj), 256, 0, s>>>(jobs);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// a: n x n input (not modified); inv: n x n output; work: dense_invert_work(n) bytes.
-int dense_invert(int n, const double* a, double* inv, double* work, int* status, hipStream_t s) {
-  return bgj_run(nullptr, gj_make_job(n, a, inv, work, status), 1, n, n, s);
-}
+int dense_invert(const GJJob& job, hipStream_t s) { return bgj_run(GJOne{job}, 1, job.n, job.n, s); }
 // tab_dev: device table of the jobs of sizes ns
 int dense_invert_batch(const GJJob* tab_dev, const std::vector<int>& ns, hipStream_t s) {
   if (ns.empty()) return 0;
   const auto [lo, hi] = std::minmax_element(ns.begin(), ns.end());
-  return bgj_run(tab_dev, GJJob{}, (int)ns.size(), *lo, *hi, s);
+  return bgj_run(GJTab{tab_dev}, (int)ns.size(), *lo, *hi, s);
 }
 
 // x = Ainv b on the coarsest level; one wavefront per output unknown, FP64

@@ -300,6 +300,8 @@ struct mvpf_problem {
   double* coarse_work = nullptr;     // dense scratch when V is too small
   bool coarse_pending = false;
   int coarse_overlap = -1;           // 1: side stream, 0: problem stream, -1: by size
+  int coarse_pivoting = 0;           // 1: invert with pivoting over all rows without trying the block elimination
+  bool coarse_pivoted = false;       // the last system's coarsest inverse came from there
   // Galerkin coarse levels (opts.coarse): element matrices of level l >= 1,
   // [(p * NBLK + q) * NEpad_l + E], allocated on first use
   double* gal[mvpf::MAX_LEVELS] = {nullptr};
@@ -410,9 +412,8 @@ void launch_inject_mask(const Grid& fine, const Grid& coarse, const uint16_t* mf
 // coarse direct solve
 void launch_dense_from_bsr(const Grid& g, const double* A64, double* dense, hipStream_t s);
 size_t dense_invert_work(int n);  // bytes of scratch needed by dense_invert
-// status bits of the Newton system's setup
-constexpr int SETUP_SINGULAR = 1;  // a diagonal block or the coarsest operator is singular
-constexpr int GJ_REJECTED = 2;     // the coarsest inverse failed its check: dense_invert_pivoted is due
+// status of the Newton system's setup: a diagonal block or the coarsest operator is singular
+constexpr int SETUP_SINGULAR = 1;
 // one dense inversion: pointers into its dense_invert_work(n) workspace
 struct GJJob {
   int n;
@@ -421,14 +422,16 @@ struct GJJob {
   double *b0, *b1, *dinv, *rp, *xv;         // block elimination
   double *M, *F, *Wc, *R, *Pinv, *Yo, *Rb;  // elimination with pivoting over all rows (same memory)
   int *cand, *done, *prow;
-  int* status;
+  int* status;    // gets SETUP_SINGULAR (pivoting over all rows)
+  int* rejected;  // set by the block elimination's check: dense_invert_pivoted is due
 };
-GJJob gj_make_job(int n, const double* a, double* inv, double* work, int* status);
-// several inversions at once: tab_dev = device table of the jobs of sizes ns
+GJJob gj_make_job(int n, const double* a, double* inv, double* work, int* status, int* rejected);
+// block elimination with a check, or pivoting over all rows; several at once:
+// tab_dev = device table of the jobs of sizes ns
+int dense_invert(const GJJob& job, hipStream_t s);
 int dense_invert_batch(const GJJob* tab_dev, const std::vector<int>& ns, hipStream_t s);
-int dense_invert(int n, const double* a, double* inv, double* work, int* status, hipStream_t s);
-// the same with partial pivoting over all rows (status: SETUP_SINGULAR)
-int dense_invert_pivoted(int n, const double* a, double* inv, double* work, int* status, hipStream_t s);
+int dense_invert_pivoted(const GJJob& job, hipStream_t s);
+int dense_invert_pivoted_batch(const GJJob* tab_dev, const std::vector<int>& ns, hipStream_t s);
 template <typename T>
 void launch_coarse_solve(const Grid& g, const double* Ainv, const T* b, T* x, hipStream_t s);
 // vectors

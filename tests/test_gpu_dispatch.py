@@ -131,3 +131,68 @@ def test_batch_of_both_coarse_elimination_kinds():
         assert torch.equal(B.problem(i).precondition(v), z), i
         gp.close()
     B.close()
+
+
+def _indefinite(p):
+    """c11 < c12: about a quarter of the coarsest operator's eigenvalues are negative."""
+    return replace(p, material=replace(p.material, cubic=(60.0, 126.0, 96.0)))
+
+
+def _two_level(nx, ny, nz, seed=synth.BASE_SEED):
+    h = 1.0 / max(nx, ny, nz)
+    return synth.Problem(nx, ny, nz, lx=nx * h, ly=ny * h, lz=nz * h, n_levels=2, patch=2, depth_increment=0.01, seed=seed)
+
+
+@pytest.mark.parametrize("overlap", [1, 0])
+def test_rejected_coarse_inverse_is_reported_and_replaced(overlap):
+    """A definite coarsest operator (1080 unknowns) keeps the block
+    elimination's inverse, an indefinite one is rejected by its check and
+    inverted with pivoting over all rows, on the side stream or in order: the
+    V-cycle is bitwise that of an inversion by pivoting alone, also in the
+    next system of the same problem."""
+    for p, rejected in ((_two_level(6, 8, 10), 0), (_indefinite(_two_level(6, 8, 10)), 1)):
+        U, En = seeded_state(p, 5e-4)
+        v = _dev(np.random.default_rng(7).standard_normal(9 * p.n_nodes))
+        gp = gpu_problem(p, U, En, "fp64")
+        gp.set_tuning("coarse_overlap", 0, overlap)
+        out = []
+        for force in (0, 1, 0):
+            gp.set_tuning("coarse_pivoting", 0, force)
+            gp.newton_system(p.depth_increment)
+            assert gp.get_tuning("coarse_pivoted") == (1 if force else rejected)
+            out.append(gp.precondition(v))
+        gp.close()
+        assert torch.equal(out[0], out[2])
+        if rejected:
+            assert torch.equal(out[0], out[1])
+        else:
+            assert float((out[0] - out[1]).norm() / out[1].norm()) < 1e-10
+
+
+def test_batch_with_rejected_coarse_inverses():
+    """Indefinite and definite coarsest operators of several panel variants
+    (576, 1080 and 1296 unknowns rejected, 576 and 72 kept) in one batch: the
+    rejected ones are inverted again together, and every V-cycle is bitwise
+    the one of the problem by itself."""
+    from paper_2011_08802_amd import mvpf
+    shapes = [(6, 6, 6, 1), (6, 6, 6, 0), (6, 8, 10, 1), (2, 2, 2, 0), (6, 10, 10, 1)]
+    probs = []
+    for i, (nx, ny, nz, bad) in enumerate(shapes):
+        p = _two_level(nx, ny, nz, synth.BASE_SEED + 60 + i)
+        probs.append(_indefinite(p) if bad else p)
+    states = [seeded_state(p, 5e-4) for p in probs]
+    B = mvpf.Batch(probs, "fp64")
+    for i, (U, En) in enumerate(states):
+        B.problem(i).set_state(U[:, :3], U[:, 3:], En, 0.0)
+    for _ in range(2):
+        B.newton_system([p.depth_increment for p in probs])
+        for i, (p, (U, En)) in enumerate(zip(probs, states)):
+            assert B.problem(i).get_tuning("coarse_pivoted") == shapes[i][3], i
+            v = _dev(np.random.default_rng(11 + i).standard_normal(9 * p.n_nodes))
+            gp = gpu_problem(p, U, En, "fp64")
+            gp.newton_system(p.depth_increment)
+            z = gp.precondition(v)
+            assert torch.isfinite(z).all()
+            assert torch.equal(B.problem(i).precondition(v), z), i
+            gp.close()
+    B.close()
