@@ -884,7 +884,7 @@ __device__ __forceinline__ double bgj_reciprocal(double x) {
 // Inverse of the 64 x 64 block in T (stride BG_LDA) to out (row-major): in-place
 // Gauss-Jordan in registers, lane = row, wavefront w holds columns 8 w .. 8 w
 // + 7.  The pivot of a column is the largest of its remaining entries by the
-// upper 31 bits of the magnitude (within 2^-19), ties to the lowest row; rows
+// upper 30 bits of the magnitude (within 2^-19), ties to the lowest row; rows
 // stay in place and the permutation is undone in the final store, which also
 // takes the symmetric part (the tiles of the other triangle are never formed,
 // so an asymmetry of D grows from step to step: on a random matrix of 1125
@@ -1102,9 +1102,12 @@ __global__ void __launch_bounds__(BGT) bgj_step_kernel(Jobs jobs, int k) {
 // Check of the inverse X on one vector v of signs: x = X v, and in a second
 // pass |A x - v| <= 1e-15 sqrt(n) (|A| |x| + 1) in every row.  Measured for the
 // largest row of that ratio: 0.1 sqrt(n) 1e-15 on definite matrices of 1 to
-// 3645 unknowns (0.2 with pivoting over all rows), 2 to 27000 times sqrt(n)
-// 1e-15 on random symmetric indefinite ones of 243 and more, where the block
-// elimination loses digits.  Otherwise, or where anything is not
+// 3645 unknowns (0.2 with pivoting over all rows), below a quarter of the bound
+// on two-level operators of up to 8100 unknowns and in 48 systems of running
+// load sequences at 32^3; 2 to 27000 times sqrt(n) 1e-15 on random symmetric
+// indefinite ones of 243 and more, where the block elimination loses digits,
+// and 2 to 18 times on a slender column's operator of 1539 unknowns with 4 to 22
+// negative eigenvalues.  Otherwise, or where anything is not
 // finite, the matrix is marked for the elimination with pivoting over all rows.
 __device__ __forceinline__ double bgj_sign(int j) { return (((unsigned)j * 2654435761u) >> 16) & 1 ? 1.0 : -1.0; }
 template <class Jobs>

@@ -196,3 +196,46 @@ def test_batch_with_rejected_coarse_inverses():
             assert torch.equal(B.problem(i).precondition(v), z), i
             gp.close()
     B.close()
+
+
+@pytest.mark.parametrize("nx,ny,nz,coarse_dof", [
+    (2, 2, 2, 72),      # one row per thread, one narrow sub-panel
+    (6, 6, 6, 576),     # two rows per thread, five outer panels
+    (6, 8, 10, 1080),   # five rows per thread of a half-size workgroup
+    (6, 10, 10, 1296),  # three rows per thread
+    (4, 4, 36, 1539),   # four rows per thread
+    (12, 12, 12, 3087), # tournament pivoting, seven blocks of rows, the last one short
+])
+def test_pivoting_over_all_rows(nx, ny, nz, coarse_dof):
+    """The inversion with pivoting over all rows by itself, in each of its
+    panel variants: the V-cycle against the oracle's LU (as the tests of the
+    block elimination), on the side stream and in order bitwise the same."""
+    p = _two_level(nx, ny, nz)
+    U, En = seeded_state(p, 5e-4)
+    oc = OracleCase(p, U, En, p.depth_increment, direct=False)
+    assert oc.mg.levels[-1].A.shape[0] == coarse_dof
+    v = np.random.default_rng(7).standard_normal(oc.sys.b.shape[0])
+    gp = gpu_problem(p, U, En, "fp64")
+    gp.set_tuning("coarse_pivoting", 0, 1)
+    out = []
+    for overlap in (1, 0):
+        gp.set_tuning("coarse_overlap", 0, overlap)
+        gp.newton_system(p.depth_increment)
+        assert gp.get_tuning("coarse_pivoted") == 1
+        out.append(gp.precondition(_dev(v)))
+    gp.close()
+    assert torch.equal(out[0], out[1])
+    err = rel(out[0].cpu().numpy(), oc.mg.precondition(v))
+    assert err < 1e-10, err
+
+
+@pytest.mark.parametrize("nx,ny,nz", [(2, 2, 2), (6, 6, 6), (6, 10, 10), (12, 12, 12), (16, 16, 16), (16, 18, 18)])
+def test_definite_coarse_operators_keep_the_block_elimination(nx, ny, nz):
+    """The check does not reject the definite operators of the workloads, up
+    to 6561 unknowns (128^3's coarsest level) and 8100."""
+    p = _two_level(nx, ny, nz)
+    U, En = seeded_state(p, 5e-4)
+    gp = gpu_problem(p, U, En, "mixed")
+    gp.newton_system(p.depth_increment)
+    assert gp.get_tuning("coarse_pivoted") == 0
+    gp.close()
