@@ -438,7 +438,8 @@ int mvpf_indent(mvpf_problem* p, const mvpf_indent_opts* o, mvpf_indent_callback
  * "assembly_slab_elements": elements per assembly slab (0 = the capacity
  * allocated by mvpf_create: the whole finest level if its Gauss-point and
  * element-matrix buffers take at most 96 GiB, else slabs of 40 GiB).  Levels
- * with more elements are assembled in slabs of whole element layers, one
+ * with more elements are assembled in slabs of whole element layers (of a
+ * matrix-free finest level: its diagonal blocks), one
  * halo layer recomputed per slab; at least 2 nx ny + 64, at most the
  * capacity; level ignored; results bitwise unchanged.
  * "matrix_free": 1 (default for problems with two or more levels) = the
@@ -477,7 +478,7 @@ int mvpf_autotune(mvpf_problem* p, int* row_blocks_out);
 /* Per-kernel device timing with HIP events on the problem's stream.  name:
  * "pbj_sweep" (finest-level smoother sweep), "spmv_outer" (finest FP64
  * operator product), "residual" (finest defect), "qp_hessian" (finest-level
- * Gauss-point gradient and Hessian of the density, Sec. 3.2; bytes = its
+ * Gauss-point Hessian of the density, Sec. 3.2; bytes = its
  * output).  enable != 0 starts
  * recording (and clears totals); stats: launches, summed ms, algorithmic
  * bytes moved per launch. */

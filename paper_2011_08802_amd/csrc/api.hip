@@ -1151,12 +1151,14 @@ void finest_tangents(mvpf_problem* p) {
 
 // diagonal blocks of the matrix-free finest level from its Gauss-point
 // tangents, slab by slab where the element buffer does not hold the whole level
+// or smaller slabs are asked for
 int mf_diagonal(mvpf_problem* p, double depth) {
   Level& L0 = p->lev[0];
   const int64_t have = (int64_t)NPAIR * NBLK * p->ne_cap;
   int64_t cap = L0.g.NEpad;
   while (mf_diag_values(cap, L0.g.nx) > have) cap = cap / 2 / TILE * TILE;
   cap = std::max<int64_t>(cap, std::min<int64_t>(p->ne_cap, L0.g.NEpad));
+  if (p->ne_use < p->ne_cap) cap = std::min(cap, p->ne_use);
   for (const Chunk& ck : make_chunks(L0.g, cap))
     launch_mf_diag(L0.g, ck, p->Dmf64, p->card, p->elem, L0.diag64, p->stream);
   if (contact(p)) launch_contact_diag(L0.g, make_sphere(L0.g, p->load, depth), L0.state, L0.diag64, p->stream);

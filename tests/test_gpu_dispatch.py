@@ -239,3 +239,40 @@ def test_definite_coarse_operators_keep_the_block_elimination(nx, ny, nz):
     gp.newton_system(p.depth_increment)
     assert gp.get_tuning("coarse_pivoted") == 0
     gp.close()
+
+
+@pytest.mark.parametrize("kind,coarse,matrix_free,n_var", [
+    ("patch", "rediscretise", 1, 6), ("sphere", "galerkin", 1, 6), ("sphere", "rediscretise", 0, 6),
+    ("patch", "galerkin", 0, 6), ("patch", "rediscretise", 0, 12)])
+def test_slabs_of_every_assembly_path(kind, coarse, matrix_free, n_var):
+    """Slabs of one, two and four node layers on 8 x 6 x 12 elements (slabs
+    that begin inside a workgroup's 32 elements and inside a tile of 64
+    nodes): the diagonal blocks of a matrix-free finest level, the stored
+    blocks of an assembled one and its Galerkin products are bitwise those of
+    the whole level; seen in the right-hand side, every level's product and
+    the V-cycle."""
+    from paper_2011_08802_amd import mvpf
+    nx, ny, nz = 8, 6, 12
+    h = 1.0 / nz
+    m = synth.config_material() if n_var == 6 else synth.twelve_variant_material(rho=10.0)
+    p = synth.Problem(nx, ny, nz, lx=nx * h, ly=ny * h, lz=nz * h, n_levels=2, kind=kind, patch=2, radius=0.4,
+                      depth_increment=0.01, material=m)
+    U, En = seeded_state(p, 1e-3)
+    nd = 3 + n_var
+    rng = np.random.default_rng(8)
+    xs = [_dev(rng.standard_normal(nd * (nx // s + 1) * (ny // s + 1) * (nz // s + 1))) for s in (1, 2)]
+    nxy = nx * ny
+    outs = []
+    gp = gpu_problem(p, U, En, "mixed", coarse=coarse)
+    if n_var == 6:
+        gp.set_tuning("matrix_free", 0, matrix_free)
+    # a slab of L node layers holds L + 1 element layers, rounded up to 64
+    for slab in (0, *((L + 1) * nxy + 64 for L in (1, 2, 4))):
+        gp.set_tuning("assembly_slab_elements", 0, slab)
+        gp.newton_system(p.depth_increment)
+        outs.append([gp.get_rhs(), gp.jacobian_apply(0, xs[0], mvpf.FP64), gp.jacobian_apply(0, xs[0], mvpf.MIXED),
+                     gp.jacobian_apply(1, xs[1], mvpf.FP64), gp.precondition(xs[0])])
+    gp.close()
+    for o in outs[1:]:
+        for k, (a, b) in enumerate(zip(o, outs[0])):
+            assert torch.isfinite(a).all() and torch.equal(a, b), k
