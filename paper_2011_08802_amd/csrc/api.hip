@@ -918,11 +918,12 @@ int allocate(mvpf_problem* p) {
     }
     if (!coarsest) {
       TRY(dalloc(p, &L.diag64, (size_t)nD64));
-      if (p->mixed)
-        TRY(dalloc(p, &L.Dinv32, (size_t)nD32));
-      else
+      if (!p->mixed)
         TRY(dalloc(p, &L.Dinv64, (size_t)nD64));
-      if (mf0 && p->mixed) TRY(dalloc(p, &L.DinvS32, (size_t)L.g.ntiles * LaySym<float>::SLICE));
+      else if (mf0)
+        TRY(dalloc(p, &L.DinvS32, (size_t)L.g.ntiles * LaySym<float>::SLICE));
+      else
+        TRY(dalloc(p, &L.Dinv32, (size_t)nD32));
     }
     const size_t es = p->mixed ? sizeof(float) : sizeof(double);
     for (void** v : {&L.x, &L.x2, &L.b, &L.r}) {
@@ -1117,7 +1118,9 @@ int finish_system(mvpf_problem* p, bool coarse_inline) {
   hipStream_t s = p->stream;
   for (int l = 0; l < p->L - 1; ++l) {
     Level& L = p->lev[l];
-    launch_block_inverse(L.g, L.diag64, L.Dinv64, L.Dinv32, L.DinvS32, setup_status(p), s);
+    const bool packed = l == 0 && use_mf(p);
+    launch_block_inverse(L.g, L.diag64, L.Dinv64, packed ? nullptr : L.Dinv32, packed ? L.DinvS32 : nullptr,
+                         setup_status(p), s);
   }
   TRY(launch_check(p, "assembly"));
   if (coarse_inline) {
@@ -2379,8 +2382,9 @@ int batch_assemble(mvpf_batch* b, const double* depths, hipStream_t s) {
         j.g = L.g;
         j.diag64 = L.diag64;
         j.Dinv64 = L.Dinv64;
-        j.Dinv32 = L.Dinv32;
-        j.DinvS32 = L.DinvS32;
+        const bool packed = l == 0 && use_mf(p);
+        j.Dinv32 = packed ? nullptr : L.Dinv32;
+        j.DinvS32 = packed ? L.DinvS32 : nullptr;
         j.status = setup_status(p);
         bi.push_back(j);
       }
@@ -3092,6 +3096,7 @@ int mvpf_set_tuning(mvpf_problem* p, const char* key, int level, int value) {
       TRY(dalloc(p, &L0.A64, (size_t)L0.g.ntiles * NUP * Lay<double>::SLICE));
       if (p->mixed) TRY(dalloc(p, &L0.A32, (size_t)L0.g.ntiles * NUP * Lay<float>::SLICE));
     }
+    if (!value && p->mixed && !L0.Dinv32) TRY(dalloc(p, &L0.Dinv32, (size_t)L0.g.ntiles * Lay<float>::SLICE));
     p->mf = value;
     p->have_system = p->have_solution = false;  // the finest operator must be rebuilt
   } else {

@@ -208,8 +208,8 @@ struct Level {
   float* A32 = nullptr;       // FP32 operator (mixed mode, all but coarsest)
   double* diag64 = nullptr;   // FP64 diagonal blocks [ntiles][NBLK][64]
   double* Dinv64 = nullptr;   // FP64 block inverses (FP64 mode)
-  float* Dinv32 = nullptr;    // FP32 block inverses (mixed mode)
-  float* DinvS32 = nullptr;   // their upper triangles, packed (matrix-free finest level, mixed mode)
+  float* Dinv32 = nullptr;    // FP32 block inverses (mixed mode, assembled levels)
+  float* DinvS32 = nullptr;   // their upper triangles, packed (mixed mode, matrix-free finest level)
   // work vectors of the V-cycle (type per precision mode), [9][Npad]
   void* x = nullptr;
   void* x2 = nullptr;

@@ -171,3 +171,29 @@ def test_mf_fp32_product_rounds_no_more_than_packed_hessians(amp, bound, bound_e
     err_eta = float(d[:, 3:].norm() / y64[:, 3:].norm())
     say(f"    FP32 product against FP64: {err:.3e}, order parameters {err_eta:.3e}")
     assert err <= bound and err_eta <= bound_eta, (err, err_eta)
+
+
+@pytest.mark.parametrize("precision", ["mixed", "fp64"])
+def test_mf_finest_level_holds_only_what_it_reads(precision):
+    """A matrix-free finest level in mixed precision keeps its block inverses
+    packed; the stored blocks and the full inverses of the assembled one are
+    allocated when it is switched off (tiles of 64 rows: 14 blocks of 82 FP64
+    and 84 FP32 entries, one block of 84).  Switching back gives bitwise the
+    same V-cycle."""
+    p = synth.tiny()
+    U, En = seeded_state(p, 1e-3)
+    v = _dev(np.random.default_rng(4).standard_normal(9 * U.shape[0]))
+    gp = _mf_problem(p, U, En, p.depth_increment, precision)
+    z = gp.precondition(v)
+    before = gp.info().bytes_device
+    gp.set_tuning("matrix_free", 0, 0)
+    tiles = (U.shape[0] + 63) // 64
+    want = 14 * 82 * 8 + ((14 * 84 + 84) * 4 if precision == "mixed" else 0)
+    assert gp.info().bytes_device - before == 64 * tiles * want
+    gp.newton_system(p.depth_increment)
+    za = gp.precondition(v)
+    assert float((za - z).norm() / z.norm()) < (1e-4 if precision == "mixed" else 1e-12)
+    gp.set_tuning("matrix_free", 0, 1)
+    gp.newton_system(p.depth_increment)
+    assert torch.equal(gp.precondition(v), z)
+    gp.close()
