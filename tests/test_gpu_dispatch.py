@@ -276,3 +276,32 @@ def test_slabs_of_every_assembly_path(kind, coarse, matrix_free, n_var):
     for o in outs[1:]:
         for k, (a, b) in enumerate(zip(o, outs[0])):
             assert torch.isfinite(a).all() and torch.equal(a, b), k
+
+
+@pytest.mark.parametrize("precision,tol,ptol", [("fp64", 1e-12, 3e-14), ("mixed", 1e-4, 2e-5)])
+@pytest.mark.parametrize("kind,nx,ny,nz", [("patch", 24, 24, 24), ("patch", 28, 24, 24), ("sphere", 2, 2, 2),
+                                           ("sphere", 16, 28, 32), ("sphere", 28, 24, 24)])
+def test_finest_level_gathers_against_the_assembled_level(kind, nx, ny, nz, precision, tol, ptol):
+    """The node gathers by tiles (up to 256 tiles of 64 nodes: 25^3 nodes, 245
+    tiles, and 17 x 29 x 33, 255) and by nodes (29 x 25 x 25), product, defect and sweep with
+    contact faces and without, against the assembled finest level: the product
+    relative to |A x| + |A |x|| and the V-cycle, tolerances as for the two
+    kernel families of the assembled levels."""
+    from paper_2011_08802_amd import mvpf
+    h = 1.0 / nx
+    p = synth.Problem(nx, ny, nz, lx=1.0, ly=ny * h, lz=nz * h, n_levels=2 if nx == 2 else 3, kind=kind,
+                      patch=2, radius=0.4, depth_increment=0.01)
+    U, En = seeded_state(p, 1e-3)
+    x = _dev(np.random.default_rng(5).standard_normal(9 * p.n_nodes))
+    k = mvpf.FP64 if precision == "fp64" else mvpf.MIXED
+    gp = gpu_problem(p, U, En, precision)
+    out = []
+    for mf in (1, 0):
+        gp.set_tuning("matrix_free", 0, mf)
+        gp.newton_system(p.depth_increment)
+        out.append((gp.jacobian_apply(0, x, k), gp.jacobian_apply(0, x.abs(), k), gp.precondition(x)))
+    gp.close()
+    (y, ya, z), (y0, ya0, z0) = out
+    assert torch.isfinite(y).all() and torch.isfinite(z).all()
+    assert float((y - y0).norm() / (y0.norm() + ya0.norm())) < ptol
+    assert float((z - z0).norm() / z0.norm()) < tol
