@@ -170,3 +170,36 @@ def test_batch_contact_and_assembled_finest_bitwise(precision):
             assert stats[i].converged and stats[i].iterations == ref[i][1], (i, stats[i].iterations, ref[i][1])
             assert np.array_equal(_state(B.problem(i)), ref[i][0]), i
     B.close()
+
+
+@pytest.mark.parametrize("precision", ["mixed", "fp64"])
+def test_batch_bitwise_cycles_beyond_the_register_kernels(precision):
+    """A Krylov space of 64 and a weak smoother: the Arnoldi steps pass the 32
+    basis vectors up to which the Gram-Schmidt kernels keep a row's entries in
+    registers (single solves and batches alike), so updates and projections
+    go through the separate kernels, grouped by eight vectors.  The batch is
+    bitwise the single solves, whose residuals are the true FP64 ones."""
+    from paper_2011_08802_amd import mvpf
+    probs = small_batch()[:3]
+    states = [seeded_state(p, 1e-3) for p in probs]
+    opts = dict(nu_pre=1, nu_post=1, omega=0.3, rtol=1e-11, restart=64)
+    ref = []
+    for p, (U, En) in zip(probs, states):
+        gp = mvpf.Problem(p, precision, **opts)
+        gp.set_state(U[:, :3], U[:, 3:], En, 0.0)
+        gp.newton_system(p.depth_increment)
+        _, st = gp.solve(want_x=False)
+        assert st.converged and st.rel_residual <= 1e-11 and st.iterations > 33, st.iterations
+        gp.newton_update()
+        ref.append((_state(gp), st.iterations))
+        gp.close()
+    B = mvpf.Batch(probs, precision, **opts)
+    for i, (U, En) in enumerate(states):
+        B.problem(i).set_state(U[:, :3], U[:, 3:], En, 0.0)
+    B.newton_system([p.depth_increment for p in probs])
+    stats = B.solve()
+    B.newton_update()
+    for i in range(len(probs)):
+        assert stats[i].converged and stats[i].iterations == ref[i][1], (i, stats[i].iterations, ref[i][1])
+        assert np.array_equal(_state(B.problem(i)), ref[i][0]), i
+    B.close()
