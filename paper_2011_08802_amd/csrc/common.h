@@ -75,11 +75,17 @@ constexpr int TILE = 64;
 constexpr int NHP_PAD = (NHP + 7) / 8 * 8;
 constexpr int MAX_LEVELS = 8;
 constexpr int MAX_RESTART = 64;
-// default size limit of the small-grid kernels: a V-cycle is faster with them
-// on levels of 35937 nodes (FP32 1051 -> 1045 us, FP64 2052 -> 2008, 15
-// unknowns per node 856 -> 760), slower on the next larger ones (71825 nodes,
-// FP64: 3942 -> 4101 us; 139425, FP32: 3914 -> 4055), whose blocks, read twice,
-// no longer come out of an L2; a batch gains as well (92.8 -> 87 ms)
+// Default size limit of the small-grid kernels.  In nodes, not bytes: the
+// two-pass kernels hold a row per thread, 65536 of them for a wavefront on every
+// SIMD, so what they lack on a smaller level is rows, whatever a row's bytes.
+// V-cycle (us) with the finest assembled level by two passes and by 27 threads a
+// row, at 9261, 24389, 44649, 117649 nodes: FP32 166 and 124, 237 and 232, 308
+// and 320, 772 and 809; FP64 197 and 162, 347 and 358, 603 and 620, 1395 and
+// 1615; at 9261, 24389, 44649, 68921 nodes of 15 unknowns: FP32 317 and 231, 605
+// and 556, 898 and 892, 1290 and 1368; FP64 942 and 443, 1334 and 1191, 2352 and
+// 2004, 3514 and 2977.  Between 24389 and 68921 nodes of 9 unknowns neither is
+// ahead by more than 8 % (33^3 and 41^3, rows that straddle more lines, favour
+// 27 threads).  A batch gains as well (92.8 -> 87 ms).
 constexpr int SMALL_GRID_NODES = 40000;
 
 struct Grid {

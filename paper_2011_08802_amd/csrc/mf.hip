@@ -372,13 +372,10 @@ __global__ void __launch_bounds__(256) mf_gather_kernel(Grid g, const T* __restr
   mf_gather_body<MODE, T, TX, TY>(g, E, Cf, epw, mask, x, b, Dinv, omega, y, blockIdx.x);
 }
 
-// The same for grids of at most a tile of 64 nodes per CU, where a thread per
-// node leaves most of the chip idle and walks its loads in turn: a workgroup
-// takes a tile, one wavefront per component, with the tile's block inverses
-// staged in LDS while the element outputs arrive.  Sums and rounding as above.
-// FP64 Jacobi update: 9^3 nodes 8.2 -> 5.6 us; above the limit every block
-// inverse passes through LDS for no gain (41^3 nodes: 16.4 us by node, 28.6
-// by tile; 65^3, FP32: 21 and 55).
+// The same for small grids, where a thread per node leaves most of the chip
+// idle and walks its loads in turn: a workgroup takes a tile of 64 nodes, one
+// wavefront per component, with the tile's block inverses staged in LDS while
+// the element outputs arrive.  Sums and rounding as above.
 constexpr int GT = 9 * TILE;
 template <int MODE, typename T, typename TX, typename TY>
 __global__ void __launch_bounds__(GT) mf_gather_tile_kernel(Grid g, const T* __restrict__ E, const T* __restrict__ Cf,
@@ -714,14 +711,22 @@ void launch_mf_element(const Grid& g, const TD* D, const TX* x, const uint16_t* 
     mf_element_kernel<TD, TX, T, MINB, PF, false><<<blocks, wg, 0, s>>>(g, D, x, mask, cd, E);
 }
 
-constexpr int MF_GATHER_TILE_NODES = 256 * TILE;  // a tile per CU (measured at mf_gather_tile_kernel)
+// Tiles up to which a grid is gathered by tiles.  A tile per CU where that is
+// ahead (V-cycle or product, us by tile and by node): FP64 V-cycle 9^3 nodes 106
+// and 121, 21^3 148 and 167, 25^3 (245 tiles) 202 and 216, 33^3 (562 tiles) 346
+// and 326; products in either type 33 and 36, 41 and 44 (25^3), 45.7 and 47.6
+// (329 tiles).  The FP32 sweep reads its packed blocks back from LDS in words
+// four apart, at a quarter of the banks: 17 x 17 x 13 (59 tiles) 127 to 136 and
+// 132, 17^3 140 and 135, 21^3 163 and 142, 25^3 202 and 169.
+template <int MODE, typename T>
+constexpr int MF_GATHER_TILES = MODE == 2 && sizeof(T) == 4 ? 64 : 256;
 template <int MODE, typename T, typename TX, typename TY>
 void launch_mf_gather(const Grid& g, const T* E, bool contact, int elems_per_wg, const uint16_t* mask, const TX* x,
                       const T* b, const T* Dinv, T omega, TY* y, hipStream_t s) {
   if constexpr (!MF_AVAILABLE) return;
   const T* Cf = contact ? E + mf_cf_offset(g) : nullptr;
   const int epw = mf_epw_of(elems_per_wg);
-  if (g.Npad <= MF_GATHER_TILE_NODES)
+  if (g.ntiles <= MF_GATHER_TILES<MODE, T>)
     mf_gather_tile_kernel<MODE, T, TX, TY><<<g.ntiles, GT, 0, s>>>(g, E, Cf, epw, mask, x, b, Dinv, omega, y);
   else
     mf_gather_kernel<MODE, T, TX, TY><<<(g.Npad + 255) / 256, 256, 0, s>>>(g, E, Cf, epw, mask, x, b, Dinv, omega, y);

@@ -280,11 +280,13 @@ def test_slabs_of_every_assembly_path(kind, coarse, matrix_free, n_var):
 
 @pytest.mark.parametrize("precision,tol,ptol", [("fp64", 1e-12, 3e-14), ("mixed", 1e-4, 2e-5)])
 @pytest.mark.parametrize("kind,nx,ny,nz", [("patch", 24, 24, 24), ("patch", 28, 24, 24), ("sphere", 2, 2, 2),
-                                           ("sphere", 16, 28, 32), ("sphere", 28, 24, 24)])
+                                           ("sphere", 16, 28, 32), ("sphere", 28, 24, 24), ("patch", 12, 16, 16),
+                                           ("sphere", 16, 16, 16)])
 def test_finest_level_gathers_against_the_assembled_level(kind, nx, ny, nz, precision, tol, ptol):
     """The node gathers by tiles (up to 256 tiles of 64 nodes: 25^3 nodes, 245
-    tiles, and 17 x 29 x 33, 255) and by nodes (29 x 25 x 25), product, defect and sweep with
-    contact faces and without, against the assembled finest level: the product
+    tiles, and 17 x 29 x 33, 255; the FP32 sweep 64: 13 x 17 x 17, 59, and 17^3,
+    77) and by nodes (29 x 25 x 25), product, defect and sweep with contact
+    faces and without, against the assembled finest level: the product
     relative to |A x| + |A |x|| and the V-cycle, tolerances as for the two
     kernel families of the assembled levels."""
     from paper_2011_08802_amd import mvpf
