@@ -59,6 +59,16 @@ def log(msg):
     print(msg, file=sys.stderr, flush=True)
 
 
+def emit(out, detail, path):
+    """Print the result's one JSON line.  `detail` (records of every Newton
+    system; stderr has a line for each) would make it tens of kilobytes long:
+    it goes to the file `path`, together with the line, if one is named."""
+    print(json.dumps(out), flush=True)
+    if path:
+        with open(path, "w") as f:
+            json.dump({**out, "detail": detail}, f)
+
+
 class NewtonRun:
     """Newton iterations of one problem's load-step sequence through the
     C ABI, with the library's own step rule (Sec. 3.4, as mvpf_time_step):
@@ -649,6 +659,7 @@ def main():
     ap.add_argument("--coarse", default="galerkin", choices=["galerkin", "rediscretise"],
                     help="coarse multigrid operators: Galerkin products of the finest tangent (default) or the "
                          "paper's rediscretisation at the injected state")
+    ap.add_argument("--detail", default="", help="file for the whole record, every Newton system included (JSON)")
     ap.add_argument("--calib-copy-mb", type=int, default=0,
                     help="first run an elementwise copy of this many MiB (counter calibration)")
     a = ap.parse_args()
@@ -757,9 +768,9 @@ def single_main(a):
                    "load": prob.kind, "depth_increment": prob.depth_increment, "load_steps": prob.steps,
                    "seed": prob.seed, "precision": "mixed", "coarse": a.coarse},
         "mixed": ms,
-        "newton_iterations": [{k: (round(r[k], 4) if isinstance(r[k], float) and k.endswith("ms") else r[k])
-                               for k in keep} for r in mixed["recs"]],
     }
+    detail = {"newton_iterations": [{k: (round(r[k], 4) if isinstance(r[k], float) and k.endswith("ms") else r[k])
+                                     for k in keep} for r in mixed["recs"]]}
     if fp64 is not None:
         fs = summary(fp64)
         fs["launch_shapes"] = fp64["shapes"]
@@ -806,7 +817,9 @@ def single_main(a):
         for prec in ("fp64", "mixed"):
             log(f"[bench] whole 64^3 run ({med.steps} load steps of {med.depth_increment}), {prec} ...")
             try:
-                out["multistep_64cubed"][prec] = multistep(med, prec, coarse=a.coarse)
+                run = multistep(med, prec, coarse=a.coarse)
+                detail[f"multistep_64cubed_{prec}"] = run.pop("solves", None)
+                out["multistep_64cubed"][prec] = run
             except Exception as err:  # reported, not fatal for the headline
                 out["multistep_64cubed"][prec] = {"error": str(err)}
     if not a.no_pade and a.workload in ("tiny", "medium"):
@@ -815,7 +828,7 @@ def single_main(a):
     if not a.no_cpu_baseline:
         log("[bench] oracle cpu baseline ...")
         out["cpu_baseline"] = cpu_baseline(SAMPLES[a.workload](prob), a.coarse)
-    print(json.dumps(out), flush=True)
+    emit(out, detail, a.detail)
 
 
 if __name__ == "__main__":
