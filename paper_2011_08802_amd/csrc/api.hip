@@ -1050,13 +1050,14 @@ int* setup_rejected(mvpf_problem* p) { return setup_status(p) + 1; }  // GJJob::
 int* host_status(mvpf_problem* p) { return (int*)(p->hhost + 3 * (MAX_RESTART + 2)); }
 int* host_rejected(mvpf_problem* p) { return host_status(p) + 1; }
 
-// The coarsest operator is assembled first; its dense gather and inversion
-// then run on the side stream while the main stream assembles the finer
-// levels.  setup_solver joins the two streams.
+// A Newton system: the coarsest operator is assembled first; its dense gather
+// and inversion then run on the side stream while the main stream assembles
+// the finer levels.  setup_solver joins the two streams.
 // coarse_inline = false (batches): the coarsest operator is gathered into its
 // dense matrix on the problem's stream, ev_fork marks it ready, and the
 // batch inverts all problems' matrices at once and records ev_join.
-// status word, Dirichlet masks of `depth`, injected masks and states
+//
+// Its start: status words, Dirichlet masks of `depth`, injected masks and states
 int system_prelude(mvpf_problem* p, double depth) {
   hipStream_t s = p->stream;
   Level& L0 = p->lev[0];
@@ -1261,8 +1262,8 @@ int build_system(mvpf_problem* p, double depth, bool coarse_inline = true) {
   Level& L0 = p->lev[0];
   const int Lc = p->L - 1;
   TRY(system_prelude(p, depth));
-  // coarsest level first, as a dense matrix; its inversion (a chain of
-  // several hundred launches) is enqueued after the finer levels' assembly,
+  // coarsest level first, as a dense matrix; its inversion (a chain of one or
+  // two launches per 64 unknowns) is enqueued after the finer levels' assembly,
   // so that the host feeds the main stream first and the side stream's chain
   // then runs beside it
   assemble_coarse_level(p, Lc, depth);
@@ -1280,7 +1281,7 @@ int build_system(mvpf_problem* p, double depth, bool coarse_inline = true) {
     for (const Chunk& ck : make_chunks(L0.g, p->ne_use)) {
       timer_begin(p, p->t_qp);
       launch_qp(L0.g, ck, L0.state, p->card, p->pade, p->mixing, p->qp, s);
-      // written: gradient (15) and packed Hessian (120) per Gauss point
+      // written: the packed Hessian per Gauss point
       timer_end(p, p->t_qp, 8.0 * 8 * NHP * (double)ck.NEc);
       launch_element_matrices(L0.g, ck, p->qp, p->card, p->elem, s);
       if (contact(p)) launch_contact_element(L0.g, ck, make_sphere(L0.g, p->load, depth), L0.state, p->elem, s);
@@ -3207,9 +3208,6 @@ int mvpf_create_batch(int n, const mvpf_mesh* meshes, const mvpf_material* mats,
   for (int i = 0; i < n && rc == 0; ++i) {
     rc = mvpf_create(&meshes[i], &mats[i], &loads[i], opts, stream, &b->probs[i]);
     if (rc) break;
-    // a batched launch is wide even where each problem's level is small: the
-    // two-pass kernels (every stored block read once) beat the small-grid
-    // ones there (batched solve 336 -> 314 ms on the 32-problem workload)
     const int64_t nv = nvec(b->probs[i]->lev[0].g);
     if (hipMalloc((void**)&b->vin[i], sizeof(double) * nv) != hipSuccess ||
         hipMalloc(&b->zout[i], (b->mixed ? sizeof(float) : sizeof(double)) * nv) != hipSuccess ||

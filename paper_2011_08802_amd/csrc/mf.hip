@@ -14,12 +14,11 @@
 // them.  64^3, FP32: 188 -> 156 us per product (0.81 GB, 5.2 TB/s); 128x128x64:
 // FP32 750 -> 611 us, FP64 1513 -> 1212 us (5.3 TB/s).
 // eps and sigma are intermediate results that a product with the packed entries
-// does not round.  So the sums of D v are taken in 64 bits for either storage
-// type: a vector instruction costs the same in both, the product is bound by
-// its stream, and only 12 instead of 20 vectors are in flight (registers).
-// Error of the FP32 product against 64 bits at 64^3: 6.1e-8 with the packed
-// entries, 6.4e-8 in this form with 32-bit sums, 5.7e-8 with 64-bit ones
-// (219 and 216 us with the layout conversions around the product).
+// does not round.  So eps and D_ee eps are formed in 64 bits for either storage
+// type, and the parts of sigma and t summed apart: error of the FP32 product
+// against 64 bits at 64^3 6.1e-8 with the packed entries, 6.4e-8 in this form
+// with plain 32-bit sums, 5.7e-8 so, as with every sum in 64 bits, whose
+// conversions made the FP32 sweep 3 % slower (41^3 nodes 53.4, 55.1, now 52.2 us).
 // Stored per element: 3 KB in FP32 instead of the half-stencil blocks of its
 // node (4.7 KB) plus the assembled path's transposed contributions (0.9 KB
 // written and read per sweep).
@@ -142,8 +141,8 @@ __device__ __forceinline__ void mf_element_body(const Grid& g, const TD* __restr
   }
   // w = D v: with F = I + G, eps = sym(F^T dF) (engineering shears),
   // sigma = D_ee eps + D_ek eta, t = D_ek^T eps + D_kk eta, and back through
-  // dF: F sigma + dF S.  All sums in 64 bits (see the head of the file); G and
-  // S wait in the storage type for their use at the end.
+  // dF: F sigma + dF S.  eps and D_ee eps in 64 bits, the other sums of a
+  // result kept apart until its end (see the head of the file).
   T w[15];
 #pragma unroll
   for (int k = 0; k < 15; ++k) w[k] = 0;
@@ -162,12 +161,12 @@ __device__ __forceinline__ void mf_element_body(const Grid& g, const TD* __restr
   if (load) {
     // entry k of the stream (each taken once, in order): its vector's first
     // entry issues the load PF vectors ahead
-    auto entry = [&](int k) -> TD {
+    auto entry = [&](int k) -> T {
       if (!SPARSE && k % V == 0 && k / V + PF < NV) dq[k / V + PF] = __builtin_nontemporal_load(Dp + (k / V + PF) * ks);
-      return dq[k / V][k % V];
+      return (T)dq[k / V][k % V];
     };
-    TD G[9], S[6];
-    double eps[6], sig[6], t[6];
+    T G[9], S[6], eps[6], sk[6], tk[6], tl[6];
+    double e[6], sig[6];
 #pragma unroll
     for (int k = 0; k < 9; ++k) G[k] = entry(MF_G + k);
 #pragma unroll
@@ -179,8 +178,9 @@ __device__ __forceinline__ void mf_element_body(const Grid& g, const TD* __restr
         s += (double)G[3 * i + j] * (double)v[3 * i + l];
         if (j != l) s += (double)G[3 * i + l] * (double)v[3 * i + j];
       }
-      eps[u] = s;
-      sig[u] = t[u] = 0;
+      e[u] = s;
+      eps[u] = (T)s;
+      sig[u] = sk[u] = tk[u] = tl[u] = 0;
     }
 #pragma unroll
     for (int u = 0; u < 6; ++u) S[u] = entry(MF_S + u);
@@ -189,36 +189,40 @@ __device__ __forceinline__ void mf_element_body(const Grid& g, const TD* __restr
 #pragma unroll
       for (int q = p; q < 6; ++q, ++k) {
         const double d = entry(k);
-        sig[p] += d * eps[q];
-        if (q != p) sig[q] += d * eps[p];
+        sig[p] += d * e[q];
+        if (q != p) sig[q] += d * e[p];
       }
 #pragma unroll
     for (int m = 0; m < 6; ++m)
 #pragma unroll
       for (int u = 0; u < 6; ++u) {
-        const double d = entry(MF_EK + 6 * m + u);
-        sig[u] += d * (double)v[9 + m];
-        t[m] += d * eps[u];
+        const T d = entry(MF_EK + 6 * m + u);
+        sk[u] += d * v[9 + m];
+        tk[m] += d * eps[u];
       }
 #pragma unroll
     for (int m = 0, k = MF_KK; m < 6; ++m)
 #pragma unroll
       for (int l = 0; l <= m; ++l, ++k) {
-        const double d = entry(k);
-        t[m] += d * (double)v[9 + l];
-        if (l != m) t[l] += d * (double)v[9 + m];
+        const T d = entry(k);
+        tl[m] += d * v[9 + l];
+        if (l != m) tl[l] += d * v[9 + m];
       }
 #pragma unroll
-    for (int m = 0; m < 6; ++m) w[9 + m] = (T)t[m];
+    for (int m = 0; m < 6; ++m) {
+      w[9 + m] = tk[m] + tl[m];
+      sk[m] = (T)(sig[m] + (double)sk[m]);
+    }
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
-        double s = sig[SI(i, j)];
+        T s = 0;
 #pragma unroll
-        for (int l = 0; l < 3; ++l)
-          s += (double)G[3 * i + l] * sig[SI(l, j)] + (double)S[SI(l, j)] * (double)v[3 * i + l];
-        w[3 * i + j] = (T)s;
+        for (int l = 0; l < 3; ++l) s += S[SI(l, j)] * v[3 * i + l];
+#pragma unroll
+        for (int l = 0; l < 3; ++l) s += G[3 * i + l] * sk[SI(l, j)];
+        w[3 * i + j] = s + sk[SI(i, j)];
       }
   }
   // gradient energy: z = (Mg (x) I) grad_ref eta
@@ -693,9 +697,10 @@ void launch_mf_diag_batch(int op, const AJob* jobs, int njobs, int blocks, hipSt
 }
 
 // Register budgets (measured equal within 1 % for prefetch depths 12 and more
-// at 2 ... 4 waves per SIMD): FP32 tangents 12 vectors ahead at >= 3 waves
-// per SIMD (162 registers; 14 spill), FP64 16 ahead at >= 2.
-constexpr int MF_PF32 = 12, MF_MINB32 = 3, MF_PF64 = 16, MF_MINB64 = 2;
+// at 2 ... 4 waves per SIMD): FP64 tangents 16 vectors ahead at >= 2 waves per
+// SIMD.  FP32 8 ahead at >= 3 waves (144 registers): 12 and 14 are 1 and 2 %
+// slower, from 16 on registers spill, and 2 waves cost 8 %.
+constexpr int MF_PF32 = 8, MF_MINB32 = 3, MF_PF64 = 16, MF_MINB64 = 2;
 template <typename TD, typename TX, typename T>
 void launch_mf_element(const Grid& g, const TD* D, const TX* x, const uint16_t* mask, const DevCard* cd, T* E,
                        hipStream_t s, bool sparse_x, int elems_per_wg) {

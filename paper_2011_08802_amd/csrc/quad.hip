@@ -126,7 +126,8 @@ void launch_qp(const Grid& g, const Chunk& ck, const double* state, const DevCar
 // gradient (and the gradient energy's) goes back to the corners through the
 // transposed stages.  The corner values are merged along x in the workgroup and
 // a node sum of at most 4 merged rows follows.  Bound: FP64 issue of the local
-// gradient (~1300 instructions per point); 64^3: 0.19 ms and 0.03 ms for the
+// gradient (3200 instructions per lane, 1500 of
+// them FP64, at two wavefronts per SIMD); 64^3: 0.19 ms and 0.03 ms for the
 // node sums, against 0.30 ms for gradients stored per point and 0.35 ms for a
 // node gather that read each of them eight times.
 template <int PD, int MIX>

@@ -559,7 +559,6 @@ void launch_free_norm_partial(const Grid& g, const double* v, const uint16_t* ma
   free_norm_kernel<<<red_blocks((int64_t)g.N * NDOF), RB, 0, s>>>(g, v, mask, part);
 }
 
-// flat type conversion out[i] = (TO) in[i]
 // Preconditioner output: z = V-cycle result on free dofs, z = v on
 // constrained dofs of the finest level (identity there).
 template <typename T, typename TZ>
