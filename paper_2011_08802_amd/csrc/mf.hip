@@ -14,11 +14,12 @@
 // them.  64^3, FP32: 188 -> 156 us per product (0.81 GB, 5.2 TB/s); 128x128x64:
 // FP32 750 -> 611 us, FP64 1513 -> 1212 us (5.3 TB/s).
 // eps and sigma are intermediate results that a product with the packed entries
-// does not round.  So eps and D_ee eps are formed in 64 bits for either storage
-// type, and the parts of sigma and t summed apart: error of the FP32 product
-// against 64 bits at 64^3 6.1e-8 with the packed entries, 6.4e-8 in this form
-// with plain 32-bit sums, 5.7e-8 so, as with every sum in 64 bits, whose
-// conversions made the FP32 sweep 3 % slower (41^3 nodes 53.4, 55.1, now 52.2 us).
+// does not round, so the sums of D v are taken in 64 bits for either storage
+// type.  Error of the FP32 product against 64 bits at 64^3: 6.1e-8 with the packed
+// entries, 6.4e-8 in this form with 32-bit sums, 5.7e-8 so; evaluated on the CPU,
+// also where one kind of unknown dominates the input (32-bit sums of the parts
+// that hold the other kind exceed the packed entries' error there by 1 %).  The
+// 108 conversions per lane cost the FP32 sweep 2 % (41^3 nodes 52.8 -> 53.8 us).
 // Stored per element: 3 KB in FP32 instead of the half-stencil blocks of its
 // node (4.7 KB) plus the assembled path's transposed contributions (0.9 KB
 // written and read per sweep).
@@ -141,8 +142,8 @@ __device__ __forceinline__ void mf_element_body(const Grid& g, const TD* __restr
   }
   // w = D v: with F = I + G, eps = sym(F^T dF) (engineering shears),
   // sigma = D_ee eps + D_ek eta, t = D_ek^T eps + D_kk eta, and back through
-  // dF: F sigma + dF S.  eps and D_ee eps in 64 bits, the other sums of a
-  // result kept apart until its end (see the head of the file).
+  // dF: F sigma + dF S.  All sums in 64 bits (see the head of the file); G and
+  // S wait in the storage type for their use at the end.
   T w[15];
 #pragma unroll
   for (int k = 0; k < 15; ++k) w[k] = 0;
@@ -161,12 +162,12 @@ __device__ __forceinline__ void mf_element_body(const Grid& g, const TD* __restr
   if (load) {
     // entry k of the stream (each taken once, in order): its vector's first
     // entry issues the load PF vectors ahead
-    auto entry = [&](int k) -> T {
+    auto entry = [&](int k) -> TD {
       if (!SPARSE && k % V == 0 && k / V + PF < NV) dq[k / V + PF] = __builtin_nontemporal_load(Dp + (k / V + PF) * ks);
-      return (T)dq[k / V][k % V];
+      return dq[k / V][k % V];
     };
-    T G[9], S[6], eps[6], sk[6], tk[6], tl[6];
-    double e[6], sig[6];
+    TD G[9], S[6];
+    double eps[6], sig[6], t[6];
 #pragma unroll
     for (int k = 0; k < 9; ++k) G[k] = entry(MF_G + k);
 #pragma unroll
@@ -178,9 +179,8 @@ __device__ __forceinline__ void mf_element_body(const Grid& g, const TD* __restr
         s += (double)G[3 * i + j] * (double)v[3 * i + l];
         if (j != l) s += (double)G[3 * i + l] * (double)v[3 * i + j];
       }
-      e[u] = s;
-      eps[u] = (T)s;
-      sig[u] = sk[u] = tk[u] = tl[u] = 0;
+      eps[u] = s;
+      sig[u] = t[u] = 0;
     }
 #pragma unroll
     for (int u = 0; u < 6; ++u) S[u] = entry(MF_S + u);
@@ -189,40 +189,36 @@ __device__ __forceinline__ void mf_element_body(const Grid& g, const TD* __restr
 #pragma unroll
       for (int q = p; q < 6; ++q, ++k) {
         const double d = entry(k);
-        sig[p] += d * e[q];
-        if (q != p) sig[q] += d * e[p];
+        sig[p] += d * eps[q];
+        if (q != p) sig[q] += d * eps[p];
       }
 #pragma unroll
     for (int m = 0; m < 6; ++m)
 #pragma unroll
       for (int u = 0; u < 6; ++u) {
-        const T d = entry(MF_EK + 6 * m + u);
-        sk[u] += d * v[9 + m];
-        tk[m] += d * eps[u];
+        const double d = entry(MF_EK + 6 * m + u);
+        sig[u] += d * (double)v[9 + m];
+        t[m] += d * eps[u];
       }
 #pragma unroll
     for (int m = 0, k = MF_KK; m < 6; ++m)
 #pragma unroll
       for (int l = 0; l <= m; ++l, ++k) {
-        const T d = entry(k);
-        tl[m] += d * v[9 + l];
-        if (l != m) tl[l] += d * v[9 + m];
+        const double d = entry(k);
+        t[m] += d * (double)v[9 + l];
+        if (l != m) t[l] += d * (double)v[9 + m];
       }
 #pragma unroll
-    for (int m = 0; m < 6; ++m) {
-      w[9 + m] = tk[m] + tl[m];
-      sk[m] = (T)(sig[m] + (double)sk[m]);
-    }
+    for (int m = 0; m < 6; ++m) w[9 + m] = (T)t[m];
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
-        T s = 0;
+        double s = sig[SI(i, j)];
 #pragma unroll
-        for (int l = 0; l < 3; ++l) s += S[SI(l, j)] * v[3 * i + l];
-#pragma unroll
-        for (int l = 0; l < 3; ++l) s += G[3 * i + l] * sk[SI(l, j)];
-        w[3 * i + j] = s + sk[SI(i, j)];
+        for (int l = 0; l < 3; ++l)
+          s += (double)G[3 * i + l] * sig[SI(l, j)] + (double)S[SI(l, j)] * (double)v[3 * i + l];
+        w[3 * i + j] = (T)s;
       }
   }
   // gradient energy: z = (Mg (x) I) grad_ref eta
@@ -698,8 +694,9 @@ void launch_mf_diag_batch(int op, const AJob* jobs, int njobs, int blocks, hipSt
 
 // Register budgets (measured equal within 1 % for prefetch depths 12 and more
 // at 2 ... 4 waves per SIMD): FP64 tangents 16 vectors ahead at >= 2 waves per
-// SIMD.  FP32 8 ahead at >= 3 waves (144 registers): 12 and 14 are 1 and 2 %
-// slower, from 16 on registers spill, and 2 waves cost 8 %.
+// SIMD.  FP32 8 ahead at >= 3 waves (160 registers): 12 ahead take 1 to 2 %
+// longer, from 14 on registers spill (41^3 nodes: 54 and 60 us), and 16 ahead at
+// 2 waves take 57.
 constexpr int MF_PF32 = 8, MF_MINB32 = 3, MF_PF64 = 16, MF_MINB64 = 2;
 template <typename TD, typename TX, typename T>
 void launch_mf_element(const Grid& g, const TD* D, const TX* x, const uint16_t* mask, const DevCard* cd, T* E,

@@ -146,10 +146,12 @@ def test_mf_merged_outputs_independent_of_workgroup_size(name):
             assert np.array_equal(a, b)
 
 
-@pytest.mark.parametrize("amp,bound,bound_eta", [(2e-4, 6.71e-8, 8.96e-8), (5e-3, 6.73e-8, 8.34e-8)])
-def test_mf_fp32_product_rounds_no_more_than_packed_hessians(amp, bound, bound_eta):
+@pytest.mark.parametrize("amp,u,bound,bound_eta", [(2e-4, 1, 6.71e-8, 8.96e-8), (5e-3, 1, 6.73e-8, 8.34e-8),
+                                                   (2e-4, 0, 7.95e-8, 6.13e-8), (5e-3, 0, 7.69e-8, 6.27e-8)])
+def test_mf_fp32_product_rounds_no_more_than_packed_hessians(amp, u, bound, bound_eta):
     """Error of the FP32 product against the FP64 one, for an input that FP32
-    holds, on the free unknowns of a 16^3 patch problem.  The bounds are the
+    holds (with displacements and without), on the free unknowns of a 16^3
+    patch problem.  The bounds are the
     errors of a product from the 120 packed FP32 Hessian entries of each point
     on the same input, all sums in FP32 with fused multiply-adds in the
     kernel's order, evaluated on the CPU (all unknowns; order parameters); the
@@ -161,6 +163,7 @@ def test_mf_fp32_product_rounds_no_more_than_packed_hessians(amp, bound, bound_e
     U, En = seeded_state(p, amp)
     mask, _ = S.dirichlet(Mesh.from_problem(p), p.kind, p.patch, p.radius, depth=p.depth_increment, ndof=9)
     x = np.random.default_rng(17).standard_normal(U.shape).astype(np.float32).astype(float)
+    x[:, :3] *= u
     x[mask] = 0.0
     gp = _mf_problem(p, U, En, p.depth_increment, "mixed")
     free = torch.as_tensor(~mask.ravel()).cuda()
