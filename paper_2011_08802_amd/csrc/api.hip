@@ -2211,7 +2211,7 @@ int batch_invert_again(mvpf_batch* b, const std::vector<hipStream_t>& streams) {
     which.push_back(i);
   }
   if (!tab.empty()) {
-    BCHK(hipMemcpyAsync(b->gj_again, tab.data(), sizeof(GJJob) * tab.size(), hipMemcpyHostToDevice, b->work));
+    BCHK(hipMemcpy(b->gj_again, tab.data(), sizeof(GJJob) * tab.size(), hipMemcpyHostToDevice));
     if (dense_invert_pivoted_batch(b->gj_again, ns, b->work) != 0) {
       b->err = "batched coarse inversion launch failed";
       return MVPF_EDEVICE;

@@ -784,8 +784,8 @@ int dense_invert_pivoted_batch(const GJJob* tab_dev, const std::vector<int>& ns,
 // that publishes the next column has half the columns to update after it
 // (against 4 wavefronts: 1125 unknowns 0.81 -> 0.66 ms, 3645 4.2 -> 3.1 ms).
 // Measured against four launches per 16 or 32 columns of the elimination
-// above: 576 unknowns 2.07 -> 0.33 ms, 1125 4.23 -> 0.66, 2187 12.1 -> 1.6,
-// 3645 22.7 -> 3.1 ms.
+// above: 576 unknowns 2.07 -> 0.32 ms, 1125 4.23 -> 0.65, 2187 12.1 -> 1.6,
+// 3645 22.7 -> 3.0 ms.
 typedef double bg_vec4 __attribute__((ext_vector_type(4)));
 constexpr int BGT = 512;  // threads of a tile's workgroup
 constexpr int BG_LDA = 66, BG_LDB = 72;  // LDS strides: the matrix instructions' operand reads meet every bank evenly

@@ -19,7 +19,7 @@
 // entries, 6.4e-8 in this form with 32-bit sums, 5.7e-8 so; evaluated on the CPU,
 // also where one kind of unknown dominates the input (32-bit sums of the parts
 // that hold the other kind exceed the packed entries' error there by 1 %).  The
-// 108 conversions per lane cost the FP32 sweep 2 % (41^3 nodes 52.8 -> 53.8 us).
+// 108 conversions per lane cost the FP32 sweep 2 % (41^3 nodes 53.3 -> 54.4 us).
 // Stored per element: 3 KB in FP32 instead of the half-stencil blocks of its
 // node (4.7 KB) plus the assembled path's transposed contributions (0.9 KB
 // written and read per sweep).

@@ -125,11 +125,10 @@ void launch_qp(const Grid& g, const Chunk& ck, const double* state, const DevCar
 // grad eta and eta_n come from three pair interpolations, and the density's
 // gradient (and the gradient energy's) goes back to the corners through the
 // transposed stages.  The corner values are merged along x in the workgroup and
-// a node sum of at most 4 merged rows follows.  Bound: FP64 issue of the local
-// gradient (3200 instructions per lane, 1500 of
-// them FP64, at two wavefronts per SIMD); 64^3: 0.19 ms and 0.03 ms for the
-// node sums, against 0.30 ms for gradients stored per point and 0.35 ms for a
-// node gather that read each of them eight times.
+// a node sum of at most 4 merged rows follows.  Bound: vector issue (2500
+// instructions per point, 1500 of them FP64) at two wavefronts per SIMD; 64^3:
+// 0.19 ms and 0.03 ms for the node sums, against 0.30 ms for gradients stored
+// per point and 0.35 ms for a node gather that read each of them eight times.
 template <int PD, int MIX>
 __device__ __forceinline__ void residual_element_body(const Grid& g, const Chunk& ck, const double* __restrict__ state,
                                                       const DevCard* __restrict__ cd, double* __restrict__ E, int wg,
@@ -241,13 +240,15 @@ void launch_residual(const Grid& g, const Chunk& ck, const double* state, const 
   residual_nodes_kernel<<<(ck.n1 - ck.n0 + 255) / 256 * NDOF, 256, 0, s>>>(g, ck, E, R);
 }
 
-// Gauss-point tangents of a matrix-free level, straight into the matrix-free layout (no pass over a scratch form).  A
-// wavefront holds 8 elements x 8 points (lane = 8 * element + point): lane j
-// loads the 15 state values of corner j of its element and the point's F, eta
-// and eta_n come from three pair interpolations, instead of 120 loads per
-// point.  Bound: FP64 issue at one wavefront per SIMD (~6000 instructions per
-// point); 64^3: 0.81 ms, 1.27 KB written per point (3.3 TB/s), against 2.43 ms
-// for the Hessian in (F, eta) and 1.10 ms for the pass that repacked it.
+// Gauss-point tangents of a matrix-free level, straight into the matrix-free
+// layout (no pass over a scratch form).  A wavefront holds 8 elements x 8 points
+// (lane = 8 * element + point): lane j loads the 9 unknowns of corner j of its
+// element, and the point's F and eta come from three pair interpolations,
+// instead of 72 loads per point.  Bound: vector issue at one wavefront per SIMD
+// (7800 instructions per point, 5600 of them FP64, 1200 moves from and to the
+// accumulation registers); 64^3: 0.69 ms, 1.15 KB written per point (3.5 TB/s),
+// against 2.43 ms for the Hessian in (F, eta) and 1.10 ms for the pass that
+// repacked it.
 struct MfOut {
   const double* F;
   double2* D64;   // the wavefront's group of 8 elements
