@@ -307,3 +307,31 @@ def test_finest_level_gathers_against_the_assembled_level(kind, nx, ny, nz, prec
     assert torch.isfinite(y).all() and torch.isfinite(z).all()
     assert float((y - y0).norm() / (y0.norm() + ya0.norm())) < ptol
     assert float((z - z0).norm() / z0.norm()) < tol
+
+
+def test_batch_assembled_in_slabs_with_a_rejected_coarse_inverse():
+    """A batch of which one problem assembles in slabs takes a stream per
+    problem: its coarsest operators are still inverted together, the rejected
+    one again beside the others' assembly, and every V-cycle and right-hand side is
+    bitwise the one of the problem by itself."""
+    from paper_2011_08802_amd import mvpf
+    probs = [_two_level(6, 6, 6, synth.BASE_SEED + 80), _indefinite(_two_level(6, 8, 10, synth.BASE_SEED + 81)),
+             _two_level(8, 6, 12, synth.BASE_SEED + 82)]
+    states = [seeded_state(p, 5e-4) for p in probs]
+    B = mvpf.Batch(probs, "mixed")
+    B.problem(2).set_tuning("assembly_slab_elements", 0, 2 * 48 + 64)
+    for i, (U, En) in enumerate(states):
+        B.problem(i).set_state(U[:, :3], U[:, 3:], En, 0.0)
+    for _ in range(2):
+        B.newton_system([p.depth_increment for p in probs])
+        for i, (p, (U, En)) in enumerate(zip(probs, states)):
+            assert B.problem(i).get_tuning("coarse_pivoted") == (i == 1)
+            v = _dev(np.random.default_rng(11 + i).standard_normal(9 * p.n_nodes))
+            gp = gpu_problem(p, U, En, "mixed")
+            gp.newton_system(p.depth_increment)
+            z = gp.precondition(v)
+            assert torch.isfinite(z).all()
+            assert torch.equal(B.problem(i).precondition(v), z), i
+            assert torch.equal(B.problem(i).get_rhs(), gp.get_rhs()), i
+            gp.close()
+    B.close()
